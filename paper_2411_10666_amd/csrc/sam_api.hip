@@ -463,6 +463,14 @@ static int batch_check_args(const char *fn, const sam_corpus *corpus, const int3
     return SAM_OK;
 }
 
+static int64_t longest_prompt(const int64_t *offs, int32_t n)
+{
+    int64_t most = 0;
+    for (int32_t i = 0; i < n; i++)
+        if (offs[i + 1] - offs[i] > most) most = offs[i + 1] - offs[i];
+    return most;
+}
+
 static int batch_check_offsets(const char *fn, const int64_t *offs, int32_t batch,
                                int32_t max_seq_len)
 {
@@ -567,8 +575,8 @@ int sam_batch_init(const sam_corpus *corpus, const int32_t *prompt_tokens,
     StaticView S = corpus ? corpus->view : StaticView{};
     if ((e = hipMemsetAsync(v.dyn_slots, 0xFF, bb.slots, stream)) != hipSuccess ||
         (e = launch_reset(v, nullptr, batch, stream)) != hipSuccess ||
-        (e = launch_feed(S, v, nullptr, batch, prompt_tokens, prompt_offsets, nullptr, nullptr,
-                         nullptr, nullptr, nullptr, stream)) != hipSuccess ||
+        (e = launch_ingest(S, v, nullptr, batch, prompt_tokens, prompt_offsets,
+                           longest_prompt(offs.data(), batch), stream)) != hipSuccess ||
         (e = hipStreamSynchronize(stream)) != hipSuccess) {
         batch_release(bt);
         return fail_hip("sam_batch_init: prompt ingest", e);
@@ -648,8 +656,8 @@ int sam_batch_init_noalloc(const sam_corpus *corpus, const int32_t *prompt_token
     hipError_t e;
     if ((e = launch_fill_empty(v.dyn_slots, bb.slots, stream)) != hipSuccess ||
         (e = launch_reset(v, nullptr, batch, stream)) != hipSuccess ||
-        (e = launch_feed(S, v, nullptr, batch, prompt_tokens, prompt_offsets, nullptr, nullptr,
-                         nullptr, nullptr, nullptr, stream)) != hipSuccess) {
+        (e = launch_ingest(S, v, nullptr, batch, prompt_tokens, prompt_offsets,
+                           longest_prompt(prompt_offsets_host, batch), stream)) != hipSuccess) {
         batch_release(bt);
         return fail_hip("sam_batch_init_noalloc: launch", e);
     }
@@ -756,8 +764,8 @@ int sam_batch_reset(sam_batch *bt, const int32_t *slots, int32_t n_slots,
     StaticView S = bt->corpus ? bt->corpus->view : StaticView{};
     hipError_t e;
     if ((e = launch_reset(v, slots, n_slots, stream)) != hipSuccess ||
-        (e = launch_feed(S, v, slots, n_slots, prompt_tokens, prompt_offsets, nullptr, nullptr,
-                         nullptr, nullptr, nullptr, stream)) != hipSuccess)
+        (e = launch_ingest(S, v, slots, n_slots, prompt_tokens, prompt_offsets,
+                           longest_prompt(offs.data(), n_slots), stream)) != hipSuccess)
         return fail_hip("sam_batch_reset: launch", e);
     return SAM_OK;
 }

@@ -1,0 +1,670 @@
+// A prompt's automaton built by a whole workgroup at once.
+//
+// Online extension (Algorithm 2) is a serial chain: one token after the other, each with
+// two or three dependent memory round trips.  A prompt is known in full, though, and what
+// the chain leaves behind is fixed by the text alone:
+//
+//   * the states are the prefixes of the text and the strings that occur with two
+//     different tokens in front of them; the suffix links form the compressed trie of
+//     all prefixes read BACKWARDS (the suffix tree of the reversed text);
+//   * a prefix state's id is its step's first new id; the state of a string w that is no
+//     prefix is cloned in the step in which w first occurs with a second token in front
+//     of it, i.e. at the second smallest of the first end positions of w's children in
+//     that tree, and at most one state is cloned in a step;
+//   * min_endpos of a state is the smallest prefix in its subtree;
+//   * (v, t) leads to the state on the suffix path of the prefix x[..i+1] whose lengths
+//     include len(v) + 1, for any occurrence of v that ends at i and is followed by t.
+//
+// So the workgroup sorts the reversed prefixes by doubling (names of the last h tokens
+// before every position; equal pairs of names get equal names for 2h), takes the common
+// lengths of neighbours, finds every interval's parent by the nearest smaller values,
+// numbers the states, and inserts the transitions with compare-and-swap.  Children are in
+// no particular order (a tree has none), so a round of the sort is a hash table of pairs
+// and no radix passes.  Everything is exact: tokens and names are compared, never hashes.
+//
+// Written as phases over an index range with a barrier between them (Ctx::each,
+// Ctx::sync); nothing is carried from one phase to the next in a thread, so the same
+// source also runs phase by phase on the CPU.
+#pragma once
+#include <stdint.h>
+
+#include "sam_layout.h"
+
+#if defined(__HIPCC__)
+#define SAM_HD __host__ __device__ __forceinline__
+#else
+#define SAM_HD inline
+#endif
+
+namespace sam {
+
+constexpr uint32_t kIngestMaxTokens = 1u << 18;      // beyond: the serial kernel
+
+struct IngestSeq {
+    const int32_t *tok;        // the prompt, every token inside the vocabulary
+    uint32_t n;                // tokens, >= 1
+    int32_t *text;
+    void *rec;                 // record table of the sequence
+    void *slots;               // slot table
+    uint32_t n_buckets;
+};
+
+// ---- the two table layouts, as single threads write them ----------------------
+
+struct IngestWide {
+    static constexpr uint32_t kSlots = 8;
+    static SAM_HD void store(void *rec, uint32_t s, uint32_t len, uint32_t link, uint32_t endpos,
+                             uint32_t itok, uint32_t idst)
+    {
+        DynRec *r = reinterpret_cast<DynRec *>(rec) + s;
+        r->len = len; r->link = link; r->endpos = endpos; r->head = kNil;
+        r->itok = itok; r->idst = idst;
+    }
+    static SAM_HD void store_idst(void *rec, uint32_t s, uint32_t dst)
+    {
+        (reinterpret_cast<DynRec *>(rec) + s)->idst = dst;
+    }
+    static SAM_HD uint32_t len(const void *rec, uint32_t s) { return (reinterpret_cast<const DynRec *>(rec) + s)->len; }
+    static SAM_HD uint32_t link(const void *rec, uint32_t s) { return (reinterpret_cast<const DynRec *>(rec) + s)->link; }
+    static SAM_HD void load(const void *rec, uint32_t s, uint32_t &len, uint32_t &link, uint32_t &endpos,
+                            uint32_t &itok)
+    {
+        const DynRec *r = reinterpret_cast<const DynRec *>(rec) + s;
+        len = r->len; link = r->link; endpos = r->endpos; itok = r->itok;
+    }
+    static SAM_HD uint32_t idst(const void *rec, uint32_t s) { return (reinterpret_cast<const DynRec *>(rec) + s)->idst; }
+    // claim the slot for (p, t): 0 claimed, 1 the key was there already, 2 another key
+    template <class C>
+    static SAM_HD int claim(C &ctx, void *slots, uint32_t at, uint32_t p, uint32_t t)
+    {
+        const uint64_t key = (uint64_t)p | ((uint64_t)t << 32);
+        const uint64_t old = ctx.cas(reinterpret_cast<uint64_t *>(reinterpret_cast<Slot *>(slots) + at), ~(uint64_t)0, key);
+        return old == ~(uint64_t)0 ? 0 : (old == key ? 1 : 2);
+    }
+    template <class C>
+    static SAM_HD void fill(C &ctx, void *rec, void *slots, uint32_t at, uint32_t p, uint32_t, uint32_t dst)
+    {
+        Slot *s = reinterpret_cast<Slot *>(slots) + at;
+        s->dst = dst;
+        s->w = ctx.exch(&(reinterpret_cast<DynRec *>(rec) + p)->head, at);
+    }
+    template <class C>
+    static SAM_HD uint32_t head(C &ctx, void *rec, uint32_t s)
+    {
+        return ctx.fresh(&(reinterpret_cast<DynRec *>(rec) + s)->head);
+    }
+};
+
+struct IngestCompact {
+    static constexpr uint32_t kSlots = 16;
+    static SAM_HD uint32_t widen(uint32_t v16) { return v16 == 0xFFFFu ? kNil : v16; }
+    static SAM_HD void store(void *rec, uint32_t s, uint32_t len, uint32_t link, uint32_t endpos,
+                             uint32_t itok, uint32_t idst)
+    {
+        uint32_t *r = reinterpret_cast<uint32_t *>(rec) + 4 * (size_t)s;
+        r[0] = (len & 0xFFFFu) | (link << 16);
+        r[1] = (endpos & 0xFFFFu) | 0xFFFF0000u;
+        r[2] = itok;
+        r[3] = idst & 0xFFFFu;
+    }
+    static SAM_HD void store_idst(void *rec, uint32_t s, uint32_t dst)
+    {
+        (reinterpret_cast<uint32_t *>(rec) + 4 * (size_t)s)[3] = dst & 0xFFFFu;
+    }
+    static SAM_HD uint32_t len(const void *rec, uint32_t s) { return (reinterpret_cast<const uint32_t *>(rec) + 4 * (size_t)s)[0] & 0xFFFFu; }
+    static SAM_HD uint32_t link(const void *rec, uint32_t s) { return widen((reinterpret_cast<const uint32_t *>(rec) + 4 * (size_t)s)[0] >> 16); }
+    static SAM_HD void load(const void *rec, uint32_t s, uint32_t &len, uint32_t &link, uint32_t &endpos,
+                            uint32_t &itok)
+    {
+        const uint32_t *r = reinterpret_cast<const uint32_t *>(rec) + 4 * (size_t)s;
+        const uint32_t a = r[0], b = r[1];
+        len = a & 0xFFFFu; link = widen(a >> 16); endpos = b & 0xFFFFu; itok = r[2];
+    }
+    static SAM_HD uint32_t idst(const void *rec, uint32_t s) { return (reinterpret_cast<const uint32_t *>(rec) + 4 * (size_t)s)[3]; }
+    template <class C>
+    static SAM_HD int claim(C &ctx, void *slots, uint32_t at, uint32_t p, uint32_t t)
+    {
+        const uint32_t key = (p << 17) | t;
+        const uint32_t old = ctx.cas(reinterpret_cast<uint32_t *>(slots) + 2 * (size_t)at, kNil, key);
+        return old == kNil ? 0 : (old == key ? 1 : 2);
+    }
+    // the head shares its word with the end position, which does not change
+    template <class C>
+    static SAM_HD void fill(C &ctx, void *rec, void *slots, uint32_t at, uint32_t p, uint32_t endpos,
+                            uint32_t dst)
+    {
+        const uint32_t old = ctx.exch(reinterpret_cast<uint32_t *>(rec) + 4 * (size_t)p + 1,
+                                      (endpos & 0xFFFFu) | (at << 16));
+        (reinterpret_cast<uint32_t *>(slots) + 2 * (size_t)at)[1] = (dst & 0xFFFFu) | (old & 0xFFFF0000u);
+    }
+    template <class C>
+    static SAM_HD uint32_t head(C &ctx, void *rec, uint32_t s)
+    {
+        return widen(ctx.fresh(reinterpret_cast<uint32_t *>(rec) + 4 * (size_t)s + 1) >> 16);
+    }
+};
+
+// ---- working arrays -------------------------------------------------------------
+//
+// I: index type (16 bits up to kIngestIdx16 tokens), K: a pair of names.
+constexpr uint32_t kIngestIdx16 = 16366;
+
+template <class I, class K>
+struct IngestArrays {
+    // sort
+    K        *key;       // [h_size] pairs of names (empty: all ones)
+    K        *val;       // [h_size] lower half: positions that have it; upper: where they start
+    K        *cursor;    // [n] a bucket of a group: lower half its positions, then their start;
+                         // upper half the first of its pairs (+ 1) in key[]
+    I        *grp;       // [n] name of position i = start of its group; top bit: alone in it
+    I        *slot;      // [n] where its pair is in key[]
+    I        *next;      // [h_size] the next pair (+ 1) of the same bucket
+    I        *size;      // [n] size of the group that starts here
+    I        *name1;     // [n] names of single tokens (unused if the text is read instead)
+    uint8_t  *lev;       // [n] round in which a group came to start here
+    uint32_t  h_size;
+    // tree; boundary k lies between places k-1 and k of the sorted order
+    I        *sa;        // [n]
+    I        *lcp;       // [n]
+    I        *node;      // [n]
+    I        *tab;       // [2n]
+    I        *par;       // [n]
+    I        *pfx;       // [n]
+    I        *leaf;      // [n]
+    uint32_t *m;         // [n]
+    uint32_t *sec;       // [n]
+    I        *names;     // [7][stride] names of the last 16 * 4^j tokens (tables in device memory only)
+    uint32_t  stride;    // n rounded up to 16
+    // always in LDS
+    I        *bmin;      // [n / 32 + 1]
+    uint32_t *bits;      // [n / 32 + 1] steps that clone
+    uint32_t *rank;      // [n / 32 + 1] clones before the word
+    uint32_t *small;     // [128] flags and results
+    uint32_t *part;      // [kIngestParts] partial sums
+};
+
+constexpr uint32_t kIngestParts = 1024;
+
+SAM_HD uint32_t ingest_h_size(uint32_t n) { return n + n / 4 + 64; }
+
+struct IngestBump {
+    char *p;
+    template <class T>
+    SAM_HD T *take(size_t count)
+    {
+        T *r = reinterpret_cast<T *>(p);
+        p += (count * sizeof(T) + 15) / 16 * 16;
+        return r;
+    }
+};
+
+template <class I>
+SAM_HD size_t ingest_small_bytes(uint32_t n)
+{
+    const size_t w = n / 32 + 1;
+    return 512 + 4 * kIngestParts + (w * sizeof(I) + 15) / 16 * 16 + 2 * ((w * 4 + 15) / 16 * 16);
+}
+
+template <class I, class K>
+SAM_HD void ingest_place_small(IngestArrays<I, K> &A, IngestBump &b, uint32_t n)
+{
+    A.small = b.take<uint32_t>(128);
+    A.part = b.take<uint32_t>(kIngestParts);
+    A.bmin = b.take<I>(n / 32 + 1);
+    A.bits = b.take<uint32_t>(n / 32 + 1);
+    A.rank = b.take<uint32_t>(n / 32 + 1);
+}
+
+// All of it in LDS.  The tree's arrays lie over the sort's: what overlaps is never
+// alive at the same time (node over grp, pfx over name1, the rest over the hash table).
+SAM_HD size_t ingest_lds_bytes(uint32_t n)
+{
+    const size_t h = ingest_h_size(n);
+    auto up = [](size_t x) { return (x + 15) / 16 * 16; };
+    const size_t sort = 2 * up(4 * h) + up(2 * h) + up(4 * (size_t)n) + 2 * up(2 * (size_t)n);
+    const size_t tree = 4 * up(2 * (size_t)n) + 2 * up(4 * (size_t)n);
+    return ingest_small_bytes<uint16_t>(n) + up(n) + 2 * up(2 * (size_t)n) + (sort > tree ? sort : tree);
+}
+
+SAM_HD void ingest_place_lds(IngestArrays<uint16_t, uint32_t> &A, char *lds, uint32_t n)
+{
+    IngestBump b{lds};
+    ingest_place_small(A, b, n);
+    A.h_size = ingest_h_size(n);
+    A.lev = b.take<uint8_t>(n);
+    A.name1 = b.take<uint16_t>(n);
+    A.grp = b.take<uint16_t>(n);
+    A.pfx = A.name1;
+    A.node = A.grp;
+    IngestBump t = b;
+    A.key = b.take<uint32_t>(A.h_size);
+    A.val = b.take<uint32_t>(A.h_size);
+    A.next = b.take<uint16_t>(A.h_size);
+    A.cursor = b.take<uint32_t>(n);
+    A.slot = b.take<uint16_t>(n);
+    A.size = b.take<uint16_t>(n);
+    A.sa = t.take<uint16_t>(n);
+    A.lcp = t.take<uint16_t>(n);
+    A.par = t.take<uint16_t>(n);
+    A.leaf = t.take<uint16_t>(n);
+    A.m = t.take<uint32_t>(n);
+    A.tab = reinterpret_cast<uint16_t *>(A.m);
+    A.sec = t.take<uint32_t>(n);
+}
+
+// The large arrays in the sequence's own tables, which hold nothing yet: 16 indices a
+// token in the record table, 8 in the slot table (plus its 64 spare slots).  What the
+// records are written from is in the slot table, which is emptied again afterwards.
+template <class I, class K>
+SAM_HD void ingest_place_tables(IngestArrays<I, K> &A, const IngestSeq &q, char *lds, uint32_t n)
+{
+    IngestBump s{lds};
+    ingest_place_small(A, s, n);
+    A.h_size = ingest_h_size(n);
+    A.name1 = nullptr;
+    IngestBump r{reinterpret_cast<char *>(q.rec)};
+    A.grp = r.take<I>(n);
+    A.lev = r.take<uint8_t>(n);
+    IngestBump r2 = r;                     // the sort's arrays, and then the tree's
+    A.key = r.take<K>(A.h_size);
+    A.val = r.take<K>(A.h_size);
+    A.cursor = r.take<K>(n);
+    A.slot = r.take<I>(n);
+    A.next = r.take<I>(A.h_size);
+    A.size = r.take<I>(n);
+    A.sa = r2.take<I>(n);
+    A.node = r2.take<I>(n);
+    A.tab = r2.take<I>(2 * (size_t)n);
+    IngestBump t{reinterpret_cast<char *>(q.slots)};
+    A.lcp = t.take<I>(n);
+    A.names = reinterpret_cast<I *>(t.p);  // names live until lcp is known, the rest after it
+    A.stride = (n + 15) & ~15u;
+    A.par = t.take<I>(n);
+    A.pfx = t.take<I>(n);
+    A.leaf = t.take<I>(n);
+    A.m = t.take<uint32_t>(n);
+    A.sec = t.take<uint32_t>(n);
+}
+
+// Do the working arrays of n tokens fit into tables of these sizes?  (They do unless the
+// slot table is smaller than usual.)
+template <class I, class K>
+inline bool ingest_tables_fit(uint32_t n, size_t rec_bytes, size_t slot_bytes)
+{
+    const size_t h = ingest_h_size(n), N = n;
+    auto up = [](size_t x) { return (x + 15) / 16 * 16; };
+    size_t levels = 0;
+    for (size_t w = 16; w < N; w *= 4) levels++;
+    const size_t sort = 2 * up(sizeof(K) * h) + up(sizeof(I) * h) + up(sizeof(K) * N) + 2 * up(sizeof(I) * N);
+    const size_t tree = 2 * up(sizeof(I) * N) + up(2 * sizeof(I) * N);
+    const size_t names = levels * sizeof(I) * ((N + 15) / 16 * 16);
+    const size_t rest = 3 * up(sizeof(I) * N) + 2 * up(4 * N);
+    return up(sizeof(I) * N) + up(N) + (sort > tree ? sort : tree) <= rec_bytes &&
+           up(sizeof(I) * N) + (names > rest ? names : rest) <= slot_bytes;
+}
+
+// ---- the build --------------------------------------------------------------------
+
+SAM_HD uint32_t ingest_hash(uint32_t k)
+{
+    k *= 0x9E3779B1u;
+    k ^= k >> 15;
+    return k * 0x2C1B3C6Du;
+}
+SAM_HD uint32_t ingest_hash(uint64_t k) { return ingest_hash((uint32_t)k ^ (uint32_t)(k >> 32) * 0x85EBCA77u); }
+
+// Results: small[123] id of the last prefix, small[124] states, small[125] transitions.
+template <class L, bool kLds, class I, class K, class C>
+SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A)
+{
+    const uint32_t n = q.n, hs = A.h_size;
+    constexpr K kEmpty = (K)~(K)0;
+    constexpr uint32_t kHalf = sizeof(K) * 4;
+    constexpr I kAlone = (I)((I)1 << (sizeof(I) * 8 - 1));
+    constexpr I kNone = (I)~(I)0, kRoot = (I)(kNone - 1);
+    constexpr K kLow = (K)(((K)1 << kHalf) - 1);
+    uint32_t *const small = A.small;
+    uint32_t *const active = small;                  // [64] one flag per round
+    const uint32_t words = n / 32 + 1;
+
+    auto insert = [&](K key) -> uint32_t {
+        uint32_t at = ctx.mulhi(ingest_hash(key), hs);
+        for (uint32_t left = hs; left; left--) {
+            const K old = ctx.cas(&A.key[at], kEmpty, key);
+            if (old == kEmpty || old == key) break;
+            at = at + 1 == hs ? 0 : at + 1;
+        }
+        ctx.add(&A.val[at], (K)1);
+        return at;
+    };
+
+    // names of single tokens
+    ctx.each(128, [&](uint32_t i) { small[i] = 0; });
+    ctx.each(words, [&](uint32_t i) { A.bits[i] = 0; });
+    ctx.each(hs, [&](uint32_t i) { A.key[i] = kEmpty; A.val[i] = 0; });
+    ctx.sync();
+    ctx.each(n, [&](uint32_t i) {
+        const int32_t t = q.tok[i];
+        q.text[i] = t;
+        A.slot[i] = (I)insert((K)(uint32_t)t);
+    });
+    ctx.sync();
+    ctx.each_full(hs, [&](uint32_t i, bool on) {
+        const uint32_t c = on ? (uint32_t)A.val[i] : 0u;
+        const uint32_t start = ctx.wave_add(&small[127], c);
+        if (c) {
+            A.val[i] = (K)(((K)start << kHalf) | c);
+            A.lev[start] = 0;
+        }
+    });
+    ctx.sync();
+    auto take_names = [&](uint32_t i, uint32_t round) -> uint32_t {
+        const K v = A.val[A.slot[i]];
+        const uint32_t g = (uint32_t)(v >> kHalf), c = (uint32_t)(v & kLow);
+        A.grp[i] = (I)(c == 1 ? g | (uint32_t)kAlone : g);
+        A.size[g] = (I)c;
+        if (c > 1) active[round] = 1;
+        return g;
+    };
+    ctx.each(n, [&](uint32_t i) {
+        const uint32_t g = take_names(i, 0);
+        if (kLds) A.name1[i] = (I)g;
+    });
+    ctx.sync();
+
+    // Names of the last 2h tokens from those of the last h.  The order inside a group is
+    // that of the second names.  A group of c positions has c buckets, which cut the range of
+    // second names evenly; a running sum over all buckets says where each starts, and the few
+    // different pairs in one bucket (no more than c, nor than names in its range, hence no
+    // more than about the square root of n) are compared with each other.
+    const uint32_t shift = ctx.log2(n) + 1;          // second names are 0 .. n
+    auto bucket_of_pair = [&](K key) -> uint32_t {
+        const uint32_t g = (uint32_t)(key >> kHalf);
+        return g + (uint32_t)(((uint64_t)(key & kLow) * A.size[g]) >> shift);
+    };
+    const uint32_t prun = (n + kIngestParts - 1) / kIngestParts;
+    uint32_t round = 1;
+    for (uint32_t h = 1; h < n; h *= 2, round++) {
+        if (!active[round - 1]) break;
+        if (!kLds && h >= 16 && (ctx.log2(h) & 1) == 0) {
+            const uint32_t j = (ctx.log2(h) - 4) / 2;
+            if (j < 7) ctx.each(n, [&](uint32_t i) { A.names[j * A.stride + i] = A.grp[i]; });
+        }
+        ctx.each(hs, [&](uint32_t i) { A.key[i] = kEmpty; A.val[i] = 0; });
+        ctx.each(n, [&](uint32_t i) { A.cursor[i] = 0; });
+        ctx.sync();
+        ctx.each(n, [&](uint32_t i) {
+            const I g = A.grp[i];
+            if (g & kAlone) { A.cursor[g & (I)~kAlone] = 1; return; }
+            const uint32_t second = i >= h ? (uint32_t)(A.grp[i - h] & (I)~kAlone) + 1u : 0u;
+            A.slot[i] = (I)insert((K)(((K)g << kHalf) | (K)second));
+        });
+        ctx.sync();
+        ctx.each(hs, [&](uint32_t i) {
+            const K key = A.key[i];
+            if (key != kEmpty) ctx.add(&A.cursor[bucket_of_pair(key)], A.val[i]);
+        });
+        ctx.sync();
+        ctx.each(kIngestParts, [&](uint32_t c) {
+            uint32_t sum = 0;
+            for (uint32_t k = c * prun; k < (c + 1) * prun && k < n; k++) sum += (uint32_t)A.cursor[k];
+            A.part[c] = sum;
+        });
+        ctx.sync();
+        ctx.exclusive_sums(A.part);
+        ctx.each(kIngestParts, [&](uint32_t c) {
+            uint32_t sum = A.part[c];
+            for (uint32_t k = c * prun; k < (c + 1) * prun && k < n; k++) {
+                const uint32_t mine = (uint32_t)A.cursor[k];
+                A.cursor[k] = sum;
+                sum += mine;
+            }
+        });
+        ctx.sync();
+        ctx.each(hs, [&](uint32_t i) {
+            const K key = A.key[i];
+            if (key == kEmpty) return;
+            K *const w = &A.cursor[bucket_of_pair(key)];
+            for (K seen = *w;;) {
+                A.next[i] = (I)(seen >> kHalf);
+                const K old = ctx.cas(w, seen, (K)((seen & kLow) | ((K)(i + 1) << kHalf)));
+                if (old == seen) break;
+                seen = old;
+            }
+        });
+        ctx.sync();
+        ctx.each(hs, [&](uint32_t i) {
+            const K key = A.key[i];
+            if (key == kEmpty) return;
+            const K w = A.cursor[bucket_of_pair(key)];
+            uint32_t start = (uint32_t)(w & kLow);
+            for (uint32_t j = (uint32_t)(w >> kHalf); j; j = A.next[j - 1])
+                if (A.key[j - 1] < key) start += (uint32_t)(A.val[j - 1] & kLow);
+            A.val[i] |= (K)((K)start << kHalf);
+            if (start != (uint32_t)(key >> kHalf)) A.lev[start] = (uint8_t)round;
+        });
+        ctx.sync();
+        ctx.each(n, [&](uint32_t i) {
+            if (!(A.grp[i] & kAlone)) take_names(i, round);
+        });
+        ctx.sync();
+    }
+    // sorted order, and the common length of neighbours: at least h tokens if their groups
+    // parted in the round that took h to 2h, and fewer than 2h
+    ctx.each(n, [&](uint32_t i) { A.sa[A.grp[i] & (I)~kAlone] = (I)i; });
+    ctx.sync();
+    ctx.each(n, [&](uint32_t k) {
+        const uint32_t r = A.lev[k];
+        uint32_t l = 0;
+        if (k > 0 && r > 0) {
+            l = 1u << (r - 1);
+            const uint32_t a = A.sa[k - 1], b = A.sa[k];
+            const uint32_t most = (a < b ? a : b) + 1;
+            if (kLds) {
+                while (l < most && A.name1[a - l] == A.name1[b - l]) l++;
+            } else {
+                // strides of 16 * 4^j tokens by their names, the last few token by token
+                for (int j = 6; j >= 0; j--) {
+                    const uint32_t w = 16u << (2 * j);
+                    if (w >= (1u << (r - 1)) * 2u) continue;          // not named, or too long
+                    while (l + w <= most) {
+                        const I *const nj = A.names + (uint32_t)j * A.stride;
+                        const I x = nj[a - l], y = nj[b - l];
+                        if (x != y) break;
+                        l += w;
+                    }
+                }
+                while (l < most && q.tok[a - l] == q.tok[b - l]) l++;
+            }
+        }
+        A.lcp[k] = (I)l;
+    });
+    ctx.sync();
+    ctx.each(words, [&](uint32_t w) {
+        uint32_t least = n;
+        const uint32_t hi = 32 * w + 32 < n ? 32 * w + 32 : n;
+        for (uint32_t k = 32 * w; k < hi; k++) least = A.lcp[k] < least ? A.lcp[k] : least;
+        A.bmin[w] = (I)least;
+    });
+    ctx.sync();
+
+    // Interval of boundary k: from lb to rb, the nearest boundaries with a smaller value.
+    // Of the intervals that share lb only the widest has lcp[lb] >= lcp[rb], of those that
+    // share rb only the widest of the others: one index each, in tab[].
+    auto at_or_zero = [&](uint32_t k) -> uint32_t { return k < n ? A.lcp[k] : 0u; };
+    ctx.each(n, [&](uint32_t k) {
+        const uint32_t l = A.lcp[k];
+        if (l == 0) { A.node[k] = kNone; return; }
+        uint32_t lb = k - 1;
+        while (A.lcp[lb] >= l) {                       // ends at 0 at the latest: lcp[0] = 0
+            if ((lb & 31) == 0) {
+                uint32_t w = (lb >> 5) - 1;
+                while (A.bmin[w] >= l) w--;
+                lb = 32 * w + 31;
+            } else {
+                lb--;
+            }
+        }
+        uint32_t rb = k + 1;
+        while (rb < n && A.lcp[rb] >= l) {
+            if ((rb & 31) == 31) {
+                uint32_t w = (rb >> 5) + 1;
+                while (32 * w < n && A.bmin[w] >= l) w++;
+                rb = 32 * w;
+            } else {
+                rb++;
+            }
+        }
+        if (rb > n) rb = n;
+        const bool left = A.lcp[lb] >= at_or_zero(rb);
+        const uint32_t id = left ? lb : n + rb;
+        A.tab[id] = (I)k;                              // any boundary of the interval will do
+        A.node[k] = (I)id;
+        A.par[k] = (I)(left ? lb : rb);
+    });
+    ctx.sync();
+    ctx.each(n, [&](uint32_t k) { if (A.lcp[k]) A.node[k] = A.tab[A.node[k]]; });
+    ctx.sync();
+    ctx.each(n, [&](uint32_t k) {
+        const bool rep = A.lcp[k] && A.node[k] == (I)k;
+        A.par[k] = !rep ? kNone : (A.lcp[A.par[k]] == 0 ? kRoot : A.node[A.par[k]]);
+        A.pfx[k] = kNone;
+        A.m[k] = kNil;
+        A.sec[k] = kNil;
+    });
+    ctx.sync();
+    ctx.each(n, [&](uint32_t k) {
+        const uint32_t i = A.sa[k], lk = A.lcp[k], rk = at_or_zero(k + 1), l = lk > rk ? lk : rk;
+        I v = kRoot;
+        if (l) {
+            v = A.node[lk >= rk ? k : k + 1];
+            // the prefix is as long as what it shares with a neighbour: it is that node
+            if (l == i + 1) { A.pfx[v] = (I)i; v = A.par[v]; }
+        }
+        A.leaf[i] = v;
+    });
+    ctx.sync();
+    // first end positions: every prefix goes up until a smaller one has been there
+    ctx.each(n, [&](uint32_t i) {
+        for (I v = A.leaf[i]; v != kRoot && A.pfx[v] == kNone; v = A.par[v])
+            if (ctx.lower(&A.m[v], i) < i) break;
+    });
+    ctx.sync();
+    ctx.each(n, [&](uint32_t i) {
+        const I v = A.leaf[i];
+        if (v != kRoot && A.pfx[v] == kNone && A.m[v] != i) ctx.lower(&A.sec[v], i);
+        const I p = A.par[i];
+        if (p != kNone && A.pfx[i] == kNone && p != kRoot && A.pfx[p] == kNone && A.m[p] != A.m[i])
+            ctx.lower(&A.sec[p], A.m[i]);
+    });
+    ctx.sync();
+    ctx.each(n, [&](uint32_t k) {
+        if (A.par[k] != kNone && A.pfx[k] == kNone) ctx.bit_or(&A.bits[A.sec[k] >> 5], 1u << (A.sec[k] & 31));
+    });
+    ctx.sync();
+    // ids
+    uint32_t *const part = small + 64;               // [60]: sums of runs of words
+    constexpr uint32_t kParts = 56;
+    const uint32_t run = (words + kParts - 1) / kParts;
+    auto run_of = [&](uint32_t c, uint32_t &lo, uint32_t &hi) {
+        lo = c * run; hi = lo + run;
+        if (lo > words) lo = words;
+        if (hi > words) hi = words;
+    };
+    ctx.each(kParts, [&](uint32_t c) {
+        uint32_t lo, hi, sum = 0;
+        run_of(c, lo, hi);
+        for (uint32_t w = lo; w < hi; w++) sum += ctx.popc(A.bits[w]);
+        part[c] = sum;
+    });
+    ctx.sync();
+    ctx.each(kParts, [&](uint32_t c) {
+        uint32_t lo, hi, sum = 0;
+        run_of(c, lo, hi);
+        for (uint32_t j = 0; j < c; j++) sum += part[j];
+        for (uint32_t w = lo; w < hi; w++) { A.rank[w] = sum; sum += ctx.popc(A.bits[w]); }
+        if (c == kParts - 1) small[124] = 1 + n + sum;
+    });
+    ctx.sync();
+    auto prefix_id = [&](uint32_t i) -> uint32_t {
+        return 1 + i + A.rank[i >> 5] + ctx.popc(A.bits[i >> 5] & ((1u << (i & 31)) - 1u));
+    };
+    auto node_id = [&](I v) -> uint32_t {
+        if (v == kRoot) return 0;
+        return A.pfx[v] != kNone ? prefix_id(A.pfx[v]) : prefix_id(A.sec[v]) + 1;
+    };
+    // records, with the transition of the first occurrence inline
+    ctx.each(n, [&](uint32_t i) {
+        const uint32_t id = prefix_id(i);
+        if (i == 0) L::store(q.rec, 0, 0, kNil, 0, (uint32_t)q.tok[0], 1);
+        const bool more = i + 1 < n;
+        L::store(q.rec, id, i + 1, node_id(A.leaf[i]), i + 1, more ? (uint32_t)q.tok[i + 1] : kNil,
+                 more ? prefix_id(i + 1) : 0u);
+        if (A.par[i] != kNone && A.pfx[i] == kNone)
+            L::store(q.rec, prefix_id(A.sec[i]) + 1, A.lcp[i], node_id(A.par[i]), A.m[i] + 1,
+                     (uint32_t)q.tok[A.m[i] + 1], 0u);
+    });
+    ctx.sync();
+    if (!kLds) {
+        // the slot table held the arrays above: empty again
+        uint64_t *const s = reinterpret_cast<uint64_t *>(q.slots);
+        ctx.each(q.n_buckets * 16u, [&](uint32_t i) { s[i] = ~0ull; });
+    }
+    // The state that holds `w` tokens of the suffix path of u (u longer than that).
+    auto ancestor = [&](uint32_t u, uint32_t w) -> uint32_t {
+        for (;;) {
+            const uint32_t up = L::link(q.rec, u);
+            if (up == kNil || L::len(q.rec, up) < w) return u;
+            u = up;
+        }
+    };
+    // inline targets of the clones: they are the ids that follow a prefix with its bit set
+    ctx.each(n, [&](uint32_t i) {
+        if (!((A.bits[i >> 5] >> (i & 31)) & 1u)) return;
+        const uint32_t v = prefix_id(i) + 1;
+        uint32_t len, link, endpos, itok;
+        L::load(q.rec, v, len, link, endpos, itok);
+        L::store_idst(q.rec, v, ancestor(prefix_id(endpos), len + 1));
+    });
+    ctx.sync();
+    // All other transitions.  Position i brings the token t behind it to every state on its
+    // suffix path, up to one that has it from an earlier comer: that one goes on from there.
+    // A state whose first occurrence ends at i has t inline already, and only i passes it.
+    ctx.each(n - 1, [&](uint32_t i) {
+        const uint32_t t = (uint32_t)q.tok[i + 1];
+        uint32_t u = prefix_id(i + 1), v = L::link(q.rec, prefix_id(i)), made = 0;
+        for (;;) {
+            uint32_t len, link, endpos, itok;
+            L::load(q.rec, v, len, link, endpos, itok);
+            if (itok == t) {
+                if (endpos != i + 1) break;
+            } else {
+                const uint32_t hsh = dyn_hash(v, t);
+                uint32_t b = ctx.mulhi(hsh, q.n_buckets), at = 0;
+                int got = 2;
+                for (uint32_t left = q.n_buckets; left && got == 2; left--) {
+                    for (uint32_t j = 0; j < L::kSlots && got == 2; j++) {
+                        at = b * L::kSlots + ((hsh + j) & (L::kSlots - 1));
+                        got = L::claim(ctx, q.slots, at, v, t);
+                    }
+                    b = b + 1 == q.n_buckets ? 0 : b + 1;
+                }
+                if (got) break;
+                u = ancestor(u, len + 1);
+                L::fill(ctx, q.rec, q.slots, at, v, endpos, u);
+                made++;
+            }
+            if (v == 0) break;
+            v = link;
+        }
+        if (made) ctx.add(&small[126], made);
+    });
+    ctx.sync();
+    ctx.each(1, [&](uint32_t) {
+        small[125] = small[126] + small[124] - 1;
+        small[123] = prefix_id(n - 1);
+    });
+    ctx.sync();
+}
+
+}  // namespace sam

@@ -31,7 +31,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "sam_device.h"
+#include "sam_ingest.h"
 
 namespace sam {
 
@@ -298,15 +301,10 @@ struct Probe {
     uint32_t mh, me;
 };
 
-// Home bucket of (p, t) in a sequence's private table.  The tables are small
-// and at most half full, so a short mix is enough; one multiply-high maps the
-// hash onto the bucket count.
+// Home bucket of (p, t) in a sequence's private table.
 __device__ __forceinline__ uint32_t dyn_bucket(const DynSeq &D, uint32_t p, uint32_t t)
 {
-    uint32_t h = (p * 0x9E3779B1u) ^ (t * 0x85EBCA77u);
-    h ^= h >> 15;
-    h *= 0x2C1B3C6Du;
-    return __umulhi(h, D.n_buckets);
+    return __umulhi(dyn_hash(p, t), D.n_buckets);
 }
 
 template <class L>
@@ -1704,6 +1702,216 @@ __global__ __launch_bounds__(kScout ? 256 : 128) void sam_feed_kernel(StaticView
     emit_draft(S, B, b, lane, l1, e1, sh[3], sh[4], sh[5], match_len, draft, draft_len, source);
 }
 
+// ---- prompts: the whole automaton at once (sam_ingest.h) -----------------------
+
+//
+// Extending a sequence token by token takes 0.6 to 1.2 us a token whatever the chip has
+// free, so a prompt of 3000 tokens took 1.8 ms.  Built whole, by one workgroup with its
+// working arrays in LDS (27 bytes a token, 16-bit indices), the bound is the LDS pipeline of
+// one compute unit.  Measured, prompts and first draft together: 77 prompts of up to 3000
+// tokens 1797 -> 256 us, 48 of up to 1999 (with the batch's allocation) 1241 -> 267 us, 12 of
+// 40 001 tokens (arrays in the sequence's own tables instead of LDS) 46 -> 6 ms, 1024 of
+// 6000 5.3 -> 2.2 ms.
+constexpr int kPromptThreads = 1024;
+// The fixed cost of about sixty barriers is what the serial loops need for this many tokens.
+constexpr int64_t kPromptMinTokens = 64;
+constexpr int kPromptWaves = kPromptThreads / 64;
+
+struct PromptCtx {
+    uint32_t tid;
+    uint32_t *wsum;            // [kPromptWaves]
+
+    template <class F>
+    __device__ __forceinline__ void each(uint32_t n, F f)
+    {
+        for (uint32_t i = tid; i < n; i += kPromptThreads) f(i);
+    }
+    template <class F>
+    __device__ __forceinline__ void each_full(uint32_t n, F f)     // whole waves
+    {
+        for (uint32_t i = tid; i - tid < n; i += kPromptThreads) f(i, i < n);
+    }
+    __device__ __forceinline__ void sync() { __syncthreads(); }
+    template <class T>
+    __device__ __forceinline__ T cas(T *p, T expected, T v)
+    {
+        __hip_atomic_compare_exchange_strong(p, &expected, v, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_WORKGROUP);
+        return expected;
+    }
+    template <class T>
+    __device__ __forceinline__ T add(T *p, T v)
+    {
+        return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __device__ __forceinline__ uint32_t lower(uint32_t *p, uint32_t v)
+    {
+        return __hip_atomic_fetch_min(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __device__ __forceinline__ void bit_or(uint32_t *p, uint32_t v)
+    {
+        __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __device__ __forceinline__ uint32_t exch(uint32_t *p, uint32_t v)
+    {
+        return __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __device__ __forceinline__ uint32_t fresh(uint32_t *p)
+    {
+        return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ __forceinline__ uint32_t mulhi(uint32_t a, uint32_t b) { return __umulhi(a, b); }
+    __device__ __forceinline__ uint32_t popc(uint32_t x) { return (uint32_t)__popc(x); }
+    __device__ __forceinline__ uint32_t log2(uint32_t x) { return 31u - (uint32_t)__clz((int)x); }
+    // sum over the lower lanes and this one
+    __device__ __forceinline__ uint32_t wave_sums(uint32_t v)
+    {
+        for (int d = 1; d < 64; d *= 2) {
+            const uint32_t below = (uint32_t)__shfl_up((int)v, d);
+            if ((tid & 63) >= (uint32_t)d) v += below;
+        }
+        return v;
+    }
+    // where this lane's v places start in a counter that all lanes of the wave add to
+    __device__ __forceinline__ uint32_t wave_add(uint32_t *p, uint32_t v)
+    {
+        const uint32_t upto = wave_sums(v);
+        uint32_t base = 0;
+        if ((tid & 63) == 63 && upto) base = add(p, upto);
+        return (uint32_t)__shfl((int)base, 63) + upto - v;
+    }
+    // part[i] becomes the sum of the entries before it; thread i reads entry i
+    __device__ __forceinline__ void exclusive_sums(uint32_t *part)
+    {
+        static_assert(kIngestParts == kPromptThreads, "one entry per thread");
+        const uint32_t v = part[tid], upto = wave_sums(v);
+        if ((tid & 63) == 63) wsum[tid >> 6] = upto;
+        __syncthreads();
+        uint32_t before = 0;
+        for (uint32_t w = 0; w < (tid >> 6); w++) before += wsum[w];
+        part[tid] = before + upto - v;
+    }
+};
+
+// The static cursor after a prompt belongs to the longest suffix of the prompt that occurs
+// in the corpus, so the walk need not start at the first token: started at the root w
+// tokens before the end it finds the longest such suffix of at most w tokens, and if that is
+// shorter than w it is the one looked for.  Otherwise the window was too short: four times
+// as much.  (48 tokens cover all but a few prompts; a walk costs about 0.6 us a token.)
+__device__ __forceinline__ void static_tail(const StaticView &S, const int32_t *tok, uint32_t n,
+                                            uint32_t vocab, int lane, uint32_t &s, uint32_t &l,
+                                            uint32_t &e, uint32_t &fault, bool use_asm)
+{
+    for (uint64_t w = 48;; w *= 4) {
+        const uint32_t k = w < n ? (uint32_t)w : n;
+        s = 0; l = 0; e = 0;
+        static_feed(S, tok + (n - k), k, vocab, lane, s, l, e, fault, use_asm);
+        if (uni(l) < k || k == n || fault) return;
+    }
+}
+
+// Fresh sequences (just reset) take their prompts.  Workgroups 0 .. n_static-1 walk the
+// corpus automaton, one wave per sequence; workgroup n_static + i builds the automaton of
+// sequence i (n_static is a multiple of 8, so it runs on the XCD on which the steps of
+// sequence i will find its tables).  A token outside the vocabulary ends its prompt.
+template <class L, bool kAsm>
+__global__ __launch_bounds__(kPromptThreads) void sam_prompt_kernel(StaticView S, BatchView B,
+                                                          const int32_t *__restrict__ seq_map,
+                                                          int n_seqs, int n_static,
+                                                          const int32_t *__restrict__ tokens,
+                                                          const int64_t *__restrict__ offsets,
+                                                          uint32_t lds_tokens, uint32_t max_tokens)
+{
+    extern __shared__ __align__(16) char lds[];
+    __shared__ uint32_t bad, wsum[kPromptWaves];
+    const uint32_t vocab = (uint32_t)B.vocab;
+    const int lane = threadIdx.x & 63;
+    const bool walks = (int)blockIdx.x < n_static;
+    const int i = walks ? (int)blockIdx.x * kPromptWaves + (int)(threadIdx.x >> 6)
+                        : (int)blockIdx.x - n_static;
+    if (i >= n_seqs) return;
+    const int b = seq_map ? seq_map[i] : i;
+    SeqMeta *meta = &B.meta[b];
+    const int32_t *tok = tokens + offsets[i];
+    const int64_t count = offsets[i + 1] - offsets[i];
+    if (count <= 0) return;
+    if (count > (int64_t)B.max_seq_len || count > (int64_t)max_tokens) {
+        if (!walks && threadIdx.x == 0) {
+            meta->status |= SAM_STATUS_CAPACITY_BIT;
+            atomicOr(B.status, SAM_STATUS_CAPACITY_BIT);
+        }
+        return;
+    }
+    uint32_t n = (uint32_t)count;
+    if (walks) {
+        uint32_t first = n;
+        for (uint32_t base = 0; base < n && first == n; base += 256) {
+            uint32_t at = n;
+#pragma unroll
+            for (int u = 3; u >= 0; u--) {
+                const uint32_t j = base + 64 * u + lane;
+                if (j < n && (uint32_t)tok[j] >= vocab) at = j;
+            }
+            if (__any(at < n))
+                for (int d = 32; d; d /= 2) {
+                    const uint32_t other = (uint32_t)__shfl_xor((int)at, d);
+                    at = other < at ? other : at;
+                }
+            first = uni(at);
+        }
+        n = first;
+        uint32_t s = 0, l = 0, e = 0, fault = 0;
+        if (n) static_tail(S, tok, n, vocab, lane, s, l, e, fault, kAsm);
+        if (lane == 0) {
+            meta->s1 = s; meta->l1 = l; meta->e1 = e;
+            if (fault & SAM_STATUS_INTERNAL_BIT) atomicOr(B.status, SAM_STATUS_INTERNAL_BIT);
+        }
+        return;
+    }
+
+    if (threadIdx.x == 0) bad = n;
+    __syncthreads();
+    for (uint32_t j = threadIdx.x; j < n; j += kPromptThreads)
+        if ((uint32_t)tok[j] >= vocab) atomicMin(&bad, j);
+    __syncthreads();
+    const uint32_t first_bad = bad;
+    if (first_bad < n && threadIdx.x == 0) {
+        meta->status |= SAM_STATUS_TOKEN_BIT;
+        atomicOr(B.status, SAM_STATUS_TOKEN_BIT);
+    }
+    n = first_bad;
+    if (n == 0) return;
+    constexpr bool kCompact = L::kSlots == 16;
+    typedef typename std::conditional<kCompact, IngestCompact, IngestWide>::type IL;
+    typedef typename std::conditional<kCompact, uint16_t, uint32_t>::type I;
+    typedef typename std::conditional<kCompact, uint32_t, uint64_t>::type K;
+    const DynSeq D = dyn_region<L>(B, b);
+    const IngestSeq q{tok, n, D.text, D.rec, D.slots, D.n_buckets};
+    PromptCtx ctx{threadIdx.x, wsum};
+    uint32_t *small;
+    if (n <= lds_tokens) {
+        IngestArrays<uint16_t, uint32_t> A;
+        ingest_place_lds(A, lds, n);
+        small = A.small;
+        ingest_build<IL, true>(ctx, q, A);
+    } else {
+        IngestArrays<I, K> A;
+        ingest_place_tables(A, q, lds, n);
+        small = A.small;
+        ingest_build<IL, false>(ctx, q, A);
+    }
+    if (threadIdx.x == 0) {
+        const uint32_t last = small[123], P = IL::link(D.rec, last);
+        uint32_t len, link, endpos, itok;
+        IL::load(D.rec, P, len, link, endpos, itok);
+        meta->n = n; meta->n_states = small[124]; meta->last = last; meta->n_trans = small[125];
+        meta->s2 = P;
+        meta->p_len = len; meta->p_link = link; meta->p_endpos = endpos;
+        meta->p_head = IL::head(ctx, D.rec, P);
+        meta->p_itok = itok; meta->p_idst = IL::idst(D.rec, P);
+    }
+}
+
 // The same work for a whole schedule of steps in one launch: workgroup b runs
 // sequence b through steps 0 .. n_steps-1 on its own, so no sequence waits for
 // the longest row of another and nothing is launched in between.  Step s reads
@@ -2053,6 +2261,52 @@ hipError_t launch_feed(const StaticView &S, const BatchView &B, const int32_t *s
              break;
     }
 #undef SAM_LAUNCH_FEED
+    return hipGetLastError();
+}
+
+hipError_t launch_ingest(const StaticView &S, const BatchView &B, const int32_t *seq_map,
+                         int n_seqs, const int32_t *tokens, const int64_t *offsets,
+                         int64_t max_tokens, hipStream_t stream)
+{
+    if (max_tokens < kPromptMinTokens || max_tokens > (int64_t)kIngestMaxTokens)
+        return launch_feed(S, B, seq_map, n_seqs, tokens, offsets, nullptr, nullptr, nullptr,
+                           nullptr, nullptr, stream);
+    int dev = 0, lds_limit = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess)
+        e = hipDeviceGetAttribute(&lds_limit, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
+    if (e != hipSuccess) return e;
+    const size_t room = (size_t)lds_limit - 256;             // the kernel's own words
+    // the most tokens whose working arrays fit
+    uint32_t fit = 0, over = kIngestIdx16 + 1;
+    while (over - fit > 1) {
+        const uint32_t mid = (fit + over) / 2;
+        if (ingest_lds_bytes(mid) <= room) fit = mid; else over = mid;
+    }
+    const uint32_t most = (uint32_t)max_tokens, lds_tokens = most < fit ? most : fit;
+    size_t bytes = ingest_lds_bytes(lds_tokens);
+    if (most > lds_tokens) {
+        const size_t small = B.compact ? ingest_small_bytes<uint16_t>(most) : ingest_small_bytes<uint32_t>(most);
+        bytes = small > bytes ? small : bytes;
+        const size_t rec_bytes = (size_t)B.max_states * (B.compact ? sizeof(DynRecCompact) : sizeof(DynRec)),
+                     slot_bytes = (size_t)B.dyn_buckets * 128;
+        if (!(B.compact ? ingest_tables_fit<uint16_t, uint32_t>(most, rec_bytes, slot_bytes)
+                        : ingest_tables_fit<uint32_t, uint64_t>(most, rec_bytes, slot_bytes)) || bytes > room)
+            return launch_feed(S, B, seq_map, n_seqs, tokens, offsets, nullptr, nullptr, nullptr,
+                               nullptr, nullptr, stream);
+    }
+    const int n_static = B.has_static ? (((n_seqs + kPromptWaves - 1) / kPromptWaves + 7) & ~7) : 0;
+#define SAM_LAUNCH_PROMPT(LAYOUT, ASM)                                                          \
+    hipLaunchKernelGGL((sam_prompt_kernel<LAYOUT, ASM>), dim3(n_static + n_seqs),               \
+                       dim3(kPromptThreads), bytes, stream, S, B, seq_map, n_seqs, n_static,     \
+                       tokens, offsets, lds_tokens, most)
+    const bool cxx = B.no_asm || (S.n_buckets >> 32);
+    if (B.compact) {
+        if (cxx) SAM_LAUNCH_PROMPT(CompactDyn, false); else SAM_LAUNCH_PROMPT(CompactDyn, true);
+    } else {
+        if (cxx) SAM_LAUNCH_PROMPT(WideDyn, false); else SAM_LAUNCH_PROMPT(WideDyn, true);
+    }
+#undef SAM_LAUNCH_PROMPT
     return hipGetLastError();
 }
 

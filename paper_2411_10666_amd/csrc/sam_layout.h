@@ -141,6 +141,18 @@ inline uint64_t bucket_of(uint32_t h, uint64_t n_buckets)
     return ((uint64_t)h * n_buckets) >> 32;
 }
 
+// Hash of a transition of a sequence's own automaton.  Those tables are small and at most
+// half full, so a short mix is enough; one multiply-high maps it onto the bucket count.
+#if defined(__HIPCC__)
+__host__ __device__
+#endif
+inline uint32_t dyn_hash(uint32_t state, uint32_t token)
+{
+    uint32_t h = (state * 0x9E3779B1u) ^ (token * 0x85EBCA77u);
+    h ^= h >> 15;
+    return h * 0x2C1B3C6Du;
+}
+
 inline uint64_t static_buckets_for(int64_t n_tokens)
 {
     // transitions <= 3n; sized so that the usual ~2.1n gives a load near 0.5

@@ -1,0 +1,103 @@
+"""Prompts taken whole (one workgroup builds a sequence's automaton) against the CPU
+checker: state ids, links, lengths, transitions (through the steps that follow), bit-exact."""
+import numpy as np
+import pytest
+
+from parity_util import assert_same, run_gpu, run_oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def _text(kind, n, vocab, rng):
+    x = np.minimum((vocab * rng.random(n) ** 5).astype(np.int64), vocab - 1).astype(np.int32)
+    if kind == "copies":
+        i = 20
+        while i < n:
+            k = int(rng.integers(1, 80))
+            s = int(rng.integers(0, i))
+            k = min(k, i - s, n - i)
+            x[i:i + k] = x[s:s + k]
+            i += k + int(rng.integers(0, 40))
+    elif kind == "one token":
+        x[:] = vocab - 1
+    elif kind == "periodic":
+        x = np.resize(x[:7], n).astype(np.int32)
+        x[n // 2] = vocab - 1
+    elif kind == "every other":                    # one large group of ever new pairs
+        x = (np.arange(n) // 2 % vocab).astype(np.int32)
+        x[::2] = 0
+    return x
+
+
+def _compare(prompts, vocab, T, mode, corpus=None, steps=3, A=12, L=20):
+    from paper_2411_10666_amd import binding as sam
+    rng = np.random.default_rng(len(prompts[0]))
+    B = len(prompts)
+    acc = np.stack([[np.resize(p[len(p) // 3:], (steps, A))[s] if len(p) else np.zeros(A, np.int32)
+                     for p in prompts] for s in range(steps)]).astype(np.int32)
+    acc[:, :, 5] = rng.integers(0, vocab, size=(steps, B))
+    cnt = rng.integers(0, A + 1, size=(steps, B)).astype(np.int32)
+    try:
+        sam.sam_set_layout_override(mode)
+        g, status, _ = run_gpu(corpus, vocab, prompts, acc, cnt, T, A, L)
+    finally:
+        sam.sam_set_layout_override(0)
+    assert status == 0
+    r, _ = run_oracle(corpus, prompts, acc, cnt, A, L)
+    assert_same(g, r, has_static=corpus is not None)
+
+
+# around the shortest prompt taken whole, a workgroup's threads, the most whose arrays fit
+# into LDS (about 6230 tokens), the compact tables' limit and beyond
+@pytest.mark.parametrize("n", [63, 64, 65, 1023, 1024, 1025, 2049, 6000, 6200, 6260, 9001, 16300, 16400, 23456])
+@pytest.mark.parametrize("kind,vocab", [("zipf", 32000), ("copies", 500), ("copies", 2)])
+def test_sizes(n, kind, vocab):
+    rng = np.random.default_rng(n)
+    prompts = [_text(kind, k, vocab, rng) for k in (n, n, 1, n // 2 + 1, 0, n - 1, 40)]
+    corpus = _text("copies", 3000, vocab, rng)
+    corpus[500:1500] = np.resize(prompts[0][-900:], 1000)   # a match far longer than the first window
+    _compare(prompts, vocab, n + 40, 0, corpus)
+
+
+@pytest.mark.parametrize("kind", ["one token", "periodic", "every other"])
+@pytest.mark.parametrize("n", [700, 6100, 6400, 17001])
+def test_degenerate_texts(kind, n):
+    rng = np.random.default_rng(n)
+    _compare([_text(kind, n, 9000, rng)] * 2, 9000, n + 36, 0)
+
+
+# forced wide, tight slot tables (too small to build in: the serial kernel), C++ loops, large vocabulary
+@pytest.mark.parametrize("mode,vocab", [(1, 700), (2, 700), (3, 700), (4, 700), (5, 700), (0, 160000)])
+@pytest.mark.parametrize("n", [300, 6500])
+def test_layouts(mode, vocab, n):
+    rng = np.random.default_rng(mode)
+    prompts = [_text("copies", k, vocab, rng) for k in (n, n // 3, 77)]
+    _compare(prompts, vocab, n + 40, mode, _text("copies", 2000, vocab, rng))
+
+
+@pytest.mark.parametrize("at", [0, 1, 99, 299])
+def test_a_bad_token_ends_its_prompt(at):
+    """sam_batch_reset with a token outside the vocabulary: the prompt ends in front of it."""
+    import torch
+    from paper_2411_10666_amd import binding as sam
+    rng = np.random.default_rng(at)
+    vocab, n = 50, 300
+    corpus = _text("copies", 1000, vocab, rng)
+    prompts = [_text("copies", n, vocab, rng) for _ in range(3)]
+    dev = torch.device("cuda")
+    c = sam.sam_build(corpus, vocab)
+    offs = torch.arange(4, dtype=torch.int64, device=dev) * n
+    flat = np.concatenate(prompts)
+    batch = sam.sam_batch_init(c, torch.from_numpy(flat).to(dev), offs, 3, vocab, n + 10, 4, 4, 0)
+    bad = flat.copy()
+    bad[n + at] = vocab
+    sam.sam_batch_reset(batch, torch.arange(3, dtype=torch.int32, device=dev), torch.from_numpy(bad).to(dev), offs)
+    assert sam.sam_batch_status(batch) == sam.SAM_STATUS_TOKEN
+    out = [torch.empty(3, dtype=torch.int32, device=dev) for _ in range(7)]
+    sam.sam_batch_debug(batch, *out[:4])
+    sam.sam_batch_sizes(batch, *out[4:])
+    got = np.stack([t.cpu().numpy() for t in out], axis=1)
+    r, _ = run_oracle(corpus, [prompts[0], prompts[1][:at], prompts[2]], np.zeros((1, 3, 4), np.int32),
+                      np.zeros((1, 3), np.int32), 4, 4)
+    assert np.array_equal(got[:, :4], r[0]["cursors"])
+    assert np.array_equal(got[:, 4:], r[0]["sizes"])
