@@ -53,6 +53,9 @@ struct IngestSeq {
 
 struct IngestWide {
     static constexpr uint32_t kSlots = 8;
+    static constexpr bool kHead16 = false;       // slot indices beyond 16 bits
+    static SAM_HD void fill_next(void *, uint32_t, uint32_t, uint32_t) {}
+    static SAM_HD void store_head(void *, uint32_t, uint32_t) {}
     static SAM_HD void store(void *rec, uint32_t s, uint32_t len, uint32_t link, uint32_t endpos,
                              uint32_t itok, uint32_t idst)
     {
@@ -97,6 +100,15 @@ struct IngestWide {
 
 struct IngestCompact {
     static constexpr uint32_t kSlots = 16;
+    static constexpr bool kHead16 = true;
+    static SAM_HD void fill_next(void *slots, uint32_t at, uint32_t dst, uint32_t next)
+    {
+        (reinterpret_cast<uint32_t *>(slots) + 2 * (size_t)at)[1] = (dst & 0xFFFFu) | (next << 16);
+    }
+    static SAM_HD void store_head(void *rec, uint32_t s, uint32_t head)
+    {
+        reinterpret_cast<uint16_t *>(rec)[8 * (size_t)s + 3] = (uint16_t)head;
+    }
     static SAM_HD uint32_t widen(uint32_t v16) { return v16 == 0xFFFFu ? kNil : v16; }
     static SAM_HD void store(void *rec, uint32_t s, uint32_t len, uint32_t link, uint32_t endpos,
                              uint32_t itok, uint32_t idst)
@@ -175,8 +187,12 @@ struct IngestArrays {
     uint32_t *sec;       // [n]
     I        *names;     // [7][stride] names of the last 16 * 4^j tokens (tables in device memory only)
     uint32_t  stride;    // n rounded up to 16
+    // the states, once their records are written, and the text (all in LDS only)
+    uint32_t *state;     // [2n + 1][2] len | link << 16, min_endpos | head << 16
+    int32_t  *text;      // [n]
     // always in LDS
-    I        *bmin;      // [n / 32 + 1]
+    I        *mins1;     // minima of 8 boundaries each (with device-memory tables: there)
+    I        *mins;      // the levels above, 8 to 1, one behind the other; part[] says where
     uint32_t *bits;      // [n / 32 + 1] steps that clone
     uint32_t *rank;      // [n / 32 + 1] clones before the word
     uint32_t *small;     // [128] flags and results
@@ -198,11 +214,23 @@ struct IngestBump {
     }
 };
 
+// Minima over runs of 8, 64, 512 ... boundaries.  Every level is padded with zeros to whole
+// runs and has at least one of them, so a search to the right always ends.
+SAM_HD uint32_t ingest_pad(uint32_t count) { return (count / 8 + 1) * 8; }
+SAM_HD uint32_t ingest_first_mins(uint32_t n) { return ingest_pad(ingest_pad(n) / 8); }
+SAM_HD uint32_t ingest_upper_mins(uint32_t n)
+{
+    uint32_t sum = 0;
+    for (uint32_t c = ingest_first_mins(n); c > 8; sum += c) c = ingest_pad(c / 8);
+    return sum;
+}
+
 template <class I>
-SAM_HD size_t ingest_small_bytes(uint32_t n)
+SAM_HD size_t ingest_small_bytes(uint32_t n, bool mins)
 {
     const size_t w = n / 32 + 1;
-    return 512 + 4 * kIngestParts + (w * sizeof(I) + 15) / 16 * 16 + 2 * ((w * 4 + 15) / 16 * 16);
+    return 512 + 4 * kIngestParts + 2 * ((w * 4 + 15) / 16 * 16) +
+           (mins ? (ingest_upper_mins(n) * sizeof(I) + 15) / 16 * 16 : 0);
 }
 
 template <class I, class K>
@@ -210,7 +238,6 @@ SAM_HD void ingest_place_small(IngestArrays<I, K> &A, IngestBump &b, uint32_t n)
 {
     A.small = b.take<uint32_t>(128);
     A.part = b.take<uint32_t>(kIngestParts);
-    A.bmin = b.take<I>(n / 32 + 1);
     A.bits = b.take<uint32_t>(n / 32 + 1);
     A.rank = b.take<uint32_t>(n / 32 + 1);
 }
@@ -222,14 +249,18 @@ SAM_HD size_t ingest_lds_bytes(uint32_t n)
     const size_t h = ingest_h_size(n);
     auto up = [](size_t x) { return (x + 15) / 16 * 16; };
     const size_t sort = 2 * up(4 * h) + up(2 * h) + up(4 * (size_t)n) + 2 * up(2 * (size_t)n);
-    const size_t tree = 4 * up(2 * (size_t)n) + 2 * up(4 * (size_t)n);
-    return ingest_small_bytes<uint16_t>(n) + up(n) + 2 * up(2 * (size_t)n) + (sort > tree ? sort : tree);
+    const size_t tree = 3 * up(2 * (size_t)n) + up(2 * (size_t)ingest_pad(n)) + 2 * up(4 * (size_t)n) +
+                        up(2 * (size_t)ingest_first_mins(n)) + up(2 * (size_t)ingest_upper_mins(n));
+    const size_t all = up(n) + 2 * up(2 * (size_t)n) + (sort > tree ? sort : tree);
+    const size_t state = up(8 * (2 * (size_t)n + 1)) + up(4 * (size_t)n);
+    return ingest_small_bytes<uint16_t>(n, false) + (all > state ? all : state);
 }
 
 SAM_HD void ingest_place_lds(IngestArrays<uint16_t, uint32_t> &A, char *lds, uint32_t n)
 {
     IngestBump b{lds};
     ingest_place_small(A, b, n);
+    const IngestBump common = b;
     A.h_size = ingest_h_size(n);
     A.lev = b.take<uint8_t>(n);
     A.name1 = b.take<uint16_t>(n);
@@ -244,12 +275,17 @@ SAM_HD void ingest_place_lds(IngestArrays<uint16_t, uint32_t> &A, char *lds, uin
     A.slot = b.take<uint16_t>(n);
     A.size = b.take<uint16_t>(n);
     A.sa = t.take<uint16_t>(n);
-    A.lcp = t.take<uint16_t>(n);
+    A.lcp = t.take<uint16_t>(ingest_pad(n));
     A.par = t.take<uint16_t>(n);
     A.leaf = t.take<uint16_t>(n);
     A.m = t.take<uint32_t>(n);
     A.tab = reinterpret_cast<uint16_t *>(A.m);
     A.sec = t.take<uint32_t>(n);
+    A.mins1 = t.take<uint16_t>(ingest_first_mins(n));
+    A.mins = t.take<uint16_t>(ingest_upper_mins(n));
+    IngestBump u = common;                 // after the records are written
+    A.state = u.take<uint32_t>(2 * (2 * (size_t)n + 1));
+    A.text = u.take<int32_t>(n);
 }
 
 // The large arrays in the sequence's own tables, which hold nothing yet: 16 indices a
@@ -260,6 +296,9 @@ SAM_HD void ingest_place_tables(IngestArrays<I, K> &A, const IngestSeq &q, char 
 {
     IngestBump s{lds};
     ingest_place_small(A, s, n);
+    A.mins = s.take<I>(ingest_upper_mins(n));
+    A.state = nullptr;
+    A.text = nullptr;
     A.h_size = ingest_h_size(n);
     A.name1 = nullptr;
     IngestBump r{reinterpret_cast<char *>(q.rec)};
@@ -275,8 +314,9 @@ SAM_HD void ingest_place_tables(IngestArrays<I, K> &A, const IngestSeq &q, char 
     A.sa = r2.take<I>(n);
     A.node = r2.take<I>(n);
     A.tab = r2.take<I>(2 * (size_t)n);
+    A.mins1 = r2.take<I>(ingest_first_mins(n));
     IngestBump t{reinterpret_cast<char *>(q.slots)};
-    A.lcp = t.take<I>(n);
+    A.lcp = t.take<I>(ingest_pad(n));
     A.names = reinterpret_cast<I *>(t.p);  // names live until lcp is known, the rest after it
     A.stride = (n + 15) & ~15u;
     A.par = t.take<I>(n);
@@ -296,12 +336,15 @@ inline bool ingest_tables_fit(uint32_t n, size_t rec_bytes, size_t slot_bytes)
     size_t levels = 0;
     for (size_t w = 16; w < N; w *= 4) levels++;
     const size_t sort = 2 * up(sizeof(K) * h) + up(sizeof(I) * h) + up(sizeof(K) * N) + 2 * up(sizeof(I) * N);
-    const size_t tree = 2 * up(sizeof(I) * N) + up(2 * sizeof(I) * N);
+    const size_t tree = 2 * up(sizeof(I) * N) + up(2 * sizeof(I) * N) + up(sizeof(I) * ingest_first_mins(n));
     const size_t names = levels * sizeof(I) * ((N + 15) / 16 * 16);
     const size_t rest = 3 * up(sizeof(I) * N) + 2 * up(4 * N);
     return up(sizeof(I) * N) + up(N) + (sort > tree ? sort : tree) <= rec_bytes &&
-           up(sizeof(I) * N) + (names > rest ? names : rest) <= slot_bytes;
+           up(sizeof(I) * ingest_pad(n)) + (names > rest ? names : rest) <= slot_bytes;
 }
+
+template <class I>
+struct alignas(16) Eight { I v[8]; };
 
 // ---- the build --------------------------------------------------------------------
 
@@ -480,13 +523,63 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
         A.lcp[k] = (I)l;
     });
     ctx.sync();
-    ctx.each(words, [&](uint32_t w) {
-        uint32_t least = n;
-        const uint32_t hi = 32 * w + 32 < n ? 32 * w + 32 : n;
-        for (uint32_t k = 32 * w; k < hi; k++) least = A.lcp[k] < least ? A.lcp[k] : least;
-        A.bmin[w] = (I)least;
-    });
+    ctx.each(ingest_pad(n) - n, [&](uint32_t k) { A.lcp[n + k] = 0; });
     ctx.sync();
+    uint32_t *const level_at = A.part;               // where level j >= 2 starts in mins
+    uint32_t tops = 1;
+    {
+        const I *below = A.lcp;
+        uint32_t count = ingest_pad(n);
+        I *out = A.mins1;
+        for (;;) {
+            const uint32_t real = count / 8, padded = ingest_pad(real);
+            ctx.each(padded, [&](uint32_t w) {
+                I least = 0;
+                if (w < real) {
+                    const Eight<I> e = *reinterpret_cast<const Eight<I> *>(below + 8 * w);
+                    least = e.v[0];
+                    for (int j = 1; j < 8; j++) least = e.v[j] < least ? e.v[j] : least;
+                }
+                out[w] = least;
+            });
+            if (tops >= 2) ctx.each(1, [&](uint32_t) { level_at[tops] = (uint32_t)(out - A.mins); });
+            ctx.sync();
+            if (padded == 8) break;
+            below = out;
+            out = tops == 1 ? A.mins : out + padded;
+            count = padded;
+            tops++;
+        }
+    }
+    // of the run that holds entry `at` of a level: which entries are below l
+    auto run_mask = [&](uint32_t level, uint32_t at, uint32_t l) -> uint32_t {
+        const I *p = level == 0 ? A.lcp : (level == 1 ? A.mins1 : A.mins + level_at[level]);
+        const Eight<I> e = *reinterpret_cast<const Eight<I> *>(p + (at & ~7u));
+        uint32_t mask = 0;
+        for (int j = 0; j < 8; j++) mask |= (e.v[j] < l ? 1u : 0u) << j;
+        return mask;
+    };
+    // the nearest boundary left of k with less than l (there is one: lcp[0] = 0), and right
+    auto smaller_left = [&](uint32_t k, uint32_t l) -> uint32_t {
+        uint32_t level = 0, at = k, mask;
+        while (!(mask = run_mask(level, at, l) & ((1u << (at & 7)) - 1u)) && level < tops) { at >>= 3; level++; }
+        at = (at & ~7u) + ctx.log2(mask | 1u);
+        for (; level; level--) {
+            at *= 8;
+            at += ctx.log2(run_mask(level - 1, at, l) | 1u);
+        }
+        return at;
+    };
+    auto smaller_right = [&](uint32_t k, uint32_t l) -> uint32_t {
+        uint32_t level = 0, at = k, mask;
+        while (!(mask = run_mask(level, at, l) & (0xFEu << (at & 7)) & 0xFFu) && level < tops) { at >>= 3; level++; }
+        at = (at & ~7u) + ctx.first(mask | 0x80u);
+        for (; level; level--) {
+            at *= 8;
+            at += ctx.first(run_mask(level - 1, at, l) | 0x80u);
+        }
+        return at < n ? at : n;
+    };
 
     // Interval of boundary k: from lb to rb, the nearest boundaries with a smaller value.
     // Of the intervals that share lb only the widest has lcp[lb] >= lcp[rb], of those that
@@ -495,27 +588,7 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
     ctx.each(n, [&](uint32_t k) {
         const uint32_t l = A.lcp[k];
         if (l == 0) { A.node[k] = kNone; return; }
-        uint32_t lb = k - 1;
-        while (A.lcp[lb] >= l) {                       // ends at 0 at the latest: lcp[0] = 0
-            if ((lb & 31) == 0) {
-                uint32_t w = (lb >> 5) - 1;
-                while (A.bmin[w] >= l) w--;
-                lb = 32 * w + 31;
-            } else {
-                lb--;
-            }
-        }
-        uint32_t rb = k + 1;
-        while (rb < n && A.lcp[rb] >= l) {
-            if ((rb & 31) == 31) {
-                uint32_t w = (rb >> 5) + 1;
-                while (32 * w < n && A.bmin[w] >= l) w++;
-                rb = 32 * w;
-            } else {
-                rb++;
-            }
-        }
-        if (rb > n) rb = n;
+        const uint32_t lb = smaller_left(k, l), rb = smaller_right(k, l);
         const bool left = A.lcp[lb] >= at_or_zero(rb);
         const uint32_t id = left ? lb : n + rb;
         A.tab[id] = (I)k;                              // any boundary of the interval will do
@@ -605,16 +678,30 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
                      (uint32_t)q.tok[A.m[i] + 1], 0u);
     });
     ctx.sync();
-    if (!kLds) {
+    const uint32_t states = small[124];
+    if (kLds) {
+        // the walks below read the states and the text from LDS
+        ctx.each(states, [&](uint32_t v) {
+            uint32_t len, link, endpos, itok;
+            L::load(q.rec, v, len, link, endpos, itok);
+            A.state[2 * v] = len | (link << 16);
+            A.state[2 * v + 1] = endpos | 0xFFFF0000u;
+        });
+        ctx.each(n, [&](uint32_t i) { A.text[i] = q.tok[i]; });
+        ctx.sync();
+    } else {
         // the slot table held the arrays above: empty again
         uint64_t *const s = reinterpret_cast<uint64_t *>(q.slots);
-        ctx.each(q.n_buckets * 16u, [&](uint32_t i) { s[i] = ~0ull; });
+        ctx.each(q.n_buckets * 16u, [&](uint32_t i) { s[i] = ~(uint64_t)0; });
     }
-    // The state that holds `w` tokens of the suffix path of u (u longer than that).
+    // the root's link reads as kNil or, from LDS, as 0xFFFF; nothing asks for it
+    auto link_of = [&](uint32_t v) -> uint32_t { return kLds ? A.state[2 * v] >> 16 : L::link(q.rec, v); };
+    auto len_of = [&](uint32_t v) -> uint32_t { return kLds ? A.state[2 * v] & 0xFFFFu : L::len(q.rec, v); };
+    // The state that holds w tokens of the suffix path of u (u is that long, w > 0).
     auto ancestor = [&](uint32_t u, uint32_t w) -> uint32_t {
         for (;;) {
-            const uint32_t up = L::link(q.rec, u);
-            if (up == kNil || L::len(q.rec, up) < w) return u;
+            const uint32_t up = link_of(u);
+            if (len_of(up) < w) return u;
             u = up;
         }
     };
@@ -623,7 +710,12 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
         if (!((A.bits[i >> 5] >> (i & 31)) & 1u)) return;
         const uint32_t v = prefix_id(i) + 1;
         uint32_t len, link, endpos, itok;
-        L::load(q.rec, v, len, link, endpos, itok);
+        if (kLds) {
+            len = len_of(v);
+            endpos = A.state[2 * v + 1] & 0xFFFFu;
+        } else {
+            L::load(q.rec, v, len, link, endpos, itok);
+        }
         L::store_idst(q.rec, v, ancestor(prefix_id(endpos), len + 1));
     });
     ctx.sync();
@@ -631,11 +723,19 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
     // suffix path, up to one that has it from an earlier comer: that one goes on from there.
     // A state whose first occurrence ends at i has t inline already, and only i passes it.
     ctx.each(n - 1, [&](uint32_t i) {
-        const uint32_t t = (uint32_t)q.tok[i + 1];
-        uint32_t u = prefix_id(i + 1), v = L::link(q.rec, prefix_id(i)), made = 0;
+        const uint32_t t = (uint32_t)(kLds ? A.text[i + 1] : q.tok[i + 1]);
+        uint32_t u = prefix_id(i + 1), v = link_of(prefix_id(i)), made = 0;
         for (;;) {
             uint32_t len, link, endpos, itok;
-            L::load(q.rec, v, len, link, endpos, itok);
+            if (kLds) {
+                const uint32_t a = A.state[2 * v];
+                len = a & 0xFFFFu;
+                link = a >> 16;
+                endpos = A.state[2 * v + 1] & 0xFFFFu;
+                itok = (uint32_t)A.text[endpos];
+            } else {
+                L::load(q.rec, v, len, link, endpos, itok);
+            }
             if (itok == t) {
                 if (endpos != i + 1) break;
             } else {
@@ -651,7 +751,10 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
                 }
                 if (got) break;
                 u = ancestor(u, len + 1);
-                L::fill(ctx, q.rec, q.slots, at, v, endpos, u);
+                if (kLds && L::kHead16)
+                    L::fill_next(q.slots, at, u, ctx.exch(&A.state[2 * v + 1], endpos | (at << 16)) >> 16);
+                else
+                    L::fill(ctx, q.rec, q.slots, at, v, endpos, u);
                 made++;
             }
             if (v == 0) break;
@@ -659,6 +762,13 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
         }
         if (made) ctx.add(&small[126], made);
     });
+    if (kLds && L::kHead16) {
+        ctx.sync();
+        ctx.each(states, [&](uint32_t v) {
+            const uint32_t head = A.state[2 * v + 1] >> 16;
+            if (head != 0xFFFFu) L::store_head(q.rec, v, head);
+        });
+    }
     ctx.sync();
     ctx.each(1, [&](uint32_t) {
         small[125] = small[126] + small[124] - 1;

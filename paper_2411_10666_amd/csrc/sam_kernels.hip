@@ -1708,10 +1708,14 @@ __global__ __launch_bounds__(kScout ? 256 : 128) void sam_feed_kernel(StaticView
 // Extending a sequence token by token takes 0.6 to 1.2 us a token whatever the chip has
 // free, so a prompt of 3000 tokens took 1.8 ms.  Built whole, by one workgroup with its
 // working arrays in LDS (27 bytes a token, 16-bit indices), the bound is the LDS pipeline of
-// one compute unit.  Measured, prompts and first draft together: 77 prompts of up to 3000
-// tokens 1797 -> 256 us, 48 of up to 1999 (with the batch's allocation) 1241 -> 267 us, 12 of
-// 40 001 tokens (arrays in the sequence's own tables instead of LDS) 46 -> 6 ms, 1024 of
-// 6000 5.3 -> 2.2 ms.
+// one compute unit.  Measured, sam_batch_reset: one prompt of 6000 tokens 210 us, 64 of 2048
+// 125 us (1.2 ms token by token), 1024 of 2048 424 us, 1024 of 6000 1.16 ms (5.3 ms), 12 of
+// 40 001 tokens (arrays in the sequence's own tables instead of LDS) 4.5 ms (46 ms).  Of the
+// 165 us that one workgroup needs for 6000 tokens, the sort takes 75, the intervals 19 and
+// the transitions 61 (a compare-and-swap in the slot table each).  Two parts were three
+// times that: the nearest smaller values scanned in runs of 32 (130 us; now a tree of minima
+// of 8, one 16-byte read a level) and the transitions walking the records in memory instead
+// of their copies in LDS (122 us).
 constexpr int kPromptThreads = 1024;
 // The fixed cost of about sixty barriers is what the serial loops need for this many tokens.
 constexpr int64_t kPromptMinTokens = 64;
@@ -1762,6 +1766,7 @@ struct PromptCtx {
     }
     __device__ __forceinline__ uint32_t mulhi(uint32_t a, uint32_t b) { return __umulhi(a, b); }
     __device__ __forceinline__ uint32_t popc(uint32_t x) { return (uint32_t)__popc(x); }
+    __device__ __forceinline__ uint32_t first(uint32_t x) { return (uint32_t)__builtin_ctz(x); }
     __device__ __forceinline__ uint32_t log2(uint32_t x) { return 31u - (uint32_t)__clz((int)x); }
     // sum over the lower lanes and this one
     __device__ __forceinline__ uint32_t wave_sums(uint32_t v)
@@ -2286,7 +2291,8 @@ hipError_t launch_ingest(const StaticView &S, const BatchView &B, const int32_t 
     const uint32_t most = (uint32_t)max_tokens, lds_tokens = most < fit ? most : fit;
     size_t bytes = ingest_lds_bytes(lds_tokens);
     if (most > lds_tokens) {
-        const size_t small = B.compact ? ingest_small_bytes<uint16_t>(most) : ingest_small_bytes<uint32_t>(most);
+        const size_t small = B.compact ? ingest_small_bytes<uint16_t>(most, true)
+                                       : ingest_small_bytes<uint32_t>(most, true);
         bytes = small > bytes ? small : bytes;
         const size_t rec_bytes = (size_t)B.max_states * (B.compact ? sizeof(DynRecCompact) : sizeof(DynRec)),
                      slot_bytes = (size_t)B.dyn_buckets * 128;
