@@ -10,55 +10,63 @@ namespace sam {
 
 namespace {
 
-// Maximum of a value over the 64 lanes, the same in every lane.  Within a row of
-// 16 lanes by four data-parallel-primitive moves (a butterfly would need the LDS
-// crossbar, whose round trip is what a pop of the queue would then be spent on),
-// across the four rows through the scalar unit.
+__device__ __forceinline__ uint32_t uni(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
+
+// Maximum of a value over the 64 lanes: data-parallel-primitive moves that the compiler
+// folds into the maximum itself (0 is what a lane without a partner compares with), within
+// rows of 16 lanes and then row by row; the last lane has it.
 __device__ __forceinline__ uint32_t wave_max_u32(uint32_t x)
 {
-    uint32_t y;
-    y = (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0xB1, 0xF, 0xF, false);   // lanes i ^ 1
-    x = x > y ? x : y;
-    y = (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x4E, 0xF, 0xF, false);   // lanes i ^ 2
-    x = x > y ? x : y;
-    y = (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x141, 0xF, 0xF, false);  // 7 - i in each half row
-    x = x > y ? x : y;
-    y = (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x140, 0xF, 0xF, false);  // 15 - i in each row
-    x = x > y ? x : y;
-    const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)x, 0);
-    const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)x, 16);
-    const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)x, 32);
-    const uint32_t d = (uint32_t)__builtin_amdgcn_readlane((int)x, 48);
-    const uint32_t ab = a > b ? a : b, cd = c > d ? c : d;
-    return ab > cd ? ab : cd;
+#define SAM_DPP_MAX(ctrl, rows)                                                                    \
+    do {                                                                                           \
+        const uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, rows, 0xF, false); \
+        x = x > y ? x : y;                                                                         \
+    } while (0)
+    SAM_DPP_MAX(0xB1, 0xF);       // lanes i ^ 1
+    SAM_DPP_MAX(0x4E, 0xF);       // lanes i ^ 2
+    SAM_DPP_MAX(0x141, 0xF);      // 7 - i in each half row
+    SAM_DPP_MAX(0x140, 0xF);      // 15 - i in each row
+    SAM_DPP_MAX(0x142, 0xA);      // rows 1 and 3: the last lane of the row before
+    SAM_DPP_MAX(0x143, 0xC);      // rows 2 and 3: the last lane of row 1
+#undef SAM_DPP_MAX
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
 }
 
 }  // namespace
 
 // Tree draft by best-first expansion over the top-k successors (Algorithm 4),
-// one wavefront per sequence.  The priority queue lives in LDS as an append-only
-// array; an entry's key packs (probability bits, ~push index), so the maximum
-// key is the largest probability and, among equals, the entry pushed first.  The
-// k children of the popped state are fetched by k lanes in one request and appended
-// in table order; while that request travels, the lanes scan the entries already
-// queued and reduce them to their best (two 32-bit wave reductions), so that the next
-// pop (that best, or the first of the new children) is known as soon as the children are.
-// Probabilities are float products rounded once per edge.
+// one wavefront per sequence.  Entry number i of the priority queue (in the order of the
+// pushes) lives in lane i % 64, register i / 64: its probability bits (0: popped or not
+// there yet) and its state.  The largest probability comes first and, among equals, the
+// entry pushed first.
+//
+// A pop is one dependent memory read (the table row of the popped state's k children) and
+// the work between its arrival and the next request.  The lanes that will hold the
+// children request them, so they arrive where they stay.  Of the children only the first
+// can be the next pop (a row is ordered by falling probability, and the product with the
+// parent's probability keeps that order), and the best of the entries already queued was
+// found while the request travelled: when the row is here, one product, two lane reads and
+// a compare give the next state, and its row is requested before anything else is done.
+// Queueing the children and the search for the best entry follow in that request's shadow.
+// Nothing on that path goes through LDS; it takes tokens and parents (written when pushed)
+// and the popped entries, and gives them back once, when the draft is written out.
+// Probabilities are float products rounded once per edge.  The rest of a pop's 0.45 us is
+// the row's round trip (a 69 MB table; a call of 256 drafts of 40 entries, k = 4: 18 us,
+// 21 us with the queue in LDS).  Asking for the row of the queue's best entry ahead, in case
+// the next pop is that one, cost 2.4 us a call: the two requests are waited for together.
+template <int R>
 __global__ __launch_bounds__(64) void sam_tree_kernel(StaticView S, BatchView B, int max_size,
                                                        int32_t *__restrict__ tokens,
                                                        int32_t *__restrict__ parents,
                                                        float *__restrict__ probs,
                                                        int32_t *__restrict__ sizes)
 {
-    constexpr int kQ = kMaxTreeSize * kMaxTopK + 1;
-    __shared__ unsigned long long qkey[kQ];
-    __shared__ uint32_t qstate[kQ];
-    __shared__ int32_t qtok[kQ];
-    __shared__ int32_t qpar[kQ];
-    // the draft is collected here and written out once at the end: a store per pop would
-    // sit in the same in-order queue as the pop's table read and be waited for with it
-    __shared__ int32_t otok[kMaxTreeSize];
-    __shared__ int32_t opar[kMaxTreeSize];
+    __shared__ int32_t qtok[64 * R];
+    __shared__ int32_t qpar[64 * R];
+    __shared__ int32_t oidx[kMaxTreeSize];
     __shared__ float   oprob[kMaxTreeSize];
     const int b = blockIdx.x;
     const int lane = threadIdx.x;
@@ -66,85 +74,83 @@ __global__ __launch_bounds__(64) void sam_tree_kernel(StaticView S, BatchView B,
     const int k = S.top_k;
     int dn = 0;
     if (m.n > 0) {
+        uint32_t prob[R], state[R];
+#pragma unroll
+        for (int r = 0; r < R; r++) { prob[r] = 0; state[r] = 0; }
         if (lane == 0) {
-            qkey[0] = ((unsigned long long)__float_as_uint(1.0f) << 32) | 0xFFFFFFFFull;
-            qstate[0] = m.s1;
             qtok[0] = B.dyn_text[(size_t)b * B.max_seq_len + m.n - 1];
             qpar[0] = -1;
         }
-        __syncthreads();
         int qn = 1;
-        unsigned long long best = qkey[0];              // the next entry to pop (0: queue empty)
-        while (dn < max_size && best != 0) {
-            const uint32_t idx = 0xFFFFFFFFu - (uint32_t)best;
-            const float p = __uint_as_float((uint32_t)(best >> 32));
-            const uint32_t st = qstate[idx];
-            // the children's table row is the one dependent memory read of a pop: request
-            // it first, and look for the best of the entries already queued while it travels
-            TopEnt e = {0, 0, 0.0f};
-            if (lane < k) e = S.topk[(size_t)st * k + lane];
-            if (lane == 0) {
-                otok[dn] = qtok[idx];
-                opar[dn] = qpar[idx];
-                oprob[dn] = p;
-            }
-            unsigned long long mine = 0;
-            for (int i = lane; i < qn; i += 256) {
-                // four independent reads per round (clamped, then masked), one wait
-                unsigned long long key[4];
-#pragma unroll
-                for (int u = 0; u < 4; u++) {
-                    const int at = i + 64 * u;
-                    key[u] = qkey[at < kQ ? at : kQ - 1];
-                }
-#pragma unroll
-                for (int u = 0; u < 4; u++) {
-                    const int at = i + 64 * u;
-                    if (at >= qn || (uint32_t)at == idx) key[u] = 0;
-                    mine = key[u] > mine ? key[u] : mine;
-                }
-            }
-            // the best of the entries already queued, still in the shadow of the request: the
-            // largest 64-bit key is the largest upper half, then the largest lower half
-            // among the lanes that hold that upper half
-            const uint32_t hi = wave_max_u32((uint32_t)(mine >> 32));
-            const uint32_t lo = wave_max_u32((uint32_t)(mine >> 32) == hi ? (uint32_t)mine : 0u);
-            best = ((unsigned long long)hi << 32) | lo;
-            // (the children are first looked at here, after the reductions: the empty
-            // statement keeps the compiler from waiting for them in their middle)
-            asm volatile("" : "+v"(e.dst) : "s"(hi), "s"(lo));
-            const bool valid = e.dst != 0;
-            const unsigned long long mask = __ballot(valid);
-            unsigned long long mine_new = 0;
-            if (valid) {
-                const int pos = qn + __popcll(mask & ((1ull << lane) - 1ull));
-                const float pn = __fmul_rn(p, e.prob);
-                const unsigned long long key = ((unsigned long long)__float_as_uint(pn) << 32) |
-                                               (unsigned long long)(0xFFFFFFFFu - (uint32_t)pos);
-                qkey[pos] = key;
-                qstate[pos] = e.dst;
-                qtok[pos] = (int32_t)e.token;
-                qpar[pos] = dn;
-                mine_new = key;
-            }
-            if (lane == 0) qkey[idx] = 0;               // popped
-            // A table row lists a state's successors by falling frequency, hence by falling
-            // probability (the product with p rounds monotonically), and is filled from its
-            // first entry on: the best of the new children is lane 0's, and among equal
-            // products it is also the one pushed first.
-            const unsigned long long first_new =
-                ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(mine_new >> 32)) << 32) |
-                (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)mine_new);
-            best = first_new > best ? first_new : best;
-            qn += __popcll(mask);
+        uint32_t st = (uint32_t)__builtin_amdgcn_readfirstlane((int)m.s1);
+        uint32_t p = __float_as_uint(1.0f);
+        int idx = 0;                                     // the popped entry
+        // Lane (first + j) % 64 asks for child j, the other lanes for child 0 once more: no
+        // branch, so the result stays in the registers it arrives in until it is needed.
+        auto request = [&](uint32_t of, int first) {
+            const int j = (lane - first) & 63;
+            return S.topk[(size_t)of * (uint32_t)k + (uint32_t)(j < k ? j : 0)];
+        };
+        TopEnt e = request(st, qn);
+        uint32_t best = 0, best_state = 0;               // of the queue, the popped entry left out
+        int best_at = 0;
+        for (;;) {
+            oidx[dn] = idx;                              // (every lane writes the same)
+            oprob[dn] = __uint_as_float(p);
             dn++;
-            __syncthreads();
+            if (dn == max_size) break;
+            const int mine_no = (lane - qn) & 63;
+            const bool valid = e.dst != 0 && mine_no < k;
+            const uint32_t pn = valid ? __float_as_uint(__fmul_rn(__uint_as_float(p), e.prob)) : 0u;
+            const uint32_t first_p = (uint32_t)__builtin_amdgcn_readlane((int)pn, qn & 63);
+            const uint32_t first_state = (uint32_t)__builtin_amdgcn_readlane((int)e.dst, qn & 63);
+            const bool child = first_p > best;           // a tie goes to the entry pushed earlier
+            if (!child && best == 0) break;              // nothing left
+            // the number a child in this lane takes (the compares below never meet -1)
+            const int slot = valid ? qn + mine_no : -1;
+            idx = (int)uni((uint32_t)(child ? qn : best_at));
+            qn = (int)uni((uint32_t)(qn + __popcll(__ballot(valid))));
+            st = uni(child ? first_state : best_state);
+            p = uni(child ? first_p : best);
+            const TopEnt coming = request(st, qn);
+            if (valid) {
+                qtok[slot] = (int32_t)e.token;
+                qpar[slot] = dn - 1;
+            }
+#pragma unroll
+            for (int r = 0; r < R; r++) {
+                const bool here = slot == 64 * r + lane;
+                prob[r] = here ? pn : prob[r];
+                state[r] = here ? e.dst : state[r];
+                prob[r] = idx == 64 * r + lane ? 0u : prob[r];       // popped
+            }
+            // The best of the queue.  Among equals the entry pushed first is the one in the
+            // lowest register that has one, and there in the lowest lane.
+            uint32_t mine = prob[0];
+#pragma unroll
+            for (int r = 1; r < R; r++) mine = prob[r] > mine ? prob[r] : mine;
+            best = wave_max_u32(mine);
+#pragma unroll
+            for (int r = R - 1; r >= 0; r--) {
+                const unsigned long long holders = __ballot(prob[r] == best);
+                const int from = __builtin_ctzll(holders | (1ull << 63));
+                const uint32_t its = (uint32_t)__builtin_amdgcn_readlane((int)state[r], from);
+                best_at = holders ? 64 * r + from : best_at;
+                best_state = holders ? its : best_state;
+            }
+            // Only here is the row waited for: as plain assignments these moves (and the wait
+            // for the row with them) end up in front of the search.
+            asm volatile("v_mov_b32 %0, %3\n\tv_mov_b32 %1, %4\n\tv_mov_b32 %2, %5"
+                         : "=&v"(e.token), "=&v"(e.dst), "=&v"(e.prob)
+                         : "v"(coming.token), "v"(coming.dst), "v"(coming.prob), "s"(best));
         }
     }
+    __syncthreads();
     for (int i = lane; i < max_size; i += 64) {
         const bool have = i < dn;
-        tokens[(size_t)b * max_size + i] = have ? otok[i] : -1;
-        parents[(size_t)b * max_size + i] = have ? opar[i] : -1;
+        const int q = have ? oidx[i] : 0;
+        tokens[(size_t)b * max_size + i] = have ? qtok[q] : -1;
+        parents[(size_t)b * max_size + i] = have ? qpar[q] : -1;
         probs[(size_t)b * max_size + i] = have ? oprob[i] : 0.0f;
     }
     if (lane == 0) sizes[b] = dn;
@@ -153,8 +159,18 @@ __global__ __launch_bounds__(64) void sam_tree_kernel(StaticView S, BatchView B,
 hipError_t launch_tree(const StaticView &S, const BatchView &B, int max_size, int32_t *tokens,
                        int32_t *parents, float *probs, int32_t *sizes, hipStream_t stream)
 {
-    hipLaunchKernelGGL(sam_tree_kernel, dim3(B.batch), dim3(64), 0, stream, S, B, max_size, tokens,
-                       parents, probs, sizes);
+    // entries that can ever be pushed: the start and k children of every pop but the last
+    const int most = 1 + (max_size - 1) * S.top_k;
+#define SAM_LAUNCH_TREE(R)                                                                     \
+    hipLaunchKernelGGL((sam_tree_kernel<R>), dim3(B.batch), dim3(64), 0, stream, S, B,         \
+                       max_size, tokens, parents, probs, sizes)
+    static_assert(1 + (kMaxTreeSize - 1) * kMaxTopK <= 64 * 16, "the largest queue");
+    if (most <= 64 * 2) SAM_LAUNCH_TREE(2);
+    else if (most <= 64 * 3) SAM_LAUNCH_TREE(3);
+    else if (most <= 64 * 5) SAM_LAUNCH_TREE(5);
+    else if (most <= 64 * 8) SAM_LAUNCH_TREE(8);
+    else SAM_LAUNCH_TREE(16);
+#undef SAM_LAUNCH_TREE
     return hipGetLastError();
 }
 
