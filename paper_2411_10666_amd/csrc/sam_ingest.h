@@ -199,7 +199,7 @@ struct IngestArrays {
     uint32_t *part;      // [kIngestParts] partial sums
 };
 
-constexpr uint32_t kIngestParts = 1024;
+constexpr uint32_t kIngestParts = 1024;      // at least one for every thread of a workgroup
 
 SAM_HD uint32_t ingest_h_size(uint32_t n) { return n + n / 4 + 64; }
 
@@ -425,7 +425,9 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
         const uint32_t g = (uint32_t)(key >> kHalf);
         return g + (uint32_t)(((uint64_t)(key & kLow) * A.size[g]) >> shift);
     };
-    const uint32_t prun = (n + kIngestParts - 1) / kIngestParts;
+    constexpr uint32_t kRuns = C::kThreads;          // of the running sum, one for each thread
+    static_assert(kRuns <= kIngestParts, "part[] holds one sum for each thread");
+    const uint32_t prun = (n + kRuns - 1) / kRuns;
     uint32_t round = 1;
     for (uint32_t h = 1; h < n; h *= 2, round++) {
         if (!active[round - 1]) break;
@@ -448,14 +450,14 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
             if (key != kEmpty) ctx.add(&A.cursor[bucket_of_pair(key)], A.val[i]);
         });
         ctx.sync();
-        ctx.each(kIngestParts, [&](uint32_t c) {
+        ctx.each(kRuns, [&](uint32_t c) {
             uint32_t sum = 0;
             for (uint32_t k = c * prun; k < (c + 1) * prun && k < n; k++) sum += (uint32_t)A.cursor[k];
             A.part[c] = sum;
         });
         ctx.sync();
         ctx.exclusive_sums(A.part);
-        ctx.each(kIngestParts, [&](uint32_t c) {
+        ctx.each(kRuns, [&](uint32_t c) {
             uint32_t sum = A.part[c];
             for (uint32_t k = c * prun; k < (c + 1) * prun && k < n; k++) {
                 const uint32_t mine = (uint32_t)A.cursor[k];

@@ -1704,47 +1704,60 @@ __global__ __launch_bounds__(kScout ? 256 : 128) void sam_feed_kernel(StaticView
 
 // ---- prompts: the whole automaton at once (sam_ingest.h) -----------------------
 
-//
 // Extending a sequence token by token takes 0.6 to 1.2 us a token whatever the chip has
 // free, so a prompt of 3000 tokens took 1.8 ms.  Built whole, by one workgroup with its
 // working arrays in LDS (27 bytes a token, 16-bit indices), the bound is the LDS pipeline of
 // one compute unit.  Measured, sam_batch_reset: one prompt of 6000 tokens 210 us, 64 of 2048
 // 125 us (1.2 ms token by token), 1024 of 2048 424 us, 1024 of 6000 1.16 ms (5.3 ms), 12 of
-// 40 001 tokens (arrays in the sequence's own tables instead of LDS) 4.5 ms (46 ms).  Of the
+// 40 001 tokens (arrays in the sequence's own tables instead of LDS) 3.5 ms (46 ms).  Of the
 // 165 us that one workgroup needs for 6000 tokens, the sort takes 75, the intervals 19 and
 // the transitions 61 (a compare-and-swap in the slot table each).  Two parts were three
 // times that: the nearest smaller values scanned in runs of 32 (130 us; now a tree of minima
 // of 8, one 16-byte read a level) and the transitions walking the records in memory instead
-// of their copies in LDS (122 us).
-constexpr int kPromptThreads = 1024;
+// of their copies in LDS (122 us).  What is left of the transitions is the rate at which one
+// compute unit gets compare-and-swaps on scattered lines through: lanes that go on with the
+// next position as soon as theirs has ended, instead of waiting for the longest path of their
+// wave, took 218 against 218 us for one prompt of 6000 tokens, and 1.22 against 1.18 ms for 1024.
+//
+// A workgroup has 1024 threads, or 256 where there are more workgroups than are resident at
+// 1024 threads and the prompts are so short that 256 suffice.  Measured, 1024 against 256
+// threads: 256 prompts of 256 tokens 88 against 90 us, of 1024 121 against 155; 300 of 64 97
+// against 78, of 256 116 against 96, of 1024 164 against 181; 512 of 512 137 against 127, of
+// 1024 178 against 195; 640 of 1024 223 against 207; 1024 of 64 150 against 82 (92 token by
+// token), of 512 215 against 152, of 1024 287 against 250, of 1500 387 against 422.
+inline bool short_prompts(int n_seqs, int64_t max_tokens, int n_cu)
+{
+    return (n_seqs > n_cu && max_tokens <= 512) || (n_seqs > 2 * n_cu && max_tokens <= 1024);
+}
 // The fixed cost of about sixty barriers is what the serial loops need for this many tokens.
 constexpr int64_t kPromptMinTokens = 64;
-constexpr int kPromptWaves = kPromptThreads / 64;
 
+template <int T>
 struct PromptCtx {
+    static constexpr uint32_t kThreads = T;
     uint32_t tid;
-    uint32_t *wsum;            // [kPromptWaves]
+    uint32_t *wsum;            // [T / 64]
 
     template <class F>
     __device__ __forceinline__ void each(uint32_t n, F f)
     {
-        for (uint32_t i = tid; i < n; i += kPromptThreads) f(i);
+        for (uint32_t i = tid; i < n; i += T) f(i);
     }
     template <class F>
     __device__ __forceinline__ void each_full(uint32_t n, F f)     // whole waves
     {
-        for (uint32_t i = tid; i - tid < n; i += kPromptThreads) f(i, i < n);
+        for (uint32_t i = tid; i - tid < n; i += T) f(i, i < n);
     }
     __device__ __forceinline__ void sync() { __syncthreads(); }
-    template <class T>
-    __device__ __forceinline__ T cas(T *p, T expected, T v)
+    template <class U>
+    __device__ __forceinline__ U cas(U *p, U expected, U v)
     {
         __hip_atomic_compare_exchange_strong(p, &expected, v, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_WORKGROUP);
         return expected;
     }
-    template <class T>
-    __device__ __forceinline__ T add(T *p, T v)
+    template <class U>
+    __device__ __forceinline__ U add(U *p, U v)
     {
         return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
@@ -1788,7 +1801,6 @@ struct PromptCtx {
     // part[i] becomes the sum of the entries before it; thread i reads entry i
     __device__ __forceinline__ void exclusive_sums(uint32_t *part)
     {
-        static_assert(kIngestParts == kPromptThreads, "one entry per thread");
         const uint32_t v = part[tid], upto = wave_sums(v);
         if ((tid & 63) == 63) wsum[tid >> 6] = upto;
         __syncthreads();
@@ -1819,8 +1831,8 @@ __device__ __forceinline__ void static_tail(const StaticView &S, const int32_t *
 // corpus automaton, one wave per sequence; workgroup n_static + i builds the automaton of
 // sequence i (n_static is a multiple of 8, so it runs on the XCD on which the steps of
 // sequence i will find its tables).  A token outside the vocabulary ends its prompt.
-template <class L, bool kAsm>
-__global__ __launch_bounds__(kPromptThreads) void sam_prompt_kernel(StaticView S, BatchView B,
+template <class L, bool kAsm, int T>
+__global__ __launch_bounds__(T) void sam_prompt_kernel(StaticView S, BatchView B,
                                                           const int32_t *__restrict__ seq_map,
                                                           int n_seqs, int n_static,
                                                           const int32_t *__restrict__ tokens,
@@ -1828,11 +1840,11 @@ __global__ __launch_bounds__(kPromptThreads) void sam_prompt_kernel(StaticView S
                                                           uint32_t lds_tokens, uint32_t max_tokens)
 {
     extern __shared__ __align__(16) char lds[];
-    __shared__ uint32_t bad, wsum[kPromptWaves];
+    __shared__ uint32_t bad, wsum[T / 64];
     const uint32_t vocab = (uint32_t)B.vocab;
     const int lane = threadIdx.x & 63;
     const bool walks = (int)blockIdx.x < n_static;
-    const int i = walks ? (int)blockIdx.x * kPromptWaves + (int)(threadIdx.x >> 6)
+    const int i = walks ? (int)blockIdx.x * (T / 64) + (int)(threadIdx.x >> 6)
                         : (int)blockIdx.x - n_static;
     if (i >= n_seqs) return;
     const int b = seq_map ? seq_map[i] : i;
@@ -1876,7 +1888,7 @@ __global__ __launch_bounds__(kPromptThreads) void sam_prompt_kernel(StaticView S
 
     if (threadIdx.x == 0) bad = n;
     __syncthreads();
-    for (uint32_t j = threadIdx.x; j < n; j += kPromptThreads)
+    for (uint32_t j = threadIdx.x; j < n; j += T)
         if ((uint32_t)tok[j] >= vocab) atomicMin(&bad, j);
     __syncthreads();
     const uint32_t first_bad = bad;
@@ -1892,7 +1904,7 @@ __global__ __launch_bounds__(kPromptThreads) void sam_prompt_kernel(StaticView S
     typedef typename std::conditional<kCompact, uint32_t, uint64_t>::type K;
     const DynSeq D = dyn_region<L>(B, b);
     const IngestSeq q{tok, n, D.text, D.rec, D.slots, D.n_buckets};
-    PromptCtx ctx{threadIdx.x, wsum};
+    PromptCtx<T> ctx{threadIdx.x, wsum};
     uint32_t *small;
     if (n <= lds_tokens) {
         IngestArrays<uint16_t, uint32_t> A;
@@ -2276,10 +2288,12 @@ hipError_t launch_ingest(const StaticView &S, const BatchView &B, const int32_t 
     if (max_tokens < kPromptMinTokens || max_tokens > (int64_t)kIngestMaxTokens)
         return launch_feed(S, B, seq_map, n_seqs, tokens, offsets, nullptr, nullptr, nullptr,
                            nullptr, nullptr, stream);
-    int dev = 0, lds_limit = 0;
+    int dev = 0, lds_limit = 0, n_cu = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess)
         e = hipDeviceGetAttribute(&lds_limit, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
+    if (e == hipSuccess)
+        e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess) return e;
     const size_t room = (size_t)lds_limit - 256;             // the kernel's own words
     // the most tokens whose working arrays fit
@@ -2301,11 +2315,17 @@ hipError_t launch_ingest(const StaticView &S, const BatchView &B, const int32_t 
             return launch_feed(S, B, seq_map, n_seqs, tokens, offsets, nullptr, nullptr, nullptr,
                                nullptr, nullptr, stream);
     }
-    const int n_static = B.has_static ? (((n_seqs + kPromptWaves - 1) / kPromptWaves + 7) & ~7) : 0;
+    const int threads = short_prompts(n_seqs, max_tokens, n_cu) ? 256 : 1024, waves = threads / 64;
+    const int n_static = B.has_static ? (((n_seqs + waves - 1) / waves + 7) & ~7) : 0;
+#define SAM_LAUNCH_PROMPT_T(LAYOUT, ASM, T)                                                     \
+    hipLaunchKernelGGL((sam_prompt_kernel<LAYOUT, ASM, T>), dim3(n_static + n_seqs), dim3(T),    \
+                       bytes, stream, S, B, seq_map, n_seqs, n_static, tokens, offsets,          \
+                       lds_tokens, most)
 #define SAM_LAUNCH_PROMPT(LAYOUT, ASM)                                                          \
-    hipLaunchKernelGGL((sam_prompt_kernel<LAYOUT, ASM>), dim3(n_static + n_seqs),               \
-                       dim3(kPromptThreads), bytes, stream, S, B, seq_map, n_seqs, n_static,     \
-                       tokens, offsets, lds_tokens, most)
+    do {                                                                                        \
+        if (threads == 256) SAM_LAUNCH_PROMPT_T(LAYOUT, ASM, 256);                              \
+        else SAM_LAUNCH_PROMPT_T(LAYOUT, ASM, 1024);                                            \
+    } while (0)
     const bool cxx = B.no_asm || (S.n_buckets >> 32);
     if (B.compact) {
         if (cxx) SAM_LAUNCH_PROMPT(CompactDyn, false); else SAM_LAUNCH_PROMPT(CompactDyn, true);
@@ -2313,6 +2333,7 @@ hipError_t launch_ingest(const StaticView &S, const BatchView &B, const int32_t 
         if (cxx) SAM_LAUNCH_PROMPT(WideDyn, false); else SAM_LAUNCH_PROMPT(WideDyn, true);
     }
 #undef SAM_LAUNCH_PROMPT
+#undef SAM_LAUNCH_PROMPT_T
     return hipGetLastError();
 }
 

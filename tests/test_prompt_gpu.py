@@ -75,6 +75,18 @@ def test_layouts(mode, vocab, n):
     _compare(prompts, vocab, n + 40, mode, _text("copies", 2000, vocab, rng))
 
 
+# small workgroups: more prompts than compute units (up to 512 tokens) and than twice as many
+# (up to 1024), and one past either length; ragged, with and without a corpus
+@pytest.mark.parametrize("batch,n", [(257, 64), (270, 512), (270, 513), (513, 65), (520, 1024), (520, 1025)])
+@pytest.mark.parametrize("mode,with_corpus", [(0, True), (1, False)])
+def test_many_prompts(batch, n, mode, with_corpus):
+    rng = np.random.default_rng(batch + n)
+    sizes = np.concatenate([[n, n - 1, 0, 1, 63, 256, 257], rng.integers(1, n + 1, size=batch)])[:batch]
+    prompts = [_text("copies", min(int(k), n), 300, rng) for k in sizes]
+    corpus = _text("copies", 3000, 300, rng) if with_corpus else None
+    _compare(prompts, 300, n + 40, mode, corpus)
+
+
 @pytest.mark.parametrize("at", [0, 1, 99, 299])
 def test_a_bad_token_ends_its_prompt(at):
     """sam_batch_reset with a token outside the vocabulary: the prompt ends in front of it."""
