@@ -1,0 +1,139 @@
+// A prompt's automaton built whole (sam_ingest.h, its phases run one after the other on the
+// CPU) against the token-by-token host builder: ids, lengths, links, end positions and every
+// transition.  All arrays have exactly the sizes that the library gives them, so that an
+// access outside them is seen by AddressSanitizer.
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include <random>
+#include <string>
+#include <vector>
+
+#include "../paper_2411_10666_amd/csrc/sam_host.h"
+#include "../paper_2411_10666_amd/csrc/sam_ingest.h"
+
+using namespace sam;
+
+template <uint32_t T>
+struct CpuCtx {
+    static constexpr uint32_t kThreads = T;
+    template <class F> void each(uint32_t n, F f) { for (uint32_t i = 0; i < n; i++) f(i); }
+    template <class F> void each_full(uint32_t n, F f) { for (uint32_t i = 0; i < n; i++) f(i, true); }
+    void sync() {}
+    template <class U> U cas(U *p, U expected, U v) { const U old = *p; if (old == expected) *p = v; return old; }
+    template <class U> U add(U *p, U v) { const U old = *p; *p = (U)(old + v); return old; }
+    uint32_t lower(uint32_t *p, uint32_t v) { const uint32_t old = *p; if (v < old) *p = v; return old; }
+    void bit_or(uint32_t *p, uint32_t v) { *p |= v; }
+    uint32_t exch(uint32_t *p, uint32_t v) { const uint32_t old = *p; *p = v; return old; }
+    uint32_t fresh(uint32_t *p) { return *p; }
+    uint32_t mulhi(uint32_t a, uint32_t b) { return (uint32_t)(((uint64_t)a * b) >> 32); }
+    uint32_t popc(uint32_t x) { return (uint32_t)__builtin_popcount(x); }
+    uint32_t first(uint32_t x) { return (uint32_t)__builtin_ctz(x); }
+    uint32_t log2(uint32_t x) { return 31u - (uint32_t)__builtin_clz(x); }
+    uint32_t wave_add(uint32_t *p, uint32_t v) { return add(p, v); }
+    void exclusive_sums(uint32_t *part)
+    {
+        uint32_t sum = 0;
+        for (uint32_t i = 0; i < T; i++) { const uint32_t v = part[i]; part[i] = sum; sum += v; }
+    }
+};
+
+static int bad(const char *what, uint32_t n, uint32_t at)
+{
+    printf("%s differs: %u tokens, at %u\n", what, n, at);
+    return 1;
+}
+
+struct Aligned {
+    void *p;
+    explicit Aligned(size_t bytes, int fill) : p(aligned_alloc(128, (bytes + 127) / 128 * 128)) { memset(p, fill, bytes); }
+    ~Aligned() { free(p); }
+};
+
+template <class IL, bool kLds, class I, class K, uint32_t T>
+static int one(const std::vector<int32_t> &x, int32_t vocab, uint32_t max_seq_len)
+{
+    const uint32_t n = (uint32_t)x.size();
+    constexpr bool compact = IL::kSlots == 16;
+    const size_t rec_bytes = (size_t)(2 * max_seq_len + 2) * (compact ? sizeof(DynRecCompact) : sizeof(DynRec));
+    const size_t slot_bytes = (size_t)dynamic_slots_for(max_seq_len) * (compact ? sizeof(SlotCompact) : sizeof(Slot));
+    const uint32_t n_buckets = (uint32_t)(slot_bytes / 128);
+    // the library leaves such prompts to the token-by-token kernel; long ones always fit
+    if (!kLds && !ingest_tables_fit<I, K>(n, rec_bytes, (size_t)n_buckets * 128))
+        return n < 2000 ? 0 : bad("room", n, 0);
+    Aligned rec(rec_bytes, 0x5A), slots((size_t)n_buckets * 128, 0xFF), text((size_t)max_seq_len * 4, 0);
+    Aligned lds(kLds ? ingest_lds_bytes(n) : ingest_small_bytes<I>(n, true), 0xA5);
+    const IngestSeq q{x.data(), n, (int32_t *)text.p, rec.p, slots.p, n_buckets};
+    IngestArrays<I, K> A;
+    if constexpr (kLds) ingest_place_lds(A, (char *)lds.p, n);
+    else ingest_place_tables(A, q, (char *)lds.p, n);
+    CpuCtx<T> ctx;
+    ingest_build<IL, kLds>(ctx, q, A);
+
+    HostSam h;
+    std::string err;
+    if (h.build(x.data(), n, vocab, err) != 0) return bad(err.c_str(), n, 0);
+    if (A.small[124] != h.n_states) return bad("states", n, A.small[124]);
+    if (A.small[125] != h.n_trans) return bad("transitions", n, A.small[125]);
+    if (memcmp(text.p, x.data(), (size_t)n * 4)) return bad("text", n, 0);
+    if (h.len[A.small[123]] != n) return bad("last state", n, A.small[123]);
+    uint64_t seen = 0;
+    for (uint32_t v = 0; v < h.n_states; v++) {
+        uint32_t len, link, endpos, itok;
+        IL::load(rec.p, v, len, link, endpos, itok);
+        if (len != h.len[v]) return bad("length", n, v);
+        if (link != h.link[v]) return bad("link", n, v);
+        if (endpos != h.endpos[v]) return bad("end position", n, v);
+        if (itok != kNil) {
+            if (h.find(v, itok) != IL::idst(rec.p, v)) return bad("inline transition", n, v);
+            seen++;
+        }
+        for (uint32_t at = IL::head(ctx, rec.p, v); at != kNil; seen++) {
+            if (at >= n_buckets * IL::kSlots) return bad("slot", n, v);
+            uint32_t state, token, dst, next;
+            if (compact) {
+                const SlotCompact &s = ((const SlotCompact *)slots.p)[at];
+                state = s.key >> 17; token = s.key & 0x1FFFFu; dst = s.dst;
+                next = s.next == 0xFFFFu ? kNil : s.next;
+            } else {
+                const Slot &s = ((const Slot *)slots.p)[at];
+                state = s.state; token = s.token; dst = s.dst; next = s.w;
+            }
+            if (state != v || h.find(v, token) != dst) return bad("transition", n, v);
+            at = next;
+        }
+    }
+    return seen == h.n_trans ? 0 : bad("transition lists", n, (uint32_t)seen);
+}
+
+int main()
+{
+    std::mt19937 rng(5);
+    const uint32_t sizes[] = {1, 2, 3, 7, 8, 9, 63, 64, 65, 255, 256, 257, 511, 513, 1023, 1024, 1025, 2500, 6200};
+    for (const uint32_t n : sizes)
+        for (int kind = 0; kind < 5; kind++)
+            for (const int32_t vocab : {2, 60, 9000}) {
+                std::vector<int32_t> x(n);
+                for (uint32_t i = 0; i < n; i++) {
+                    const double u = rng() / 4294967296.0;
+                    x[i] = kind == 2 ? vocab - 1 : kind == 3 ? (int32_t)(i % 7) % vocab
+                         : kind == 4 ? (i % 2 ? (int32_t)(i / 2) % vocab : 0) : (int32_t)(u * u * u * vocab);
+                }
+                if (kind == 1)                                  // copies of earlier spans
+                    for (uint32_t i = 20; i < n; i += 1 + rng() % 40) {
+                        const uint32_t from = rng() % i;
+                        const uint32_t back = i - from;
+                        for (uint32_t k = rng() % 80; k && i < n; k--, i++) x[i] = x[i - back];
+                    }
+                const uint32_t cap = n + rng() % 20;
+                if (one<IngestCompact, true, uint16_t, uint32_t, 1024>(x, vocab, cap) ||
+                    one<IngestWide, true, uint16_t, uint32_t, 256>(x, vocab, cap))
+                    return 1;
+                if (n >= 64 && (one<IngestCompact, false, uint16_t, uint32_t, 1024>(x, vocab, cap) ||
+                                one<IngestWide, false, uint32_t, uint64_t, 1024>(x, vocab, cap)))
+                    return 1;
+            }
+    printf("ok\n");
+    return 0;
+}

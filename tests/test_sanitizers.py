@@ -43,3 +43,19 @@ def test_oracle_and_host_builder_under_asan_ubsan(tmp_path):
     assert p.returncode == 0, p.stdout[-2000:] + p.stderr[-4000:]
     assert p.stdout.strip().endswith("ok")
     assert "runtime error" not in p.stderr and "AddressSanitizer" not in p.stderr
+
+
+def test_prompt_build_under_asan_ubsan(tmp_path):
+    """A prompt's automaton built whole, its phases on the CPU, equals the token-by-token one."""
+    if not (shutil.which("gcc") and shutil.which("g++")):
+        pytest.skip("gcc / g++ not available")
+    if not _have_sanitizer_runtime(tmp_path):
+        pytest.skip("the sanitizer runtime (libasan / libubsan) is not installed")
+    exe = tmp_path / "prompt_build_driver"
+    subprocess.check_call(["g++", "-std=c++17", "-pthread"] + FLAGS + [
+        os.path.join(ROOT, "tests", "prompt_build_driver.cpp"),
+        os.path.join(ROOT, "paper_2411_10666_amd", "csrc", "sam_host.cpp"), "-o", str(exe)])
+    env = dict(os.environ, ASAN_OPTIONS="verify_asan_link_order=0")
+    p = subprocess.run([str(exe)], capture_output=True, text=True, env=env, timeout=600)
+    assert p.returncode == 0, p.stdout[-2000:] + p.stderr[-4000:]
+    assert p.stdout.strip().endswith("ok")
