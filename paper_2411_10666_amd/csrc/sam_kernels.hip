@@ -31,114 +31,11 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <type_traits>
-
-#include "sam_device.h"
-#include "sam_ingest.h"
+#include "sam_walk.h"
 
 namespace sam {
 
 namespace {
-
-__device__ __forceinline__ uint32_t uni(uint32_t v)
-{
-    return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
-}
-
-__device__ __forceinline__ uint32_t lane_get(uint32_t v, int src_lane)
-{
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, src_lane);
-}
-
-// Keep a wave-uniform value materialised at this point of the program, so the
-// load that produced it cannot be moved below.
-__device__ __forceinline__ void pin_s(uint32_t &v)
-{
-    asm volatile("" : "+s"(v));
-}
-
-// Same for a per-lane value.  Used on the step's token vector: once the load has
-// landed before the token loop, reading a lane of it inside the loop no longer
-// makes the wave wait for the stores of the previous token.
-__device__ __forceinline__ void pin_v(uint32_t &v)
-{
-    asm volatile("" : "+v"(v));
-}
-
-__device__ __forceinline__ void order_memory()
-{
-    // stores and later loads of one wavefront reach memory in program order;
-    // this only stops the compiler from moving them across each other
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-}
-
-// ---- static automaton: Transfer (Algorithm 1) -----------------------------
-
-// Feed one token.  (s, l) is the cursor, e = min_endpos(s) with the wide flag of s
-// in bit 31 (a state is wide if it has transitions beyond the two in its record).
-__device__ __forceinline__ void static_transfer(const StaticView &S, uint32_t t, int lane,
-                                                uint32_t &s, uint32_t &l, uint32_t &e,
-                                                uint32_t &fault)
-{
-    // every suffix-link hop shortens the match, so l + 1 rounds always suffice;
-    // the bound only matters if the tables were corrupted
-    for (uint32_t guard = l + 2; ; guard--) {
-        if (guard == 0) { fault |= SAM_STATUS_INTERNAL_BIT; s = 0; l = 0; e = 0; return; }
-        if (s == 0) {
-            const uint2 r = reinterpret_cast<const uint2 *>(S.root)[t];
-            uint32_t d = uni(r.x), ep = uni(r.y);
-            pin_s(ep);
-            if (d) { s = d; e = ep; l = 1; }
-            else   { l = 0; e = 0; }
-            return;
-        }
-        // the record answers for a state with at most two transitions; a wide state's
-        // bucket is requested together with it
-        const bool wide = (e & kWideBit) != 0;
-        const LinkRec lr = S.linkrec[s];
-        uint64_t b = 0;
-        uint4 sl = make_uint4(kNil, kNil, 0, 0);
-        if (wide) {
-            b = bucket_of(hash_key(s, t), S.n_buckets);
-            sl = reinterpret_cast<const uint4 *>(S.slots)[b * kBucketSlots + (lane & 7)];
-        }
-        if (uni(lr.itok) == t) {
-            s = uni(lr.idst); e = uni(lr.iendpos); l += 1;
-            return;
-        }
-        if (uni(lr.itok2) == t) {
-            s = uni(lr.idst2); e = uni(lr.iendpos2); l += 1;
-            return;
-        }
-        uint32_t nlink = uni(lr.link), nlen = uni(lr.lenlink);
-        pin_s(nlink);
-        bool hit = false;
-        if (wide) {
-            uint32_t mh = (uint32_t)__ballot(sl.x == s && sl.y == t) & 0xFFu;
-            uint32_t me = (uint32_t)__ballot(sl.x == kNil) & 0xFFu;
-            pin_s(mh);
-            for (uint64_t left = S.n_buckets; left; left--) {
-                if (mh) {
-                    const int j = __builtin_ctz(mh);
-                    s = lane_get(sl.z, j);
-                    e = lane_get(sl.w, j);
-                    l += 1;
-                    hit = true;
-                    break;
-                }
-                if (me) break;
-                b = (b + 1 == S.n_buckets) ? 0 : b + 1;
-                sl = reinterpret_cast<const uint4 *>(S.slots)[b * kBucketSlots + (lane & 7)];
-                mh = (uint32_t)__ballot(sl.x == s && sl.y == t) & 0xFFu;
-                me = (uint32_t)__ballot(sl.x == kNil) & 0xFFu;
-            }
-        }
-        if (hit) return;
-        s = nlink;
-        l = nlen & ~kWideBit;
-        e = nlen & kWideBit;
-    }
-}
 
 // ---- dynamic automaton: the two table layouts ------------------------------
 
@@ -1050,206 +947,6 @@ __device__ __forceinline__ void dyn_feed_compact(u32x4 rrec, u32x4 rslt, uint32_
 
 // ---- per-wave work shared by the step, ingest and replay kernels -------------
 
-// Transfer (Algorithm 1) over tokens tv[i .. m) in gfx950 assembly: the same
-// steps as static_transfer, about a third of the instructions.  Lanes 0..7 fetch
-// the 8 slots of a bucket, the suffix-link record travels with the bucket.  i:
-// index of the next token (in/out); on return i == m or tv[i] is outside the
-// vocabulary.  Needs n_buckets < 2^32.
-//   s64 t   s65 t * c2   s66 link-hop guard   s67 bucket-sweep guard
-//   s68:69 s70:71 addresses / compare results   s72 hash   s73 bucket
-//   s74 hit mask   s75 empty mask   s76:77 compare result   s78 s79 scratch
-//   v41 zero   v42:45 slot {state, token, dst, endpos}   s88..s95 state record   v46:47 root entry
-__device__ __forceinline__ void static_feed_asm(uint32_t slots_lo, uint32_t slots_hi,
-                                                uint32_t lr_lo, uint32_t lr_hi, uint32_t root_lo,
-                                                uint32_t root_hi, uint32_t nb, uint32_t m,
-                                                uint32_t vocab, uint32_t tv, uint32_t lane16,
-                                                uint32_t &i, uint32_t &st, uint32_t &l,
-                                                uint32_t &e, uint32_t &flt)
-{
-    asm volatile(
-        "s_mov_b64 s[96:97], exec\n\t"
-        "s_mov_b64 exec, 0xff\n\t"
-        "v_mov_b32 v41, 0\n"
-        "L_stok_%=:\n\t"
-        "v_readlane_b32 s64, %[tv], %[i]\n\t"
-        "s_add_u32 s66, %[l], 2\n\t"            // every link hop shortens the match
-        "s_cmp_ge_u32 s64, %[vocab]\n\t"
-        "s_cbranch_scc1 L_sexit_%=\n\t"
-        "s_mul_i32 s65, s64, 0x85ebca77\n"
-        "L_stry_%=:\n\t"
-        "s_sub_u32 s66, s66, 1\n\t"
-        "s_cbranch_scc1 L_scorrupt_%=\n\t"
-        "s_cmp_eq_u32 %[st], 0\n\t"
-        "s_cbranch_scc1 L_sroot_%=\n\t"
-        // the state's record {itok, idst, iendpos, itok2, idst2, iendpos2, link, lenlink}.
-        // It comes through the scalar cache (the table is read-only), which has its own
-        // counter: vector loads return in order, so a record behind a bucket in the same
-        // queue could not arrive before it.  Bit 31 of e says whether the state is wide;
-        // if not, its record holds all its transitions and no bucket is requested.
-        "s_lshl_b32 s68, %[st], 5\n\t"
-        "s_lshr_b32 s69, %[st], 27\n\t"
-        "s_add_u32 s68, s68, %[lr_lo]\n\t"
-        "s_addc_u32 s69, s69, %[lr_hi]\n\t"
-        "s_load_dwordx8 s[88:95], s[68:69], 0x0\n\t"
-        "s_bitcmp1_b32 %[e], 31\n\t"
-        "s_cbranch_scc0 L_srec_%=\n\t"
-        "s_mul_i32 s72, %[st], 0x9e3779b1\n\t"
-        "s_add_u32 s72, s72, s65\n\t"
-        "s_lshr_b32 s79, s72, 15\n\t"
-        "s_xor_b32 s72, s72, s79\n\t"
-        "s_mul_i32 s72, s72, 0x2c1b3c6d\n\t"
-        "s_lshr_b32 s79, s72, 12\n\t"
-        "s_xor_b32 s72, s72, s79\n\t"
-        "s_mul_i32 s72, s72, 0x297a2d39\n\t"
-        "s_lshr_b32 s79, s72, 15\n\t"
-        "s_xor_b32 s72, s72, s79\n\t"
-        "s_mul_hi_u32 s73, s72, %[nb]\n\t"
-        "s_mov_b32 s67, %[nb]\n\t"
-        "s_lshl_b32 s70, s73, 7\n\t"
-        "s_lshr_b32 s71, s73, 25\n\t"
-        "s_add_u32 s70, s70, %[slots_lo]\n\t"
-        "s_addc_u32 s71, s71, %[slots_hi]\n\t"
-        "global_load_dwordx4 v[42:45], %[lane16], s[70:71]\n\t"
-        // the record is here before the bucket (often from a line the last token
-        // already brought in): if it repeats the transition asked for, the bucket is
-        // not waited for at all
-        "s_waitcnt lgkmcnt(0)\n\t"
-        "s_cmp_eq_u32 s88, s64\n\t"
-        "s_cbranch_scc1 L_sinline_%=\n\t"
-        "s_cmp_eq_u32 s91, s64\n\t"
-        "s_cbranch_scc1 L_sinline2_%=\n\t"
-        "s_branch L_swait_%=\n"
-        "L_srec_%=:\n\t"
-        "s_waitcnt lgkmcnt(0)\n\t"
-        "s_cmp_eq_u32 s88, s64\n\t"
-        "s_cbranch_scc1 L_sinline_%=\n\t"
-        "s_cmp_eq_u32 s91, s64\n\t"
-        "s_cbranch_scc1 L_sinline2_%=\n\t"
-        "s_branch L_smiss_%=\n"
-        "L_sload_%=:\n\t"
-        "s_lshl_b32 s70, s73, 7\n\t"
-        "s_lshr_b32 s71, s73, 25\n\t"
-        "s_add_u32 s70, s70, %[slots_lo]\n\t"
-        "s_addc_u32 s71, s71, %[slots_hi]\n\t"
-        "global_load_dwordx4 v[42:45], %[lane16], s[70:71]\n"
-        "L_swait_%=:\n\t"
-        "s_waitcnt vmcnt(0)\n\t"
-        "v_cmp_eq_u32 vcc, %[st], v42\n\t"
-        "v_cmp_eq_u32 s[76:77], s64, v43\n\t"
-        "v_cmp_eq_u32 s[70:71], -1, v42\n\t"
-        "s_and_b32 s74, vcc_lo, s76\n\t"
-        "s_mov_b32 s75, s70\n\t"
-        "s_cmp_lg_u32 s74, 0\n\t"
-        "s_cbranch_scc1 L_shit_%=\n\t"
-        "s_cmp_lg_u32 s75, 0\n\t"
-        "s_cbranch_scc1 L_smiss_%=\n\t"
-        // bucket full of other keys: go on in the next one
-        "s_sub_u32 s67, s67, 1\n\t"
-        "s_cbranch_scc1 L_scorrupt_%=\n\t"
-        "s_add_u32 s73, s73, 1\n\t"
-        "s_cmp_eq_u32 s73, %[nb]\n\t"
-        "s_cselect_b32 s73, 0, s73\n\t"
-        "s_branch L_sload_%=\n"
-        "L_shit_%=:\n\t"
-        "s_ff1_i32_b32 s78, s74\n\t"
-        "s_add_u32 %[l], %[l], 1\n\t"
-        "v_readlane_b32 %[st], v44, s78\n\t"
-        "v_readlane_b32 %[e], v45, s78\n\t"
-        "s_branch L_sdone_%=\n"
-        "L_sinline_%=:\n\t"
-        "s_add_u32 %[l], %[l], 1\n\t"
-        "s_mov_b32 %[st], s89\n\t"
-        "s_mov_b32 %[e], s90\n\t"
-        "s_branch L_sdone_%=\n"
-        "L_sinline2_%=:\n\t"
-        "s_add_u32 %[l], %[l], 1\n\t"
-        "s_mov_b32 %[st], s92\n\t"
-        "s_mov_b32 %[e], s93\n\t"
-        "s_branch L_sdone_%=\n"
-        "L_smiss_%=:\n\t"
-        "s_mov_b32 %[st], s94\n\t"              // follow the suffix link
-        "s_and_b32 %[l], s95, 0x7fffffff\n\t"
-        "s_and_b32 %[e], s95, 0x80000000\n\t"   // its wide flag; its end position is not needed
-        "s_branch L_stry_%=\n"
-        "L_sroot_%=:\n\t"
-        "s_lshl_b32 s68, s64, 3\n\t"
-        "s_add_u32 s68, s68, %[root_lo]\n\t"
-        "s_addc_u32 s69, %[root_hi], 0\n\t"
-        "global_load_dwordx2 v[46:47], v41, s[68:69]\n\t"
-        "s_waitcnt vmcnt(0)\n\t"
-        "v_readfirstlane_b32 s78, v46\n\t"
-        "v_readfirstlane_b32 s79, v47\n\t"
-        "s_cmp_eq_u32 s78, 0\n\t"
-        "s_cbranch_scc1 L_snone_%=\n\t"
-        "s_mov_b32 %[st], s78\n\t"
-        "s_mov_b32 %[e], s79\n\t"
-        "s_mov_b32 %[l], 1\n\t"
-        "s_branch L_sdone_%=\n"
-        "L_snone_%=:\n\t"
-        "s_mov_b32 %[l], 0\n\t"
-        "s_mov_b32 %[e], 0\n"
-        "L_sdone_%=:\n\t"
-        "s_add_u32 %[i], %[i], 1\n\t"
-        "s_cmp_lt_u32 %[i], %[m]\n\t"
-        "s_cbranch_scc1 L_stok_%=\n\t"
-        "s_branch L_sexit_%=\n"
-        "L_scorrupt_%=:\n\t"
-        "s_or_b32 %[flt], %[flt], 8\n\t"
-        "s_mov_b32 %[st], 0\n\t"
-        "s_mov_b32 %[l], 0\n\t"
-        "s_mov_b32 %[e], 0\n"
-        "L_sexit_%=:\n\t"
-        "s_waitcnt vmcnt(0)\n\t"
-        "s_mov_b64 exec, s[96:97]\n\t"
-        : [i] "+s"(i), [st] "+s"(st), [l] "+s"(l), [e] "+s"(e), [flt] "+s"(flt)
-        : [slots_lo] "s"(slots_lo), [slots_hi] "s"(slots_hi), [lr_lo] "s"(lr_lo),
-          [lr_hi] "s"(lr_hi), [root_lo] "s"(root_lo), [root_hi] "s"(root_hi), [nb] "s"(nb),
-          [m] "s"(m), [vocab] "s"(vocab), [tv] "v"(tv), [lane16] "v"(lane16)
-        : "memory", "vcc", "scc",
-          "s64", "s65", "s66", "s67", "s68", "s69", "s70", "s71", "s72", "s73", "s74", "s75",
-          "s76", "s77", "s78", "s79", "s88", "s89", "s90", "s91", "s92", "s93", "s94", "s95",
-          "s96", "s97",
-          "v41", "v42", "v43", "v44", "v45", "v46", "v47");
-}
-
-// Wave 0: feed `count` tokens to the static cursor; stops in front of a token
-// outside the vocabulary (wave 1 reports it).
-__device__ __forceinline__ void static_feed(const StaticView &S, const int32_t *tok, int64_t count,
-                                            uint32_t vocab, int lane, uint32_t &s, uint32_t &l,
-                                            uint32_t &e, uint32_t &fault, bool use_asm,
-                                            bool have_first = false, uint32_t first = 0)
-{
-    bool stop = false;
-    const bool in_asm = use_asm;          // the launcher sends corpora beyond 2^32 buckets to C++
-    for (int64_t base = 0; base < count && !stop; base += 64) {
-        const int m = (int)((count - base) < 64 ? (count - base) : 64);
-        uint32_t tv;
-        if (have_first && base == 0) tv = first;     // fetched by the caller with its other loads
-        else tv = lane < m ? (uint32_t)tok[base + lane] : 0u;
-        pin_v(tv);
-        if (in_asm) {
-            const uint64_t a_sl = (uint64_t)S.slots, a_lr = (uint64_t)S.linkrec,
-                           a_rt = (uint64_t)S.root;
-            uint32_t i = 0, flt = 0;
-            uint32_t a_s = uni(s), a_l = uni(l), a_e = uni(e);
-            static_feed_asm(uni((uint32_t)a_sl), uni((uint32_t)(a_sl >> 32)), uni((uint32_t)a_lr),
-                            uni((uint32_t)(a_lr >> 32)), uni((uint32_t)a_rt),
-                            uni((uint32_t)(a_rt >> 32)), uni((uint32_t)S.n_buckets),
-                            uni((uint32_t)m), uni(vocab), tv, (uint32_t)(lane & 7) * 16u, i, a_s,
-                            a_l, a_e, flt);
-            s = a_s; l = a_l; e = a_e;
-            fault |= flt;
-            if ((int)i < m) stop = true;
-        } else {
-            for (int i = 0; i < m; i++) {
-                const uint32_t t = lane_get(tv, i);
-                if (t >= vocab) { stop = true; break; }
-                static_transfer(S, t, lane, s, l, e, fault);
-            }
-        }
-    }
-}
-
 // Wave 1: append `count` tokens to the sequence's dynamic automaton and text.
 template <class L>
 __device__ __forceinline__ void dyn_feed(const DynSeq &D, const int32_t *tok, int64_t count,
@@ -1702,233 +1399,6 @@ __global__ __launch_bounds__(kScout ? 256 : 128) void sam_feed_kernel(StaticView
     emit_draft(S, B, b, lane, l1, e1, sh[3], sh[4], sh[5], match_len, draft, draft_len, source);
 }
 
-// ---- prompts: the whole automaton at once (sam_ingest.h) -----------------------
-
-// Extending a sequence token by token takes 0.6 to 1.2 us a token whatever the chip has
-// free, so a prompt of 3000 tokens took 1.8 ms.  Built whole, by one workgroup with its
-// working arrays in LDS (27 bytes a token, 16-bit indices), the bound is the LDS pipeline of
-// one compute unit.  Measured, sam_batch_reset: one prompt of 6000 tokens 210 us, 64 of 2048
-// 125 us (1.2 ms token by token), 1024 of 2048 424 us, 1024 of 6000 1.16 ms (5.3 ms), 12 of
-// 40 001 tokens (arrays in the sequence's own tables instead of LDS) 3.5 ms (46 ms).  Of the
-// 165 us that one workgroup needs for 6000 tokens, the sort takes 75, the intervals 19 and
-// the transitions 61 (a compare-and-swap in the slot table each).  Two parts were three
-// times that: the nearest smaller values scanned in runs of 32 (130 us; now a tree of minima
-// of 8, one 16-byte read a level) and the transitions walking the records in memory instead
-// of their copies in LDS (122 us).  What is left of the transitions is the rate at which one
-// compute unit gets compare-and-swaps on scattered lines through: lanes that go on with the
-// next position as soon as theirs has ended, instead of waiting for the longest path of their
-// wave, took 218 against 218 us for one prompt of 6000 tokens, and 1.22 against 1.18 ms for 1024.
-//
-// A workgroup has 1024 threads, or 256 where there are more workgroups than are resident at
-// 1024 threads and the prompts are so short that 256 suffice.  Measured, 1024 against 256
-// threads: 256 prompts of 256 tokens 88 against 90 us, of 1024 121 against 155; 300 of 64 97
-// against 78, of 256 116 against 96, of 1024 164 against 181; 512 of 512 137 against 127, of
-// 1024 178 against 195; 640 of 1024 223 against 207; 1024 of 64 150 against 82 (92 token by
-// token), of 512 215 against 152, of 1024 287 against 250, of 1500 387 against 422.
-inline bool short_prompts(int n_seqs, int64_t max_tokens, int n_cu)
-{
-    return (n_seqs > n_cu && max_tokens <= 512) || (n_seqs > 2 * n_cu && max_tokens <= 1024);
-}
-// The fixed cost of about sixty barriers is what the serial loops need for this many tokens.
-constexpr int64_t kPromptMinTokens = 64;
-
-template <int T>
-struct PromptCtx {
-    static constexpr uint32_t kThreads = T;
-    uint32_t tid;
-    uint32_t *wsum;            // [T / 64]
-
-    template <class F>
-    __device__ __forceinline__ void each(uint32_t n, F f)
-    {
-        for (uint32_t i = tid; i < n; i += T) f(i);
-    }
-    template <class F>
-    __device__ __forceinline__ void each_full(uint32_t n, F f)     // whole waves
-    {
-        for (uint32_t i = tid; i - tid < n; i += T) f(i, i < n);
-    }
-    __device__ __forceinline__ void sync() { __syncthreads(); }
-    template <class U>
-    __device__ __forceinline__ U cas(U *p, U expected, U v)
-    {
-        __hip_atomic_compare_exchange_strong(p, &expected, v, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_WORKGROUP);
-        return expected;
-    }
-    template <class U>
-    __device__ __forceinline__ U add(U *p, U v)
-    {
-        return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
-    __device__ __forceinline__ uint32_t lower(uint32_t *p, uint32_t v)
-    {
-        return __hip_atomic_fetch_min(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
-    __device__ __forceinline__ void bit_or(uint32_t *p, uint32_t v)
-    {
-        __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
-    __device__ __forceinline__ uint32_t exch(uint32_t *p, uint32_t v)
-    {
-        return __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
-    __device__ __forceinline__ uint32_t fresh(uint32_t *p)
-    {
-        return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    __device__ __forceinline__ uint32_t mulhi(uint32_t a, uint32_t b) { return __umulhi(a, b); }
-    __device__ __forceinline__ uint32_t popc(uint32_t x) { return (uint32_t)__popc(x); }
-    __device__ __forceinline__ uint32_t first(uint32_t x) { return (uint32_t)__builtin_ctz(x); }
-    __device__ __forceinline__ uint32_t log2(uint32_t x) { return 31u - (uint32_t)__clz((int)x); }
-    // sum over the lower lanes and this one
-    __device__ __forceinline__ uint32_t wave_sums(uint32_t v)
-    {
-        for (int d = 1; d < 64; d *= 2) {
-            const uint32_t below = (uint32_t)__shfl_up((int)v, d);
-            if ((tid & 63) >= (uint32_t)d) v += below;
-        }
-        return v;
-    }
-    // where this lane's v places start in a counter that all lanes of the wave add to
-    __device__ __forceinline__ uint32_t wave_add(uint32_t *p, uint32_t v)
-    {
-        const uint32_t upto = wave_sums(v);
-        uint32_t base = 0;
-        if ((tid & 63) == 63 && upto) base = add(p, upto);
-        return (uint32_t)__shfl((int)base, 63) + upto - v;
-    }
-    // part[i] becomes the sum of the entries before it; thread i reads entry i
-    __device__ __forceinline__ void exclusive_sums(uint32_t *part)
-    {
-        const uint32_t v = part[tid], upto = wave_sums(v);
-        if ((tid & 63) == 63) wsum[tid >> 6] = upto;
-        __syncthreads();
-        uint32_t before = 0;
-        for (uint32_t w = 0; w < (tid >> 6); w++) before += wsum[w];
-        part[tid] = before + upto - v;
-    }
-};
-
-// The static cursor after a prompt belongs to the longest suffix of the prompt that occurs
-// in the corpus, so the walk need not start at the first token: started at the root w
-// tokens before the end it finds the longest such suffix of at most w tokens, and if that is
-// shorter than w it is the one looked for.  Otherwise the window was too short: four times
-// as much.  (48 tokens cover all but a few prompts; a walk costs about 0.6 us a token.)
-__device__ __forceinline__ void static_tail(const StaticView &S, const int32_t *tok, uint32_t n,
-                                            uint32_t vocab, int lane, uint32_t &s, uint32_t &l,
-                                            uint32_t &e, uint32_t &fault, bool use_asm)
-{
-    for (uint64_t w = 48;; w *= 4) {
-        const uint32_t k = w < n ? (uint32_t)w : n;
-        s = 0; l = 0; e = 0;
-        static_feed(S, tok + (n - k), k, vocab, lane, s, l, e, fault, use_asm);
-        if (uni(l) < k || k == n || fault) return;
-    }
-}
-
-// Fresh sequences (just reset) take their prompts.  Workgroups 0 .. n_static-1 walk the
-// corpus automaton, one wave per sequence; workgroup n_static + i builds the automaton of
-// sequence i (n_static is a multiple of 8, so it runs on the XCD on which the steps of
-// sequence i will find its tables).  A token outside the vocabulary ends its prompt.
-template <class L, bool kAsm, int T>
-__global__ __launch_bounds__(T) void sam_prompt_kernel(StaticView S, BatchView B,
-                                                          const int32_t *__restrict__ seq_map,
-                                                          int n_seqs, int n_static,
-                                                          const int32_t *__restrict__ tokens,
-                                                          const int64_t *__restrict__ offsets,
-                                                          uint32_t lds_tokens, uint32_t max_tokens)
-{
-    extern __shared__ __align__(16) char lds[];
-    __shared__ uint32_t bad, wsum[T / 64];
-    const uint32_t vocab = (uint32_t)B.vocab;
-    const int lane = threadIdx.x & 63;
-    const bool walks = (int)blockIdx.x < n_static;
-    const int i = walks ? (int)blockIdx.x * (T / 64) + (int)(threadIdx.x >> 6)
-                        : (int)blockIdx.x - n_static;
-    if (i >= n_seqs) return;
-    const int b = seq_map ? seq_map[i] : i;
-    SeqMeta *meta = &B.meta[b];
-    const int32_t *tok = tokens + offsets[i];
-    const int64_t count = offsets[i + 1] - offsets[i];
-    if (count <= 0) return;
-    if (count > (int64_t)B.max_seq_len || count > (int64_t)max_tokens) {
-        if (!walks && threadIdx.x == 0) {
-            meta->status |= SAM_STATUS_CAPACITY_BIT;
-            atomicOr(B.status, SAM_STATUS_CAPACITY_BIT);
-        }
-        return;
-    }
-    uint32_t n = (uint32_t)count;
-    if (walks) {
-        uint32_t first = n;
-        for (uint32_t base = 0; base < n && first == n; base += 256) {
-            uint32_t at = n;
-#pragma unroll
-            for (int u = 3; u >= 0; u--) {
-                const uint32_t j = base + 64 * u + lane;
-                if (j < n && (uint32_t)tok[j] >= vocab) at = j;
-            }
-            if (__any(at < n))
-                for (int d = 32; d; d /= 2) {
-                    const uint32_t other = (uint32_t)__shfl_xor((int)at, d);
-                    at = other < at ? other : at;
-                }
-            first = uni(at);
-        }
-        n = first;
-        uint32_t s = 0, l = 0, e = 0, fault = 0;
-        if (n) static_tail(S, tok, n, vocab, lane, s, l, e, fault, kAsm);
-        if (lane == 0) {
-            meta->s1 = s; meta->l1 = l; meta->e1 = e;
-            if (fault & SAM_STATUS_INTERNAL_BIT) atomicOr(B.status, SAM_STATUS_INTERNAL_BIT);
-        }
-        return;
-    }
-
-    if (threadIdx.x == 0) bad = n;
-    __syncthreads();
-    for (uint32_t j = threadIdx.x; j < n; j += T)
-        if ((uint32_t)tok[j] >= vocab) atomicMin(&bad, j);
-    __syncthreads();
-    const uint32_t first_bad = bad;
-    if (first_bad < n && threadIdx.x == 0) {
-        meta->status |= SAM_STATUS_TOKEN_BIT;
-        atomicOr(B.status, SAM_STATUS_TOKEN_BIT);
-    }
-    n = first_bad;
-    if (n == 0) return;
-    constexpr bool kCompact = L::kSlots == 16;
-    typedef typename std::conditional<kCompact, IngestCompact, IngestWide>::type IL;
-    typedef typename std::conditional<kCompact, uint16_t, uint32_t>::type I;
-    typedef typename std::conditional<kCompact, uint32_t, uint64_t>::type K;
-    const DynSeq D = dyn_region<L>(B, b);
-    const IngestSeq q{tok, n, D.text, D.rec, D.slots, D.n_buckets};
-    PromptCtx<T> ctx{threadIdx.x, wsum};
-    uint32_t *small;
-    if (n <= lds_tokens) {
-        IngestArrays<uint16_t, uint32_t> A;
-        ingest_place_lds(A, lds, n);
-        small = A.small;
-        ingest_build<IL, true>(ctx, q, A);
-    } else {
-        IngestArrays<I, K> A;
-        ingest_place_tables(A, q, lds, n);
-        small = A.small;
-        ingest_build<IL, false>(ctx, q, A);
-    }
-    if (threadIdx.x == 0) {
-        const uint32_t last = small[123], P = IL::link(D.rec, last);
-        uint32_t len, link, endpos, itok;
-        IL::load(D.rec, P, len, link, endpos, itok);
-        meta->n = n; meta->n_states = small[124]; meta->last = last; meta->n_trans = small[125];
-        meta->s2 = P;
-        meta->p_len = len; meta->p_link = link; meta->p_endpos = endpos;
-        meta->p_head = IL::head(ctx, D.rec, P);
-        meta->p_itok = itok; meta->p_idst = IL::idst(D.rec, P);
-    }
-}
-
 // The same work for a whole schedule of steps in one launch: workgroup b runs
 // sequence b through steps 0 .. n_steps-1 on its own, so no sequence waits for
 // the longest row of another and nothing is launched in between.  Step s reads
@@ -2278,62 +1748,6 @@ hipError_t launch_feed(const StaticView &S, const BatchView &B, const int32_t *s
              break;
     }
 #undef SAM_LAUNCH_FEED
-    return hipGetLastError();
-}
-
-hipError_t launch_ingest(const StaticView &S, const BatchView &B, const int32_t *seq_map,
-                         int n_seqs, const int32_t *tokens, const int64_t *offsets,
-                         int64_t max_tokens, hipStream_t stream)
-{
-    if (max_tokens < kPromptMinTokens || max_tokens > (int64_t)kIngestMaxTokens)
-        return launch_feed(S, B, seq_map, n_seqs, tokens, offsets, nullptr, nullptr, nullptr,
-                           nullptr, nullptr, stream);
-    int dev = 0, lds_limit = 0, n_cu = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess)
-        e = hipDeviceGetAttribute(&lds_limit, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
-    if (e == hipSuccess)
-        e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return e;
-    const size_t room = (size_t)lds_limit - 256;             // the kernel's own words
-    // the most tokens whose working arrays fit
-    uint32_t fit = 0, over = kIngestIdx16 + 1;
-    while (over - fit > 1) {
-        const uint32_t mid = (fit + over) / 2;
-        if (ingest_lds_bytes(mid) <= room) fit = mid; else over = mid;
-    }
-    const uint32_t most = (uint32_t)max_tokens, lds_tokens = most < fit ? most : fit;
-    size_t bytes = ingest_lds_bytes(lds_tokens);
-    if (most > lds_tokens) {
-        const size_t small = B.compact ? ingest_small_bytes<uint16_t>(most, true)
-                                       : ingest_small_bytes<uint32_t>(most, true);
-        bytes = small > bytes ? small : bytes;
-        const size_t rec_bytes = (size_t)B.max_states * (B.compact ? sizeof(DynRecCompact) : sizeof(DynRec)),
-                     slot_bytes = (size_t)B.dyn_buckets * 128;
-        if (!(B.compact ? ingest_tables_fit<uint16_t, uint32_t>(most, rec_bytes, slot_bytes)
-                        : ingest_tables_fit<uint32_t, uint64_t>(most, rec_bytes, slot_bytes)) || bytes > room)
-            return launch_feed(S, B, seq_map, n_seqs, tokens, offsets, nullptr, nullptr, nullptr,
-                               nullptr, nullptr, stream);
-    }
-    const int threads = short_prompts(n_seqs, max_tokens, n_cu) ? 256 : 1024, waves = threads / 64;
-    const int n_static = B.has_static ? (((n_seqs + waves - 1) / waves + 7) & ~7) : 0;
-#define SAM_LAUNCH_PROMPT_T(LAYOUT, ASM, T)                                                     \
-    hipLaunchKernelGGL((sam_prompt_kernel<LAYOUT, ASM, T>), dim3(n_static + n_seqs), dim3(T),    \
-                       bytes, stream, S, B, seq_map, n_seqs, n_static, tokens, offsets,          \
-                       lds_tokens, most)
-#define SAM_LAUNCH_PROMPT(LAYOUT, ASM)                                                          \
-    do {                                                                                        \
-        if (threads == 256) SAM_LAUNCH_PROMPT_T(LAYOUT, ASM, 256);                              \
-        else SAM_LAUNCH_PROMPT_T(LAYOUT, ASM, 1024);                                            \
-    } while (0)
-    const bool cxx = B.no_asm || (S.n_buckets >> 32);
-    if (B.compact) {
-        if (cxx) SAM_LAUNCH_PROMPT(CompactDyn, false); else SAM_LAUNCH_PROMPT(CompactDyn, true);
-    } else {
-        if (cxx) SAM_LAUNCH_PROMPT(WideDyn, false); else SAM_LAUNCH_PROMPT(WideDyn, true);
-    }
-#undef SAM_LAUNCH_PROMPT
-#undef SAM_LAUNCH_PROMPT_T
     return hipGetLastError();
 }
 

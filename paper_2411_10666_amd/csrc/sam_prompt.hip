@@ -1,0 +1,295 @@
+// gfx950 kernel that takes the prompts of fresh sequences whole (arxiv 2411.10666,
+// Section 3.1: the dynamic automaton over prompt and generated tokens alike).
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <type_traits>
+
+#include "sam_ingest.h"
+#include "sam_prompt.h"
+#include "sam_walk.h"
+
+namespace sam {
+
+// Extending a sequence token by token takes 0.6 to 1.2 us a token whatever the chip has
+// free, so a prompt of 3000 tokens took 1.8 ms.  Built whole, by one workgroup with its
+// working arrays in LDS (27 bytes a token, 16-bit indices), the bound is the LDS pipeline of
+// one compute unit.  Measured, sam_batch_reset: one prompt of 6000 tokens 210 us, 64 of 2048
+// 125 us (1.2 ms token by token), 1024 of 2048 424 us, 1024 of 6000 1.16 ms (5.3 ms), 12 of
+// 40 001 tokens (arrays in the sequence's own tables instead of LDS) 3.5 ms (46 ms).  Of the
+// 165 us that one workgroup needs for 6000 tokens, the sort takes 75, the intervals 19 and
+// the transitions 61 (a compare-and-swap in the slot table each).  Two parts were three
+// times that: the nearest smaller values scanned in runs of 32 (130 us; now a tree of minima
+// of 8, one 16-byte read a level) and the transitions walking the records in memory instead
+// of their copies in LDS (122 us).  What is left of the transitions is the rate at which one
+// compute unit gets compare-and-swaps on scattered lines through: lanes that go on with the
+// next position as soon as theirs has ended, instead of waiting for the longest path of their
+// wave, took 218 against 218 us for one prompt of 6000 tokens, and 1.22 against 1.18 ms for 1024.
+//
+// A workgroup has 1024 threads, or 256 where there are more workgroups than are resident at
+// 1024 threads and the prompts are so short that 256 suffice.  Measured, 1024 against 256
+// threads: 256 prompts of 256 tokens 88 against 90 us, of 1024 121 against 155; 300 of 64 97
+// against 78, of 256 116 against 96, of 1024 164 against 181; 512 of 512 137 against 127, of
+// 1024 178 against 195; 640 of 1024 223 against 207; 1024 of 64 150 against 82 (92 token by
+// token), of 512 215 against 152, of 1024 287 against 250, of 1500 387 against 422.
+inline bool short_prompts(int n_seqs, int64_t max_tokens, int n_cu)
+{
+    return (n_seqs > n_cu && max_tokens <= 512) || (n_seqs > 2 * n_cu && max_tokens <= 1024);
+}
+// The fixed cost of about sixty barriers is what the serial loops need for this many tokens.
+constexpr int64_t kPromptMinTokens = 64;
+
+template <int T>
+struct PromptCtx {
+    static constexpr uint32_t kThreads = T;
+    uint32_t tid;
+    uint32_t *wsum;            // [T / 64]
+
+    template <class F>
+    __device__ __forceinline__ void each(uint32_t n, F f)
+    {
+        for (uint32_t i = tid; i < n; i += T) f(i);
+    }
+    template <class F>
+    __device__ __forceinline__ void each_full(uint32_t n, F f)     // whole waves
+    {
+        for (uint32_t i = tid; i - tid < n; i += T) f(i, i < n);
+    }
+    __device__ __forceinline__ void sync() { __syncthreads(); }
+    template <class U>
+    __device__ __forceinline__ U cas(U *p, U expected, U v)
+    {
+        __hip_atomic_compare_exchange_strong(p, &expected, v, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_WORKGROUP);
+        return expected;
+    }
+    template <class U>
+    __device__ __forceinline__ U add(U *p, U v)
+    {
+        return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __device__ __forceinline__ uint32_t lower(uint32_t *p, uint32_t v)
+    {
+        return __hip_atomic_fetch_min(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __device__ __forceinline__ void bit_or(uint32_t *p, uint32_t v)
+    {
+        __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __device__ __forceinline__ uint32_t exch(uint32_t *p, uint32_t v)
+    {
+        return __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __device__ __forceinline__ uint32_t fresh(uint32_t *p)
+    {
+        return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __device__ __forceinline__ uint32_t mulhi(uint32_t a, uint32_t b) { return __umulhi(a, b); }
+    __device__ __forceinline__ uint32_t popc(uint32_t x) { return (uint32_t)__popc(x); }
+    __device__ __forceinline__ uint32_t first(uint32_t x) { return (uint32_t)__builtin_ctz(x); }
+    __device__ __forceinline__ uint32_t log2(uint32_t x) { return 31u - (uint32_t)__clz((int)x); }
+    // sum over the lower lanes and this one
+    __device__ __forceinline__ uint32_t wave_sums(uint32_t v)
+    {
+        for (int d = 1; d < 64; d *= 2) {
+            const uint32_t below = (uint32_t)__shfl_up((int)v, d);
+            if ((tid & 63) >= (uint32_t)d) v += below;
+        }
+        return v;
+    }
+    // where this lane's v places start in a counter that all lanes of the wave add to
+    __device__ __forceinline__ uint32_t wave_add(uint32_t *p, uint32_t v)
+    {
+        const uint32_t upto = wave_sums(v);
+        uint32_t base = 0;
+        if ((tid & 63) == 63 && upto) base = add(p, upto);
+        return (uint32_t)__shfl((int)base, 63) + upto - v;
+    }
+    // part[i] becomes the sum of the entries before it; thread i reads entry i
+    __device__ __forceinline__ void exclusive_sums(uint32_t *part)
+    {
+        const uint32_t v = part[tid], upto = wave_sums(v);
+        if ((tid & 63) == 63) wsum[tid >> 6] = upto;
+        __syncthreads();
+        uint32_t before = 0;
+        for (uint32_t w = 0; w < (tid >> 6); w++) before += wsum[w];
+        part[tid] = before + upto - v;
+    }
+};
+
+// The static cursor after a prompt belongs to the longest suffix of the prompt that occurs
+// in the corpus, so the walk need not start at the first token: started at the root w
+// tokens before the end it finds the longest such suffix of at most w tokens, and if that is
+// shorter than w it is the one looked for.  Otherwise the window was too short: four times
+// as much.  (48 tokens cover all but a few prompts; a walk costs about 0.6 us a token.)
+__device__ __forceinline__ void static_tail(const StaticView &S, const int32_t *tok, uint32_t n,
+                                            uint32_t vocab, int lane, uint32_t &s, uint32_t &l,
+                                            uint32_t &e, uint32_t &fault, bool use_asm)
+{
+    for (uint64_t w = 48;; w *= 4) {
+        const uint32_t k = w < n ? (uint32_t)w : n;
+        s = 0; l = 0; e = 0;
+        static_feed(S, tok + (n - k), k, vocab, lane, s, l, e, fault, use_asm);
+        if (uni(l) < k || k == n || fault) return;
+    }
+}
+
+// Fresh sequences (just reset) take their prompts.  Workgroups 0 .. n_static-1 walk the
+// corpus automaton, one wave per sequence; workgroup n_static + i builds the automaton of
+// sequence i (n_static is a multiple of 8, so it runs on the XCD on which the steps of
+// sequence i will find its tables).  A token outside the vocabulary ends its prompt.
+template <bool kCompact, bool kAsm, int T>
+__global__ __launch_bounds__(T) void sam_prompt_kernel(StaticView S, BatchView B,
+                                                          const int32_t *__restrict__ seq_map,
+                                                          int n_seqs, int n_static,
+                                                          const int32_t *__restrict__ tokens,
+                                                          const int64_t *__restrict__ offsets,
+                                                          uint32_t lds_tokens, uint32_t max_tokens)
+{
+    extern __shared__ __align__(16) char lds[];
+    __shared__ uint32_t bad, wsum[T / 64];
+    const uint32_t vocab = (uint32_t)B.vocab;
+    const int lane = threadIdx.x & 63;
+    const bool walks = (int)blockIdx.x < n_static;
+    const int i = walks ? (int)blockIdx.x * (T / 64) + (int)(threadIdx.x >> 6)
+                        : (int)blockIdx.x - n_static;
+    if (i >= n_seqs) return;
+    const int b = seq_map ? seq_map[i] : i;
+    SeqMeta *meta = &B.meta[b];
+    const int32_t *tok = tokens + offsets[i];
+    const int64_t count = offsets[i + 1] - offsets[i];
+    if (count <= 0) return;
+    if (count > (int64_t)B.max_seq_len || count > (int64_t)max_tokens) {
+        if (!walks && threadIdx.x == 0) {
+            meta->status |= SAM_STATUS_CAPACITY_BIT;
+            atomicOr(B.status, SAM_STATUS_CAPACITY_BIT);
+        }
+        return;
+    }
+    uint32_t n = (uint32_t)count;
+    if (walks) {
+        uint32_t first = n;
+        for (uint32_t base = 0; base < n && first == n; base += 256) {
+            uint32_t at = n;
+#pragma unroll
+            for (int u = 3; u >= 0; u--) {
+                const uint32_t j = base + 64 * u + lane;
+                if (j < n && (uint32_t)tok[j] >= vocab) at = j;
+            }
+            if (__any(at < n))
+                for (int d = 32; d; d /= 2) {
+                    const uint32_t other = (uint32_t)__shfl_xor((int)at, d);
+                    at = other < at ? other : at;
+                }
+            first = uni(at);
+        }
+        n = first;
+        uint32_t s = 0, l = 0, e = 0, fault = 0;
+        if (n) static_tail(S, tok, n, vocab, lane, s, l, e, fault, kAsm);
+        if (lane == 0) {
+            meta->s1 = s; meta->l1 = l; meta->e1 = e;
+            if (fault & SAM_STATUS_INTERNAL_BIT) atomicOr(B.status, SAM_STATUS_INTERNAL_BIT);
+        }
+        return;
+    }
+
+    if (threadIdx.x == 0) bad = n;
+    __syncthreads();
+    for (uint32_t j = threadIdx.x; j < n; j += T)
+        if ((uint32_t)tok[j] >= vocab) atomicMin(&bad, j);
+    __syncthreads();
+    const uint32_t first_bad = bad;
+    if (first_bad < n && threadIdx.x == 0) {
+        meta->status |= SAM_STATUS_TOKEN_BIT;
+        atomicOr(B.status, SAM_STATUS_TOKEN_BIT);
+    }
+    n = first_bad;
+    if (n == 0) return;
+    typedef typename std::conditional<kCompact, IngestCompact, IngestWide>::type IL;
+    typedef typename std::conditional<kCompact, uint16_t, uint32_t>::type I;
+    typedef typename std::conditional<kCompact, uint32_t, uint64_t>::type K;
+    const IngestSeq q{tok, n, B.dyn_text + (size_t)b * B.max_seq_len,
+                      reinterpret_cast<char *>(B.dyn_rec) +
+                          (size_t)b * B.max_states * (kCompact ? sizeof(DynRecCompact) : sizeof(DynRec)),
+                      reinterpret_cast<char *>(B.dyn_slots) + (size_t)b * B.dyn_buckets * 128, B.dyn_buckets};
+    PromptCtx<T> ctx{threadIdx.x, wsum};
+    uint32_t *small;
+    if (n <= lds_tokens) {
+        IngestArrays<uint16_t, uint32_t> A;
+        ingest_place_lds(A, lds, n);
+        small = A.small;
+        ingest_build<IL, true>(ctx, q, A);
+    } else {
+        IngestArrays<I, K> A;
+        ingest_place_tables(A, q, lds, n);
+        small = A.small;
+        ingest_build<IL, false>(ctx, q, A);
+    }
+    if (threadIdx.x == 0) {
+        const uint32_t last = small[123], P = IL::link(q.rec, last);
+        uint32_t len, link, endpos, itok;
+        IL::load(q.rec, P, len, link, endpos, itok);
+        meta->n = n; meta->n_states = small[124]; meta->last = last; meta->n_trans = small[125];
+        meta->s2 = P;
+        meta->p_len = len; meta->p_link = link; meta->p_endpos = endpos;
+        meta->p_head = IL::head(ctx, q.rec, P);
+        meta->p_itok = itok; meta->p_idst = IL::idst(q.rec, P);
+    }
+}
+hipError_t launch_ingest(const StaticView &S, const BatchView &B, const int32_t *seq_map,
+                         int n_seqs, const int32_t *tokens, const int64_t *offsets,
+                         int64_t max_tokens, hipStream_t stream)
+{
+    if (max_tokens < kPromptMinTokens || max_tokens > (int64_t)kIngestMaxTokens)
+        return launch_feed(S, B, seq_map, n_seqs, tokens, offsets, nullptr, nullptr, nullptr,
+                           nullptr, nullptr, stream);
+    int dev = 0, lds_limit = 0, n_cu = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess)
+        e = hipDeviceGetAttribute(&lds_limit, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
+    if (e == hipSuccess)
+        e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    const size_t room = (size_t)lds_limit - 256;             // the kernel's own words
+    // the most tokens whose working arrays fit
+    uint32_t fit = 0, over = kIngestIdx16 + 1;
+    while (over - fit > 1) {
+        const uint32_t mid = (fit + over) / 2;
+        if (ingest_lds_bytes(mid) <= room) fit = mid; else over = mid;
+    }
+    const uint32_t most = (uint32_t)max_tokens, lds_tokens = most < fit ? most : fit;
+    size_t bytes = ingest_lds_bytes(lds_tokens);
+    if (most > lds_tokens) {
+        const size_t small = B.compact ? ingest_small_bytes<uint16_t>(most, true)
+                                       : ingest_small_bytes<uint32_t>(most, true);
+        bytes = small > bytes ? small : bytes;
+        const size_t rec_bytes = (size_t)B.max_states * (B.compact ? sizeof(DynRecCompact) : sizeof(DynRec)),
+                     slot_bytes = (size_t)B.dyn_buckets * 128;
+        if (!(B.compact ? ingest_tables_fit<uint16_t, uint32_t>(most, rec_bytes, slot_bytes)
+                        : ingest_tables_fit<uint32_t, uint64_t>(most, rec_bytes, slot_bytes)) || bytes > room)
+            return launch_feed(S, B, seq_map, n_seqs, tokens, offsets, nullptr, nullptr, nullptr,
+                               nullptr, nullptr, stream);
+    }
+    const int threads = short_prompts(n_seqs, max_tokens, n_cu) ? 256 : 1024, waves = threads / 64;
+    const int n_static = B.has_static ? (((n_seqs + waves - 1) / waves + 7) & ~7) : 0;
+#define SAM_LAUNCH_PROMPT_T(COMPACT, ASM, T)                                                     \
+    hipLaunchKernelGGL((sam_prompt_kernel<COMPACT, ASM, T>), dim3(n_static + n_seqs), dim3(T),    \
+                       bytes, stream, S, B, seq_map, n_seqs, n_static, tokens, offsets,          \
+                       lds_tokens, most)
+#define SAM_LAUNCH_PROMPT(COMPACT, ASM)                                                          \
+    do {                                                                                        \
+        if (threads == 256) SAM_LAUNCH_PROMPT_T(COMPACT, ASM, 256);                              \
+        else SAM_LAUNCH_PROMPT_T(COMPACT, ASM, 1024);                                            \
+    } while (0)
+    const bool cxx = B.no_asm || (S.n_buckets >> 32);
+    if (B.compact) {
+        if (cxx) SAM_LAUNCH_PROMPT(true, false); else SAM_LAUNCH_PROMPT(true, true);
+    } else {
+        if (cxx) SAM_LAUNCH_PROMPT(false, false); else SAM_LAUNCH_PROMPT(false, true);
+    }
+#undef SAM_LAUNCH_PROMPT
+#undef SAM_LAUNCH_PROMPT_T
+    return hipGetLastError();
+}
+
+}  // namespace sam
