@@ -356,7 +356,9 @@ SAM_HD uint32_t ingest_hash(uint32_t k)
 }
 SAM_HD uint32_t ingest_hash(uint64_t k) { return ingest_hash((uint32_t)k ^ (uint32_t)(k >> 32) * 0x85EBCA77u); }
 
-// Results: small[123] id of the last prefix, small[124] states, small[125] transitions.
+// Results: small[123] id of the last prefix, small[124] states, small[125] transitions,
+// small[121] not 0: a loop that follows table contents ran into its guard (only if something
+// else wrote to the tables meanwhile), the automaton is not to be used.
 template <class L, bool kLds, class I, class K, class C>
 SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A)
 {
@@ -369,14 +371,16 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
     uint32_t *const small = A.small;
     uint32_t *const active = small;                  // [64] one flag per round
     const uint32_t words = n / 32 + 1;
+    auto corrupt = [&] { ctx.bit_or(&small[121], 1u); };
 
     auto insert = [&](K key) -> uint32_t {
-        uint32_t at = ctx.mulhi(ingest_hash(key), hs);
-        for (uint32_t left = hs; left; left--) {
+        uint32_t at = ctx.mulhi(ingest_hash(key), hs), left = hs;
+        for (; left; left--) {
             const K old = ctx.cas(&A.key[at], kEmpty, key);
             if (old == kEmpty || old == key) break;
             at = at + 1 == hs ? 0 : at + 1;
         }
+        if (!kLds && !left) corrupt();
         ctx.add(&A.val[at], (K)1);
         return at;
     };
@@ -482,9 +486,11 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
             const K key = A.key[i];
             if (key == kEmpty) return;
             const K w = A.cursor[bucket_of_pair(key)];
-            uint32_t start = (uint32_t)(w & kLow);
-            for (uint32_t j = (uint32_t)(w >> kHalf); j; j = A.next[j - 1])
+            uint32_t start = (uint32_t)(w & kLow), left = hs;
+            for (uint32_t j = (uint32_t)(w >> kHalf); j; j = A.next[j - 1]) {
                 if (A.key[j - 1] < key) start += (uint32_t)(A.val[j - 1] & kLow);
+                if (!kLds && !--left) { corrupt(); return; }
+            }
             A.val[i] |= (K)((K)start << kHalf);
             if (start != (uint32_t)(key >> kHalf)) A.lev[start] = (uint8_t)round;
         });
@@ -621,8 +627,11 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
     ctx.sync();
     // first end positions: every prefix goes up until a smaller one has been there
     ctx.each(n, [&](uint32_t i) {
-        for (I v = A.leaf[i]; v != kRoot && A.pfx[v] == kNone; v = A.par[v])
+        uint32_t left = n + 1;
+        for (I v = A.leaf[i]; v != kRoot && A.pfx[v] == kNone; v = A.par[v]) {
             if (ctx.lower(&A.m[v], i) < i) break;
+            if (!kLds && !--left) { corrupt(); break; }
+        }
     });
     ctx.sync();
     ctx.each(n, [&](uint32_t i) {
@@ -691,6 +700,14 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
         });
         ctx.each(n, [&](uint32_t i) { A.text[i] = q.tok[i]; });
         ctx.sync();
+        // LDS is this workgroup's alone, but what was just read went through the tables: links that
+        // lead to shorter states end at the root
+        ctx.each(states, [&](uint32_t v) {
+            const uint32_t up = A.state[2 * v] >> 16;
+            if (v && (up >= states || (A.state[2 * up] & 0xFFFFu) >= (A.state[2 * v] & 0xFFFFu))) corrupt();
+        });
+        ctx.sync();
+        if (small[121]) return;
     } else {
         // the slot table held the arrays above: empty again
         uint64_t *const s = reinterpret_cast<uint64_t *>(q.slots);
@@ -701,10 +718,11 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
     auto len_of = [&](uint32_t v) -> uint32_t { return kLds ? A.state[2 * v] & 0xFFFFu : L::len(q.rec, v); };
     // The state that holds w tokens of the suffix path of u (u is that long, w > 0).
     auto ancestor = [&](uint32_t u, uint32_t w) -> uint32_t {
-        for (;;) {
+        for (uint32_t left = states;;) {
             const uint32_t up = link_of(u);
             if (len_of(up) < w) return u;
             u = up;
+            if (!kLds && !--left) { corrupt(); return u; }
         }
     };
     // inline targets of the clones: they are the ids that follow a prefix with its bit set
@@ -727,7 +745,7 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
     ctx.each(n - 1, [&](uint32_t i) {
         const uint32_t t = (uint32_t)(kLds ? A.text[i + 1] : q.tok[i + 1]);
         uint32_t u = prefix_id(i + 1), v = link_of(prefix_id(i)), made = 0;
-        for (;;) {
+        for (uint32_t left = states;;) {
             uint32_t len, link, endpos, itok;
             if (kLds) {
                 const uint32_t a = A.state[2 * v];
@@ -751,6 +769,7 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
                     }
                     b = b + 1 == q.n_buckets ? 0 : b + 1;
                 }
+                if (got == 2) corrupt();
                 if (got) break;
                 u = ancestor(u, len + 1);
                 if (kLds && L::kHead16)
@@ -761,6 +780,7 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
             }
             if (v == 0) break;
             v = link;
+            if (!kLds && !--left) { corrupt(); break; }
         }
         if (made) ctx.add(&small[126], made);
     });

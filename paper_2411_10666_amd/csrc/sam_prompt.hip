@@ -226,6 +226,11 @@ __global__ __launch_bounds__(T) void sam_prompt_kernel(StaticView S, BatchView B
         ingest_build<IL, false>(ctx, q, A);
     }
     if (threadIdx.x == 0) {
+        if (small[121]) {
+            meta->status |= SAM_STATUS_INTERNAL_BIT;
+            atomicOr(B.status, SAM_STATUS_INTERNAL_BIT);
+            return;                          // nothing of this sequence is valid from here on
+        }
         const uint32_t last = small[123], P = IL::link(q.rec, last);
         uint32_t len, link, endpos, itok;
         IL::load(q.rec, P, len, link, endpos, itok);

@@ -107,8 +107,54 @@ static int one(const std::vector<int32_t> &x, int32_t vocab, uint32_t max_seq_le
     return seen == h.n_trans ? 0 : bad("transition lists", n, (uint32_t)seen);
 }
 
+// Tables that something else writes to, or that are too small: every loop ends, and says so.
+struct MeddlingCtx : CpuCtx<256> {
+    uint32_t syncs = 0, at = 0, states = 0;
+    uint32_t *rec = nullptr;
+    void sync()
+    {
+        if (++syncs != at) return;
+        for (uint32_t v = 0; v < states; v++) rec[4 * v] = 0xFFFFu | (v << 16);      // links that lead nowhere
+    }
+};
+
+static int guards()
+{
+    const uint32_t n = 3000, cap = 3000;
+    std::mt19937 rng(7);
+    std::vector<int32_t> x(n);
+    for (int32_t &t : x) t = (int32_t)(rng() % 3);
+    uint32_t syncs[2], caught[2] = {0, 0};
+    // left alone but for a slot table of two buckets (run 0), left alone (1), meddled with at
+    // each of the last barriers; arrays in LDS and in the tables
+    for (uint32_t k = 0; k < 20; k++) {
+        const uint32_t run = k / 2;
+        const bool lds = k % 2 == 0;
+        const uint32_t n_buckets = run == 0 ? 2 : (uint32_t)(dynamic_slots_for(cap) / 16);
+        if (!lds && (run == 0 || run > 5)) continue;        // before that the records hold other arrays
+        Aligned rec((2 * cap + 2) * sizeof(DynRecCompact), 0x5A), slots((size_t)n_buckets * 128, 0xFF), text(cap * 4, 0);
+        Aligned mem(lds ? ingest_lds_bytes(n) : ingest_small_bytes<uint16_t>(n, true), 0xA5);
+        const IngestSeq q{x.data(), n, (int32_t *)text.p, rec.p, slots.p, n_buckets};
+        IngestArrays<uint16_t, uint32_t> A;
+        if (lds) ingest_place_lds(A, (char *)mem.p, n);
+        else ingest_place_tables(A, q, (char *)mem.p, n);
+        MeddlingCtx ctx;
+        ctx.rec = (uint32_t *)rec.p;
+        ctx.states = n;
+        ctx.at = run < 2 ? 0 : syncs[lds] - (run - 2);
+        if (lds) ingest_build<IngestCompact, true>(ctx, q, A);
+        else ingest_build<IngestCompact, false>(ctx, q, A);
+        if (run == 0 && !A.small[121]) return bad("guard of the slot table", n, run);
+        if (run == 1 && A.small[121]) return bad("guard, nothing wrong", n, run);
+        if (run == 1) syncs[lds] = ctx.syncs;
+        if (run > 1 && A.small[121]) caught[lds]++;
+    }
+    return caught[0] && caught[1] ? 0 : bad("guards of the links", n, caught[0]);
+}
+
 int main()
 {
+    if (guards()) return 1;
     std::mt19937 rng(5);
     const uint32_t sizes[] = {1, 2, 3, 7, 8, 9, 63, 64, 65, 255, 256, 257, 511, 513, 1023, 1024, 1025, 2500, 6200};
     for (const uint32_t n : sizes)
