@@ -204,7 +204,10 @@ int sam_batch_init(const sam_corpus *corpus, const int32_t *prompt_tokens,
  * allocate and free no device memory.
  *   prompt_offsets_host : host, int64 [batch+1]; the same values as the device
  *                    array.  They are validated from this copy, so the call does
- *                    not read anything back and does not synchronise.
+ *                    not read anything back and does not synchronise.  A call captured
+ *                    in a graph may be replayed with other prompts and offsets in the
+ *                    same device arrays, each prompt of at most max_seq_len tokens; it
+ *                    is fastest where none is longer than when it was captured.
  *   all other arguments as for sam_batch_init.
  * Differences from sam_batch_init: asynchronous; a prompt token outside the
  * vocabulary is reported by sam_batch_status (SAM_STATUS_TOKEN), not by the

@@ -464,12 +464,13 @@ static int batch_check_args(const char *fn, const sam_corpus *corpus, const int3
     return SAM_OK;
 }
 
-static int64_t longest_prompt(const int64_t *offs, int32_t n)
+static PromptSizes prompt_sizes(const int64_t *offs, int32_t n)
 {
-    int64_t most = 0;
+    PromptSizes p = {0, 0};
     for (int32_t i = 0; i < n; i++)
-        if (offs[i + 1] - offs[i] > most) most = offs[i + 1] - offs[i];
-    return most;
+        if (offs[i + 1] - offs[i] > p.longest) p.longest = offs[i + 1] - offs[i];
+    p.most = p.longest;
+    return p;
 }
 
 static int batch_check_offsets(const char *fn, const int64_t *offs, int32_t batch,
@@ -577,7 +578,7 @@ int sam_batch_init(const sam_corpus *corpus, const int32_t *prompt_tokens,
     if ((e = hipMemsetAsync(v.dyn_slots, 0xFF, bb.slots, stream)) != hipSuccess ||
         (e = launch_reset(v, nullptr, batch, stream)) != hipSuccess ||
         (e = launch_ingest(S, v, nullptr, batch, prompt_tokens, prompt_offsets,
-                           longest_prompt(offs.data(), batch), stream)) != hipSuccess ||
+                           prompt_sizes(offs.data(), batch), stream)) != hipSuccess ||
         (e = hipStreamSynchronize(stream)) != hipSuccess) {
         batch_release(bt);
         return fail_hip("sam_batch_init: prompt ingest", e);
@@ -654,11 +655,15 @@ int sam_batch_init_noalloc(const sam_corpus *corpus, const int32_t *prompt_token
     // the buffer keeps what the last batch left: empty the slot tables, then fresh
     // records, cursors and status word (the reset kernel), then the prompts
     StaticView S = corpus ? corpus->view : StaticView{};
+    // the device's offsets are read when the kernel runs; in a captured graph they may be others
+    // by then, up to what a sequence holds
+    PromptSizes sizes = prompt_sizes(prompt_offsets_host, batch);
+    sizes.most = max_seq_len;
     hipError_t e;
     if ((e = launch_fill_empty(v.dyn_slots, bb.slots, stream)) != hipSuccess ||
         (e = launch_reset(v, nullptr, batch, stream)) != hipSuccess ||
-        (e = launch_ingest(S, v, nullptr, batch, prompt_tokens, prompt_offsets,
-                           longest_prompt(prompt_offsets_host, batch), stream)) != hipSuccess) {
+        (e = launch_ingest(S, v, nullptr, batch, prompt_tokens, prompt_offsets, sizes,
+                           stream)) != hipSuccess) {
         batch_release(bt);
         return fail_hip("sam_batch_init_noalloc: launch", e);
     }
@@ -766,7 +771,7 @@ int sam_batch_reset(sam_batch *bt, const int32_t *slots, int32_t n_slots,
     hipError_t e;
     if ((e = launch_reset(v, slots, n_slots, stream)) != hipSuccess ||
         (e = launch_ingest(S, v, slots, n_slots, prompt_tokens, prompt_offsets,
-                           longest_prompt(offs.data(), n_slots), stream)) != hipSuccess)
+                           prompt_sizes(offs.data(), n_slots), stream)) != hipSuccess)
         return fail_hip("sam_batch_reset: launch", e);
     return SAM_OK;
 }

@@ -241,11 +241,12 @@ __global__ __launch_bounds__(T) void sam_prompt_kernel(StaticView S, BatchView B
         meta->p_itok = itok; meta->p_idst = IL::idst(q.rec, P);
     }
 }
+
 hipError_t launch_ingest(const StaticView &S, const BatchView &B, const int32_t *seq_map,
                          int n_seqs, const int32_t *tokens, const int64_t *offsets,
-                         int64_t max_tokens, hipStream_t stream)
+                         const PromptSizes &sizes, hipStream_t stream)
 {
-    if (max_tokens < kPromptMinTokens || max_tokens > (int64_t)kIngestMaxTokens)
+    if (sizes.longest < kPromptMinTokens || sizes.most > (int64_t)kIngestMaxTokens)
         return launch_feed(S, B, seq_map, n_seqs, tokens, offsets, nullptr, nullptr, nullptr,
                            nullptr, nullptr, stream);
     int dev = 0, lds_limit = 0, n_cu = 0;
@@ -262,7 +263,8 @@ hipError_t launch_ingest(const StaticView &S, const BatchView &B, const int32_t 
         const uint32_t mid = (fit + over) / 2;
         if (ingest_lds_bytes(mid) <= room) fit = mid; else over = mid;
     }
-    const uint32_t most = (uint32_t)max_tokens, lds_tokens = most < fit ? most : fit;
+    const uint32_t most = (uint32_t)sizes.most;
+    uint32_t lds_tokens = (uint32_t)sizes.longest < fit ? (uint32_t)sizes.longest : fit;
     size_t bytes = ingest_lds_bytes(lds_tokens);
     if (most > lds_tokens) {
         const size_t small = B.compact ? ingest_small_bytes<uint16_t>(most, true)
@@ -271,11 +273,16 @@ hipError_t launch_ingest(const StaticView &S, const BatchView &B, const int32_t 
         const size_t rec_bytes = (size_t)B.max_states * (B.compact ? sizeof(DynRecCompact) : sizeof(DynRec)),
                      slot_bytes = (size_t)B.dyn_buckets * 128;
         if (!(B.compact ? ingest_tables_fit<uint16_t, uint32_t>(most, rec_bytes, slot_bytes)
-                        : ingest_tables_fit<uint32_t, uint64_t>(most, rec_bytes, slot_bytes)) || bytes > room)
-            return launch_feed(S, B, seq_map, n_seqs, tokens, offsets, nullptr, nullptr, nullptr,
-                               nullptr, nullptr, stream);
+                        : ingest_tables_fit<uint32_t, uint64_t>(most, rec_bytes, slot_bytes)) || bytes > room) {
+            // (small tables have too little room beside the fixed parts)
+            if (most > fit)
+                return launch_feed(S, B, seq_map, n_seqs, tokens, offsets, nullptr, nullptr, nullptr,
+                                   nullptr, nullptr, stream);
+            lds_tokens = most;
+            bytes = ingest_lds_bytes(lds_tokens);
+        }
     }
-    const int threads = short_prompts(n_seqs, max_tokens, n_cu) ? 256 : 1024, waves = threads / 64;
+    const int threads = short_prompts(n_seqs, sizes.longest, n_cu) ? 256 : 1024, waves = threads / 64;
     const int n_static = B.has_static ? (((n_seqs + waves - 1) / waves + 7) & ~7) : 0;
 #define SAM_LAUNCH_PROMPT_T(COMPACT, ASM, T)                                                     \
     hipLaunchKernelGGL((sam_prompt_kernel<COMPACT, ASM, T>), dim3(n_static + n_seqs), dim3(T),    \

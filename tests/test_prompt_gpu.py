@@ -113,3 +113,54 @@ def test_a_bad_token_ends_its_prompt(at):
                       np.zeros((1, 3), np.int32), 4, 4)
     assert np.array_equal(got[:, :4], r[0]["cursors"])
     assert np.array_equal(got[:, 4:], r[0]["sizes"])
+
+
+# a captured init, replayed with prompts of other lengths in the same buffers: longer ones than it was
+# captured with, within and beyond what LDS holds, in tables with room for the working arrays and without
+@pytest.mark.parametrize("captured,replayed,T", [(100, 300, 340), (100, 2500, 2600), (2000, 9000, 9040),
+                                                 (70, 20_000, 20_040), (30, 500, 540)])
+def test_replayed_init_takes_longer_prompts(captured, replayed, T):
+    import torch
+    from paper_2411_10666_amd import binding as sam
+    rng = np.random.default_rng(captured)
+    vocab, B, A, L = 400, 2, 8, 8
+    corpus = _text("copies", 2000, vocab, rng)
+    c = sam.sam_build(corpus, vocab)
+    dev = torch.device("cuda")
+    first = [_text("copies", n, vocab, rng) for n in (captured, captured // 2)]
+    tokens = torch.zeros(2 * replayed, dtype=torch.int32, device=dev)
+    offsets = torch.zeros(B + 1, dtype=torch.int64, device=dev)
+
+    def put(prompts):
+        flat = np.concatenate(prompts)
+        tokens[:len(flat)].copy_(torch.from_numpy(flat))
+        offsets.copy_(torch.from_numpy(np.cumsum([0] + [len(p) for p in prompts])))
+        torch.cuda.synchronize()
+
+    put(first)
+    offs = offsets.cpu().numpy()
+    del_me = sam.sam_batch_init_noalloc(c, tokens, offsets, offs, B, vocab, T, A, L)      # looks the buffer up
+    del del_me
+    graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=stream):
+        batch = sam.sam_batch_init_noalloc(c, tokens, offsets, offs, B, vocab, T, A, L, 0, stream)
+    i32 = dict(dtype=torch.int32, device=dev)
+    zero = np.zeros((1, B, A), np.int32), np.zeros((1, B), np.int32)
+    accepted, counts = (torch.from_numpy(z[0]).to(dev) for z in zero)
+    for prompts in (first, [_text("copies", n, vocab, rng) for n in (replayed // 3, replayed)],
+                    [_text("copies", n, vocab, rng) for n in (replayed, 5)], first):
+        put(prompts)
+        graph.replay()
+        torch.cuda.synchronize()
+        ml, dl, src = (torch.empty(B, **i32) for _ in range(3))
+        dr = torch.empty(B, L, **i32)
+        state = [torch.empty(B, **i32) for _ in range(7)]
+        sam.sam_batch_step(batch, accepted, counts, ml, dr, dl, src)
+        sam.sam_batch_debug(batch, *state[:4])
+        sam.sam_batch_sizes(batch, *state[4:])
+        assert sam.sam_batch_status(batch) == 0
+        g = dict(match_len=ml, draft_len=dl, source=src, draft=dr, cursors=torch.stack(state[:4], 1),
+                 sizes=torch.stack(state[4:], 1))
+        r, _ = run_oracle(corpus, prompts, *zero, A, L)
+        assert_same([{k: v.cpu().numpy() for k, v in g.items()}], r)
+    del batch
