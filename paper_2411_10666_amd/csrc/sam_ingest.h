@@ -187,6 +187,7 @@ struct IngestArrays {
     uint32_t *sec;       // [n]
     I        *names;     // [7][stride] names of the last 16 * 4^j tokens (tables in device memory only)
     uint32_t  stride;    // n rounded up to 16
+    size_t    dirty;     // bytes of the slot table that held any of this (tables in device memory only)
     // the states, once their records are written, and the text (all in LDS only)
     uint32_t *state;     // [2n + 1][2] len | link << 16, min_endpos | head << 16
     int32_t  *text;      // [n]
@@ -288,9 +289,18 @@ SAM_HD void ingest_place_lds(IngestArrays<uint16_t, uint32_t> &A, char *lds, uin
     A.text = u.take<int32_t>(n);
 }
 
+// Levels of names that n tokens have: 16, 64, 256 ... of them at a time.
+SAM_HD uint32_t ingest_name_levels(uint32_t n)
+{
+    uint32_t levels = 0;
+    for (uint32_t w = 16; w < n; w *= 4) levels++;
+    return levels;
+}
+
 // The large arrays in the sequence's own tables, which hold nothing yet: 16 indices a
 // token in the record table, 8 in the slot table (plus its 64 spare slots).  What the
-// records are written from is in the slot table, which is emptied again afterwards.
+// records are written from is in the slot table; the part of it that was used is emptied again
+// afterwards.
 template <class I, class K>
 SAM_HD void ingest_place_tables(IngestArrays<I, K> &A, const IngestSeq &q, char *lds, uint32_t n)
 {
@@ -299,6 +309,7 @@ SAM_HD void ingest_place_tables(IngestArrays<I, K> &A, const IngestSeq &q, char 
     A.mins = s.take<I>(ingest_upper_mins(n));
     A.state = nullptr;
     A.text = nullptr;
+    A.names = nullptr;
     A.h_size = ingest_h_size(n);
     A.name1 = nullptr;
     IngestBump r{reinterpret_cast<char *>(q.rec)};
@@ -324,6 +335,10 @@ SAM_HD void ingest_place_tables(IngestArrays<I, K> &A, const IngestSeq &q, char 
     A.leaf = t.take<I>(n);
     A.m = t.take<uint32_t>(n);
     A.sec = t.take<uint32_t>(n);
+    const size_t rest = (size_t)(t.p - reinterpret_cast<char *>(q.slots)),
+                 names = (size_t)(reinterpret_cast<char *>(A.names + ingest_name_levels(n) * (size_t)A.stride) -
+                                  reinterpret_cast<char *>(q.slots));
+    A.dirty = names > rest ? names : rest;
 }
 
 // Do the working arrays of n tokens fit into tables of these sizes?  (They do unless the
@@ -333,11 +348,9 @@ inline bool ingest_tables_fit(uint32_t n, size_t rec_bytes, size_t slot_bytes)
 {
     const size_t h = ingest_h_size(n), N = n;
     auto up = [](size_t x) { return (x + 15) / 16 * 16; };
-    size_t levels = 0;
-    for (size_t w = 16; w < N; w *= 4) levels++;
     const size_t sort = 2 * up(sizeof(K) * h) + up(sizeof(I) * h) + up(sizeof(K) * N) + 2 * up(sizeof(I) * N);
     const size_t tree = 2 * up(sizeof(I) * N) + up(2 * sizeof(I) * N) + up(sizeof(I) * ingest_first_mins(n));
-    const size_t names = levels * sizeof(I) * ((N + 15) / 16 * 16);
+    const size_t names = ingest_name_levels(n) * sizeof(I) * ((N + 15) / 16 * 16);
     const size_t rest = 3 * up(sizeof(I) * N) + 2 * up(4 * N);
     return up(sizeof(I) * N) + up(N) + (sort > tree ? sort : tree) <= rec_bytes &&
            up(sizeof(I) * ingest_pad(n)) + (names > rest ? names : rest) <= slot_bytes;
@@ -709,9 +722,10 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
         ctx.sync();
         if (small[121]) return;
     } else {
-        // the slot table held the arrays above: empty again
+        // What of the slot table held the arrays above is emptied again, about 20 bytes a token
+        // (24 to 32 with 32-bit indices); the rest, which may be far larger, still is empty.
         uint64_t *const s = reinterpret_cast<uint64_t *>(q.slots);
-        ctx.each(q.n_buckets * 16u, [&](uint32_t i) { s[i] = ~(uint64_t)0; });
+        ctx.each((uint32_t)(A.dirty / 8), [&](uint32_t i) { s[i] = ~(uint64_t)0; });
     }
     // the root's link reads as kNil or, from LDS, as 0xFFFF; nothing asks for it
     auto link_of = [&](uint32_t v) -> uint32_t { return kLds ? A.state[2 * v] >> 16 : L::link(q.rec, v); };

@@ -18,7 +18,8 @@ using namespace sam;
 template <uint32_t T>
 struct CpuCtx {
     static constexpr uint32_t kThreads = T;
-    template <class F> void each(uint32_t n, F f) { for (uint32_t i = 0; i < n; i++) f(i); }
+    uint32_t widest = 0;                   // the most indices that a phase runs over
+    template <class F> void each(uint32_t n, F f) { if (n > widest) widest = n; for (uint32_t i = 0; i < n; i++) f(i); }
     template <class F> void each_full(uint32_t n, F f) { for (uint32_t i = 0; i < n; i++) f(i, true); }
     void sync() {}
     template <class U> U cas(U *p, U expected, U v) { const U old = *p; if (old == expected) *p = v; return old; }
@@ -74,6 +75,8 @@ static int one(const std::vector<int32_t> &x, int32_t vocab, uint32_t max_seq_le
     HostSam h;
     std::string err;
     if (h.build(x.data(), n, vocab, err) != 0) return bad(err.c_str(), n, 0);
+    // no phase works on more than the prompt's own share of the tables, however large they are
+    if (ctx.widest > 6 * n + 1024) return bad("widest phase", n, ctx.widest);
     if (A.small[124] != h.n_states) return bad("states", n, A.small[124]);
     if (A.small[125] != h.n_trans) return bad("transitions", n, A.small[125]);
     if (memcmp(text.p, x.data(), (size_t)n * 4)) return bad("text", n, 0);
@@ -180,6 +183,14 @@ int main()
                                 one<IngestWide, false, uint32_t, uint64_t, 1024>(x, vocab, cap)))
                     return 1;
             }
+    // a short prompt in a long sequence's tables
+    for (const uint32_t n : {64u, 700u, 3000u}) {
+        std::vector<int32_t> x(n);
+        for (int32_t &t : x) t = (int32_t)(rng() % 9);
+        if (one<IngestCompact, false, uint16_t, uint32_t, 1024>(x, 9, 16366) ||
+            one<IngestWide, false, uint32_t, uint64_t, 1024>(x, 9, 200000))
+            return 1;
+    }
     printf("ok\n");
     return 0;
 }
