@@ -55,6 +55,20 @@ struct PromptCtx {
     {
         for (uint32_t i = tid; i - tid < n; i += T) f(i, i < n);
     }
+    // one wave for each index, with 64 words of part[] to itself
+    template <class F>
+    __device__ __forceinline__ void each_wave(uint32_t n, uint32_t *part, F f)
+    {
+        for (uint32_t i = tid / 64; i < n; i += T / 64) f(i, part + (tid & ~63u));
+    }
+    template <class F>
+    __device__ __forceinline__ void lanes(F f) { f(tid & 63); }
+    __device__ __forceinline__ void wave_sync()
+    {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    }
     __device__ __forceinline__ void sync() { __syncthreads(); }
     template <class U>
     __device__ __forceinline__ U cas(U *p, U expected, U v)

@@ -19,10 +19,22 @@ template <uint32_t T>
 struct CpuCtx {
     static constexpr uint32_t kThreads = T;
     uint32_t widest = 0;                   // the most indices that a phase runs over
-    template <class F> void each(uint32_t n, F f) { if (n > widest) widest = n; for (uint32_t i = 0; i < n; i++) f(i); }
+    uint32_t swaps = 0, most_swaps = 0;    // compare-and-swaps that one index makes, one after the other
+    template <class F> void each(uint32_t n, F f)
+    {
+        if (n > widest) widest = n;
+        for (uint32_t i = 0; i < n; i++) {
+            swaps = 0;
+            f(i);
+            if (swaps > most_swaps) most_swaps = swaps;
+        }
+    }
+    template <class F> void each_wave(uint32_t n, uint32_t *part, F f) { for (uint32_t i = 0; i < n; i++) f(i, part); }
+    template <class F> void lanes(F f) { for (uint32_t i = 0; i < 64; i++) f(i); }
+    void wave_sync() {}
     template <class F> void each_full(uint32_t n, F f) { for (uint32_t i = 0; i < n; i++) f(i, true); }
     void sync() {}
-    template <class U> U cas(U *p, U expected, U v) { const U old = *p; if (old == expected) *p = v; return old; }
+    template <class U> U cas(U *p, U expected, U v) { swaps++; const U old = *p; if (old == expected) *p = v; return old; }
     template <class U> U add(U *p, U v) { const U old = *p; *p = (U)(old + v); return old; }
     uint32_t lower(uint32_t *p, uint32_t v) { const uint32_t old = *p; if (v < old) *p = v; return old; }
     void bit_or(uint32_t *p, uint32_t v) { *p |= v; }
@@ -77,6 +89,7 @@ static int one(const std::vector<int32_t> &x, int32_t vocab, uint32_t max_seq_le
     if (h.build(x.data(), n, vocab, err) != 0) return bad(err.c_str(), n, 0);
     // no phase works on more than the prompt's own share of the tables, however large they are
     if (ctx.widest > 6 * n + 1024) return bad("widest phase", n, ctx.widest);
+    if (ctx.most_swaps > 500) return bad("swaps in a row", n, ctx.most_swaps);
     if (A.small[124] != h.n_states) return bad("states", n, A.small[124]);
     if (A.small[125] != h.n_trans) return bad("transitions", n, A.small[125]);
     if (memcmp(text.p, x.data(), (size_t)n * 4)) return bad("text", n, 0);
@@ -161,7 +174,7 @@ int main()
     std::mt19937 rng(5);
     const uint32_t sizes[] = {1, 2, 3, 7, 8, 9, 63, 64, 65, 255, 256, 257, 511, 513, 1023, 1024, 1025, 2500, 6200};
     for (const uint32_t n : sizes)
-        for (int kind = 0; kind < 5; kind++)
+        for (int kind = 0; kind < 9; kind++)
             for (const int32_t vocab : {2, 60, 9000}) {
                 std::vector<int32_t> x(n);
                 for (uint32_t i = 0; i < n; i++) {
@@ -174,6 +187,16 @@ int main()
                         const uint32_t from = rng() % i;
                         const uint32_t back = i - from;
                         for (uint32_t k = rng() % 80; k && i < n; k--, i++) x[i] = x[i - back];
+                    }
+                // long walks: a run and another token, a period of two and another token, two runs
+                // with different tokens around them, a run that is three quarters of the text
+                if (kind >= 5)
+                    for (uint32_t i = 0; i < n; i++) {
+                        const int32_t a = vocab - 1;
+                        if (kind == 5) x[i] = i + 1 == n ? 0 : a;
+                        if (kind == 6) x[i] = i + 1 == n ? vocab / 2 : (int32_t)(i % 2) * a;
+                        if (kind == 7) x[i] = i == 0 || i + 1 == n || i == n / 2 ? (int32_t)(i % 5) % vocab : a;
+                        if (kind == 8 && i < n * 3 / 4) x[i] = 0;
                     }
                 const uint32_t cap = n + rng() % 20;
                 if (one<IngestCompact, true, uint16_t, uint32_t, 1024>(x, vocab, cap) ||
