@@ -390,15 +390,19 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
     auto corrupt = [&] { ctx.bit_or(&small[121], 1u); };
 
     auto insert = [&](K key) -> uint32_t {
-        uint32_t at = ctx.mulhi(ingest_hash(key), hs), left = hs;
-        for (; left; left--) {
-            const K old = ctx.cas(&A.key[at], kEmpty, key);
-            if (old == kEmpty || old == key) break;
-            at = at + 1 == hs ? 0 : at + 1;
-        }
-        if (!kLds && !left) corrupt();
-        ctx.add(&A.val[at], (K)1);
-        return at;
+        auto put = [&](uint32_t times) -> uint32_t {
+            uint32_t at = ctx.mulhi(ingest_hash(key), hs), left = hs;
+            for (; left; left--) {
+                const K old = ctx.cas(&A.key[at], kEmpty, key);
+                if (old == kEmpty || old == key) break;
+                at = at + 1 == hs ? 0 : at + 1;
+            }
+            if (!kLds && !left) corrupt();
+            ctx.add(&A.val[at], (K)times);
+            return at;
+        };
+        if (kLds) return put(1);
+        return ctx.together(key, put);
     };
 
     // names of single tokens

@@ -119,6 +119,29 @@ struct PromptCtx {
         if ((tid & 63) == 63 && upto) base = add(p, upto);
         return (uint32_t)__shfl((int)base, 63) + upto - v;
     }
+    // f(times) for a key: once for all lanes of the wave that have the same one, if they are 8 or
+    // more, else once for each.  Atomics of a workgroup on one address of device memory follow
+    // each other, and in a run of one token all pairs of a round are the same: 64 prompts of 9000
+    // equal tokens took 4.6 ms with an insertion for each position, 1.1 with this.  (In LDS the
+    // same brought 3 % for such texts and cost others 4 %.)
+    template <class U, class F>
+    __device__ __forceinline__ uint32_t together(U key, F f)
+    {
+        uint32_t r = 0;
+        for (bool again = true; again;) {
+            U first = (U)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)key);
+            if constexpr (sizeof(U) == 8)
+                first |= (U)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(key >> 32)) << 32;
+            const uint64_t same = __ballot(key == first);
+            const uint32_t count = (uint32_t)__popcll(same);
+            const int lead = __builtin_ctzll(same);
+            const bool shared = count >= 8;
+            again = shared && key != first;
+            if (!shared || (int)(tid & 63) == lead) r = f(shared ? count : 1u);
+            if (key == first && shared) r = (uint32_t)__builtin_amdgcn_readlane((int)r, lead);
+        }
+        return r;
+    }
     // part[i] becomes the sum of the entries before it; thread i reads entry i
     __device__ __forceinline__ void exclusive_sums(uint32_t *part)
     {

@@ -32,6 +32,7 @@ struct CpuCtx {
     template <class F> void each_wave(uint32_t n, uint32_t *part, F f) { for (uint32_t i = 0; i < n; i++) f(i, part); }
     template <class F> void lanes(F f) { for (uint32_t i = 0; i < 64; i++) f(i); }
     void wave_sync() {}
+    template <class U, class F> uint32_t together(U, F f) { return f(1); }
     template <class F> void each_full(uint32_t n, F f) { for (uint32_t i = 0; i < n; i++) f(i, true); }
     void sync() {}
     template <class U> U cas(U *p, U expected, U v) { swaps++; const U old = *p; if (old == expected) *p = v; return old; }

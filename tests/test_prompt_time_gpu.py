@@ -1,0 +1,76 @@
+"""A prompt taken whole is not slower than the same tokens fed one by one (to empty sequences,
+through sam_batch_step), for texts that are hard on the whole build.  Both are measured here, on
+the same device, the shortest of several runs each; the build takes two thirds of the time at most."""
+import time
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _shortest(f, runs=7):
+    import torch
+    best = float("inf")
+    for _ in range(runs):
+        torch.cuda.synchronize()
+        start = time.perf_counter()
+        f()
+        torch.cuda.synchronize()
+        best = min(best, time.perf_counter() - start)
+    return best
+
+
+def _whole_and_one_by_one(prompts, corpus, vocab):
+    """All prompts have the same length."""
+    import torch
+    from paper_2411_10666_amd import binding as sam
+    dev = torch.device("cuda")
+    B, n = prompts.shape
+    A = next(a for a in range(4096, 0, -1) if n % a == 0)
+    i32 = dict(dtype=torch.int32, device=dev)
+    flat = torch.from_numpy(prompts.reshape(-1)).to(dev)
+    offsets = torch.arange(B + 1, dtype=torch.int64, device=dev) * n
+    nothing = torch.zeros(B + 1, dtype=torch.int64, device=dev)
+    slots = torch.arange(B, **i32)
+    rows = torch.from_numpy(np.ascontiguousarray(prompts.reshape(B, n // A, A).transpose(1, 0, 2))).to(dev)
+    counts = torch.full((B,), A, **i32)
+    out = torch.empty(B, **i32), torch.empty(B, 4, **i32), torch.empty(B, **i32), torch.empty(B, **i32)
+    c = sam.sam_build(corpus, vocab) if corpus is not None else None
+    batch = sam.sam_batch_init(c, flat, nothing, B, vocab, n + 8, A, 4, 0)
+    states = []
+
+    def state():
+        s = [torch.empty(B, **i32) for _ in range(7)]
+        sam.sam_batch_debug(batch, *s[:4])
+        sam.sam_batch_sizes(batch, *s[4:])
+        states.append(torch.stack(s)[(0 if c is not None else 2):].cpu().numpy())
+
+    def one_by_one():
+        sam.sam_batch_reset(batch, slots, flat, nothing)
+        for row in rows:
+            sam.sam_batch_step(batch, row, counts, *out)
+
+    slow = _shortest(one_by_one)
+    state()
+    fast = _shortest(lambda: sam.sam_batch_reset(batch, slots, flat, offsets))
+    state()
+    assert np.array_equal(*states)
+    print("%d x %d: whole %.0f us, one by one %.0f us" % (B, n, fast * 1e6, slow * 1e6), flush=True)
+    return fast, slow
+
+
+@pytest.mark.parametrize("kind", ["equal tokens", "run, then another", "left padding", "period of two"])
+@pytest.mark.parametrize("batch,n", [(1, 1000), (64, 6000), (64, 9000)])
+def test_repeating_texts(kind, batch, n):
+    rng = np.random.default_rng(n)
+    x = np.full((batch, n), 7, np.int32)
+    if kind == "run, then another":
+        x[:, -1] = 9
+    elif kind == "left padding":
+        x[:, n * 3 // 4:] = rng.integers(0, 500, size=(batch, n - n * 3 // 4))
+    elif kind == "period of two":
+        x[:, ::2] = 3
+        x[:, -1] = 9
+    fast, slow = _whole_and_one_by_one(x, None, 500)
+    assert fast < slow
