@@ -115,6 +115,28 @@ def test_a_bad_token_ends_its_prompt(at):
     assert np.array_equal(got[:, 4:], r[0]["sizes"])
 
 
+# The static cursor after a prompt: its end occurs in the corpus with `match` tokens and no more
+# (around the first window, its double, half the prompt, all of it), once, or first with fewer in
+# front of it (the first occurrence then says too little, several times over), or at the very start
+@pytest.mark.parametrize("n", [49, 65, 130, 700])
+@pytest.mark.parametrize("how", ["once", "shorter first", "at the start"])
+def test_matches_at_the_end(n, how):
+    rng = np.random.default_rng(n)
+    vocab = 3000
+    matches = sorted({m for m in (0, 1, 46, 47, 48, 49, 50, 94, 95, 96, 97, 98, 191, 193, 400, n // 2 - 1, n // 2,
+                                  n // 2 + 1, n - 2, n - 1, n) if 0 <= m <= n})
+    prompts, parts = [], [rng.integers(0, vocab, size=300, dtype=np.int32)]
+    for m in matches:
+        p = rng.integers(0, vocab, size=n, dtype=np.int32)
+        prompts.append(p)
+        pieces = [k for k in (48, 49, 55, 100, 210, 430) if k < m] if how == "shorter first" else []
+        for k in pieces + [m]:
+            parts += [p[n - k:], rng.integers(0, vocab, size=7, dtype=np.int32)]
+    if how == "at the start":
+        parts = [prompts[-1]] + parts
+    _compare(prompts, vocab, n + 40, 0, np.concatenate(parts))
+
+
 # a captured init, replayed with prompts of other lengths in the same buffers: longer ones than it was
 # captured with, within and beyond what LDS holds, in tables with room for the working arrays and without
 @pytest.mark.parametrize("captured,replayed,T", [(100, 300, 340), (100, 2500, 2600), (2000, 9000, 9040),

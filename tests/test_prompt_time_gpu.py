@@ -74,3 +74,14 @@ def test_repeating_texts(kind, batch, n):
         x[:, -1] = 9
     fast, slow = _whole_and_one_by_one(x, None, 500)
     assert fast < slow
+
+
+@pytest.mark.parametrize("batch,n", [(64, 3073), (256, 3073), (1024, 800), (64, 12_300)])
+def test_passages_of_the_corpus(batch, n):
+    """Prompts that occur in the corpus as a whole: the walk over the corpus automaton decides."""
+    rng = np.random.default_rng(n)
+    vocab = 8000
+    corpus = np.minimum((vocab * rng.random(2_000_000) ** 4).astype(np.int64), vocab - 1).astype(np.int32)
+    starts = rng.integers(0, corpus.size - n, size=batch)
+    fast, slow = _whole_and_one_by_one(np.stack([corpus[a:a + n] for a in starts]), corpus, vocab)
+    assert fast < slow
