@@ -464,15 +464,6 @@ static int batch_check_args(const char *fn, const sam_corpus *corpus, const int3
     return SAM_OK;
 }
 
-static PromptSizes prompt_sizes(const int64_t *offs, int32_t n)
-{
-    PromptSizes p = {0, 0};
-    for (int32_t i = 0; i < n; i++)
-        if (offs[i + 1] - offs[i] > p.longest) p.longest = offs[i + 1] - offs[i];
-    p.most = p.longest;
-    return p;
-}
-
 static int batch_check_offsets(const char *fn, const int64_t *offs, int32_t batch,
                                int32_t max_seq_len)
 {
@@ -578,7 +569,7 @@ int sam_batch_init(const sam_corpus *corpus, const int32_t *prompt_tokens,
     if ((e = hipMemsetAsync(v.dyn_slots, 0xFF, bb.slots, stream)) != hipSuccess ||
         (e = launch_reset(v, nullptr, batch, stream)) != hipSuccess ||
         (e = launch_ingest(S, v, nullptr, batch, prompt_tokens, prompt_offsets,
-                           prompt_sizes(offs.data(), batch), stream)) != hipSuccess ||
+                           offs.data(), 0, stream)) != hipSuccess ||
         (e = hipStreamSynchronize(stream)) != hipSuccess) {
         batch_release(bt);
         return fail_hip("sam_batch_init: prompt ingest", e);
@@ -657,13 +648,11 @@ int sam_batch_init_noalloc(const sam_corpus *corpus, const int32_t *prompt_token
     StaticView S = corpus ? corpus->view : StaticView{};
     // the device's offsets are read when the kernel runs; in a captured graph they may be others
     // by then, up to what a sequence holds
-    PromptSizes sizes = prompt_sizes(prompt_offsets_host, batch);
-    sizes.most = max_seq_len;
     hipError_t e;
     if ((e = launch_fill_empty(v.dyn_slots, bb.slots, stream)) != hipSuccess ||
         (e = launch_reset(v, nullptr, batch, stream)) != hipSuccess ||
-        (e = launch_ingest(S, v, nullptr, batch, prompt_tokens, prompt_offsets, sizes,
-                           stream)) != hipSuccess) {
+        (e = launch_ingest(S, v, nullptr, batch, prompt_tokens, prompt_offsets, prompt_offsets_host,
+                           max_seq_len, stream)) != hipSuccess) {
         batch_release(bt);
         return fail_hip("sam_batch_init_noalloc: launch", e);
     }
@@ -771,7 +760,7 @@ int sam_batch_reset(sam_batch *bt, const int32_t *slots, int32_t n_slots,
     hipError_t e;
     if ((e = launch_reset(v, slots, n_slots, stream)) != hipSuccess ||
         (e = launch_ingest(S, v, slots, n_slots, prompt_tokens, prompt_offsets,
-                           prompt_sizes(offs.data(), n_slots), stream)) != hipSuccess)
+                           offs.data(), 0, stream)) != hipSuccess)
         return fail_hip("sam_batch_reset: launch", e);
     return SAM_OK;
 }

@@ -39,6 +39,54 @@
 namespace sam {
 
 constexpr uint32_t kIngestMaxTokens = 1u << 18;      // beyond: the serial kernel
+constexpr uint32_t kIngestIdx16 = 16366;             // the most tokens that 16-bit indices do for
+
+// What the host knows of the prompts of a call.
+struct PromptSizes {
+    int64_t n_seqs;
+    int64_t longest;     // tokens; what the launch is made for
+    int64_t total;
+    int64_t most;        // what a prompt may have when the kernel runs: more than `longest` where
+                         // the host has not read the device's offsets itself (a captured call that
+                         // is replayed with other prompts)
+};
+
+// Are the prompts of a call taken whole, or token by token?  n_beyond: how many are too long for
+// LDS.  Whole, the about sixty barriers take what the serial loops need for 64 tokens as long
+// as all workgroups run at once; token by token, sequences share compute units better.  Measured
+// on 256 compute units, sam_batch_reset, token by token against whole (us):
+//   64 tokens     1 sequence 80 / 77   1024: 96 / 88   1536: 104 / 93, over a corpus 109 / 112
+//                 2048: 120 / 133   8192: 234 / 264   16384: 432 / 518
+//   96 tokens     2048: 135 / 134   4096: 210 / 188   8192: 340 / 294
+//   20 tokens and one of n    2048, n = 64: 92 / 97, 128: 130 / 96   3000, n = 64: 100 / 104, 96: 112 / 106
+//                 8192, n = 64: 121 / 173, 128: 153 / 174, 256: 237 / 176
+//   beyond LDS    6300 tokens: 1024: 6176 / 5550   1280: 6473 / 6861   1536: 6822 / 8190   2048: 7615 / 10771
+//                 16000: 1280: 19655 / 18764   1536: 20385 / 21944   40000: 1280: 76443 / 79013   1536: 78160 / 94476
+//                 20000 (wide layout, half the working set): 1280: 36934 / 31489   1536: 37795 / 37370
+inline bool prompts_whole(const PromptSizes &p, int64_t n_beyond, int64_t n_cu)
+{
+    if (p.longest < 64 || p.most > (int64_t)kIngestMaxTokens) return false;
+    if (p.n_seqs > 5 * n_cu) {
+        if (p.longest < 96) return false;
+        // mostly short ones: each costs a workgroup its barriers
+        if (p.total < 32 * p.n_seqs && p.longest < 64 + 8 * p.n_seqs / (3 * n_cu)) return false;
+    }
+    return n_beyond <= (p.longest > kIngestIdx16 && p.longest <= 32768 ? 6 : 5) * n_cu;
+}
+
+// Do they get workgroups of 256 threads, or of 1024?  Of 1024 one fits on a compute unit (70 VGPRs a
+// thread), so it is 256 where there are more workgroups than compute units (n_walks of them walk
+// the corpus automaton) and the prompts are so short that 256 threads suffice.  Measured, 1024
+// against 256 threads: 256 prompts of 256 tokens 88 against 90 us, over a corpus 120 against 103, of
+// 512 130 against 134, of 1024 (no corpus) 121 against 155; 300 of 64 97 against 78, of 256 116
+// against 96, of 1024 164 against 181; 512 of 512 137 against 127, of 1024 178 against 195; 640 of 1024
+// 223 against 207; 1024 of 64 150 against 82, of 512 215 against 152, of 1024 287 against 250, of
+// 1500 387 against 422.
+inline bool short_prompts(const PromptSizes &p, int64_t n_walks, int64_t n_cu)
+{
+    return (p.n_seqs + n_walks > n_cu && p.longest <= 256) || (p.n_seqs > n_cu && p.longest <= 512) ||
+           (p.n_seqs > 2 * n_cu && p.longest <= 1024);
+}
 
 struct IngestSeq {
     const int32_t *tok;        // the prompt, every token inside the vocabulary
@@ -159,7 +207,6 @@ struct IngestCompact {
 // ---- working arrays -------------------------------------------------------------
 //
 // I: index type (16 bits up to kIngestIdx16 tokens), K: a pair of names.
-constexpr uint32_t kIngestIdx16 = 16366;
 
 template <class I, class K>
 struct IngestArrays {

@@ -25,19 +25,6 @@ namespace sam {
 // compute unit gets compare-and-swaps on scattered lines through: lanes that go on with the
 // next position as soon as theirs has ended, instead of waiting for the longest path of their
 // wave, took 218 against 218 us for one prompt of 6000 tokens, and 1.22 against 1.18 ms for 1024.
-//
-// A workgroup has 1024 threads, or 256 where there are more workgroups than are resident at
-// 1024 threads and the prompts are so short that 256 suffice.  Measured, 1024 against 256
-// threads: 256 prompts of 256 tokens 88 against 90 us, of 1024 121 against 155; 300 of 64 97
-// against 78, of 256 116 against 96, of 1024 164 against 181; 512 of 512 137 against 127, of
-// 1024 178 against 195; 640 of 1024 223 against 207; 1024 of 64 150 against 82 (92 token by
-// token), of 512 215 against 152, of 1024 287 against 250, of 1500 387 against 422.
-inline bool short_prompts(int n_seqs, int64_t max_tokens, int n_cu)
-{
-    return (n_seqs > n_cu && max_tokens <= 512) || (n_seqs > 2 * n_cu && max_tokens <= 1024);
-}
-// The fixed cost of about sixty barriers is what the serial loops need for this many tokens.
-constexpr int64_t kPromptMinTokens = 64;
 
 template <int T>
 struct PromptCtx {
@@ -314,11 +301,17 @@ __global__ __launch_bounds__(T) void sam_prompt_kernel(StaticView S, BatchView B
 
 hipError_t launch_ingest(const StaticView &S, const BatchView &B, const int32_t *seq_map,
                          int n_seqs, const int32_t *tokens, const int64_t *offsets,
-                         const PromptSizes &sizes, hipStream_t stream)
+                         const int64_t *host_offsets, int64_t most, hipStream_t stream)
 {
-    if (sizes.longest < kPromptMinTokens || sizes.most > (int64_t)kIngestMaxTokens)
+    auto one_by_one = [&] {
         return launch_feed(S, B, seq_map, n_seqs, tokens, offsets, nullptr, nullptr, nullptr,
                            nullptr, nullptr, stream);
+    };
+    auto prompt = [&](int i) { return host_offsets[i + 1] - host_offsets[i]; };
+    PromptSizes sizes = {n_seqs, 0, host_offsets[n_seqs] - host_offsets[0], 0};
+    for (int i = 0; i < n_seqs; i++)
+        if (prompt(i) > sizes.longest) sizes.longest = prompt(i);
+    sizes.most = most > sizes.longest ? most : sizes.longest;
     int dev = 0, lds_limit = 0, n_cu = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess)
@@ -333,31 +326,34 @@ hipError_t launch_ingest(const StaticView &S, const BatchView &B, const int32_t 
         const uint32_t mid = (fit + over) / 2;
         if (ingest_lds_bytes(mid) <= room) fit = mid; else over = mid;
     }
-    const uint32_t most = (uint32_t)sizes.most;
+    int64_t n_beyond = 0;
+    if (sizes.longest > fit)
+        for (int i = 0; i < n_seqs; i++) n_beyond += prompt(i) > fit;
+    if (!prompts_whole(sizes, n_beyond, n_cu)) return one_by_one();
+    const uint32_t max_tokens = (uint32_t)sizes.most;
     uint32_t lds_tokens = (uint32_t)sizes.longest < fit ? (uint32_t)sizes.longest : fit;
     size_t bytes = ingest_lds_bytes(lds_tokens);
-    if (most > lds_tokens) {
-        const size_t small = B.compact ? ingest_small_bytes<uint16_t>(most, true)
-                                       : ingest_small_bytes<uint32_t>(most, true);
+    if (max_tokens > lds_tokens) {
+        const size_t small = B.compact ? ingest_small_bytes<uint16_t>(max_tokens, true)
+                                       : ingest_small_bytes<uint32_t>(max_tokens, true);
         bytes = small > bytes ? small : bytes;
         const size_t rec_bytes = (size_t)B.max_states * (B.compact ? sizeof(DynRecCompact) : sizeof(DynRec)),
                      slot_bytes = (size_t)B.dyn_buckets * 128;
-        if (!(B.compact ? ingest_tables_fit<uint16_t, uint32_t>(most, rec_bytes, slot_bytes)
-                        : ingest_tables_fit<uint32_t, uint64_t>(most, rec_bytes, slot_bytes)) || bytes > room) {
+        if (!(B.compact ? ingest_tables_fit<uint16_t, uint32_t>(max_tokens, rec_bytes, slot_bytes)
+                        : ingest_tables_fit<uint32_t, uint64_t>(max_tokens, rec_bytes, slot_bytes)) || bytes > room) {
             // (small tables have too little room beside the fixed parts)
-            if (most > fit)
-                return launch_feed(S, B, seq_map, n_seqs, tokens, offsets, nullptr, nullptr, nullptr,
-                                   nullptr, nullptr, stream);
-            lds_tokens = most;
+            if (max_tokens > fit) return one_by_one();
+            lds_tokens = max_tokens;
             bytes = ingest_lds_bytes(lds_tokens);
         }
     }
-    const int threads = short_prompts(n_seqs, sizes.longest, n_cu) ? 256 : 1024, waves = threads / 64;
-    const int n_static = B.has_static ? (((n_seqs + waves - 1) / waves + 7) & ~7) : 0;
+    // workgroups for the corpus: a wave each sequence, a multiple of 8 workgroups
+    auto walks = [&](int waves) { return B.has_static ? (((n_seqs + waves - 1) / waves + 7) & ~7) : 0; };
+    const int threads = short_prompts(sizes, walks(16), n_cu) ? 256 : 1024, n_static = walks(threads / 64);
 #define SAM_LAUNCH_PROMPT_T(COMPACT, ASM, T)                                                     \
     hipLaunchKernelGGL((sam_prompt_kernel<COMPACT, ASM, T>), dim3(n_static + n_seqs), dim3(T),    \
                        bytes, stream, S, B, seq_map, n_seqs, n_static, tokens, offsets,          \
-                       lds_tokens, most)
+                       lds_tokens, max_tokens)
 #define SAM_LAUNCH_PROMPT(COMPACT, ASM)                                                          \
     do {                                                                                        \
         if (threads == 256) SAM_LAUNCH_PROMPT_T(COMPACT, ASM, 256);                              \

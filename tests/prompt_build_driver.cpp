@@ -169,9 +169,40 @@ static int guards()
     return caught[0] && caught[1] ? 0 : bad("guards of the links", n, caught[0]);
 }
 
+// Calls that are faster token by token stay so (256 compute units; the measured sizes stand with
+// the rule), the others are taken whole.
+static int rules()
+{
+    struct { int64_t n_seqs, longest, mean, n_beyond; bool whole; } calls[] = {
+        {1, 63, 63, 0, false}, {1, 64, 64, 0, true}, {1024, 64, 64, 0, true}, {1280, 64, 20, 0, true},
+        {2048, 64, 64, 0, false}, {8192, 64, 64, 0, false}, {16384, 70, 70, 0, false}, {2048, 96, 96, 0, true},
+        {8192, 96, 96, 0, true}, {16384, 128, 128, 0, true}, {2048, 128, 20, 0, true}, {3000, 64, 20, 0, false},
+        {3000, 96, 20, 0, true}, {8192, 64, 20, 0, false}, {8192, 128, 20, 0, false}, {8192, 256, 20, 0, true},
+        {4096, 6000, 6000, 0, true}, {1024, 8000, 8000, 1024, true}, {2048, 6300, 6300, 2048, false},
+        {2048, 16000, 16000, 2048, false}, {4096, 8000, 300, 100, true}, {1500, 20000, 20000, 1500, true},
+        {2048, 20000, 20000, 2048, false}, {1536, 40000, 40000, 1536, false}, {512, 40000, 40000, 512, true},
+        {1, 1 << 18, 1 << 18, 1, true}, {1, (1 << 18) + 1, (1 << 18) + 1, 1, false},
+    };
+    for (auto &c : calls) {
+        const PromptSizes p = {c.n_seqs, c.longest, c.mean * c.n_seqs, c.longest};
+        if (prompts_whole(p, c.n_beyond, 256) != c.whole) return bad("rule", (uint32_t)c.n_seqs, (uint32_t)c.longest);
+    }
+    PromptSizes p = {64, 100, 64, (1 << 18) + 1};              // may be longer when the kernel runs
+    if (prompts_whole(p, 0, 256)) return bad("rule of replayed calls", 100, 0);
+    struct { int64_t n_seqs, longest, n_walks; bool small; } sizes[] = {
+        {240, 256, 16, false}, {241, 256, 16, true}, {256, 257, 16, false}, {256, 256, 0, false}, {257, 512, 0, true},
+        {257, 513, 0, false}, {512, 1024, 0, false}, {513, 1024, 0, true}, {513, 1025, 40, false},
+    };
+    for (auto &c : sizes) {
+        const PromptSizes q = {c.n_seqs, c.longest, c.longest, c.longest};
+        if (short_prompts(q, c.n_walks, 256) != c.small) return bad("rule of threads", (uint32_t)c.n_seqs, (uint32_t)c.longest);
+    }
+    return 0;
+}
+
 int main()
 {
-    if (guards()) return 1;
+    if (guards() || rules()) return 1;
     std::mt19937 rng(5);
     const uint32_t sizes[] = {1, 2, 3, 7, 8, 9, 63, 64, 65, 255, 256, 257, 511, 513, 1023, 1024, 1025, 2500, 6200};
     for (const uint32_t n : sizes)

@@ -87,6 +87,21 @@ def test_many_prompts(batch, n, mode, with_corpus):
     _compare(prompts, 300, n + 40, mode, corpus)
 
 
+# as many prompts as compute units, the walks over the corpus beside them (small workgroups up to 256
+# tokens); more, all but two of them too short to gain (token by token up to 96 tokens)
+@pytest.mark.parametrize("batch,n", [(250, 256), (250, 257), (1300, 95), (1300, 96), (3000, 94), (3000, 96)])
+def test_lines_of_the_dispatch(batch, n):
+    rng = np.random.default_rng(batch + n)
+    sizes = rng.integers(1, n + 1, size=batch) if batch < 2000 else rng.integers(1, 30, size=batch)
+    sizes[[3, 77]] = n, n - 1
+    corpus = _text("copies", 3000, 300, rng)
+    prompts = [_text("copies", int(k), 300, rng) for k in sizes]
+    for p in prompts[::9]:
+        k = min(len(p), 60)
+        p[len(p) - k:] = corpus[700:700 + k]
+    _compare(prompts, 300, n + 40, 0, corpus)
+
+
 @pytest.mark.parametrize("at", [0, 1, 99, 299])
 def test_a_bad_token_ends_its_prompt(at):
     """sam_batch_reset with a token outside the vocabulary: the prompt ends in front of it."""
