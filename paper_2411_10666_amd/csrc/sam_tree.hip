@@ -39,9 +39,8 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t x)
 
 // Tree draft by best-first expansion over the top-k successors (Algorithm 4),
 // one wavefront per sequence.  Entry number i of the priority queue (in the order of the
-// pushes) lives in lane i % 64, register i / 64: its probability bits (0: popped or not
-// there yet) and its state.  The largest probability comes first and, among equals, the
-// entry pushed first.
+// pushes) belongs to lane i % 64, row i / 64.  The largest probability comes first and, among
+// equals, the entry pushed first.
 //
 // A pop is one dependent memory read (the table row of the popped state's k children) and
 // the work between its arrival and the next request.  The lanes that will hold the
@@ -51,21 +50,28 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t x)
 // found while the request travelled: when the row is here, one product, two lane reads and
 // a compare give the next state, and its row is requested before anything else is done.
 // Queueing the children and the search for the best entry follow in that request's shadow.
-// Nothing on that path goes through LDS; it takes tokens and parents (written when pushed)
-// and the popped entries, and gives them back once, when the draft is written out.
+// Tokens and parents go to LDS when pushed, the popped entries too, and come back once, when
+// the draft is written out.
 // Probabilities are float products rounded once per edge.  The rest of a pop's 0.45 us is
-// the row's round trip (a 69 MB table; a call of 256 drafts of 40 entries, k = 4: 18 us,
-// 21 us with the queue in LDS).  Asking for the row of the queue's best entry ahead, in case
+// the row's round trip (a 69 MB table; a call of 256 drafts of 40 entries, k = 4: 18 us).
+// Asking for the row of the queue's best entry ahead, in case
 // the next pop is that one, cost 2.4 us a call: the two requests are waited for together.
-template <int R>
+//
+// The queue has two forms, because the search has to stay in the shadow.  Up to 128 entries: two
+// rows in registers, probability bits (0: popped or not there yet) and state.  More: rows in
+// LDS, below.  Measured (us a call from the host, 64 drafts, states from the L2; all rows in
+// registers, a queue in LDS that is scanned at each pop, the two forms here): 128 entries of k = 8
+// 143, 83, 67; of k = 4 96, 83, 67; of k = 1 (two rows) 63, 84, 63, and 67 with the second form; 40
+// entries of k = 8 37, 39, 34; of k = 4 34, 39, 34.
+constexpr int kRegisterRows = 2;
 __global__ __launch_bounds__(64) void sam_tree_kernel(StaticView S, BatchView B, int max_size,
                                                        int32_t *__restrict__ tokens,
                                                        int32_t *__restrict__ parents,
                                                        float *__restrict__ probs,
                                                        int32_t *__restrict__ sizes)
 {
-    __shared__ int32_t qtok[64 * R];
-    __shared__ int32_t qpar[64 * R];
+    __shared__ int32_t qtok[64 * kRegisterRows];
+    __shared__ int32_t qpar[64 * kRegisterRows];
     __shared__ int32_t oidx[kMaxTreeSize];
     __shared__ float   oprob[kMaxTreeSize];
     const int b = blockIdx.x;
@@ -74,9 +80,9 @@ __global__ __launch_bounds__(64) void sam_tree_kernel(StaticView S, BatchView B,
     const int k = S.top_k;
     int dn = 0;
     if (m.n > 0) {
-        uint32_t prob[R], state[R];
+        uint32_t prob[kRegisterRows], state[kRegisterRows];
 #pragma unroll
-        for (int r = 0; r < R; r++) { prob[r] = 0; state[r] = 0; }
+        for (int r = 0; r < kRegisterRows; r++) { prob[r] = 0; state[r] = 0; }
         if (lane == 0) {
             qtok[0] = B.dyn_text[(size_t)b * B.max_seq_len + m.n - 1];
             qpar[0] = -1;
@@ -118,7 +124,7 @@ __global__ __launch_bounds__(64) void sam_tree_kernel(StaticView S, BatchView B,
                 qpar[slot] = dn - 1;
             }
 #pragma unroll
-            for (int r = 0; r < R; r++) {
+            for (int r = 0; r < kRegisterRows; r++) {
                 const bool here = slot == 64 * r + lane;
                 prob[r] = here ? pn : prob[r];
                 state[r] = here ? e.dst : state[r];
@@ -128,10 +134,10 @@ __global__ __launch_bounds__(64) void sam_tree_kernel(StaticView S, BatchView B,
             // lowest register that has one, and there in the lowest lane.
             uint32_t mine = prob[0];
 #pragma unroll
-            for (int r = 1; r < R; r++) mine = prob[r] > mine ? prob[r] : mine;
+            for (int r = 1; r < kRegisterRows; r++) mine = prob[r] > mine ? prob[r] : mine;
             best = wave_max_u32(mine);
 #pragma unroll
-            for (int r = R - 1; r >= 0; r--) {
+            for (int r = kRegisterRows - 1; r >= 0; r--) {
                 const unsigned long long holders = __ballot(prob[r] == best);
                 const int from = __builtin_ctzll(holders | (1ull << 63));
                 const uint32_t its = (uint32_t)__builtin_amdgcn_readlane((int)state[r], from);
@@ -156,20 +162,120 @@ __global__ __launch_bounds__(64) void sam_tree_kernel(StaticView S, BatchView B,
     if (lane == 0) sizes[b] = dn;
 }
 
+// More than 128 entries: the rows are in LDS, and every lane keeps the best entry of its own column in
+// registers.  A push changes that by one compare; a pop of a queued entry makes the one lane it
+// came from read its column again.
+template <int R>
+__global__ __launch_bounds__(64) void sam_tree_large_kernel(StaticView S, BatchView B, int max_size,
+                                                             int32_t *__restrict__ tokens,
+                                                             int32_t *__restrict__ parents,
+                                                             float *__restrict__ probs,
+                                                             int32_t *__restrict__ sizes)
+{
+    __shared__ uint32_t qprob[64 * R];                   // 0: popped
+    __shared__ uint32_t qstate[64 * R];
+    __shared__ int32_t  qtok[64 * R];
+    __shared__ int32_t  qpar[64 * R];
+    __shared__ int32_t  oidx[kMaxTreeSize];
+    __shared__ float    oprob[kMaxTreeSize];
+    const int b = blockIdx.x;
+    const int lane = threadIdx.x;
+    const SeqMeta m = B.meta[b];
+    const int k = S.top_k;
+    int dn = 0;
+    if (m.n > 0) {
+        if (lane == 0) {
+            qtok[0] = B.dyn_text[(size_t)b * B.max_seq_len + m.n - 1];
+            qpar[0] = -1;
+            qprob[0] = 0;
+        }
+        int qn = 1;
+        uint32_t st = (uint32_t)__builtin_amdgcn_readfirstlane((int)m.s1);
+        uint32_t p = __float_as_uint(1.0f);
+        int idx = 0;
+        auto request = [&](uint32_t of, int first) {
+            const int j = (lane - first) & 63;
+            return S.topk[(size_t)of * (uint32_t)k + (uint32_t)(j < k ? j : 0)];
+        };
+        TopEnt e = request(st, qn);
+        uint32_t mine = 0, my_state = 0;                 // this lane's best
+        int my_row = 0;
+        uint32_t best = 0, best_state = 0;
+        int best_at = 0;
+        for (;;) {
+            oidx[dn] = idx;
+            oprob[dn] = __uint_as_float(p);
+            dn++;
+            if (dn == max_size) break;
+            const int mine_no = (lane - qn) & 63;
+            const bool valid = e.dst != 0 && mine_no < k;
+            const uint32_t pn = valid ? __float_as_uint(__fmul_rn(__uint_as_float(p), e.prob)) : 0u;
+            const uint32_t first_p = (uint32_t)__builtin_amdgcn_readlane((int)pn, qn & 63);
+            const uint32_t first_state = (uint32_t)__builtin_amdgcn_readlane((int)e.dst, qn & 63);
+            const bool child = first_p > best;
+            if (!child && best == 0) break;
+            const int slot = qn + mine_no;
+            idx = (int)uni((uint32_t)(child ? qn : best_at));
+            qn = (int)uni((uint32_t)(qn + __popcll(__ballot(valid))));
+            st = uni(child ? first_state : best_state);
+            p = uni(child ? first_p : best);
+            const TopEnt coming = request(st, qn);
+            if (valid) {
+                const bool stays = slot != idx;
+                qprob[slot] = stays ? pn : 0u;
+                qstate[slot] = e.dst;
+                qtok[slot] = (int32_t)e.token;
+                qpar[slot] = dn - 1;
+                if (stays && pn > mine) { mine = pn; my_state = e.dst; my_row = slot >> 6; }
+            }
+            if (!child && lane == (idx & 63)) {
+                qprob[idx] = 0;
+                mine = 0;
+                for (int r = 0; 64 * r + lane < qn; r++) {
+                    const uint32_t other = qprob[64 * r + lane];
+                    if (other > mine) { mine = other; my_row = r; }
+                }
+                my_state = qstate[64 * my_row + lane];
+            }
+            best = wave_max_u32(mine);
+            // among equals the entry pushed first: the lowest row, and there the lowest lane
+            unsigned long long holders = __ballot(mine == best);
+            if (holders & (holders - 1)) {
+                const uint32_t row = 0xFFFFu - wave_max_u32(mine == best ? 0xFFFFu - (uint32_t)my_row : 0u);
+                holders = __ballot(mine == best && my_row == (int)row);
+            }
+            const int from = __builtin_ctzll(holders | (1ull << 63));
+            best_at = 64 * (int)__builtin_amdgcn_readlane(my_row, from) + from;
+            best_state = (uint32_t)__builtin_amdgcn_readlane((int)my_state, from);
+            asm volatile("v_mov_b32 %0, %3\n\tv_mov_b32 %1, %4\n\tv_mov_b32 %2, %5"
+                         : "=&v"(e.token), "=&v"(e.dst), "=&v"(e.prob)
+                         : "v"(coming.token), "v"(coming.dst), "v"(coming.prob), "s"(best));
+        }
+    }
+    __syncthreads();
+    for (int i = lane; i < max_size; i += 64) {
+        const bool have = i < dn;
+        const int q = have ? oidx[i] : 0;
+        tokens[(size_t)b * max_size + i] = have ? qtok[q] : -1;
+        parents[(size_t)b * max_size + i] = have ? qpar[q] : -1;
+        probs[(size_t)b * max_size + i] = have ? oprob[i] : 0.0f;
+    }
+    if (lane == 0) sizes[b] = dn;
+}
+
 hipError_t launch_tree(const StaticView &S, const BatchView &B, int max_size, int32_t *tokens,
                        int32_t *parents, float *probs, int32_t *sizes, hipStream_t stream)
 {
     // entries that can ever be pushed: the start and k children of every pop but the last
     const int most = 1 + (max_size - 1) * S.top_k;
-#define SAM_LAUNCH_TREE(R)                                                                     \
-    hipLaunchKernelGGL((sam_tree_kernel<R>), dim3(B.batch), dim3(64), 0, stream, S, B,         \
-                       max_size, tokens, parents, probs, sizes)
+#define SAM_LAUNCH_TREE(...)                                                                   \
+    hipLaunchKernelGGL((__VA_ARGS__), dim3(B.batch), dim3(64), 0, stream, S, B, max_size,      \
+                       tokens, parents, probs, sizes)
     static_assert(1 + (kMaxTreeSize - 1) * kMaxTopK <= 64 * 16, "the largest queue");
-    if (most <= 64 * 2) SAM_LAUNCH_TREE(2);
-    else if (most <= 64 * 3) SAM_LAUNCH_TREE(3);
-    else if (most <= 64 * 5) SAM_LAUNCH_TREE(5);
-    else if (most <= 64 * 8) SAM_LAUNCH_TREE(8);
-    else SAM_LAUNCH_TREE(16);
+    // (8 and 16 rows differ in LDS only: 16 bytes an entry, 10 drafts a compute unit at 16 rows)
+    if (most <= 64 * kRegisterRows) SAM_LAUNCH_TREE(sam_tree_kernel);
+    else if (most <= 64 * 8) SAM_LAUNCH_TREE(sam_tree_large_kernel<8>);
+    else SAM_LAUNCH_TREE(sam_tree_large_kernel<16>);
 #undef SAM_LAUNCH_TREE
     return hipGetLastError();
 }

@@ -567,7 +567,12 @@ def test_auxiliary_threshold_hook(l_threshold, l_bias):
                                                    # equal frequencies everywhere (ties in the rows
                                                    # and in the queue), full rows, the largest sizes
                                                    (66, 2, 8, 128), (67, 8, 8, 128), (68, 5, 5, 100),
-                                                   (69, 12, 3, 128), (70, 2, 1, 128), (71, 300, 8, 60)])
+                                                   (69, 12, 3, 128), (70, 2, 1, 128), (71, 300, 8, 60),
+                                                   # around the queue's forms: 128 and 129 entries,
+                                                   # 316 and 321, 511 and 513, with ties and without
+                                                   (72, 2, 1, 128), (73, 3, 8, 17), (74, 9, 5, 64),
+                                                   (75, 4, 5, 65), (76, 4, 2, 128), (77, 40, 6, 86),
+                                                   (78, 7, 8, 65), (79, 40, 4, 128)])
 def test_tree_draft_matches_checker(seed, vocab, k, max_size):
     """Algorithm 4 on the GPU against the checker: tokens, parents, probability bits."""
     import torch

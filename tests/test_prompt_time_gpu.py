@@ -85,3 +85,29 @@ def test_passages_of_the_corpus(batch, n):
     starts = rng.integers(0, corpus.size - n, size=batch)
     fast, slow = _whole_and_one_by_one(np.stack([corpus[a:a + n] for a in starts]), corpus, vocab)
     assert fast < slow
+
+
+@pytest.mark.parametrize("batch", [1, 256])
+def test_tree_drafts_with_many_children(batch):
+    """A draft's time is its chain of pops, however long the queue: 128 entries of 8 children each
+    take little longer than of one child each (1.05 times as long as measured; half as long again allowed)."""
+    import torch
+    from paper_2411_10666_amd import binding as sam
+    rng = np.random.default_rng(1)
+    vocab, n, size = 50, 60, 128
+    dev = torch.device("cuda")
+    corpus = np.minimum((vocab * rng.random(1_000_000) ** 2).astype(np.int64), vocab - 1).astype(np.int32)
+    c = sam.sam_build(corpus, vocab)
+    flat = torch.from_numpy(corpus[:batch * n].copy()).to(dev)
+    out = [torch.empty(batch, size, dtype=d, device=dev) for d in (torch.int32, torch.int32, torch.float32)]
+    sizes = torch.empty(batch, dtype=torch.int32, device=dev)
+    times = []
+    for k in (1, 8):
+        sam.sam_corpus_build_topk(c, k)
+        b = sam.sam_batch_init(c, flat, torch.arange(batch + 1, dtype=torch.int64, device=dev) * n, batch, vocab,
+                               n + 8, 4, 4)
+        times.append(_shortest(lambda: sam.sam_batch_tree_draft(b, size, *out, sizes), 30))
+        assert int(sizes.min()) == size
+        del b
+    print("128 entries, k = 1: %.0f us, k = 8: %.0f us" % (times[0] * 1e6, times[1] * 1e6), flush=True)
+    assert times[1] < 1.5 * times[0]
