@@ -219,6 +219,7 @@ struct IngestArrays {
     I        *slot;      // [n] where its pair is in key[]
     I        *next;      // [h_size] the next pair (+ 1) of the same bucket
     I        *size;      // [n] size of the group that starts here
+    uint32_t *lo, *hi;   // [n] least and largest second name in it (32-bit indices only)
     I        *name1;     // [n] names of single tokens (unused if the text is read instead)
     uint8_t  *lev;       // [n] round in which a group came to start here
     uint32_t  h_size;
@@ -372,6 +373,10 @@ SAM_HD void ingest_place_tables(IngestArrays<I, K> &A, const IngestSeq &q, char 
     A.slot = r.take<I>(n);
     A.next = r.take<I>(A.h_size);
     A.size = r.take<I>(n);
+    if (sizeof(I) == 4) {
+        A.lo = r.take<uint32_t>(n);
+        A.hi = r.take<uint32_t>(n);
+    }
     A.sa = r2.take<I>(n);
     A.node = r2.take<I>(n);
     A.tab = r2.take<I>(2 * (size_t)n);
@@ -398,7 +403,8 @@ inline bool ingest_tables_fit(uint32_t n, size_t rec_bytes, size_t slot_bytes)
 {
     const size_t h = ingest_h_size(n), N = n;
     auto up = [](size_t x) { return (x + 15) / 16 * 16; };
-    const size_t sort = 2 * up(sizeof(K) * h) + up(sizeof(I) * h) + up(sizeof(K) * N) + 2 * up(sizeof(I) * N);
+    const size_t sort = 2 * up(sizeof(K) * h) + up(sizeof(I) * h) + up(sizeof(K) * N) + 2 * up(sizeof(I) * N) +
+                        (sizeof(I) == 4 ? 2 * up(4 * N) : 0);
     const size_t tree = 2 * up(sizeof(I) * N) + up(2 * sizeof(I) * N) + up(sizeof(I) * ingest_first_mins(n));
     const size_t names = ingest_name_levels(n) * sizeof(I) * ((N + 15) / 16 * 16);
     const size_t rest = 3 * up(sizeof(I) * N) + 2 * up(4 * N);
@@ -432,7 +438,7 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
     constexpr I kNone = (I)~(I)0, kRoot = (I)(kNone - 1);
     constexpr K kLow = (K)(((K)1 << kHalf) - 1);
     uint32_t *const small = A.small;
-    uint32_t *const active = small;                  // [64] one flag per round
+    uint32_t *const active = small;                  // [32] one flag per round
     const uint32_t words = n / 32 + 1;
     auto corrupt = [&] { ctx.bit_or(&small[121], 1u); };
 
@@ -490,11 +496,24 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
     // that of the second names.  A group of c positions has c buckets, which cut the range of
     // second names evenly; a running sum over all buckets says where each starts, and the few
     // different pairs in one bucket (no more than c, nor than names in its range, hence no
-    // more than about the square root of n) are compared with each other.
+    // more than about the square root of n) are compared with each other.  In a long text of one
+    // period, say 134 tokens of 200 000, they are that many (251 ms; token by token 129): from the
+    // first round on in which more than kCrowd pairs met in a bucket, the buckets of a group cut
+    // the range of its own second names (52 ms).
+    constexpr bool kSpread = sizeof(I) == 4;
+    constexpr uint32_t kCrowd = 32;
+    uint32_t *const crowded = small + 32;            // [32] one flag per round
+    bool spread = false;
     const uint32_t shift = ctx.log2(n) + 1;          // second names are 0 .. n
     auto bucket_of_pair = [&](K key) -> uint32_t {
-        const uint32_t g = (uint32_t)(key >> kHalf);
-        return g + (uint32_t)(((uint64_t)(key & kLow) * A.size[g]) >> shift);
+        const uint32_t g = (uint32_t)(key >> kHalf), second = (uint32_t)(key & kLow), size = A.size[g];
+        if (kSpread && spread) {
+            // rises with the second name, which is all that it has to
+            const float width = (float)size / (float)(A.hi[g] - A.lo[g] + 1u);
+            const uint32_t at = (uint32_t)((float)(second - A.lo[g]) * width);
+            return g + (at < size ? at : size - 1u);
+        }
+        return g + (uint32_t)(((uint64_t)second * size) >> shift);
     };
     constexpr uint32_t kRuns = C::kThreads;          // of the running sum, one for each thread
     static_assert(kRuns <= kIngestParts, "part[] holds one sum for each thread");
@@ -507,7 +526,11 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
             if (j < 7) ctx.each(n, [&](uint32_t i) { A.names[j * A.stride + i] = A.grp[i]; });
         }
         ctx.each(hs, [&](uint32_t i) { A.key[i] = kEmpty; A.val[i] = 0; });
-        ctx.each(n, [&](uint32_t i) { A.cursor[i] = 0; });
+        spread = kSpread && round > 1 && crowded[round - 1];
+        ctx.each(n, [&](uint32_t i) {
+            A.cursor[i] = 0;
+            if (kSpread && spread) { A.lo[i] = kNil; A.hi[i] = 0; }
+        });
         ctx.sync();
         ctx.each(n, [&](uint32_t i) {
             const I g = A.grp[i];
@@ -516,6 +539,16 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
             A.slot[i] = (I)insert((K)(((K)g << kHalf) | (K)second));
         });
         ctx.sync();
+        if (kSpread && spread) {
+            ctx.each(hs, [&](uint32_t i) {
+                const K key = A.key[i];
+                if (key == kEmpty) return;
+                ctx.lower(&A.lo[key >> kHalf], (uint32_t)(key & kLow));
+                ctx.raise(&A.hi[key >> kHalf], (uint32_t)(key & kLow));
+                crowded[round] = 1;
+            });
+            ctx.sync();
+        }
         ctx.each(hs, [&](uint32_t i) {
             const K key = A.key[i];
             if (key != kEmpty) ctx.add(&A.cursor[bucket_of_pair(key)], A.val[i]);
@@ -558,6 +591,7 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
                 if (A.key[j - 1] < key) start += (uint32_t)(A.val[j - 1] & kLow);
                 if (!kLds && !--left) { corrupt(); return; }
             }
+            if (kSpread && hs - left > kCrowd) crowded[round] = 1;
             A.val[i] |= (K)((K)start << kHalf);
             if (start != (uint32_t)(key >> kHalf)) A.lev[start] = (uint8_t)round;
         });

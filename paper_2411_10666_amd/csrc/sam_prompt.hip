@@ -73,6 +73,10 @@ struct PromptCtx {
     {
         return __hip_atomic_fetch_min(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
+    __device__ __forceinline__ void raise(uint32_t *p, uint32_t v)
+    {
+        __hip_atomic_fetch_max(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
     __device__ __forceinline__ void bit_or(uint32_t *p, uint32_t v)
     {
         __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);

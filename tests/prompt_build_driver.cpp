@@ -38,6 +38,7 @@ struct CpuCtx {
     template <class U> U cas(U *p, U expected, U v) { swaps++; const U old = *p; if (old == expected) *p = v; return old; }
     template <class U> U add(U *p, U v) { const U old = *p; *p = (U)(old + v); return old; }
     uint32_t lower(uint32_t *p, uint32_t v) { const uint32_t old = *p; if (v < old) *p = v; return old; }
+    void raise(uint32_t *p, uint32_t v) { if (v > *p) *p = v; }
     void bit_or(uint32_t *p, uint32_t v) { *p |= v; }
     uint32_t exch(uint32_t *p, uint32_t v) { const uint32_t old = *p; *p = v; return old; }
     uint32_t fresh(uint32_t *p) { return *p; }
@@ -90,7 +91,8 @@ static int one(const std::vector<int32_t> &x, int32_t vocab, uint32_t max_seq_le
     if (h.build(x.data(), n, vocab, err) != 0) return bad(err.c_str(), n, 0);
     // no phase works on more than the prompt's own share of the tables, however large they are
     if (ctx.widest > 6 * n + 1024) return bad("widest phase", n, ctx.widest);
-    if (ctx.most_swaps > 500) return bad("swaps in a row", n, ctx.most_swaps);
+    // (linear probing in a table that is 0.8 full: some hundred)
+    if (ctx.most_swaps > (n < 10000 ? 500u : 3000u)) return bad("swaps in a row", n, ctx.most_swaps);
     if (A.small[124] != h.n_states) return bad("states", n, A.small[124]);
     if (A.small[125] != h.n_trans) return bad("transitions", n, A.small[125]);
     if (memcmp(text.p, x.data(), (size_t)n * 4)) return bad("text", n, 0);
@@ -238,6 +240,24 @@ int main()
                                 one<IngestWide, false, uint32_t, uint64_t, 1024>(x, vocab, cap)))
                     return 1;
             }
+    // long ones: where the 16-bit indices end and the names' levels begin, up to the longest taken
+    // whole; copies, a run, and periods whose pairs crowd into few buckets
+    for (const uint32_t n : {16365u, 16366u, 16367u, 40001u, 65536u, 65537u, 131072u, 262143u, 262144u})
+        for (int kind = 0; kind < 5; kind++) {
+            std::vector<int32_t> x(n);
+            for (int32_t &t : x) t = (int32_t)(rng() % 3000);
+            const uint32_t period = kind == 2 ? 130 : kind == 3 ? (uint32_t)(n / 500) : n;
+            for (uint32_t i = period; i < n; i++) x[i] = x[i - period];
+            if (kind == 1) for (uint32_t i = 1; i + 1 < n; i++) x[i] = 0;
+            if (kind == 4)
+                for (uint32_t i = 20; i < n; i += 1 + rng() % 40) {
+                    const uint32_t back = i - rng() % i;
+                    for (uint32_t k = rng() % 6000; k && i < n; k--, i++) x[i] = x[i - back];
+                }
+            if ((n <= kIngestIdx16 && one<IngestCompact, false, uint16_t, uint32_t, 1024>(x, 3000, n)) ||
+                one<IngestWide, false, uint32_t, uint64_t, 1024>(x, 3000, n))
+                return 1;
+        }
     // a short prompt in a long sequence's tables
     for (const uint32_t n : {64u, 700u, 3000u}) {
         std::vector<int32_t> x(n);

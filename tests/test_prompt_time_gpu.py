@@ -76,6 +76,14 @@ def test_repeating_texts(kind, batch, n):
     assert fast < slow
 
 
+@pytest.mark.parametrize("n,period", [(200_000, 134), (262_144, 512), (262_144, 60)])
+def test_long_periodic_texts(n, period):
+    rng = np.random.default_rng(n)
+    x = np.resize(rng.integers(0, 3000, size=period, dtype=np.int32), (1, n))
+    fast, slow = _whole_and_one_by_one(np.ascontiguousarray(x), None, 3000)
+    assert fast < slow
+
+
 @pytest.mark.parametrize("batch,n", [(64, 3073), (256, 3073), (1024, 800), (64, 12_300)])
 def test_passages_of_the_corpus(batch, n):
     """Prompts that occur in the corpus as a whole: the walk over the corpus automaton decides."""
