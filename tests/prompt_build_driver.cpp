@@ -1,7 +1,9 @@
 // A prompt's automaton built whole (sam_ingest.h, its phases run one after the other on the
 // CPU) against the token-by-token host builder: ids, lengths, links, end positions and every
-// transition.  All arrays have exactly the sizes that the library gives them, so that an
-// access outside them is seen by AddressSanitizer.
+// transition.  The tables and the LDS block have exactly the sizes that the library gives them:
+// an access outside one of them is seen by AddressSanitizer.  The working arrays lie in there one
+// behind the other; an access past the end of one lands in the next and shows, if at all,
+// as a difference.
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
@@ -175,6 +177,9 @@ static int guards()
 // the rule), the others are taken whole.
 static int rules()
 {
+    // the most that fits into 160 KB of LDS beside the kernel's own words
+    if (ingest_lds_bytes(6144) > 163840 - 256 || ingest_lds_bytes(6145) <= 163840 - 256)
+        return bad("LDS", 6144, (uint32_t)ingest_lds_bytes(6144));
     struct { int64_t n_seqs, longest, mean, n_beyond; bool whole; } calls[] = {
         {1, 63, 63, 0, false}, {1, 64, 64, 0, true}, {1024, 64, 64, 0, true}, {1280, 64, 20, 0, true},
         {2048, 64, 64, 0, false}, {8192, 64, 64, 0, false}, {16384, 70, 70, 0, false}, {2048, 96, 96, 0, true},

@@ -47,8 +47,9 @@ def _compare(prompts, vocab, T, mode, corpus=None, steps=3, A=12, L=20):
     assert_same(g, r, has_static=corpus is not None)
 
 
-# around the shortest prompt taken whole, a workgroup's threads, the most whose arrays fit
-# into LDS (about 6230 tokens), the compact tables' limit and beyond
+# around the shortest prompt taken whole, a workgroup's threads, below and above the most whose arrays
+# fit into LDS (6144 tokens; its very edge is test_the_most_that_fits_into_lds), the compact
+# tables' limit and beyond
 @pytest.mark.parametrize("n", [63, 64, 65, 1023, 1024, 1025, 2049, 6000, 6200, 6260, 9001, 16300, 16400, 23456])
 @pytest.mark.parametrize("kind,vocab", [("zipf", 32000), ("copies", 500), ("copies", 2)])
 def test_sizes(n, kind, vocab):
@@ -57,6 +58,35 @@ def test_sizes(n, kind, vocab):
     corpus = _text("copies", 3000, vocab, rng)
     corpus[500:1500] = np.resize(prompts[0][-900:], 1000)   # a match far longer than the first window
     _compare(prompts, vocab, n + 40, 0, corpus)
+
+
+# prompts on both sides of the limit in one launch: 6144 tokens in LDS, 6145 in the sequence's tables
+@pytest.mark.parametrize("mode,vocab", [(0, 500), (1, 500), (0, 160000)])
+def test_the_most_that_fits_into_lds(mode, vocab):
+    rng = np.random.default_rng(mode)
+    prompts = [_text("copies", k, vocab, rng) for k in (6143, 6144, 6145, 6146, 6144, 300)]
+    _compare(prompts, vocab, 6200, mode, _text("copies", 3000, vocab, rng))
+    _compare([prompts[1], prompts[0]], vocab, 6200, mode)            # all in LDS
+
+
+# the wide tables' working arrays at their largest: every level of names, the longest prompt taken
+# whole and one token more (token by token)
+@pytest.mark.parametrize("n", [40_001, 65_537, 131_073, 262_144, 262_145])
+@pytest.mark.parametrize("kind", ["long copies", "one period"])
+def test_long_prompts(n, kind):
+    rng = np.random.default_rng(n)
+    x = rng.integers(0, 3000, size=n, dtype=np.int32)
+    if kind == "one period":
+        x = np.resize(x[:200], n).astype(np.int32)
+        x[n // 2] = 2999
+    else:
+        i = 20
+        while i < n:
+            k = int(min(rng.integers(1, 70_000), i, n - i))
+            s = int(rng.integers(0, i - k + 1))
+            x[i:i + k] = x[s:s + k]
+            i += k + int(rng.integers(1, 40))
+    _compare([x, x[:n // 3]], 3000, n + 40, 0)
 
 
 @pytest.mark.parametrize("kind", ["one token", "periodic", "every other"])
