@@ -63,16 +63,16 @@ ALGO_BYTES_PER_MATCH_STEP = {
 # while those sources are unchanged.
 MEASURED_TRAFFIC = {
     # config 5, all 519 step launches of one schedule pass (8081.5 match-steps per launch):
-    # FETCH_SIZE mean 4145.76, WRITE_SIZE mean 995.16; the same counters read 131089.00
+    # FETCH_SIZE mean 4146.66, WRITE_SIZE mean 995.13; the same counters read 131088.75
     # and 262144.00 for a copy kernel that reads and writes 262144 KiB, i.e. 2.000 and
-    # 1.000 KiB per count: (4145.76 x 2.000 + 995.16) KiB = 9.510 MB per launch
-    "cfg5": {"bytes_per_match_step": 1176.7, "sources": "c150325d700c1347"},
-    # config 3, 673 launches (1558.1 match-steps each): FETCH_SIZE 938.57 x 2.000 +
+    # 1.000 KiB per count: (4146.66 x 2.000 + 995.13) KiB = 9.511 MB per launch
+    "cfg5": {"bytes_per_match_step": 1176.9, "sources": "af0ef3480bcbd084"},
+    # config 3, 673 launches (1558.1 match-steps each): FETCH_SIZE 938.73 x 2.000 +
     # WRITE_SIZE 204.75 x 1.000 KiB = 2.132 MB per launch
-    "cfg3": {"bytes_per_match_step": 1368.3, "sources": "c150325d700c1347"},
-    # config 4 (no corpus), 273 launches (7681.9 match-steps each): 2537.59 x 2.000 +
-    # 1011.09 x 1.000 KiB = 6.232 MB per launch
-    "cfg4": {"bytes_per_match_step": 811.3, "sources": "c150325d700c1347"},
+    "cfg3": {"bytes_per_match_step": 1368.4, "sources": "af0ef3480bcbd084"},
+    # config 4 (no corpus), 273 launches (7681.9 match-steps each): 2537.48 x 2.000 +
+    # 1011.34 x 1.000 KiB = 6.232 MB per launch
+    "cfg4": {"bytes_per_match_step": 811.3, "sources": "af0ef3480bcbd084"},
 }
 
 KERNEL_SOURCES = ["sam_kernels.hip", "sam_walk.h", "sam_layout.h", "sam_device.h"]

@@ -13,16 +13,17 @@ namespace sam {
 
 // Extending a sequence token by token takes 0.6 to 1.2 us a token whatever the chip has
 // free, so a prompt of 3000 tokens took 1.8 ms.  Built whole, by one workgroup with its
-// working arrays in LDS (27 bytes a token, 16-bit indices), the bound is the LDS pipeline of
-// one compute unit.  Measured, sam_batch_reset: one prompt of 6000 tokens 210 us, 64 of 2048
-// 125 us (1.2 ms token by token), 1024 of 2048 424 us, 1024 of 6000 1.16 ms (5.3 ms), 12 of
-// 40 001 tokens (arrays in the sequence's own tables instead of LDS) 3.5 ms (46 ms).  Of the
-// 165 us that one workgroup needs for 6000 tokens, the sort takes 75, the intervals 19 and
-// the transitions 61 (a compare-and-swap in the slot table each).  Two parts were three
-// times that: the nearest smaller values scanned in runs of 32 (130 us; now a tree of minima
-// of 8, one 16-byte read a level) and the transitions walking the records in memory instead
-// of their copies in LDS (122 us).  What is left of the transitions is the rate at which one
-// compute unit gets compare-and-swaps on scattered lines through: lanes that go on with the
+// working arrays in LDS (27 bytes a token, 16-bit indices), the bound is chains of dependent
+// LDS and table accesses between about sixty barriers: the LDS pipeline is busy for 27 % of
+// the cycles, the vector ALUs for 36 %.  Measured, sam_batch_reset: one prompt of 6000 tokens 222 us,
+// 64 of 2048 137 us (1.2 ms token by token), 1024 of 2048 465 us, 1024 of 6000 1.19 ms (5.3 ms).  With
+// the arrays in the sequence's own tables the bound is the rate at which one compute unit gets
+// scattered requests to the L2 through, 0.5 to 0.6 a nanosecond: 12 prompts of 40 001 tokens
+// 3.6 ms (46 ms).  Of the 165 us that one workgroup needs for 6000 tokens, the sort takes 75, the
+// intervals 19 and the transitions 61 (a compare-and-swap in the slot table each).  Two parts
+// took longer: the nearest smaller values scanned in runs of 32 (130 us; now a tree of
+// minima of 8, one 16-byte read a level, 19) and the transitions walking the records in
+// memory instead of their copies in LDS (122 us, now 61).  Lanes that go on with the
 // next position as soon as theirs has ended, instead of waiting for the longest path of their
 // wave, took 218 against 218 us for one prompt of 6000 tokens, and 1.22 against 1.18 ms for 1024.
 
@@ -196,9 +197,12 @@ __device__ __forceinline__ void static_tail(const StaticView &S, const int32_t *
 }
 
 // Fresh sequences (just reset) take their prompts.  Workgroups 0 .. n_static-1 walk the
-// corpus automaton, one wave per sequence; workgroup n_static + i builds the automaton of
-// sequence i (n_static is a multiple of 8, so it runs on the XCD on which the steps of
-// sequence i will find its tables).  A token outside the vocabulary ends its prompt.
+// corpus automaton, one wave per sequence; workgroup n_static + i builds the automaton of prompt
+// i's sequence (n_static is a multiple of 8: where all sequences of a batch take prompts, in
+// their order, it runs on the XCD on which their steps will find the tables).  The walks
+// reserve the builds' LDS without using it; beside the builds they cost little (1024 prompts
+// of 2048 tokens 465 us without a corpus, 447 over one of 4 M tokens, whose prompts repeat less).  A
+// token outside the vocabulary ends its prompt.
 template <bool kCompact, bool kAsm, int T>
 __global__ __launch_bounds__(T) void sam_prompt_kernel(StaticView S, BatchView B,
                                                           const int32_t *__restrict__ seq_map,
