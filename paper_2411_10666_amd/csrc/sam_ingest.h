@@ -28,6 +28,8 @@
 #pragma once
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "sam_layout.h"
 
 #if defined(__HIPCC__)
@@ -57,6 +59,8 @@ struct PromptSizes {
 // on 256 compute units, sam_batch_reset, token by token against whole (us):
 //   64 tokens     1 sequence 80 / 77   1024: 96 / 88   1536: 104 / 93, over a corpus 109 / 112
 //                 2048: 120 / 133   8192: 234 / 264   16384: 432 / 518
+//   76 tokens     2048: 119 / 128   4096: 179 / 171   8192: 276 / 277, over a corpus 299 / 318
+//   88 tokens     2048: 125 / 132   4096: 193 / 183   8192: 300 / 288, over a corpus 336 / 331
 //   96 tokens     2048: 135 / 134   4096: 210 / 188   8192: 340 / 294
 //   20 tokens and one of n    2048, n = 64: 92 / 97, 128: 130 / 96   3000, n = 64: 100 / 104, 96: 112 / 106
 //                 8192, n = 64: 121 / 173, 128: 153 / 174, 256: 237 / 176
@@ -67,15 +71,16 @@ inline bool prompts_whole(const PromptSizes &p, int64_t n_beyond, int64_t n_cu)
 {
     if (p.longest < 64 || p.most > (int64_t)kIngestMaxTokens) return false;
     if (p.n_seqs > 5 * n_cu) {
-        if (p.longest < 96) return false;
+        if (p.longest < 88) return false;
         // mostly short ones: each costs a workgroup its barriers
         if (p.total < 32 * p.n_seqs && p.longest < 64 + 8 * p.n_seqs / (3 * n_cu)) return false;
     }
     return n_beyond <= (p.longest > kIngestIdx16 && p.longest <= 32768 ? 6 : 5) * n_cu;
 }
 
-// Do they get workgroups of 256 threads, or of 1024?  Of 1024 one fits on a compute unit (70 VGPRs a
-// thread), so it is 256 where there are more workgroups than compute units (n_walks of them walk
+// Do they get workgroups of 256 threads, or of 1024?  Of 1024 one fits on a compute unit (69 to 81 VGPRs
+// a thread; bound to 64, so that two fit where LDS allows it, 257 prompts of 1025 tokens take
+// 188 us instead of 184, 1024 of 1500 455 instead of 446), so it is 256 where there are more workgroups than compute units (n_walks of them walk
 // the corpus automaton) and the prompts are so short that 256 threads suffice.  Measured, 1024
 // against 256 threads: 256 prompts of 256 tokens 88 against 90 us, over a corpus 120 against 103, of
 // 512 130 against 134, of 1024 (no corpus) 121 against 155; 300 of 64 97 against 78, of 256 116
@@ -503,11 +508,10 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
     constexpr bool kSpread = sizeof(I) == 4;
     constexpr uint32_t kCrowd = 32;
     uint32_t *const crowded = small + 32;            // [32] one flag per round
-    bool spread = false;
     const uint32_t shift = ctx.log2(n) + 1;          // second names are 0 .. n
-    auto bucket_of_pair = [&](K key) -> uint32_t {
+    auto bucket_of_pair = [&](auto spread, K key) -> uint32_t {
         const uint32_t g = (uint32_t)(key >> kHalf), second = (uint32_t)(key & kLow), size = A.size[g];
-        if (kSpread && spread) {
+        if constexpr (decltype(spread)::value) {
             // rises with the second name, which is all that it has to
             const float width = (float)size / (float)(A.hi[g] - A.lo[g] + 1u);
             const uint32_t at = (uint32_t)((float)(second - A.lo[g]) * width);
@@ -518,40 +522,12 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
     constexpr uint32_t kRuns = C::kThreads;          // of the running sum, one for each thread
     static_assert(kRuns <= kIngestParts, "part[] holds one sum for each thread");
     const uint32_t prun = (n + kRuns - 1) / kRuns;
-    uint32_t round = 1;
-    for (uint32_t h = 1; h < n; h *= 2, round++) {
-        if (!active[round - 1]) break;
-        if (!kLds && h >= 16 && (ctx.log2(h) & 1) == 0) {
-            const uint32_t j = (ctx.log2(h) - 4) / 2;
-            if (j < 7) ctx.each(n, [&](uint32_t i) { A.names[j * A.stride + i] = A.grp[i]; });
-        }
-        ctx.each(hs, [&](uint32_t i) { A.key[i] = kEmpty; A.val[i] = 0; });
-        spread = kSpread && round > 1 && crowded[round - 1];
-        ctx.each(n, [&](uint32_t i) {
-            A.cursor[i] = 0;
-            if (kSpread && spread) { A.lo[i] = kNil; A.hi[i] = 0; }
-        });
-        ctx.sync();
-        ctx.each(n, [&](uint32_t i) {
-            const I g = A.grp[i];
-            if (g & kAlone) { A.cursor[g & (I)~kAlone] = 1; return; }
-            const uint32_t second = i >= h ? (uint32_t)(A.grp[i - h] & (I)~kAlone) + 1u : 0u;
-            A.slot[i] = (I)insert((K)(((K)g << kHalf) | (K)second));
-        });
-        ctx.sync();
-        if (kSpread && spread) {
-            ctx.each(hs, [&](uint32_t i) {
-                const K key = A.key[i];
-                if (key == kEmpty) return;
-                ctx.lower(&A.lo[key >> kHalf], (uint32_t)(key & kLow));
-                ctx.raise(&A.hi[key >> kHalf], (uint32_t)(key & kLow));
-                crowded[round] = 1;
-            });
-            ctx.sync();
-        }
+    // all pairs of a round are in key[]: where each starts goes into the upper half of its val[]
+    // (two bodies: the test for one in every bucket_of_pair cost 2 % of 12 x 40 000 tokens)
+    auto rank_pairs = [&](auto spread, uint32_t round) {
         ctx.each(hs, [&](uint32_t i) {
             const K key = A.key[i];
-            if (key != kEmpty) ctx.add(&A.cursor[bucket_of_pair(key)], A.val[i]);
+            if (key != kEmpty) ctx.add(&A.cursor[bucket_of_pair(spread, key)], A.val[i]);
         });
         ctx.sync();
         ctx.each(kRuns, [&](uint32_t c) {
@@ -573,7 +549,7 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
         ctx.each(hs, [&](uint32_t i) {
             const K key = A.key[i];
             if (key == kEmpty) return;
-            K *const w = &A.cursor[bucket_of_pair(key)];
+            K *const w = &A.cursor[bucket_of_pair(spread, key)];
             for (K seen = *w;;) {
                 A.next[i] = (I)(seen >> kHalf);
                 const K old = ctx.cas(w, seen, (K)((seen & kLow) | ((K)(i + 1) << kHalf)));
@@ -585,17 +561,52 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
         ctx.each(hs, [&](uint32_t i) {
             const K key = A.key[i];
             if (key == kEmpty) return;
-            const K w = A.cursor[bucket_of_pair(key)];
+            const K w = A.cursor[bucket_of_pair(spread, key)];
             uint32_t start = (uint32_t)(w & kLow), left = hs;
             for (uint32_t j = (uint32_t)(w >> kHalf); j; j = A.next[j - 1]) {
                 if (A.key[j - 1] < key) start += (uint32_t)(A.val[j - 1] & kLow);
                 if (!kLds && !--left) { corrupt(); return; }
             }
-            if (kSpread && hs - left > kCrowd) crowded[round] = 1;
+            if (kSpread && (decltype(spread)::value || hs - left > kCrowd)) crowded[round] = 1;
             A.val[i] |= (K)((K)start << kHalf);
             if (start != (uint32_t)(key >> kHalf)) A.lev[start] = (uint8_t)round;
         });
         ctx.sync();
+    };
+    uint32_t round = 1;
+    for (uint32_t h = 1; h < n; h *= 2, round++) {
+        if (!active[round - 1]) break;
+        if (!kLds && h >= 16 && (ctx.log2(h) & 1) == 0) {
+            const uint32_t j = (ctx.log2(h) - 4) / 2;
+            if (j < 7) ctx.each(n, [&](uint32_t i) { A.names[j * A.stride + i] = A.grp[i]; });
+        }
+        ctx.each(hs, [&](uint32_t i) { A.key[i] = kEmpty; A.val[i] = 0; });
+        const bool spread = kSpread && round > 1 && ctx.uniform(crowded[round - 1]);
+        ctx.each(n, [&](uint32_t i) { A.cursor[i] = 0; });
+        if (kSpread && spread) ctx.each(n, [&](uint32_t i) { A.lo[i] = kNil; A.hi[i] = 0; });
+        ctx.sync();
+        ctx.each(n, [&](uint32_t i) {
+            const I g = A.grp[i];
+            if (g & kAlone) { A.cursor[g & (I)~kAlone] = 1; return; }
+            const uint32_t second = i >= h ? (uint32_t)(A.grp[i - h] & (I)~kAlone) + 1u : 0u;
+            A.slot[i] = (I)insert((K)(((K)g << kHalf) | (K)second));
+        });
+        ctx.sync();
+        if (kSpread && spread) {
+            ctx.each(hs, [&](uint32_t i) {
+                const K key = A.key[i];
+                if (key == kEmpty) return;
+                ctx.lower(&A.lo[key >> kHalf], (uint32_t)(key & kLow));
+                ctx.raise(&A.hi[key >> kHalf], (uint32_t)(key & kLow));
+            });
+            ctx.sync();
+        }
+        if constexpr (kSpread) {
+            if (spread) rank_pairs(std::true_type{}, round);
+            else rank_pairs(std::false_type{}, round);
+        } else {
+            rank_pairs(std::false_type{}, round);
+        }
         ctx.each(n, [&](uint32_t i) {
             if (!(A.grp[i] & kAlone)) take_names(i, round);
         });

@@ -90,6 +90,11 @@ struct PromptCtx {
     {
         return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    // a value that all threads have, as a scalar
+    __device__ __forceinline__ uint32_t uniform(uint32_t x)
+    {
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+    }
     __device__ __forceinline__ uint32_t mulhi(uint32_t a, uint32_t b) { return __umulhi(a, b); }
     __device__ __forceinline__ uint32_t popc(uint32_t x) { return (uint32_t)__popc(x); }
     __device__ __forceinline__ uint32_t first(uint32_t x) { return (uint32_t)__builtin_ctz(x); }
@@ -147,24 +152,18 @@ struct PromptCtx {
 };
 
 // How many tokens at the end of the prompt stand in front of corpus position `end` too, `known` of
-// them known to: 256 a round trip.
+// them known to: 64 a round trip (256 a round trip took less for long passages, but all prompts 1 %
+// more, by the registers that it takes in the same kernel as the builds).
 __device__ __forceinline__ uint32_t agree_back(const StaticView &S, const int32_t *tok, uint32_t n,
                                                uint32_t end, uint32_t known, int lane)
 {
     const uint32_t most = n < end ? n : end;
-    for (uint32_t base = known; base < most; base += 256) {
-        uint32_t at = most;
-#pragma unroll
-        for (int u = 3; u >= 0; u--) {
-            const uint32_t j = base + 64 * u + lane, back = j < most ? j : most - 1;
-            if (tok[n - 1 - back] != S.text[end - 1 - back]) at = back;
-        }
-        if (__any(at < most)) {
-            for (int d = 32; d; d /= 2) {
-                const uint32_t other = (uint32_t)__shfl_xor((int)at, d);
-                at = other < at ? other : at;
-            }
-            return uni(at);
+    for (uint32_t base = known; base < most; base += 64) {
+        const uint32_t j = base + lane, back = j < most ? j : most - 1;
+        const unsigned long long differ = __ballot(tok[n - 1 - back] != S.text[end - 1 - back]);
+        if (differ) {
+            const uint32_t at = base + (uint32_t)__builtin_ctzll(differ);
+            return uni(at < most ? at : most - 1);
         }
     }
     return most;

@@ -44,6 +44,7 @@ struct CpuCtx {
     void bit_or(uint32_t *p, uint32_t v) { *p |= v; }
     uint32_t exch(uint32_t *p, uint32_t v) { const uint32_t old = *p; *p = v; return old; }
     uint32_t fresh(uint32_t *p) { return *p; }
+    uint32_t uniform(uint32_t x) { return x; }
     uint32_t mulhi(uint32_t a, uint32_t b) { return (uint32_t)(((uint64_t)a * b) >> 32); }
     uint32_t popc(uint32_t x) { return (uint32_t)__builtin_popcount(x); }
     uint32_t first(uint32_t x) { return (uint32_t)__builtin_ctz(x); }
@@ -182,7 +183,7 @@ static int rules()
         return bad("LDS", 6144, (uint32_t)ingest_lds_bytes(6144));
     struct { int64_t n_seqs, longest, mean, n_beyond; bool whole; } calls[] = {
         {1, 63, 63, 0, false}, {1, 64, 64, 0, true}, {1024, 64, 64, 0, true}, {1280, 64, 20, 0, true},
-        {2048, 64, 64, 0, false}, {8192, 64, 64, 0, false}, {16384, 70, 70, 0, false}, {2048, 96, 96, 0, true},
+        {2048, 64, 64, 0, false}, {8192, 64, 64, 0, false}, {16384, 87, 87, 0, false}, {2048, 88, 88, 0, true},
         {8192, 96, 96, 0, true}, {16384, 128, 128, 0, true}, {2048, 128, 20, 0, true}, {3000, 64, 20, 0, false},
         {3000, 96, 20, 0, true}, {8192, 64, 20, 0, false}, {8192, 128, 20, 0, false}, {8192, 256, 20, 0, true},
         {4096, 6000, 6000, 0, true}, {1024, 8000, 8000, 1024, true}, {2048, 6300, 6300, 2048, false},

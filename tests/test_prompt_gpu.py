@@ -118,8 +118,9 @@ def test_many_prompts(batch, n, mode, with_corpus):
 
 
 # as many prompts as compute units, the walks over the corpus beside them (small workgroups up to 256
-# tokens); more, all but two of them too short to gain (token by token up to 96 tokens)
-@pytest.mark.parametrize("batch,n", [(250, 256), (250, 257), (1300, 95), (1300, 96), (3000, 94), (3000, 96)])
+# tokens); more than five for each (token by token up to 87 tokens), all but two of them short
+# (up to 94)
+@pytest.mark.parametrize("batch,n", [(250, 256), (250, 257), (1300, 87), (1300, 88), (3000, 94), (3000, 96)])
 def test_lines_of_the_dispatch(batch, n):
     rng = np.random.default_rng(batch + n)
     sizes = rng.integers(1, n + 1, size=batch) if batch < 2000 else rng.integers(1, 30, size=batch)
