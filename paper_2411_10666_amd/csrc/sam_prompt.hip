@@ -14,8 +14,8 @@ namespace sam {
 // Extending a sequence token by token takes 0.6 to 1.2 us a token whatever the chip has
 // free, so a prompt of 3000 tokens took 1.8 ms.  Built whole, by one workgroup with its
 // working arrays in LDS (27 bytes a token, 16-bit indices), the bound is chains of dependent
-// LDS and table accesses between about sixty barriers: the LDS pipeline is busy for 27 % of
-// the cycles, the vector ALUs for 36 %.  Measured, sam_batch_reset: one prompt of 6000 tokens 222 us,
+// LDS and table accesses between about sixty barriers: the LDS pipeline is busy for 28 % of
+// the cycles, the vector ALUs for 37 %.  Measured, sam_batch_reset: one prompt of 6000 tokens 222 us,
 // 64 of 2048 137 us (1.2 ms token by token), 1024 of 2048 465 us, 1024 of 6000 1.19 ms (5.3 ms).  With
 // the arrays in the sequence's own tables the bound is the rate at which one compute unit gets
 // scattered requests to the L2 through, 0.5 to 0.6 a nanosecond: 12 prompts of 40 001 tokens
