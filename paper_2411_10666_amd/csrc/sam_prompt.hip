@@ -174,11 +174,11 @@ __device__ __forceinline__ uint32_t agree_back(const StaticView &S, const int32_
 // tokens before the end it finds the longest such suffix of at most w tokens, and if that is
 // shorter than w it is the one looked for.  48 tokens do for most prompts, but a batch waits for
 // its longest walk.  If they match throughout, the corpus is compared with the prompt backwards
-// from where they occur first, and the next window is one token longer than what agrees: it is
-// too short only if the prompt's end occurs elsewhere with more in front of it.  Windows at
-// least double, and from half the prompt on all of it is walked: a prompt that is a passage of the
-// corpus costs one walk over it (0.15 to 0.3 us a token, 0.5 to 0.7 where matches break off), the
-// worst text two.  (Windows of 48, 192, 768 ... tokens, each from the root: 256 passages of 3073
+// from where they occur first, and the second window is one token longer than what agrees.  It is
+// full too only if the prompt's end occurs elsewhere with more in front of it: further windows
+// are at least four times as long.  Where more than half of the prompt agrees all of it is walked:
+// a passage of the corpus costs one walk over it (0.15 to 0.3 us a token, 0.5 to 0.7 where
+// matches break off).  (Windows of 48, 192, 768 ... tokens, each from the root: 256 passages of 3073
 // tokens 2.2 ms, now 1.0 (token by token 1.9); 256 prompts of 1024 with matches of up to 272: 0.50,
 // now 0.18.)
 __device__ __forceinline__ void static_tail(const StaticView &S, const int32_t *tok, uint32_t n,
@@ -190,8 +190,8 @@ __device__ __forceinline__ void static_tail(const StaticView &S, const int32_t *
         static_feed(S, tok + (n - w), w, vocab, lane, s, l, e, fault, use_asm);
         if (uni(l) < w || w == n || fault) return;
         const uint32_t next = agree_back(S, tok, n, uni(e) & ~kWideBit, w, lane) + 1;
-        w = next > 2 * w ? next : 2 * w;
-        if (w > n / 2) w = n;
+        w = w == 48 || next > 4 * w ? next : 4 * w;
+        if (w > n || next > n / 2) w = n;
     }
 }
 
