@@ -73,14 +73,17 @@ const char *sam_last_error(void);
 const char *sam_build_id(void);
 
 /*
- * Build-SAM (Algorithm 2) over `corpus_tokens` on the host, then copy the
- * automaton to device memory as flat arrays: the corpus text, one record per
+ * Build-SAM (Algorithm 2) over `corpus_tokens`: on the device, by all of it at once, for corpora of
+ * 10 000 tokens and more, on the host for smaller ones and where the device has no room for the
+ * working arrays (about 200 bytes a token while it builds).  The automaton is the same.  Device
+ * memory then holds it as flat arrays: the corpus text, one record per
  * state with its suffix link, the link's length and up to two of its
  * transitions, a direct-indexed table of the root's transitions and a bucketed
  * open-addressed (state, token) -> {target, min_endpos(target)} hash that holds
  * the transitions of the states with more than two.  The device holds the
  * complete transition table while the records are made (sam_corpus_info
- * reports what stays afterwards).
+ * reports what stays afterwards); host memory keeps it, in an order that depends on
+ * who built it.
  *   corpus_tokens : host, int32 [n_tokens]; a multi-document corpus is passed
  *                   already joined by a separator token (Section 3.1).
  *   n_tokens      : 1 .. 2^31-2, and at most about 10^9: the host's transition
@@ -103,7 +106,7 @@ typedef void (*sam_progress_fn)(const char *phase, int64_t done, int64_t total, 
 int sam_set_progress_callback(sam_progress_fn fn, void *user);
 
 /*
- * Same host construction as sam_build but nothing is copied to a device, so it
+ * The same automaton, built on the host and copied to no device, so it
  * runs on a machine without a GPU.  The handle can be inspected
  * (sam_corpus_info / _export / _find) but not used by sam_batch_init.
  */
@@ -346,8 +349,10 @@ int sam_batch_status(const sam_batch *batch, uint32_t *status, void *hip_stream)
  * step kernel of every later sam_batch_init run with its two prefetching waves,
  * which otherwise join for batches of 128 sequences or more and for corpus
  * automata larger than 256 MB; bit 5 keeps them
- * out whatever the batch size (for measuring what they cost and bring).  mode 0
- * restores the defaults.  Results are identical in every mode.
+ * out whatever the batch size (for measuring what they cost and bring); bit 6
+ * makes every later sam_build build on the device however small the corpus; bit 7
+ * keeps the builds by the whole chip out: corpora are built on the host, prompts
+ * too long for LDS by one workgroup each.  mode 0 restores the defaults.  Results are identical in every mode.
  */
 int sam_set_layout_override(int mode);
 

@@ -7,8 +7,8 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsam_hip.so")
-SOURCES = ["sam_api.hip", "sam_kernels.hip", "sam_prompt.hip", "sam_tree.hip", "sam_membench.hip", "sam_host.cpp"]
-HEADERS = ["sam_layout.h", "sam_ingest.h", "sam_prompt.h", "sam_walk.h", "sam_device.h", "sam_host.h", "sam_membench.h",
+SOURCES = ["sam_api.hip", "sam_kernels.hip", "sam_prompt.hip", "sam_bulk.hip", "sam_tree.hip", "sam_membench.hip", "sam_host.cpp"]
+HEADERS = ["sam_layout.h", "sam_ingest.h", "sam_bulk.h", "sam_bulk_launch.h", "sam_prompt.h", "sam_walk.h", "sam_device.h", "sam_host.h", "sam_membench.h",
            os.path.join("..", "..", "include", "sam.h")]
 
 HIPCC_FLAGS = [

@@ -9,9 +9,11 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/sam.h"
+#include "sam_bulk_launch.h"
 #include "sam_device.h"
 #include "sam_host.h"
 #include "sam_membench.h"
@@ -24,7 +26,9 @@ namespace {
 thread_local std::string g_err;
 int g_layout_override = 0;   // bit 0: always the wide layout, bit 1: tight slot tables,
                              // bit 2: C++ token loops, bit 3: corpus table beyond 4 GiB,
-                             // bit 4: scout waves whatever the batch size, bit 5: never
+                             // bit 4: scout waves whatever the batch size, bit 5: never,
+                             // bit 6: corpora on the device whatever their size,
+                             // bit 7: no builds by the whole chip
 // Scout waves pay once the tables a step touches no longer stay in the caches from one
 // launch to the next: the per-sequence tables when many sequences share the caches, the
 // corpus automaton when it is larger than the last-level cache (256 MB).  Measured:
@@ -38,6 +42,10 @@ constexpr int     kScoutMaxSeqPerCu = 6;
 constexpr int64_t kScoutMinCorpusBytes = 256ll << 20;
 // buckets of 128 bytes that make a transition table of 4.5 GiB
 constexpr uint64_t kHugeTableBuckets = (1ull << 25) + (1ull << 22);
+// Tokens from which on the corpus automaton is built on the device: about fifty launches and a few
+// allocations take what the host needs for 10 000 tokens (sam_build, device / host, ms: 5000 tokens
+// 0.59 / 0.43, 10 000 0.66 / 0.72, 20 000 0.78 / 1.32, 100 000 1.8 / 6.4, 700 000 5.9 / 104, 6 M 42 / 1384).
+int64_t device_build_min() { return g_layout_override & 128 ? INT64_MAX : (g_layout_override & 64 ? 1 : 10000); }
 HostSam::ProgressFn g_progress = nullptr;
 void *g_progress_user = nullptr;
 
@@ -138,94 +146,75 @@ static void corpus_release_device(sam_corpus *c)
     c->d_text = c->d_linkrec = c->d_root = c->d_slots = c->d_topk = nullptr;
 }
 
-static int corpus_upload(sam_corpus *c)
+// What is on the device already: text, the root's transitions, the table of all others and the link
+// pairs.  State records are made from them, and the walks' table; the pairs are freed.
+static int corpus_finish(sam_corpus *c, LinkPair *d_pairs)
 {
     const HostSam &h = c->host;
-    std::vector<LinkPair> lr;
-    try {
-        h.make_linkrec(lr);
-    } catch (const std::bad_alloc &) {
-        return fail(SAM_ENOMEM, "sam_build: out of host memory for the link records");
-    }
     const size_t b_text = (size_t)h.n_tokens * sizeof(int32_t);
     const size_t b_lr = (size_t)h.n_states * sizeof(LinkRec);
     const size_t b_root = (size_t)h.vocab * sizeof(RootEnt);
-    const size_t b_slots = (size_t)h.n_buckets * kBucketSlots * sizeof(Slot);
-    size_t b_slots_dev = b_slots;      // what stays on the device in the end
-    HIP_TRY(hipGetDevice(&c->device));
-    HIP_TRY(hipMalloc(&c->d_text, b_text));
-    HIP_TRY(hipMalloc(&c->d_linkrec, b_lr));
-    HIP_TRY(hipMalloc(&c->d_root, b_root));
-    HIP_TRY(hipMalloc(&c->d_slots, b_slots));
-    HIP_TRY(hipMemcpy(c->d_text, h.text.data(), b_text, hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(c->d_root, h.root.data(), b_root, hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(c->d_slots, h.slots, b_slots, hipMemcpyHostToDevice));
-    {
-        // link pairs -> 32-byte state records with two transitions inline
-        void *d_pairs = nullptr, *d_wide = nullptr;
-        const size_t b_pairs = (size_t)h.n_states * sizeof(LinkPair);
-        const size_t b_wide = ((size_t)h.n_states + 31) / 32 * sizeof(uint32_t);
-        HIP_TRY(hipMalloc(&d_pairs, b_pairs));
-        hipError_t e = hipMalloc(&d_wide, b_wide);
-        if (e == hipSuccess) e = hipMemset(d_wide, 0, b_wide);
-        if (e == hipSuccess) e = hipMemcpy(d_pairs, lr.data(), b_pairs, hipMemcpyHostToDevice);
+    // link pairs -> 32-byte state records with two transitions inline
+    void *d_wide = nullptr;
+    const size_t b_wide = ((size_t)h.n_states + 31) / 32 * sizeof(uint32_t);
+    hipError_t e = hipMalloc(&c->d_linkrec, b_lr);
+    if (e == hipSuccess) e = hipMalloc(&d_wide, b_wide);
+    if (e == hipSuccess) e = hipMemset(d_wide, 0, b_wide);
+    if (e == hipSuccess)
+        e = launch_staterec(d_pairs, (Slot *)c->d_slots, (RootEnt *)c->d_root, (LinkRec *)c->d_linkrec,
+                            (uint32_t *)d_wide, h.n_states, h.n_buckets * kBucketSlots, (uint32_t)h.vocab,
+                            nullptr);
+    if (e == hipSuccess) e = hipDeviceSynchronize();
+    (void)hipFree(d_pairs);
+    // The walks only ever look up transitions of wide states (a narrow state's record
+    // holds all of its own): the table they probe is rebuilt with those alone, at load
+    // 0.5, and the full one freed.  (Not in the testing mode that wants a table beyond
+    // 4 GiB.)
+    uint64_t n_buckets = h.n_buckets;
+    if (e == hipSuccess && (g_layout_override & 8) == 0) {
+        unsigned long long *d_count = nullptr, n_wide = 0;
+        void *d_new = nullptr;
+        e = hipMalloc((void **)&d_count, sizeof(*d_count));
+        if (e == hipSuccess) e = hipMemset(d_count, 0, sizeof(*d_count));
         if (e == hipSuccess)
-            e = launch_staterec((const LinkPair *)d_pairs, (Slot *)c->d_slots, (RootEnt *)c->d_root,
-                                (LinkRec *)c->d_linkrec, (uint32_t *)d_wide, h.n_states,
-                                h.n_buckets * kBucketSlots, (uint32_t)h.vocab, nullptr);
-        if (e == hipSuccess) e = hipDeviceSynchronize();
-        (void)hipFree(d_pairs);
-        // The walks only ever look up transitions of wide states (a narrow state's record
-        // holds all of its own): the table they probe is rebuilt with those alone, at load
-        // 0.5, and the full one freed.  (Not in the testing mode that wants a table beyond
-        // 4 GiB.)
-        uint64_t n_buckets = h.n_buckets;
-        if (e == hipSuccess && (g_layout_override & 8) == 0) {
-            unsigned long long *d_count = nullptr, n_wide = 0;
-            void *d_new = nullptr;
-            e = hipMalloc((void **)&d_count, sizeof(*d_count));
-            if (e == hipSuccess) e = hipMemset(d_count, 0, sizeof(*d_count));
-            if (e == hipSuccess)
-                e = launch_count_wide((const Slot *)c->d_slots, (const uint32_t *)d_wide,
-                                      h.n_buckets * kBucketSlots, d_count, nullptr);
-            if (e == hipSuccess) e = hipMemcpy(&n_wide, d_count, sizeof(n_wide), hipMemcpyDeviceToHost);
-            if (d_count) (void)hipFree(d_count);
-            const uint64_t nb_new = (2 * (uint64_t)n_wide + 64 + kBucketSlots - 1) / kBucketSlots;
-            if (e == hipSuccess && nb_new < h.n_buckets) {
-                const size_t b_new = (size_t)nb_new * kBucketSlots * sizeof(Slot);
-                if (hipMalloc(&d_new, b_new) != hipSuccess) {
-                    // no room for a second table beside the full one: the full one serves
-                    (void)hipGetLastError();
-                    d_new = nullptr;
+            e = launch_count_wide((const Slot *)c->d_slots, (const uint32_t *)d_wide,
+                                  h.n_buckets * kBucketSlots, d_count, nullptr);
+        if (e == hipSuccess) e = hipMemcpy(&n_wide, d_count, sizeof(n_wide), hipMemcpyDeviceToHost);
+        if (d_count) (void)hipFree(d_count);
+        const uint64_t nb_new = (2 * (uint64_t)n_wide + 64 + kBucketSlots - 1) / kBucketSlots;
+        if (e == hipSuccess && nb_new < h.n_buckets) {
+            const size_t b_new = (size_t)nb_new * kBucketSlots * sizeof(Slot);
+            if (hipMalloc(&d_new, b_new) != hipSuccess) {
+                // no room for a second table beside the full one: the full one serves
+                (void)hipGetLastError();
+                d_new = nullptr;
+            } else {
+                e = launch_fill_empty(d_new, b_new, nullptr);
+                if (e == hipSuccess)
+                    e = launch_compact_slots((const Slot *)c->d_slots, (const uint32_t *)d_wide,
+                                             h.n_buckets * kBucketSlots, (Slot *)d_new, nb_new,
+                                             nullptr);
+                if (e == hipSuccess) e = hipDeviceSynchronize();
+                if (e == hipSuccess) {
+                    (void)hipFree(c->d_slots);
+                    c->d_slots = d_new;
+                    n_buckets = nb_new;
                 } else {
-                    e = launch_fill_empty(d_new, b_new, nullptr);
-                    if (e == hipSuccess)
-                        e = launch_compact_slots((const Slot *)c->d_slots, (const uint32_t *)d_wide,
-                                                 h.n_buckets * kBucketSlots, (Slot *)d_new, nb_new,
-                                                 nullptr);
-                    if (e == hipSuccess) e = hipDeviceSynchronize();
-                    if (e == hipSuccess) {
-                        (void)hipFree(c->d_slots);
-                        c->d_slots = d_new;
-                        n_buckets = nb_new;
-                    } else {
-                        (void)hipFree(d_new);
-                    }
+                    (void)hipFree(d_new);
                 }
             }
         }
-        if (d_wide) (void)hipFree(d_wide);
-        if (e != hipSuccess) return fail_hip("sam_build: state records", e);
-        b_slots_dev = (size_t)n_buckets * kBucketSlots * sizeof(Slot);
-        c->view.n_buckets = n_buckets;
     }
+    if (d_wide) (void)hipFree(d_wide);
+    if (e != hipSuccess) return fail_hip("sam_build: state records", e);
+    c->view.n_buckets = n_buckets;
     c->view.text = (const int32_t *)c->d_text;
     c->view.linkrec = (const LinkRec *)c->d_linkrec;
     c->view.root = (const RootEnt *)c->d_root;
     c->view.slots = (const Slot *)c->d_slots;
     c->view.n_tokens = (uint32_t)h.n_tokens;
     c->view.n_states = h.n_states;
-    c->device_bytes = (int64_t)(b_text + b_lr + b_root + b_slots_dev);
+    c->device_bytes = (int64_t)(b_text + b_lr + b_root + (size_t)n_buckets * kBucketSlots * sizeof(Slot));
     c->on_device = true;
     if (c->device >= 0 && c->device < kMaxDevices) {
         // a set-up call: do the one-time lookup of the fixed buffer here, so that a later
@@ -237,6 +226,175 @@ static int corpus_upload(sam_corpus *c)
     return SAM_OK;
 }
 
+static int corpus_upload(sam_corpus *c)
+{
+    const HostSam &h = c->host;
+    std::vector<LinkPair> lr;
+    try {
+        h.make_linkrec(lr);
+    } catch (const std::bad_alloc &) {
+        return fail(SAM_ENOMEM, "sam_build: out of host memory for the link records");
+    }
+    const size_t b_text = (size_t)h.n_tokens * sizeof(int32_t);
+    const size_t b_root = (size_t)h.vocab * sizeof(RootEnt);
+    const size_t b_slots = (size_t)h.n_buckets * kBucketSlots * sizeof(Slot);
+    const size_t b_pairs = (size_t)h.n_states * sizeof(LinkPair);
+    HIP_TRY(hipGetDevice(&c->device));
+    HIP_TRY(hipMalloc(&c->d_text, b_text));
+    HIP_TRY(hipMalloc(&c->d_root, b_root));
+    HIP_TRY(hipMalloc(&c->d_slots, b_slots));
+    HIP_TRY(hipMemcpy(c->d_text, h.text.data(), b_text, hipMemcpyHostToDevice));
+    HIP_TRY(hipMemcpy(c->d_root, h.root.data(), b_root, hipMemcpyHostToDevice));
+    HIP_TRY(hipMemcpy(c->d_slots, h.slots, b_slots, hipMemcpyHostToDevice));
+    void *d_pairs = nullptr;
+    HIP_TRY(hipMalloc(&d_pairs, b_pairs));
+    const hipError_t e = hipMemcpy(d_pairs, lr.data(), b_pairs, hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+        (void)hipFree(d_pairs);
+        return fail_hip("sam_build: state records", e);
+    }
+    return corpus_finish(c, (LinkPair *)d_pairs);
+}
+
+// A copy to host memory that is not pinned goes through the runtime's staging buffers at the rate of one
+// thread's memcpy (17 GB/s); four threads with a stream each copy 48 MB in less than half the time.
+static hipError_t copy_down(void *dst, const void *src, size_t bytes, int device)
+{
+    constexpr size_t kWorth = 4u << 20;
+    constexpr int kThreads = 4;
+    hipError_t e[kThreads] = {hipSuccess, hipSuccess, hipSuccess, hipSuccess};
+    const size_t piece = bytes < kWorth ? bytes : (bytes / kThreads + 4095) / 4096 * 4096;
+    auto part = [&](int k) {
+        const size_t lo = k * piece, hi = lo + piece < bytes && k + 1 < kThreads ? lo + piece : bytes;
+        if (lo >= hi) return;
+        e[k] = hipSetDevice(device);
+        if (e[k] == hipSuccess)
+            e[k] = hipMemcpyAsync((char *)dst + lo, (const char *)src + lo, hi - lo, hipMemcpyDeviceToHost, hipStreamPerThread);
+        if (e[k] == hipSuccess) e[k] = hipStreamSynchronize(hipStreamPerThread);
+    };
+    std::thread others[kThreads];
+    for (int k = 1; k < kThreads; k++) {
+        try {
+            if ((size_t)k * piece < bytes) others[k] = std::thread(part, k);
+        } catch (...) {
+            part(k);
+        }
+    }
+    part(0);
+    for (int k = 1; k < kThreads; k++)
+        if (others[k].joinable()) others[k].join();
+    for (int k = 0; k < kThreads; k++)
+        if (e[k] != hipSuccess) return e[k];
+    return hipSuccess;
+}
+
+// Build-SAM on the device: the host receives what its own builder would have made, but for the order
+// of the keys in the transition table.  *done false: no room for it, or nothing for it; the host
+// builds.
+static int corpus_build_device(sam_corpus *c, const int32_t *tokens, int64_t n, int32_t vocab, bool *done)
+{
+    *done = false;
+    const uint64_t n_buckets = static_buckets_for(n), n_slots = n_buckets * kBucketSlots;
+    if (n_slots >= 0xFFFFFFFFull) return SAM_OK;
+    struct Scratch {
+        std::vector<void *> all;
+        std::thread host;
+        ~Scratch()
+        {
+            if (host.joinable()) host.join();
+            for (void *p : all) (void)hipFree(p);
+        }
+    } scratch;
+    // every failure to allocate ends here: what was allocated is freed, the host builds
+    auto none = [&] {
+        (void)hipGetLastError();
+        if (scratch.host.joinable()) scratch.host.join();
+        corpus_release_device(c);
+        c->host.~HostSam();
+        new (&c->host) HostSam();
+        return SAM_OK;
+    };
+    auto take = [&](void **p, size_t bytes) {
+        if (hipMalloc(p, bytes) != hipSuccess) return false;
+        scratch.all.push_back(*p);
+        return true;
+    };
+    HIP_TRY(hipGetDevice(&c->device));
+    hipError_t e;
+    const uint32_t un = (uint32_t)n;
+    BulkWork w;
+    if (hipMalloc(&c->d_text, (size_t)n * sizeof(int32_t)) != hipSuccess ||
+        hipMalloc(&c->d_root, (size_t)vocab * sizeof(RootEnt)) != hipSuccess)
+        return none();
+    const size_t b1 = bulk_first_bytes(un), b2 = bulk_up(bulk_second_bytes<uint32_t>(un)), b3 = bulk_up(bulk_third_bytes(un)),
+                 br = (2 * (size_t)n + 1) * sizeof(BulkCorpus::State);
+    char *work = nullptr;
+    try {
+        scratch.all.reserve(4);
+    } catch (const std::bad_alloc &) {
+        return none();
+    }
+    if (!take((void **)&work, bulk_up(b1) + b2 + b3 + bulk_up(4 * kBulkCounts) + br)) return none();
+    w.first = work;
+    w.second = w.first + bulk_up(b1);
+    w.third = w.second + b2;
+    w.counts = (uint32_t *)(w.third + b3);
+    w.rec = (BulkCorpus::State *)((char *)w.counts + bulk_up(4 * kBulkCounts));
+    // the host's memory is made ready while the device works
+    bool room = false;
+    try {
+        scratch.host = std::thread([&] { room = c->host.reserve_for_copy(tokens, n, vocab, n_buckets); });
+    } catch (...) {
+        room = c->host.reserve_for_copy(tokens, n, vocab, n_buckets);
+    }
+    uint32_t at = un;
+    HIP_TRY(hipMemcpy(c->d_text, tokens, (size_t)n * sizeof(int32_t), hipMemcpyHostToDevice));
+    HIP_TRY(hipMemcpy(w.counts, &at, sizeof(at), hipMemcpyHostToDevice));
+    HIP_TRY(bulk_check((const int32_t *)c->d_text, un, (uint32_t)vocab, w.counts, nullptr));
+    HIP_TRY(hipMemcpy(&at, w.counts, sizeof(at), hipMemcpyDeviceToHost));
+    if (at < un)
+        return fail(SAM_ETOKEN, "sam_build: corpus token " + std::to_string(tokens[at]) + " at position " +
+                                    std::to_string(at) + " is outside [0, vocab)");
+    HIP_TRY(hipMemset(c->d_root, 0, (size_t)vocab * sizeof(RootEnt)));
+    uint32_t n_states = 0;
+    uint64_t n_trans = 0;
+    bool gave_up = false;
+    HIP_TRY(bulk_corpus((const int32_t *)c->d_text, un, (uint32_t)vocab, (RootEnt *)c->d_root, w, &n_states, &n_trans,
+                        &gave_up, nullptr));
+    if (gave_up) return none();
+    LinkPair *d_pairs = nullptr;
+    if (hipMalloc(&c->d_slots, n_slots * sizeof(Slot)) != hipSuccess ||
+        hipMalloc((void **)&d_pairs, (size_t)n_states * sizeof(LinkPair)) != hipSuccess)
+        return none();
+    e = launch_fill_empty(c->d_slots, n_slots * sizeof(Slot), nullptr);
+    if (e == hipSuccess)
+        e = bulk_corpus_tables((const int32_t *)c->d_text, un, (uint32_t)vocab, n_states, (RootEnt *)c->d_root, w,
+                               (Slot *)c->d_slots, n_buckets, d_pairs, nullptr);
+    if (scratch.host.joinable()) scratch.host.join();
+    if (e == hipSuccess && !room) {
+        (void)hipFree(d_pairs);
+        return fail(SAM_ENOMEM, "sam_build: out of host memory for the automaton");
+    }
+    static_assert(sizeof(HostState) == sizeof(BulkCorpus::State), "states are copied as they are");
+    HostSam &h = c->host;
+    h.n_states = n_states;
+    h.n_trans = n_trans;
+    h.st.set_size(n_states);
+    if (e == hipSuccess) e = hipDeviceSynchronize();
+    if (e == hipSuccess) e = copy_down(h.slots, c->d_slots, n_slots * sizeof(Slot), c->device);
+    if (e == hipSuccess) e = copy_down(&h.st[0], w.rec, (size_t)n_states * sizeof(HostState), c->device);
+    if (e == hipSuccess) e = hipMemcpy(h.root.data(), c->d_root, (size_t)vocab * sizeof(RootEnt), hipMemcpyDeviceToHost);
+    if (e != hipSuccess) {
+        (void)hipFree(d_pairs);
+        return fail_hip("sam_build: tables", e);
+    }
+    (void)hipFree(work);
+    scratch.all.clear();
+    const int rc = corpus_finish(c, d_pairs);
+    *done = rc == SAM_OK;
+    return rc;
+}
+
 static int build_common(const int32_t *tokens, int64_t n, int32_t vocab, bool upload,
                         sam_corpus **out)
 {
@@ -244,6 +402,21 @@ static int build_common(const int32_t *tokens, int64_t n, int32_t vocab, bool up
     *out = nullptr;
     sam_corpus *c = new (std::nothrow) sam_corpus;
     if (!c) return fail(SAM_ENOMEM, "sam_build: out of host memory");
+    if (upload && tokens && n >= device_build_min() && n <= 0x7FFFFFFELL && vocab >= 1 &&
+        (g_layout_override & 8) == 0) {
+        bool done = false;
+        if (g_progress) g_progress("build", 0, n, g_progress_user);
+        const int rc = corpus_build_device(c, tokens, n, vocab, &done);
+        if (rc != SAM_OK || done) {
+            if (rc != SAM_OK) {
+                corpus_release_device(c);
+                delete c;
+                return rc;
+            }
+            *out = c;
+            return SAM_OK;
+        }
+    }
     std::string err;
     int rc;
     try {
@@ -506,6 +679,7 @@ static BatchBytes batch_configure(BatchView &v, const sam_corpus *corpus, int32_
     v.l_bias = l_bias;
     v.l_threshold = -1;
     v.no_asm = (g_layout_override & 4) ? 1 : 0;
+    v.no_bulk = (g_layout_override & 128) ? 1 : 0;
     int dev = 0, n_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
@@ -811,7 +985,7 @@ int sam_set_progress_callback(sam_progress_fn fn, void *user)
 
 int sam_set_layout_override(int mode)
 {
-    if (mode < 0 || mode > 63) return fail(SAM_EINVAL, "sam_set_layout_override: mode is 0 .. 63");
+    if (mode < 0 || mode > 255) return fail(SAM_EINVAL, "sam_set_layout_override: mode is 0 .. 255");
     g_layout_override = mode;
     return SAM_OK;
 }

@@ -36,11 +36,11 @@ void *huge_alloc(size_t bytes)
 // records) touch every element once and independently; Build-SAM itself is
 // sequential and stays on the calling thread.
 template <class F>
-void parallel_ranges(uint64_t n, F fn)
+void parallel_ranges(uint64_t n, F fn, uint64_t worth = 1u << 20)
 {
     unsigned hw = std::thread::hardware_concurrency();
     unsigned workers = hw < 1 ? 1 : (hw > 16 ? 16 : hw);
-    if (n < (1u << 20)) workers = 1;
+    if (n < worth) workers = 1;
     if (workers == 1) { fn((uint64_t)0, n); return; }
     std::vector<std::thread> pool;
     const uint64_t per = (n + workers - 1) / workers;
@@ -245,6 +245,34 @@ int HostSam::build(const int32_t *tokens, int64_t n, int32_t vocab_, std::string
     for (int32_t t = 0; t < vocab; t++)
         if (root[t].dst) root[t].endpos = endpos[root[t].dst];
     return SAM_OK;
+}
+
+bool HostSam::reserve_for_copy(const int32_t *tokens, int64_t n, int32_t vocab_, uint64_t n_buckets_)
+{
+    n_tokens = n;
+    vocab = vocab_;
+    n_buckets = n_buckets_;
+    const size_t n_slots = (size_t)n_buckets * kBucketSlots, cap = (size_t)2 * n + 2;
+    try {
+        text.resize((size_t)n);
+        root.resize((size_t)vocab);
+    } catch (const std::bad_alloc &) {
+        return false;
+    }
+    free(slots);
+    if (!(slots = (Slot *)huge_alloc(n_slots * sizeof(Slot))) || !st.reserve(cap)) return false;
+    memcpy(text.data(), tokens, (size_t)n * sizeof(int32_t));
+    // about 1.4 states a token: what is beyond stays untouched
+    const size_t piece = 2u << 20, b_slots = n_slots * sizeof(Slot), b_st = (size_t)(1.5 * n) * sizeof(HostState);
+    const size_t of_slots = (b_slots + piece - 1) / piece, of_st = (b_st + piece - 1) / piece;
+    parallel_ranges(of_slots + of_st, [&](uint64_t lo, uint64_t hi) {
+        for (uint64_t i = lo; i < hi; i++) {
+            volatile char *p = i < of_slots ? (volatile char *)slots + i * piece : (volatile char *)&st[0] + (i - of_slots) * piece;
+            const size_t bytes = i < of_slots ? b_slots - i * piece : b_st - (i - of_slots) * piece;
+            for (size_t at = 0; at < (bytes < piece ? bytes : piece); at += 4096) p[at] = 0;
+        }
+    }, 16);
+    return true;
 }
 
 // Algorithm 3 without recursion and without per-state transition lists: a

@@ -76,6 +76,11 @@ struct HostSam {
     int build(const int32_t *tokens, int64_t n, int32_t vocab_, std::string &err,
               ProgressFn progress = nullptr, void *user = nullptr, uint64_t min_buckets = 0);
 
+    // Room for an automaton that is built elsewhere and copied in (see sam_build): text and root
+    // filled, st of 2n + 1 and slots of n_buckets buckets without contents, their pages
+    // touched beforehand by several threads (a first write to a page takes longer than the copy).
+    bool reserve_for_copy(const int32_t *tokens, int64_t n, int32_t vocab_, uint64_t n_buckets_);
+
     // Write the built automaton to a file / read it back (same machine byte
     // order, same library layout version).  The top-k table is not stored.
     int save(const char *path, std::string &err) const;

@@ -137,6 +137,12 @@ struct IngestWide {
         const uint64_t old = ctx.cas(reinterpret_cast<uint64_t *>(reinterpret_cast<Slot *>(slots) + at), ~(uint64_t)0, key);
         return old == ~(uint64_t)0 ? 0 : (old == key ? 1 : 2);
     }
+    // what a plain read says of the slot: 0 empty (or claimed meanwhile), 1 and 2 as above
+    static SAM_HD int peek(const void *slots, uint32_t at, uint32_t p, uint32_t t)
+    {
+        const uint64_t seen = *reinterpret_cast<const uint64_t *>(reinterpret_cast<const Slot *>(slots) + at);
+        return seen == ~(uint64_t)0 ? 0 : (seen == ((uint64_t)p | ((uint64_t)t << 32)) ? 1 : 2);
+    }
     template <class C>
     static SAM_HD void fill(C &ctx, void *rec, void *slots, uint32_t at, uint32_t p, uint32_t, uint32_t dst)
     {
@@ -193,6 +199,11 @@ struct IngestCompact {
         const uint32_t old = ctx.cas(reinterpret_cast<uint32_t *>(slots) + 2 * (size_t)at, kNil, key);
         return old == kNil ? 0 : (old == key ? 1 : 2);
     }
+    static SAM_HD int peek(const void *slots, uint32_t at, uint32_t p, uint32_t t)
+    {
+        const uint32_t seen = reinterpret_cast<const uint32_t *>(slots)[2 * (size_t)at];
+        return seen == kNil ? 0 : (seen == ((p << 17) | t) ? 1 : 2);
+    }
     // the head shares its word with the end position, which does not change
     template <class C>
     static SAM_HD void fill(C &ctx, void *rec, void *slots, uint32_t at, uint32_t p, uint32_t endpos,
@@ -208,6 +219,25 @@ struct IngestCompact {
         return widen(ctx.fresh(reinterpret_cast<uint32_t *>(rec) + 4 * (size_t)s + 1) >> 16);
     }
 };
+
+// The slot of (v, t) in the table: 0 claimed now, 1 it was there, 2 the table is full.  kPeek: slots
+// are read before they are tried.
+template <class L, bool kPeek = false, class C>
+SAM_HD int ingest_claim(C &ctx, void *slots, uint32_t n_buckets, uint32_t v, uint32_t t, uint32_t &at)
+{
+    const uint32_t hsh = dyn_hash(v, t);
+    uint32_t b = ctx.mulhi(hsh, n_buckets);
+    int got = 2;
+    for (uint32_t left = n_buckets; left && got == 2; left--) {
+        for (uint32_t j = 0; j < L::kSlots && got == 2; j++) {
+            at = b * L::kSlots + ((hsh + j) & (L::kSlots - 1));
+            if (kPeek) got = L::peek(slots, at, v, t);
+            if (!kPeek || got == 0) got = L::claim(ctx, slots, at, v, t);
+        }
+        b = b + 1 == n_buckets ? 0 : b + 1;
+    }
+    return got;
+}
 
 // ---- working arrays -------------------------------------------------------------
 //
@@ -420,6 +450,139 @@ inline bool ingest_tables_fit(uint32_t n, size_t rec_bytes, size_t slot_bytes)
 template <class I>
 struct alignas(16) Eight { I v[8]; };
 
+// ---- the tree of a sorted order -------------------------------------------------
+
+// From the common lengths of neighbours in the sorted order to the states' ids: what one index
+// does in each phase.  The phases are in this order, with a barrier between any two.
+template <class I>
+struct IngestTree {
+    static constexpr I kNone = (I)~(I)0, kRoot = (I)(kNone - 1);
+    uint32_t n;
+    const I *sa;             // [n] position in each place of the sorted order
+    const I *lcp;            // [ingest_pad(n)] common length with the place before, zeros behind
+    I *node, *tab, *par, *pfx, *leaf;
+    uint32_t *m, *sec;
+    const I *mins1, *mins;   // minima of 8, and the levels above
+    const uint32_t *level_at;      // where level j >= 2 starts in mins
+    uint32_t tops;           // the highest level
+    uint32_t *bits;
+    const uint32_t *rank;
+
+    // of the run that holds entry `at` of a level: which entries are below l
+    SAM_HD uint32_t run_mask(uint32_t level, uint32_t at, uint32_t l) const
+    {
+        const I *p = level == 0 ? lcp : (level == 1 ? mins1 : mins + level_at[level]);
+        const Eight<I> e = *reinterpret_cast<const Eight<I> *>(p + (at & ~7u));
+        uint32_t mask = 0;
+        for (int j = 0; j < 8; j++) mask |= (e.v[j] < l ? 1u : 0u) << j;
+        return mask;
+    }
+    // the nearest boundary left of k with less than l (there is one: lcp[0] = 0), and right
+    template <class C>
+    SAM_HD uint32_t smaller_left(C &ctx, uint32_t k, uint32_t l) const
+    {
+        uint32_t level = 0, at = k, mask;
+        while (!(mask = run_mask(level, at, l) & ((1u << (at & 7)) - 1u)) && level < tops) { at >>= 3; level++; }
+        at = (at & ~7u) + ctx.log2(mask | 1u);
+        for (; level; level--) {
+            at *= 8;
+            at += ctx.log2(run_mask(level - 1, at, l) | 1u);
+        }
+        return at;
+    }
+    template <class C>
+    SAM_HD uint32_t smaller_right(C &ctx, uint32_t k, uint32_t l) const
+    {
+        uint32_t level = 0, at = k, mask;
+        while (!(mask = run_mask(level, at, l) & (0xFEu << (at & 7)) & 0xFFu) && level < tops) { at >>= 3; level++; }
+        at = (at & ~7u) + ctx.first(mask | 0x80u);
+        for (; level; level--) {
+            at *= 8;
+            at += ctx.first(run_mask(level - 1, at, l) | 0x80u);
+        }
+        return at < n ? at : n;
+    }
+    SAM_HD uint32_t at_or_zero(uint32_t k) const { return k < n ? lcp[k] : 0u; }
+
+    // Interval of boundary k: from lb to rb, the nearest boundaries with a smaller value.
+    // Of the intervals that share lb only the widest has lcp[lb] >= lcp[rb], of those that
+    // share rb only the widest of the others: one index each, in tab[].
+    template <class C>
+    SAM_HD void interval(C &ctx, uint32_t k) const
+    {
+        const uint32_t l = lcp[k];
+        if (l == 0) { node[k] = kNone; return; }
+        const uint32_t lb = smaller_left(ctx, k, l), rb = smaller_right(ctx, k, l);
+        const bool left = lcp[lb] >= at_or_zero(rb);
+        const uint32_t id = left ? lb : n + rb;
+        tab[id] = (I)k;                                // any boundary of the interval will do
+        node[k] = (I)id;
+        par[k] = (I)(left ? lb : rb);
+    }
+    SAM_HD void represent(uint32_t k) const { if (lcp[k]) node[k] = tab[node[k]]; }
+    SAM_HD void parent(uint32_t k) const
+    {
+        const bool rep = lcp[k] && node[k] == (I)k;
+        par[k] = !rep ? kNone : (lcp[par[k]] == 0 ? kRoot : node[par[k]]);
+        pfx[k] = kNone;
+        m[k] = kNil;
+        sec[k] = kNil;
+    }
+    SAM_HD void leaf_of(uint32_t k) const
+    {
+        const uint32_t i = sa[k], lk = lcp[k], rk = at_or_zero(k + 1), l = lk > rk ? lk : rk;
+        I v = kRoot;
+        if (l) {
+            v = node[lk >= rk ? k : k + 1];
+            // the prefix is as long as what it shares with a neighbour: it is that node
+            if (l == i + 1) { pfx[v] = (I)i; v = par[v]; }
+        }
+        leaf[i] = v;
+    }
+    // first end positions: every prefix goes up until a smaller one has been there.  False: more
+    // nodes than there are (kGuard).  kPeek: what others wrote before is read first (it only falls).
+    template <bool kGuard, bool kPeek = false, class C>
+    SAM_HD bool first_end(C &ctx, uint32_t i) const
+    {
+        uint32_t left = n + 1;
+        for (I v = leaf[i]; v != kRoot && pfx[v] == kNone; v = par[v]) {
+            if (kPeek && m[v] < i) break;
+            if (ctx.lower(&m[v], i) < i) break;
+            if (kGuard && !--left) return false;
+        }
+        return true;
+    }
+    // and the second: of the first ones of a node's children
+    template <bool kPeek = false, class C>
+    SAM_HD void second_end(C &ctx, uint32_t i) const
+    {
+        const I v = leaf[i];
+        if (v != kRoot && pfx[v] == kNone && m[v] != i && !(kPeek && sec[v] < i)) ctx.lower(&sec[v], i);
+        const I p = par[i];
+        if (p != kNone && pfx[i] == kNone && p != kRoot && pfx[p] == kNone && m[p] != m[i] &&
+            !(kPeek && sec[p] < m[i]))
+            ctx.lower(&sec[p], m[i]);
+    }
+    SAM_HD bool cloned(uint32_t k) const { return par[k] != kNone && pfx[k] == kNone; }
+    template <class C>
+    SAM_HD void mark_clone(C &ctx, uint32_t k) const
+    {
+        if (cloned(k)) ctx.bit_or(&bits[sec[k] >> 5], 1u << (sec[k] & 31));
+    }
+    // ids, once rank[] has the running sum over bits[]
+    template <class C>
+    SAM_HD uint32_t prefix_id(C &ctx, uint32_t i) const
+    {
+        return 1 + i + rank[i >> 5] + ctx.popc(bits[i >> 5] & ((1u << (i & 31)) - 1u));
+    }
+    template <class C>
+    SAM_HD uint32_t node_id(C &ctx, I v) const
+    {
+        if (v == kRoot) return 0;
+        return pfx[v] != kNone ? prefix_id(ctx, pfx[v]) : prefix_id(ctx, sec[v]) + 1;
+    }
+};
+
 // ---- the build --------------------------------------------------------------------
 
 SAM_HD uint32_t ingest_hash(uint32_t k)
@@ -440,7 +603,6 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
     constexpr K kEmpty = (K)~(K)0;
     constexpr uint32_t kHalf = sizeof(K) * 4;
     constexpr I kAlone = (I)((I)1 << (sizeof(I) * 8 - 1));
-    constexpr I kNone = (I)~(I)0, kRoot = (I)(kNone - 1);
     constexpr K kLow = (K)(((K)1 << kHalf) - 1);
     uint32_t *const small = A.small;
     uint32_t *const active = small;                  // [32] one flag per round
@@ -671,92 +833,21 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
             tops++;
         }
     }
-    // of the run that holds entry `at` of a level: which entries are below l
-    auto run_mask = [&](uint32_t level, uint32_t at, uint32_t l) -> uint32_t {
-        const I *p = level == 0 ? A.lcp : (level == 1 ? A.mins1 : A.mins + level_at[level]);
-        const Eight<I> e = *reinterpret_cast<const Eight<I> *>(p + (at & ~7u));
-        uint32_t mask = 0;
-        for (int j = 0; j < 8; j++) mask |= (e.v[j] < l ? 1u : 0u) << j;
-        return mask;
-    };
-    // the nearest boundary left of k with less than l (there is one: lcp[0] = 0), and right
-    auto smaller_left = [&](uint32_t k, uint32_t l) -> uint32_t {
-        uint32_t level = 0, at = k, mask;
-        while (!(mask = run_mask(level, at, l) & ((1u << (at & 7)) - 1u)) && level < tops) { at >>= 3; level++; }
-        at = (at & ~7u) + ctx.log2(mask | 1u);
-        for (; level; level--) {
-            at *= 8;
-            at += ctx.log2(run_mask(level - 1, at, l) | 1u);
-        }
-        return at;
-    };
-    auto smaller_right = [&](uint32_t k, uint32_t l) -> uint32_t {
-        uint32_t level = 0, at = k, mask;
-        while (!(mask = run_mask(level, at, l) & (0xFEu << (at & 7)) & 0xFFu) && level < tops) { at >>= 3; level++; }
-        at = (at & ~7u) + ctx.first(mask | 0x80u);
-        for (; level; level--) {
-            at *= 8;
-            at += ctx.first(run_mask(level - 1, at, l) | 0x80u);
-        }
-        return at < n ? at : n;
-    };
-
-    // Interval of boundary k: from lb to rb, the nearest boundaries with a smaller value.
-    // Of the intervals that share lb only the widest has lcp[lb] >= lcp[rb], of those that
-    // share rb only the widest of the others: one index each, in tab[].
-    auto at_or_zero = [&](uint32_t k) -> uint32_t { return k < n ? A.lcp[k] : 0u; };
-    ctx.each(n, [&](uint32_t k) {
-        const uint32_t l = A.lcp[k];
-        if (l == 0) { A.node[k] = kNone; return; }
-        const uint32_t lb = smaller_left(k, l), rb = smaller_right(k, l);
-        const bool left = A.lcp[lb] >= at_or_zero(rb);
-        const uint32_t id = left ? lb : n + rb;
-        A.tab[id] = (I)k;                              // any boundary of the interval will do
-        A.node[k] = (I)id;
-        A.par[k] = (I)(left ? lb : rb);
-    });
+    const IngestTree<I> tree{n, A.sa, A.lcp, A.node, A.tab, A.par, A.pfx, A.leaf, A.m, A.sec, A.mins1, A.mins,
+                             level_at, tops, A.bits, A.rank};
+    ctx.each(n, [&](uint32_t k) { tree.interval(ctx, k); });
     ctx.sync();
-    ctx.each(n, [&](uint32_t k) { if (A.lcp[k]) A.node[k] = A.tab[A.node[k]]; });
+    ctx.each(n, [&](uint32_t k) { tree.represent(k); });
     ctx.sync();
-    ctx.each(n, [&](uint32_t k) {
-        const bool rep = A.lcp[k] && A.node[k] == (I)k;
-        A.par[k] = !rep ? kNone : (A.lcp[A.par[k]] == 0 ? kRoot : A.node[A.par[k]]);
-        A.pfx[k] = kNone;
-        A.m[k] = kNil;
-        A.sec[k] = kNil;
-    });
+    ctx.each(n, [&](uint32_t k) { tree.parent(k); });
     ctx.sync();
-    ctx.each(n, [&](uint32_t k) {
-        const uint32_t i = A.sa[k], lk = A.lcp[k], rk = at_or_zero(k + 1), l = lk > rk ? lk : rk;
-        I v = kRoot;
-        if (l) {
-            v = A.node[lk >= rk ? k : k + 1];
-            // the prefix is as long as what it shares with a neighbour: it is that node
-            if (l == i + 1) { A.pfx[v] = (I)i; v = A.par[v]; }
-        }
-        A.leaf[i] = v;
-    });
+    ctx.each(n, [&](uint32_t k) { tree.leaf_of(k); });
     ctx.sync();
-    // first end positions: every prefix goes up until a smaller one has been there
-    ctx.each(n, [&](uint32_t i) {
-        uint32_t left = n + 1;
-        for (I v = A.leaf[i]; v != kRoot && A.pfx[v] == kNone; v = A.par[v]) {
-            if (ctx.lower(&A.m[v], i) < i) break;
-            if (!kLds && !--left) { corrupt(); break; }
-        }
-    });
+    ctx.each(n, [&](uint32_t i) { if (!tree.template first_end<!kLds>(ctx, i)) corrupt(); });
     ctx.sync();
-    ctx.each(n, [&](uint32_t i) {
-        const I v = A.leaf[i];
-        if (v != kRoot && A.pfx[v] == kNone && A.m[v] != i) ctx.lower(&A.sec[v], i);
-        const I p = A.par[i];
-        if (p != kNone && A.pfx[i] == kNone && p != kRoot && A.pfx[p] == kNone && A.m[p] != A.m[i])
-            ctx.lower(&A.sec[p], A.m[i]);
-    });
+    ctx.each(n, [&](uint32_t i) { tree.second_end(ctx, i); });
     ctx.sync();
-    ctx.each(n, [&](uint32_t k) {
-        if (A.par[k] != kNone && A.pfx[k] == kNone) ctx.bit_or(&A.bits[A.sec[k] >> 5], 1u << (A.sec[k] & 31));
-    });
+    ctx.each(n, [&](uint32_t k) { tree.mark_clone(ctx, k); });
     ctx.sync();
     // ids
     uint32_t *const part = small + 64;               // [60]: sums of runs of words
@@ -782,13 +873,8 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
         if (c == kParts - 1) small[124] = 1 + n + sum;
     });
     ctx.sync();
-    auto prefix_id = [&](uint32_t i) -> uint32_t {
-        return 1 + i + A.rank[i >> 5] + ctx.popc(A.bits[i >> 5] & ((1u << (i & 31)) - 1u));
-    };
-    auto node_id = [&](I v) -> uint32_t {
-        if (v == kRoot) return 0;
-        return A.pfx[v] != kNone ? prefix_id(A.pfx[v]) : prefix_id(A.sec[v]) + 1;
-    };
+    auto prefix_id = [&](uint32_t i) -> uint32_t { return tree.prefix_id(ctx, i); };
+    auto node_id = [&](I v) -> uint32_t { return tree.node_id(ctx, v); };
     // records, with the transition of the first occurrence inline
     ctx.each(n, [&](uint32_t i) {
         const uint32_t id = prefix_id(i);
@@ -796,7 +882,7 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
         const bool more = i + 1 < n;
         L::store(q.rec, id, i + 1, node_id(A.leaf[i]), i + 1, more ? (uint32_t)q.tok[i + 1] : kNil,
                  more ? prefix_id(i + 1) : 0u);
-        if (A.par[i] != kNone && A.pfx[i] == kNone)
+        if (tree.cloned(i))
             L::store(q.rec, prefix_id(A.sec[i]) + 1, A.lcp[i], node_id(A.par[i]), A.m[i] + 1,
                      (uint32_t)q.tok[A.m[i] + 1], 0u);
     });
@@ -868,16 +954,7 @@ SAM_HD void ingest_build(C &ctx, const IngestSeq &q, const IngestArrays<I, K> &A
         }
     };
     auto claim = [&](uint32_t v, uint32_t t, uint32_t &at) -> int {
-        const uint32_t hsh = dyn_hash(v, t);
-        uint32_t b = ctx.mulhi(hsh, q.n_buckets);
-        int got = 2;
-        for (uint32_t left = q.n_buckets; left && got == 2; left--) {
-            for (uint32_t j = 0; j < L::kSlots && got == 2; j++) {
-                at = b * L::kSlots + ((hsh + j) & (L::kSlots - 1));
-                got = L::claim(ctx, q.slots, at, v, t);
-            }
-            b = b + 1 == q.n_buckets ? 0 : b + 1;
-        }
+        const int got = ingest_claim<L>(ctx, q.slots, q.n_buckets, v, t, at);
         if (got == 2) corrupt();
         return got;
     };

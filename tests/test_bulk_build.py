@@ -1,0 +1,155 @@
+"""Automata built by the whole chip, phase by phase: corpora against the host builder, prompts too
+long for LDS against the CPU checker (their sizes: test_prompt_gpu.py), everything bit-exact."""
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+from test_sanitizers import FLAGS, ROOT, _have_sanitizer_runtime
+
+
+def test_phases_under_asan_ubsan(tmp_path):
+    """The phases, one after the other on the CPU, over regions of exactly the library's sizes."""
+    if not (shutil.which("gcc") and shutil.which("g++")):
+        pytest.skip("gcc / g++ not available")
+    if not _have_sanitizer_runtime(tmp_path):
+        pytest.skip("the sanitizer runtime (libasan / libubsan) is not installed")
+    exe = tmp_path / "bulk_build_driver"
+    subprocess.check_call(["g++", "-std=c++17", "-pthread"] + FLAGS + [
+        os.path.join(ROOT, "tests", "bulk_build_driver.cpp"),
+        os.path.join(ROOT, "paper_2411_10666_amd", "csrc", "sam_host.cpp"), "-o", str(exe)])
+    env = dict(os.environ, ASAN_OPTIONS="verify_asan_link_order=0")
+    p = subprocess.run([str(exe)], capture_output=True, text=True, env=env, timeout=600)
+    assert p.returncode == 0, p.stdout[-2000:] + p.stderr[-4000:]
+    assert p.stdout.strip().endswith("ok")
+
+
+def _text(kind, n, vocab, rng):
+    x = (rng.random(n) ** 3 * vocab).astype(np.int32)
+    if kind == "copies":
+        x[n // 2:] = x[:n - n // 2]
+        x[n * 3 // 4:] = x[n // 8:n // 8 + n - n * 3 // 4]
+    elif kind == "one token":
+        x[:] = vocab - 1
+        x[-1] = 0
+    elif kind == "period":
+        x = np.resize(x[:7], n).astype(np.int32)
+    return x
+
+
+def _saved(corpus, path, n, vocab):
+    """The bytes of the saved file, its root table and its transitions in order."""
+    from paper_2411_10666_amd import binding as sam
+    sam.sam_corpus_save(corpus, path)
+    raw = open(path, "rb").read()
+    at = 64 + 4 * n + 12 * sam.sam_corpus_info(corpus)[0]
+    slots = np.frombuffer(raw[at + 8 * vocab:], dtype=np.uint32).reshape(-1, 4)
+    used = slots[slots[:, 0] != 0xFFFFFFFF]
+    return raw, raw[at:at + 8 * vocab], used[np.lexsort((used[:, 1], used[:, 0]))]
+
+
+# around a wave, a workgroup's tile (2048), the largest group that is counted (1024: two tokens or one),
+# two runs of tiles, the fifth level of minima (32 768) and the size from which sam_build does it by itself
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [1, 2, 3, 9, 64, 65, 1025, 2047, 2048, 2049, 9999, 10000, 33000, 530_000])
+@pytest.mark.parametrize("kind,vocab", [("zipf", 32000), ("zipf", 2), ("copies", 200_000), ("one token", 3),
+                                        ("period", 60)])
+def test_corpus_like_the_host_builders(tmp_path, n, kind, vocab):
+    import torch
+    from paper_2411_10666_amd import binding as sam
+    if n > 100_000 and kind == "one token":
+        n = 100_000
+    x = _text(kind, n, vocab, np.random.default_rng(n))
+    host = sam.sam_build_host_only(x, vocab)
+    try:
+        sam.sam_set_layout_override(64)
+        built = [sam.sam_build(x, vocab) for _ in range(2)]
+    finally:
+        sam.sam_set_layout_override(0)
+    torch.cuda.synchronize()
+    assert sam.sam_corpus_info(built[0])[:2] == sam.sam_corpus_info(host)[:2]
+    for a, b in zip(sam.sam_corpus_export(built[0]), sam.sam_corpus_export(host)):
+        assert np.array_equal(a, b)
+    raw, root, slots = _saved(built[0], str(tmp_path / "a.sam"), n, vocab)
+    again = _saved(built[1], str(tmp_path / "b.sam"), n, vocab)[0]
+    _, host_root, host_slots = _saved(host, str(tmp_path / "c.sam"), n, vocab)
+    assert raw == again                                  # the same file every time
+    assert root == host_root and np.array_equal(slots, host_slots)
+    loaded = sam.sam_corpus_load_host_only(str(tmp_path / "a.sam"))
+    assert sam.sam_corpus_info(loaded)[:2] == sam.sam_corpus_info(host)[:2]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("vocab,n", [(5, 900), (400, 12_000)])
+def test_steps_over_a_corpus_built_on_the_device(vocab, n):
+    from parity_util import assert_same, run_gpu, run_oracle
+    from paper_2411_10666_amd import binding as sam
+    rng = np.random.default_rng(n)
+    x = _text("copies", n, vocab, rng)
+    prompts = [x[k:k + 70].copy() for k in (0, n // 3, n - 70)]
+    acc = rng.integers(0, vocab, size=(6, 3, 8)).astype(np.int32)
+    acc[:, 0] = np.resize(x[100:], (6, 8))
+    cnt = np.full((6, 3), 8, dtype=np.int32)
+    try:
+        sam.sam_set_layout_override(64)
+        corpus = sam.sam_build(x, vocab)
+    finally:
+        sam.sam_set_layout_override(0)
+    g, status, _ = run_gpu(x, vocab, prompts, acc, cnt, 200, 8, 10, gpu_corpus=corpus)
+    r, _ = run_oracle(x, prompts, acc, cnt, 8, 10)
+    assert status == 0
+    assert_same(g, r)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("bad", [-1, 50, 2**31 - 1])
+def test_corpus_token_outside_the_vocabulary(bad):
+    from paper_2411_10666_amd import binding as sam
+    x = np.zeros(30_000, dtype=np.int32)
+    x[[12_345, 20_000]] = bad
+    said = []
+    for build in (sam.sam_build, sam.sam_build_host_only):
+        with pytest.raises(sam.SamError) as e:
+            build(x, 50)
+        assert e.value.code == sam.SAM_ETOKEN
+        said.append(str(e.value))
+    assert said[0] == said[1] and "12345" in said[0]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("T,vocab", [(16_366, 300), (30_000, 300)])
+def test_long_prompts_cut_at_a_bad_token(T, vocab):
+    """Whole-chip builds, one workgroup each (testing mode) and prompts that end in front of the bad token
+    leave the same sequences."""
+    import torch
+    from paper_2411_10666_amd import binding as sam
+    rng = np.random.default_rng(T)
+    n = T - 3                                            # the most that the 16-bit tables have room for
+    prompts = [_text("copies", k, vocab, rng) for k in (n, n - 1, 7000, 6200, 9000, 300)]
+    cut = [n, 8000, 0, 1, 6500, 300]
+    whole = [np.concatenate([p[:c], [vocab + 5], p[c + 1:]]).astype(np.int32) if c < len(p) else p
+             for p, c in zip(prompts, cut)]
+    short = [p[:c] for p, c in zip(prompts, cut)]
+    dev, seen = torch.device("cuda"), []
+    for mode, ps in ((0, whole), (128, whole), (0, short)):
+        B = len(ps)
+        offs = torch.from_numpy(np.concatenate([[0], np.cumsum([len(p) for p in ps])])).to(dev)
+        flat = torch.from_numpy(np.concatenate(ps)).to(dev)
+        slots = torch.arange(B, dtype=torch.int32, device=dev)
+        try:
+            sam.sam_set_layout_override(mode)
+            batch = sam.sam_batch_init(None, flat, torch.zeros_like(offs), B, vocab, T, 2, 4, 0)
+        finally:
+            sam.sam_set_layout_override(0)
+        sam.sam_batch_reset(batch, slots, flat, offs)
+        out = [torch.zeros(B, dtype=torch.int32, device=dev) for _ in range(10)]
+        draft = torch.zeros(B, 4, dtype=torch.int32, device=dev)
+        row = torch.full((B, 2), 7, dtype=torch.int32, device=dev)
+        sam.sam_batch_step(batch, row, torch.full_like(slots, 2), out[0], draft, out[1], out[2])
+        sam.sam_batch_debug(batch, *out[3:7])
+        sam.sam_batch_sizes(batch, *out[7:])
+        assert sam.sam_batch_status(batch) == (sam.SAM_STATUS_TOKEN if ps is whole else 0)
+        seen.append(torch.cat([torch.stack(out[:3] + out[5:]).flatten(), draft.flatten()]).cpu())
+    assert torch.equal(seen[0], seen[1]) and torch.equal(seen[0], seen[2])
