@@ -5,6 +5,7 @@
 
 #include <type_traits>
 
+#include "sam_bulk_launch.h"
 #include "sam_ingest.h"
 #include "sam_prompt.h"
 #include "sam_walk.h"
@@ -208,7 +209,8 @@ __global__ __launch_bounds__(T) void sam_prompt_kernel(StaticView S, BatchView B
                                                           int n_seqs, int n_static,
                                                           const int32_t *__restrict__ tokens,
                                                           const int64_t *__restrict__ offsets,
-                                                          uint32_t lds_tokens, uint32_t max_tokens)
+                                                          uint32_t lds_tokens, uint32_t max_tokens,
+                                                          uint32_t bulk_tokens)
 {
     extern __shared__ __align__(16) char lds[];
     __shared__ uint32_t bad, wsum[T / 64];
@@ -230,10 +232,13 @@ __global__ __launch_bounds__(T) void sam_prompt_kernel(StaticView S, BatchView B
         }
         return;
     }
+    const bool bulk = bulk_tokens && bulk_takes(B, count, lds_tokens, bulk_tokens);
+    if (!walks && bulk) return;
     uint32_t n = (uint32_t)count;
     if (walks) {
         uint32_t first = n;
-        for (uint32_t base = 0; base < n && first == n; base += 256) {
+        if (bulk) first = uni(meta->n);                  // found by then, by a whole workgroup
+        else for (uint32_t base = 0; base < n && first == n; base += 256) {
             uint32_t at = n;
 #pragma unroll
             for (int u = 3; u >= 0; u--) {
@@ -354,13 +359,21 @@ hipError_t launch_ingest(const StaticView &S, const BatchView &B, const int32_t 
             bytes = ingest_lds_bytes(lds_tokens);
         }
     }
+    // Prompts beyond LDS are built by the whole chip, phase by phase, wherever their tables have room for
+    // that: one workgroup each is bound by the scattered accesses of its compute unit even where there
+    // are more of them than units (sam_batch_reset, chip / workgroups, us: 1 prompt of 6500 tokens 0.45 /
+    // 1.1 ms, 1 of 40 001 0.9 / 7.6, 12 of 40 001 1.2 / 8.1, 64 of 40 001 4.0 / 10.6, 256 of 6500 1.9 / 2.2, 600 of
+    // 8000 4.2 / 5.8).  Of one token only, 3 of 16 000 tokens take 1.9 ms against 1.7; 3 of 40 001 4.5 against 5.0.
+    const bool bulk = max_tokens > lds_tokens && lds_tokens >= kBulkLdsTokens && !B.no_bulk;
+    if (bulk && (e = launch_bulk_prompts(B, seq_map, n_seqs, tokens, offsets, lds_tokens, max_tokens, true, stream)) != hipSuccess)
+        return e;
     // workgroups for the corpus: a wave each sequence, a multiple of 8 workgroups
     auto walks = [&](int waves) { return B.has_static ? (((n_seqs + waves - 1) / waves + 7) & ~7) : 0; };
     const int threads = short_prompts(sizes, walks(16), n_cu) ? 256 : 1024, n_static = walks(threads / 64);
 #define SAM_LAUNCH_PROMPT_T(COMPACT, ASM, T)                                                     \
     hipLaunchKernelGGL((sam_prompt_kernel<COMPACT, ASM, T>), dim3(n_static + n_seqs), dim3(T),    \
                        bytes, stream, S, B, seq_map, n_seqs, n_static, tokens, offsets,          \
-                       lds_tokens, max_tokens)
+                       lds_tokens, max_tokens, bulk ? max_tokens : 0u)
 #define SAM_LAUNCH_PROMPT(COMPACT, ASM)                                                          \
     do {                                                                                        \
         if (threads == 256) SAM_LAUNCH_PROMPT_T(COMPACT, ASM, 256);                              \
@@ -374,7 +387,8 @@ hipError_t launch_ingest(const StaticView &S, const BatchView &B, const int32_t 
     }
 #undef SAM_LAUNCH_PROMPT
 #undef SAM_LAUNCH_PROMPT_T
-    return hipGetLastError();
+    if ((e = hipGetLastError()) != hipSuccess || !bulk) return e;
+    return launch_bulk_prompts(B, seq_map, n_seqs, tokens, offsets, lds_tokens, max_tokens, false, stream);
 }
 
 }  // namespace sam
