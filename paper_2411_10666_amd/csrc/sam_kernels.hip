@@ -45,6 +45,7 @@ struct Rec {              // a state record held in wave-uniform registers
 
 // 32-byte records, 16-byte slots, 8 slots per bucket: any length, any vocabulary
 struct WideDyn {
+    static constexpr bool kAsm = true;
     static constexpr int kSlots = 8;
     struct RawRec { uint4 a; uint2 b; };
     typedef uint4 RawSlot;
@@ -110,8 +111,14 @@ struct WideDyn {
     }
 };
 
+// the same, record tables of 4 GiB and more: byte offsets beyond 32 bits, so no assembly
+struct HugeDyn : WideDyn {
+    static constexpr bool kAsm = false;
+};
+
 // 16-byte records, 8-byte slots, 16 slots per bucket: 15-bit state ids
 struct CompactDyn {
+    static constexpr bool kAsm = true;
     static constexpr int kSlots = 16;
     typedef uint4 RawRec;
     typedef uint2 RawSlot;
@@ -440,7 +447,7 @@ __device__ __forceinline__ void flush_last(const DynSeq &D, const DynCursor<L> &
 // hand: one wavefront's dependent instruction chain is what a token costs, and
 // this form needs about half the instructions of the compiled one (records stay
 // packed as stored, no copies between paths, stores under a one-lane exec mask
-// without a branch).  The wide layout takes the C++ path; the kernels are
+// without a branch).  The kernels are
 // instantiated with one form or the other, never both, because the mere presence
 // of the C++ loop costs the assembly one 2 % (registers, code size).  Every table access goes through a buffer resource whose size is
 // the table's, so an index outside a table reads zeros or is dropped instead of
@@ -945,6 +952,446 @@ __device__ __forceinline__ void dyn_feed_compact(u32x4 rrec, u32x4 rslt, uint32_
 #undef SAM_NEXT_BUCKET
 #undef SAM_GUARD
 
+// ---- wide layout: the same in gfx950 assembly ---------------------------------
+//
+// 32-byte records and 16-byte slots, so a record is six scalar registers and a slot four words.
+// Eight lanes work: a record is one load of a word each (and one store, its words put into their
+// lanes), a bucket one load of a slot each.  Byte offsets have 32 bits, so it serves sequences
+// whose record table is smaller than 4 GiB.  What bounds it is what bounds the compact form: the
+// wave's chain of dependent instructions and round trips.  12 sequences of 40 000 tokens, rows of
+// up to 16: 25 us a round with the compiled loop, 16.4 with this.
+//   s64 t        s65 next token (-1: none)   s66 t * c2
+//   s67 state of a requested, not yet reduced bucket (-1: none)   s68 q   s69..s71 scratch
+//   s72 probe bucket (-1: no probe held)   s73 probe hit mask   s74 probe empty mask
+//   s75 bucket of (q, next token)   s76..s79 s62 s63 record of q {len, link, endpos, head, itok, idst}
+//   s80 s81 P and length before this token   s82 cur   s83 where the transition to q sits
+//   (slot index, -2: inline)   s84 slot index   s86 loop guard   s87 last before this token
+//   s88 clone   s89..s92 s60 s61 its record   s93 list cursor   s94 token of a copied slot
+//   s95 its target   s98 scratch (slot bit, address)   s99 the next state up the path
+//   v40 v41 addresses   v42:45 probe bucket   v56:59 next token's bucket   v46 record load, one
+//   word a lane   v47 record to be stored   v50:53 slot to be stored   v54 single words   s96:97 exec
+#define SAM_HASH(dst, state, tokmul)                                                  \
+        "s_mul_i32 s69, " state ", 0x9e3779b1\n\t"                                    \
+        "s_xor_b32 s69, s69, " tokmul "\n\t"                                          \
+        "s_lshr_b32 s70, s69, 15\n\t"                                                 \
+        "s_xor_b32 s69, s69, s70\n\t"                                                 \
+        "s_mul_i32 s69, s69, 0x2c1b3c6d\n\t"                                          \
+        "s_mul_hi_u32 " dst ", s69, %[nb]\n\t"
+#define SAM_LOAD_BUCKET(vdst, bucket)                                                 \
+        "s_lshl_b32 s69, " bucket ", 7\n\t"                                           \
+        "v_add_u32 v41, s69, %[lo16]\n\t"                                             \
+        "buffer_load_dwordx4 " vdst ", v41, %[rslt], 0 offen\n\t"
+#define SAM_LOAD_REC(state)                                                           \
+        "s_lshl_b32 s70, " state ", 5\n\t"                                            \
+        "v_add_u32 v40, s70, %[lo4]\n\t"                                              \
+        "buffer_load_dword v46, v40, %[rrec], 0 offen\n\t"
+#define SAM_READ_REC(len, link, endpos, head, itok, idst)                             \
+        "v_readlane_b32 " len ", v46, 0\n\t"                                          \
+        "v_readlane_b32 " link ", v46, 1\n\t"                                         \
+        "v_readlane_b32 " endpos ", v46, 2\n\t"                                       \
+        "v_readlane_b32 " head ", v46, 3\n\t"                                         \
+        "v_readlane_b32 " itok ", v46, 4\n\t"                                         \
+        "v_readlane_b32 " idst ", v46, 5\n\t"
+// masks of a bucket in vs (state), vt (token): s73 slots of (state, token), s74 empty ones
+#define SAM_REDUCE(state, token, vs, vt)                                              \
+        "v_cmp_eq_u32 vcc, " state ", " vs "\n\t"                                     \
+        "v_cmp_eq_u32 s[70:71], " token ", " vt "\n\t"                                \
+        "s_and_b32 s73, vcc_lo, s70\n\t"                                              \
+        "v_cmp_eq_u32 vcc, -1, " vs "\n\t"                                            \
+        "s_mov_b32 s74, vcc_lo\n\t"
+#define SAM_NEXT_BUCKET(bucket)                                                       \
+        "s_add_u32 " bucket ", " bucket ", 1\n\t"                                     \
+        "s_cmp_eq_u32 " bucket ", %[nb]\n\t"                                          \
+        "s_cselect_b32 " bucket ", 0, " bucket "\n\t"
+#define SAM_GUARD(label)                                                              \
+        "s_sub_u32 s86, s86, 1\n\t"                                                   \
+        "s_cbranch_scc1 " label "\n\t"
+// a record of six words -> table (six lanes)
+#define SAM_STORE_REC(state, len, link, endpos, head, itok, idst)                     \
+        "s_lshl_b32 s69, " state ", 5\n\t"                                            \
+        "v_add_u32 v40, s69, %[lo4]\n\t"                                              \
+        "v_writelane_b32 v47, " len ", 0\n\t"                                         \
+        "v_writelane_b32 v47, " link ", 1\n\t"                                        \
+        "v_writelane_b32 v47, " endpos ", 2\n\t"                                      \
+        "v_writelane_b32 v47, " head ", 3\n\t"                                        \
+        "v_writelane_b32 v47, " itok ", 4\n\t"                                        \
+        "v_writelane_b32 v47, " idst ", 5\n\t"                                        \
+        "s_mov_b64 exec, 0x3f\n\t"                                                    \
+        "buffer_store_dword v47, v40, %[rrec], 0 offen\n\t"                           \
+        "s_mov_b64 exec, 0xff\n\t"
+// last's record {n, P, n, none, t, cur}
+#define SAM_STORE_LAST SAM_STORE_REC("s87", "s81", "s80", "s81", "-1", "s64", "s82")
+
+__device__ __forceinline__ void dyn_feed_wide(u32x4 rrec, u32x4 rslt, uint32_t nb, uint32_t m,
+                                              uint32_t vocab, uint32_t tv, uint32_t lo4, uint32_t lo16,
+                                              uint32_t &i, uint32_t &n, uint32_t &ns, uint32_t &last,
+                                              uint32_t &nt, uint32_t &P, Rec &R, uint32_t &flt)
+{
+    uint32_t r0 = uni(R.len), r1 = uni(R.link), r2 = uni(R.endpos), r3 = uni(R.head), r4 = uni(R.itok),
+             r5 = uni(R.idst);
+    asm volatile(
+        "s_mov_b64 s[96:97], exec\n\t"
+        "s_mov_b64 exec, 0xff\n\t"
+        "s_mov_b32 s67, -1\n\t"
+        "s_mov_b32 s72, -1\n"
+        // ---- one token ---------------------------------------------------------
+        "L_token_%=:\n\t"
+        "v_readlane_b32 s64, %[tv], %[i]\n\t"
+        "s_add_u32 s69, %[i], 1\n\t"
+        "s_mov_b32 s65, -1\n\t"
+        "s_cmp_ge_u32 s64, %[vocab]\n\t"
+        "s_cbranch_scc1 L_exit_%=\n\t"
+        "s_mul_i32 s66, s64, 0x85ebca77\n\t"
+        "s_cmp_lt_u32 s69, %[m]\n\t"
+        "s_cbranch_scc0 L_notn_%=\n\t"
+        "v_readlane_b32 s65, %[tv], s69\n\t"
+        "s_cmp_lt_u32 s65, %[vocab]\n\t"
+        "s_cselect_b32 s65, s65, -1\n"
+        "L_notn_%=:\n\t"
+        "s_mov_b32 s82, %[ns]\n\t"
+        "s_mov_b32 s80, %[P]\n\t"
+        "s_mov_b32 s81, %[n]\n\t"
+        "s_add_u32 %[ns], %[ns], 1\n\t"
+        "s_add_u32 %[nt], %[nt], 1\n\t"
+        "s_add_u32 %[n], %[n], 1\n\t"
+        "s_mov_b32 s87, %[last]\n\t"
+        "s_mov_b32 %[last], s82\n\t"
+        "s_add_u32 s86, %[ns], 4\n\t"
+        "s_add_u32 s86, s86, %[nb]\n\t"
+        "s_cmp_eq_u32 %[P], -1\n\t"
+        "s_cbranch_scc0 L_walk_%=\n\t"
+        // the sequence's very first token
+        "s_mov_b32 %[P], 0\n\t"
+        "s_mov_b32 %[r0], 0\n\t"
+        "s_mov_b32 %[r1], -1\n\t"
+        "s_mov_b32 %[r2], 0\n\t"
+        "s_mov_b32 %[r3], -1\n\t"
+        "s_mov_b32 %[r4], s64\n\t"
+        "s_mov_b32 %[r5], s82\n\t"
+        "s_branch L_atroot_%=\n"
+        // ---- walk last's suffix path ---------------------------------------------
+        "L_walk_%=:\n\t"
+        SAM_GUARD("L_corrupt_%=")
+        "s_cmp_eq_u32 %[r4], s64\n\t"
+        "s_cbranch_scc1 L_inline_%=\n\t"
+        "s_cmp_eq_u32 s72, -1\n\t"
+        "s_cbranch_scc1 L_probe_%=\n\t"
+        "s_cmp_eq_u32 s67, -1\n\t"
+        "s_cbranch_scc1 L_resolve_%=\n\t"
+        // the bucket was requested at the end of the last token and not looked at yet
+        "s_waitcnt vmcnt(0)\n\t"
+        "v_mov_b32 v44, v58\n\t"
+        SAM_REDUCE("s67", "s64", "v56", "v57")
+        "s_mov_b32 s67, -1\n\t"
+        "s_branch L_resolve_%=\n"
+        "L_probe_%=:\n\t"
+        SAM_HASH("s72", "%[P]", "s66")
+        SAM_LOAD_BUCKET("v[42:45]", "s72")
+        "s_waitcnt vmcnt(0)\n\t"
+        SAM_REDUCE("%[P]", "s64", "v42", "v43")
+        "L_resolve_%=:\n\t"
+        "s_cmp_lg_u32 s73, 0\n\t"
+        "s_cbranch_scc1 L_hit_%=\n\t"
+        "s_cmp_lg_u32 s74, 0\n\t"
+        "s_cbranch_scc1 L_miss_%=\n\t"
+        SAM_GUARD("L_corrupt_%=")
+        SAM_NEXT_BUCKET("s72")
+        SAM_LOAD_BUCKET("v[42:45]", "s72")
+        "s_waitcnt vmcnt(0)\n\t"
+        SAM_REDUCE("%[P]", "s64", "v42", "v43")
+        "s_branch L_resolve_%=\n"
+        "L_hit_%=:\n\t"
+        "s_ff1_i32_b32 s69, s73\n\t"
+        "v_readlane_b32 s68, v44, s69\n\t"
+        "s_lshl_b32 s83, s72, 3\n\t"
+        "s_add_u32 s83, s83, s69\n\t"
+        "s_branch L_found_%=\n"
+        "L_inline_%=:\n\t"
+        "s_mov_b32 s68, %[r5]\n\t"
+        "s_mov_b32 s83, -2\n\t"
+        "s_mov_b32 s67, -1\n\t"
+        "s_branch L_found_%=\n"
+        "L_miss_%=:\n\t"
+        // (P, t) is missing: the next state's record and bucket first, then P's stores
+        "s_add_u32 %[nt], %[nt], 1\n\t"
+        "s_mov_b32 s99, %[r1]\n\t"
+        "s_cmp_eq_u32 s99, -1\n\t"
+        "s_cbranch_scc1 L_ins_%=\n\t"
+        SAM_LOAD_REC("s99")
+        SAM_HASH("s75", "s99", "s66")
+        SAM_LOAD_BUCKET("v[56:59]", "s75")
+        "L_ins_%=:\n\t"
+        "s_cmp_eq_u32 %[r4], -1\n\t"
+        "s_cbranch_scc1 L_ins_inline_%=\n\t"
+        "s_ff1_i32_b32 s98, s74\n\t"
+        "s_lshl_b32 s84, s72, 3\n\t"
+        "s_add_u32 s84, s84, s98\n\t"
+        "s_lshl_b32 s69, s84, 4\n\t"
+        "s_lshl_b32 s71, %[P], 5\n\t"
+        "s_mov_b64 exec, 1\n\t"
+        "v_mov_b32 v40, s69\n\t"
+        "v_mov_b32 v50, %[P]\n\t"
+        "v_mov_b32 v51, s64\n\t"
+        "v_mov_b32 v52, s82\n\t"
+        "v_mov_b32 v53, %[r3]\n\t"
+        "buffer_store_dwordx4 v[50:53], v40, %[rslt], 0 offen\n\t"
+        "v_mov_b32 v41, s71\n\t"
+        "v_mov_b32 v54, s84\n\t"
+        "buffer_store_dword v54, v41, %[rrec], 0 offen offset:12\n\t"
+        "s_mov_b64 exec, 0xff\n\t"
+        "s_mov_b32 %[r3], s84\n\t"
+        "s_cmp_eq_u32 s99, -1\n\t"
+        "s_cbranch_scc1 L_atroot_%=\n\t"        // P is the root: it stays the cursor
+        // the slot just taken still reads as empty in a bucket fetched before the store
+        "s_lshl_b32 s98, 1, s98\n\t"
+        "s_cmp_eq_u32 s72, s75\n\t"
+        "s_cselect_b32 s98, s98, 0\n\t"
+        "s_waitcnt vmcnt(2)\n\t"
+        "s_branch L_advance_%=\n"
+        "L_ins_inline_%=:\n\t"
+        "s_lshl_b32 s71, %[P], 5\n\t"
+        "s_mov_b64 exec, 1\n\t"
+        "v_mov_b32 v41, s71\n\t"
+        "v_mov_b32 v50, s64\n\t"
+        "v_mov_b32 v51, s82\n\t"
+        "buffer_store_dwordx2 v[50:51], v41, %[rrec], 0 offen offset:16\n\t"
+        "s_mov_b64 exec, 0xff\n\t"
+        "s_mov_b32 %[r4], s64\n\t"
+        "s_mov_b32 %[r5], s82\n\t"
+        "s_cmp_eq_u32 s99, -1\n\t"
+        "s_cbranch_scc1 L_atroot_%=\n\t"
+        "s_mov_b32 s98, 0\n\t"
+        "s_waitcnt vmcnt(1)\n"
+        "L_advance_%=:\n\t"
+        "s_mov_b32 %[P], s99\n\t"
+        SAM_REDUCE("s99", "s64", "v56", "v57")
+        SAM_READ_REC("%[r0]", "%[r1]", "%[r2]", "%[r3]", "%[r4]", "%[r5]")
+        "v_mov_b32 v44, v58\n\t"
+        "s_andn2_b32 s74, s74, s98\n\t"
+        "s_mov_b32 s72, s75\n\t"
+        "s_branch L_walk_%=\n"
+        // ---- q = next(P)[t] exists -----------------------------------------------
+        "L_found_%=:\n\t"
+        SAM_LOAD_REC("s68")
+        "s_cmp_eq_u32 s65, -1\n\t"
+        "s_cbranch_scc1 L_noprefetch_%=\n\t"
+        // with it, the next token's first lookup (at q)
+        "s_mul_i32 s71, s65, 0x85ebca77\n\t"
+        SAM_HASH("s75", "s68", "s71")
+        SAM_LOAD_BUCKET("v[56:59]", "s75")
+        SAM_STORE_LAST
+        "s_waitcnt vmcnt(2)\n\t"
+        "s_branch L_qrec_%=\n"
+        "L_noprefetch_%=:\n\t"
+        SAM_STORE_LAST
+        "s_waitcnt vmcnt(1)\n"
+        "L_qrec_%=:\n\t"
+        SAM_READ_REC("s76", "s77", "s78", "s79", "s62", "s63")
+        "s_cmp_lg_u32 s68, s87\n\t"
+        "s_cbranch_scc1 L_qok_%=\n\t"
+        "s_mov_b32 s76, s81\n\t"                // q is the old last: its record as just written
+        "s_mov_b32 s77, s80\n\t"
+        "s_mov_b32 s78, s81\n\t"
+        "s_mov_b32 s79, -1\n\t"
+        "s_mov_b32 s62, s64\n\t"
+        "s_mov_b32 s63, s82\n"
+        "L_qok_%=:\n\t"
+        "s_add_u32 s98, %[r0], 1\n\t"           // len(P) + 1
+        "s_cmp_eq_u32 s98, s76\n\t"
+        "s_cbranch_scc0 L_clone_%=\n\t"
+        "s_mov_b32 %[P], s68\n\t"
+        "s_mov_b32 %[r0], s76\n\t"
+        "s_mov_b32 %[r1], s77\n\t"
+        "s_mov_b32 %[r2], s78\n\t"
+        "s_mov_b32 %[r3], s79\n\t"
+        "s_mov_b32 %[r4], s62\n\t"
+        "s_mov_b32 %[r5], s63\n\t"
+        "s_mov_b32 s72, -1\n\t"
+        "s_cmp_eq_u32 s65, -1\n\t"
+        "s_cbranch_scc1 L_next_%=\n\t"
+        "s_mov_b32 s72, s75\n\t"
+        "s_waitcnt vmcnt(1)\n\t"
+        "v_mov_b32 v44, v58\n\t"
+        SAM_REDUCE("s68", "s65", "v56", "v57")
+        "s_branch L_next_%=\n"
+        // ---- clone q at length len(P) + 1 ------------------------------------------
+        "L_clone_%=:\n\t"
+        "s_mov_b32 s88, %[ns]\n\t"
+        "s_add_u32 %[ns], %[ns], 1\n\t"
+        "s_mov_b32 s89, s98\n\t"
+        "s_mov_b32 s90, s77\n\t"                // link(q)
+        "s_mov_b32 s91, s78\n\t"                // endpos(q)
+        "s_mov_b32 s92, -1\n\t"
+        "s_mov_b32 s60, s62\n\t"
+        "s_mov_b32 s61, s63\n\t"
+        "s_mov_b32 s93, s79\n\t"                // head of q's list
+        "s_waitcnt vmcnt(0)\n\t"
+        "s_cmp_eq_u32 s62, -1\n\t"
+        "s_cbranch_scc1 L_copy_%=\n\t"
+        "s_add_u32 %[nt], %[nt], 1\n"
+        "L_copy_%=:\n\t"
+        "s_cmp_eq_u32 s93, -1\n\t"
+        "s_cbranch_scc1 L_copied_%=\n\t"
+        SAM_GUARD("L_corrupt_%=")
+        "s_lshl_b32 s69, s93, 4\n\t"
+        "v_add_u32 v40, s69, %[lo4]\n\t"
+        "buffer_load_dword v46, v40, %[rslt], 0 offen\n\t"
+        "s_waitcnt vmcnt(0)\n\t"
+        "v_readlane_b32 s94, v46, 1\n\t"
+        "v_readlane_b32 s95, v46, 2\n\t"
+        "v_readlane_b32 s93, v46, 3\n\t"
+        "s_mul_i32 s71, s94, 0x85ebca77\n\t"
+        SAM_HASH("s84", "s88", "s71")
+        "L_copy_probe_%=:\n\t"
+        SAM_LOAD_BUCKET("v[42:45]", "s84")
+        "s_waitcnt vmcnt(0)\n\t"
+        "v_cmp_eq_u32 vcc, -1, v42\n\t"
+        "s_nop 1\n\t"
+        "s_and_b32 s70, vcc_lo, 0xff\n\t"
+        "s_cbranch_scc1 L_copy_put_%=\n\t"
+        SAM_GUARD("L_corrupt_%=")
+        SAM_NEXT_BUCKET("s84")
+        "s_branch L_copy_probe_%=\n"
+        "L_copy_put_%=:\n\t"
+        "s_ff1_i32_b32 s69, s70\n\t"
+        "s_lshl_b32 s84, s84, 3\n\t"
+        "s_add_u32 s84, s84, s69\n\t"           // slot index
+        "s_lshl_b32 s69, s84, 4\n\t"
+        "s_mov_b64 exec, 1\n\t"
+        "v_mov_b32 v40, s69\n\t"
+        "v_mov_b32 v50, s88\n\t"
+        "v_mov_b32 v51, s94\n\t"
+        "v_mov_b32 v52, s95\n\t"
+        "v_mov_b32 v53, s92\n\t"
+        "buffer_store_dwordx4 v[50:53], v40, %[rslt], 0 offen\n\t"
+        "s_mov_b64 exec, 0xff\n\t"
+        "s_mov_b32 s92, s84\n\t"
+        "s_add_u32 %[nt], %[nt], 1\n\t"
+        "s_branch L_copy_%=\n"
+        "L_copied_%=:\n\t"
+        SAM_STORE_REC("s88", "s89", "s90", "s91", "s92", "s60", "s61")
+        // the next token starts at the clone: request its bucket there now that the
+        // clone's transitions are all stored (a request before them could miss one)
+        "s_cmp_eq_u32 s65, -1\n\t"
+        "s_cbranch_scc1 L_redirect_%=\n\t"
+        "s_mul_i32 s71, s65, 0x85ebca77\n\t"
+        SAM_HASH("s75", "s88", "s71")
+        SAM_LOAD_BUCKET("v[56:59]", "s75")
+        // states further up the path that still lead to q now lead to the clone
+        "L_redirect_%=:\n\t"
+        "s_mov_b32 s99, %[r1]\n\t"
+        "s_lshl_b32 s98, %[P], 5\n\t"           // where the store below goes, if inline
+        "s_cmp_eq_u32 s99, -1\n\t"
+        "s_cbranch_scc1 L_red_store_%=\n\t"
+        SAM_GUARD("L_corrupt_%=")
+        // the next state's record and bucket first, then the store (not waited for)
+        "s_mov_b32 %[P], s99\n\t"
+        SAM_LOAD_REC("s99")
+        SAM_HASH("s72", "s99", "s66")
+        SAM_LOAD_BUCKET("v[42:45]", "s72")
+        "L_red_store_%=:\n\t"
+        "s_mov_b64 exec, 1\n\t"
+        "v_mov_b32 v54, s88\n\t"
+        "s_cmp_eq_u32 s83, -2\n\t"
+        "s_cbranch_scc0 L_red_slot_%=\n\t"
+        "v_mov_b32 v40, s98\n\t"
+        "buffer_store_dword v54, v40, %[rrec], 0 offen offset:20\n\t"
+        "s_branch L_red_up_%=\n"
+        "L_red_slot_%=:\n\t"
+        "s_lshl_b32 s69, s83, 4\n\t"
+        "v_mov_b32 v40, s69\n\t"
+        "buffer_store_dword v54, v40, %[rslt], 0 offen offset:8\n"
+        "L_red_up_%=:\n\t"
+        "s_mov_b64 exec, 0xff\n\t"
+        "s_cmp_eq_u32 s99, -1\n\t"
+        "s_cbranch_scc1 L_redirected_%=\n\t"
+        "s_waitcnt vmcnt(1)\n\t"
+        SAM_REDUCE("s99", "s64", "v42", "v43")
+        SAM_READ_REC("%[r0]", "%[r1]", "%[r2]", "%[r3]", "%[r4]", "%[r5]")
+        "s_cmp_eq_u32 %[r4], s64\n\t"
+        "s_cbranch_scc0 L_red_resolve_%=\n\t"
+        "s_cmp_eq_u32 %[r5], s68\n\t"
+        "s_cbranch_scc0 L_redirected_%=\n\t"
+        "s_mov_b32 s83, -2\n\t"
+        "s_branch L_redirect_%=\n"
+        "L_red_resolve_%=:\n\t"
+        "s_cmp_lg_u32 s73, 0\n\t"
+        "s_cbranch_scc1 L_red_hit_%=\n\t"
+        "s_cmp_lg_u32 s74, 0\n\t"
+        "s_cbranch_scc1 L_redirected_%=\n\t"
+        SAM_GUARD("L_corrupt_%=")
+        SAM_NEXT_BUCKET("s72")
+        SAM_LOAD_BUCKET("v[42:45]", "s72")
+        "s_waitcnt vmcnt(0)\n\t"
+        SAM_REDUCE("s99", "s64", "v42", "v43")
+        "s_branch L_red_resolve_%=\n"
+        "L_red_hit_%=:\n\t"
+        "s_ff1_i32_b32 s69, s73\n\t"
+        "v_readlane_b32 s70, v44, s69\n\t"
+        "s_lshl_b32 s83, s72, 3\n\t"
+        "s_add_u32 s83, s83, s69\n\t"
+        "s_cmp_eq_u32 s70, s68\n\t"
+        "s_cbranch_scc1 L_redirect_%=\n"
+        "L_redirected_%=:\n\t"
+        "s_lshl_b32 s69, s68, 5\n\t"
+        "s_mov_b64 exec, 1\n\t"
+        "v_mov_b32 v40, s69\n\t"
+        "v_mov_b32 v54, s88\n\t"
+        "buffer_store_dword v54, v40, %[rrec], 0 offen offset:4\n\t"
+        "s_mov_b64 exec, 0xff\n\t"
+        "s_mov_b32 %[P], s88\n\t"
+        "s_mov_b32 %[r0], s89\n\t"
+        "s_mov_b32 %[r1], s90\n\t"
+        "s_mov_b32 %[r2], s91\n\t"
+        "s_mov_b32 %[r3], s92\n\t"
+        "s_mov_b32 %[r4], s60\n\t"
+        "s_mov_b32 %[r5], s61\n\t"
+        "s_mov_b32 s72, -1\n\t"
+        "s_cmp_eq_u32 s65, -1\n\t"
+        "s_cbranch_scc1 L_next_%=\n\t"
+        // its bucket is on the way; it is waited for and reduced only if the next
+        // token does not take the clone's inline transition
+        "s_mov_b32 s67, s88\n\t"
+        "s_mov_b32 s72, s75\n\t"
+        "s_branch L_next_%=\n"
+        "L_atroot_%=:\n\t"
+        "s_mov_b32 s72, -1\n\t"
+        SAM_STORE_LAST
+        // ---- next token -------------------------------------------------------------
+        "L_next_%=:\n\t"
+        "s_add_u32 %[i], %[i], 1\n\t"
+        "s_cmp_lt_u32 %[i], %[m]\n\t"
+        "s_cbranch_scc1 L_token_%=\n\t"
+        "s_branch L_exit_%=\n"
+        "L_corrupt_%=:\n\t"
+        "s_or_b32 %[flt], %[flt], 8\n"
+        "L_exit_%=:\n\t"
+        "s_waitcnt vmcnt(0)\n\t"
+        "s_mov_b64 exec, s[96:97]\n\t"
+        : [i] "+s"(i), [n] "+s"(n), [ns] "+s"(ns), [last] "+s"(last), [nt] "+s"(nt), [P] "+s"(P),
+          [r0] "+s"(r0), [r1] "+s"(r1), [r2] "+s"(r2), [r3] "+s"(r3), [r4] "+s"(r4), [r5] "+s"(r5),
+          [flt] "+s"(flt)
+        : [rrec] "s"(rrec), [rslt] "s"(rslt), [nb] "s"(nb), [m] "s"(m), [vocab] "s"(vocab),
+          [tv] "v"(tv), [lo4] "v"(lo4), [lo16] "v"(lo16)
+        : "memory", "vcc", "scc",
+          "s60", "s61", "s62", "s63",
+          "s64", "s65", "s66", "s67", "s68", "s69", "s70", "s71", "s72", "s73", "s74", "s75",
+          "s76", "s77", "s78", "s79", "s80", "s81", "s82", "s83", "s84", "s86", "s87",
+          "s88", "s89", "s90", "s91", "s92", "s93", "s94", "s95", "s96", "s97", "s98", "s99",
+          "v40", "v41", "v42", "v43", "v44", "v45", "v46", "v47", "v50", "v51",
+          "v52", "v53", "v54", "v56", "v57", "v58", "v59");
+    R.len = r0; R.link = r1; R.endpos = r2; R.head = r3; R.itok = r4; R.idst = r5;
+}
+#undef SAM_HASH
+#undef SAM_STORE_LAST
+#undef SAM_STORE_REC
+#undef SAM_LOAD_BUCKET
+#undef SAM_LOAD_REC
+#undef SAM_READ_REC
+#undef SAM_REDUCE
+#undef SAM_NEXT_BUCKET
+#undef SAM_GUARD
+
 // ---- per-wave work shared by the step, ingest and replay kernels -------------
 
 // Wave 1: append `count` tokens to the sequence's dynamic automaton and text.
@@ -994,6 +1441,23 @@ __device__ __forceinline__ void dyn_feed(const DynSeq &D, const int32_t *tok, in
                     stop = true;
                     if (!flt) fault |= SAM_STATUS_TOKEN_BIT;
                 }
+            }
+        }
+        if constexpr (L::kSlots == 8 && L::kAsm) in_asm = use_asm;
+        if constexpr (L::kSlots == 8 && L::kAsm) if (in_asm) {
+            const uint32_t nbk = uni(D.n_buckets);
+            uint32_t i = 0, flt = 0;
+            uint32_t a_n = uni(c.n), a_ns = uni(c.n_states), a_last = uni(c.last);
+            uint32_t a_nt = uni(c.n_trans), a_P = uni(c.P);
+            dyn_feed_wide(table_rsrc(D.rec, uni(c.rec_bytes)), table_rsrc(D.slots, nbk * 128u), nbk,
+                          uni((uint32_t)m), uni(vocab), tv, (uint32_t)(lane & 7) * 4u,
+                          (uint32_t)(lane & 7) * 16u, i, a_n, a_ns, a_last, a_nt, a_P, c.RP, flt);
+            c.n = a_n; c.n_states = a_ns; c.last = a_last; c.n_trans = a_nt; c.P = a_P;
+            fed = (int)i;
+            fault |= flt;
+            if (fed < m) {
+                stop = true;
+                if (!flt) fault |= SAM_STATUS_TOKEN_BIT;
             }
         }
         if (!in_asm) {
@@ -1329,7 +1793,7 @@ __global__ __launch_bounds__(kScout ? 256 : 128) void sam_feed_kernel(StaticView
         const DynSeq D = dyn_region<L>(B, b);
         DynCursor<L> c;
         cursor_from_lanes<L>(mv, c);
-        c.rec_bytes = (uint32_t)B.max_states * 16u;
+        c.rec_bytes = (uint32_t)B.max_states * (L::kSlots == 16 ? 16u : 32u);
         // The first token of a step finds nothing of the sequence's tables in the caches,
         // and its lookups come one after the other: the bucket at P, then record and
         // bucket one suffix link up, then at the root.  Their addresses are all known
@@ -1428,7 +1892,7 @@ __global__ __launch_bounds__(128) void sam_replay_kernel(StaticView S, BatchView
     DynCursor<L> c;
     if (wave == 0) { s = uni(meta->s1); l = uni(meta->l1); e = uni(meta->e1); }
     load_cursor<L>(meta, c);
-    c.rec_bytes = (uint32_t)B.max_states * 16u;
+    c.rec_bytes = (uint32_t)B.max_states * (L::kSlots == 16 ? 16u : 32u);
     const uint32_t n_first = n_cur;
 
     for (int step = 0; step < n_steps; step++) {
@@ -1733,8 +2197,14 @@ hipError_t launch_feed(const StaticView &S, const BatchView &B, const int32_t *s
     hipLaunchKernelGGL((sam_feed_kernel<LAYOUT, INGEST, ASM, SCOUT>), grid, block, 0, stream,  \
                        S, B, seq_map, tokens, offsets, counts, match_len, draft, draft_len,    \
                        source)
-    const int which = (B.compact ? 4 : 0) | (offsets ? 2 : 0) | ((B.no_asm || (S.n_buckets >> 32)) ? 0 : 1);
+    const bool huge = !B.compact && (uint64_t)B.max_states * sizeof(DynRec) >> 32;
+    const int which = (huge ? 8 : (B.compact ? 4 : 0)) | (offsets ? 2 : 0) |
+                      ((B.no_asm || (S.n_buckets >> 32)) ? 0 : 1);
     switch (which) {
+    case 11: SAM_LAUNCH_FEED(HugeDyn, true, true, false); break;
+    case 9: if (scout) SAM_LAUNCH_FEED(HugeDyn, false, true, true);
+            else SAM_LAUNCH_FEED(HugeDyn, false, true, false);
+            break;
     case 7: SAM_LAUNCH_FEED(CompactDyn, true, true, false); break;
     case 6: SAM_LAUNCH_FEED(CompactDyn, true, false, false); break;
     case 5: if (scout) SAM_LAUNCH_FEED(CompactDyn, false, true, true);
@@ -1744,7 +2214,7 @@ hipError_t launch_feed(const StaticView &S, const BatchView &B, const int32_t *s
             else SAM_LAUNCH_FEED(CompactDyn, false, false, false);
             break;
     case 3: SAM_LAUNCH_FEED(WideDyn, true, true, false); break;
-    case 2: SAM_LAUNCH_FEED(WideDyn, true, false, false); break;
+    case 2: case 10: SAM_LAUNCH_FEED(WideDyn, true, false, false); break;
     case 1: if (scout) SAM_LAUNCH_FEED(WideDyn, false, true, true);
             else SAM_LAUNCH_FEED(WideDyn, false, true, false);
             break;
@@ -1767,6 +2237,8 @@ hipError_t launch_replay(const StaticView &S, const BatchView &B, int n_steps,
     const bool cxx = B.no_asm || (S.n_buckets >> 32);
     if (B.compact) {
         if (cxx) SAM_LAUNCH_REPLAY(CompactDyn, false); else SAM_LAUNCH_REPLAY(CompactDyn, true);
+    } else if ((uint64_t)B.max_states * sizeof(DynRec) >> 32) {
+        if (cxx) SAM_LAUNCH_REPLAY(WideDyn, false); else SAM_LAUNCH_REPLAY(HugeDyn, true);
     } else {
         if (cxx) SAM_LAUNCH_REPLAY(WideDyn, false); else SAM_LAUNCH_REPLAY(WideDyn, true);
     }
