@@ -12,6 +12,9 @@ import ctypes as C
 import os
 
 import numpy as np
+# PyTorch ships its own copy of the HIP runtime.  It has to be in the process before the library is,
+# so that both resolve to one runtime (two copies in one process do not both find the GPU).
+import torch
 
 from . import build as _build
 
@@ -41,10 +44,6 @@ class SamError(RuntimeError):
 
 
 def _load():
-    # PyTorch ships its own copy of the HIP runtime.  It has to be in the process
-    # before this library is, so that both resolve to one runtime (two copies in
-    # one process do not both find the GPU).
-    import torch  # noqa: F401
     path = _build.LIB
     if not os.path.exists(path):
         _build.build()          # nothing built yet: build once
@@ -103,22 +102,34 @@ def _check(rc: int):
         raise SamError(rc, _lib.sam_last_error().decode("utf-8", "replace"))
 
 
+_Tensor = torch.Tensor
+_i32, _i64, _f32 = torch.int32, torch.int64, torch.float32
+
+
 def _dev_ptr(t, dtype, what):
-    """Pointer of a contiguous device tensor of the given torch dtype (None -> NULL)."""
+    """Address of a contiguous device tensor of the given torch dtype (None -> NULL)."""
     if t is None:
         return None
-    import torch
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
+    if not isinstance(t, _Tensor) or not t.is_cuda:
         raise TypeError("%s must be a device tensor" % what)
-    if t.dtype != dtype or not t.is_contiguous():
+    if t.dtype is not dtype or not t.is_contiguous():
         raise TypeError("%s must be contiguous %s" % (what, dtype))
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+# A round of one sequence is bound by what the host does for the call, so the marshalling of the
+# calls of a round avoids what costs: address objects (the argument types convert plain numbers) and
+# the Stream object of current_stream().
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = torch.cuda.current_device
 
 
 def _stream_ptr(stream):
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _current_raw_stream is not None:
+        return _current_raw_stream(_current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def sam_last_error() -> str:
@@ -226,26 +237,28 @@ def sam_corpus_export_topk(corpus: Corpus):
 
 def sam_batch_tree_draft(batch: Batch, max_size: int, tokens, parents, probs, sizes,
                          stream=None) -> None:
-    import torch
-    for name, t in (("tokens", tokens), ("parents", parents), ("probs", probs)):
-        if t.numel() != batch.batch * max_size:
-            raise ValueError("%s must hold batch * max_size values" % name)
+    entries = batch.batch * max_size
+    if tokens.numel() != entries:
+        raise ValueError("tokens must hold batch * max_size values")
+    if parents.numel() != entries:
+        raise ValueError("parents must hold batch * max_size values")
+    if probs.numel() != entries:
+        raise ValueError("probs must hold batch * max_size values")
     if sizes.numel() != batch.batch:
         raise ValueError("sizes must hold batch values")
-    _check(_lib.sam_batch_tree_draft(batch._h, max_size, _dev_ptr(tokens, torch.int32, "tokens"),
-                                     _dev_ptr(parents, torch.int32, "parents"),
-                                     _dev_ptr(probs, torch.float32, "probs"),
-                                     _dev_ptr(sizes, torch.int32, "sizes"), _stream_ptr(stream)))
+    _check(_lib.sam_batch_tree_draft(batch._h, max_size, _dev_ptr(tokens, _i32, "tokens"),
+                                     _dev_ptr(parents, _i32, "parents"),
+                                     _dev_ptr(probs, _f32, "probs"),
+                                     _dev_ptr(sizes, _i32, "sizes"), _stream_ptr(stream)))
 
 
 def sam_batch_init(corpus, prompt_tokens, prompt_offsets, batch: int, vocab: int,
                    max_seq_len: int, max_accept: int, draft_len: int, l_bias: int = 0,
                    stream=None) -> Batch:
-    import torch
     h = C.c_void_p()
     _check(_lib.sam_batch_init(corpus._h if corpus is not None else None,
-                               _dev_ptr(prompt_tokens, torch.int32, "prompt_tokens"),
-                               _dev_ptr(prompt_offsets, torch.int64, "prompt_offsets"),
+                               _dev_ptr(prompt_tokens, _i32, "prompt_tokens"),
+                               _dev_ptr(prompt_offsets, _i64, "prompt_offsets"),
                                batch, vocab, max_seq_len, max_accept, draft_len, l_bias,
                                _stream_ptr(stream), C.byref(h)))
     return Batch(h, corpus, batch, max_accept, draft_len)
@@ -258,14 +271,13 @@ def sam_batch_init_noalloc(corpus, prompt_tokens, prompt_offsets, prompt_offsets
                            vocab: int, max_seq_len: int, max_accept: int, draft_len: int,
                            l_bias: int = 0, stream=None) -> Batch:
     """prompt_offsets_host: int64 numpy array, the host copy of prompt_offsets."""
-    import torch
     ho = np.ascontiguousarray(prompt_offsets_host, dtype=np.int64)
     if ho.size != batch + 1:
         raise ValueError("prompt_offsets_host must hold batch + 1 values")
     h = C.c_void_p()
     _check(_lib.sam_batch_init_noalloc(corpus._h if corpus is not None else None,
-                                       _dev_ptr(prompt_tokens, torch.int32, "prompt_tokens"),
-                                       _dev_ptr(prompt_offsets, torch.int64, "prompt_offsets"),
+                                       _dev_ptr(prompt_tokens, _i32, "prompt_tokens"),
+                                       _dev_ptr(prompt_offsets, _i64, "prompt_offsets"),
                                        ho.ctypes.data_as(C.c_void_p), batch, vocab, max_seq_len,
                                        max_accept, draft_len, l_bias, _stream_ptr(stream),
                                        C.byref(h)))
@@ -274,38 +286,38 @@ def sam_batch_init_noalloc(corpus, prompt_tokens, prompt_offsets, prompt_offsets
 
 def sam_batch_step(batch: Batch, accepted, counts, match_len, draft, draft_len, source,
                    stream=None) -> None:
-    import torch
-    i32 = torch.int32
-    if accepted is not None and accepted.numel() != batch.batch * batch.max_accept:
+    B = batch.batch
+    if accepted is not None and accepted.numel() != B * batch.max_accept:
         raise ValueError("accepted must hold batch * max_accept tokens")
-    if draft is not None and draft.numel() != batch.batch * batch.draft_len:
+    if draft is not None and draft.numel() != B * batch.draft_len:
         raise ValueError("draft must hold batch * draft_len tokens")
-    for name, t in (("counts", counts), ("match_len", match_len), ("draft_len", draft_len),
-                    ("source", source)):
-        if t is not None and t.numel() != batch.batch:
-            raise ValueError("%s must hold batch values" % name)
-    _check(_lib.sam_batch_step(batch._h, _dev_ptr(accepted, i32, "accepted"),
-                               _dev_ptr(counts, i32, "counts"),
-                               _dev_ptr(match_len, i32, "match_len"),
-                               _dev_ptr(draft, i32, "draft"),
-                               _dev_ptr(draft_len, i32, "draft_len"),
-                               _dev_ptr(source, i32, "source"), _stream_ptr(stream)))
+    if counts is not None and counts.numel() != B:
+        raise ValueError("counts must hold batch values")
+    if match_len is not None and match_len.numel() != B:
+        raise ValueError("match_len must hold batch values")
+    if draft_len is not None and draft_len.numel() != B:
+        raise ValueError("draft_len must hold batch values")
+    if source is not None and source.numel() != B:
+        raise ValueError("source must hold batch values")
+    _check(_lib.sam_batch_step(batch._h, _dev_ptr(accepted, _i32, "accepted"),
+                               _dev_ptr(counts, _i32, "counts"),
+                               _dev_ptr(match_len, _i32, "match_len"),
+                               _dev_ptr(draft, _i32, "draft"),
+                               _dev_ptr(draft_len, _i32, "draft_len"),
+                               _dev_ptr(source, _i32, "source"), _stream_ptr(stream)))
 
 
 def sam_batch_reset(batch: Batch, slots, prompt_tokens, prompt_offsets, stream=None) -> None:
-    import torch
-    _check(_lib.sam_batch_reset(batch._h, _dev_ptr(slots, torch.int32, "slots"),
+    _check(_lib.sam_batch_reset(batch._h, _dev_ptr(slots, _i32, "slots"),
                                 int(slots.numel()),
-                                _dev_ptr(prompt_tokens, torch.int32, "prompt_tokens"),
-                                _dev_ptr(prompt_offsets, torch.int64, "prompt_offsets"),
+                                _dev_ptr(prompt_tokens, _i32, "prompt_tokens"),
+                                _dev_ptr(prompt_offsets, _i64, "prompt_offsets"),
                                 _stream_ptr(stream)))
 
 
 def sam_batch_replay(batch: Batch, accepted, counts, match_len, draft, draft_len, source,
                      stream=None) -> None:
     """All rows of the [steps, ...] tensors in one launch."""
-    import torch
-    i32 = torch.int32
     S = int(counts.shape[0])
     B, A, L = batch.batch, batch.max_accept, batch.draft_len
     for t, shp, name in ((accepted, (S, B, A), "accepted"), (counts, (S, B), "counts"),
@@ -313,12 +325,12 @@ def sam_batch_replay(batch: Batch, accepted, counts, match_len, draft, draft_len
                          (draft_len, (S, B), "draft_len"), (source, (S, B), "source")):
         if tuple(t.shape) != shp:
             raise ValueError("%s must have shape %s" % (name, shp))
-    _check(_lib.sam_batch_replay(batch._h, S, _dev_ptr(accepted, i32, "accepted"),
-                                 _dev_ptr(counts, i32, "counts"),
-                                 _dev_ptr(match_len, i32, "match_len"),
-                                 _dev_ptr(draft, i32, "draft"),
-                                 _dev_ptr(draft_len, i32, "draft_len"),
-                                 _dev_ptr(source, i32, "source"), _stream_ptr(stream)))
+    _check(_lib.sam_batch_replay(batch._h, S, _dev_ptr(accepted, _i32, "accepted"),
+                                 _dev_ptr(counts, _i32, "counts"),
+                                 _dev_ptr(match_len, _i32, "match_len"),
+                                 _dev_ptr(draft, _i32, "draft"),
+                                 _dev_ptr(draft_len, _i32, "draft_len"),
+                                 _dev_ptr(source, _i32, "source"), _stream_ptr(stream)))
 
 
 MEMBENCH_CHASE, MEMBENCH_GATHER, MEMBENCH_COPY, MEMBENCH_LAUNCH = 0, 1, 2, 3
@@ -343,15 +355,13 @@ class StepPlan:
 
     def __init__(self, batch: Batch, accepted, counts, match_len, draft, draft_len, source,
                  stream=None):
-        import torch
-        i32 = torch.int32
         S = int(counts.shape[0])
         B, A, L = batch.batch, batch.max_accept, batch.draft_len
         shapes = ((accepted, (S, B, A), "accepted"), (counts, (S, B), "counts"),
                   (match_len, (S, B), "match_len"), (draft, (S, B, L), "draft"),
                   (draft_len, (S, B), "draft_len"), (source, (S, B), "source"))
         for t, shp, name in shapes:
-            _dev_ptr(t, i32, name)
+            _dev_ptr(t, _i32, name)
             if tuple(t.shape) != shp:
                 raise ValueError("%s must have shape %s" % (name, shp))
         self._keep = [t for t, _, _ in shapes]
@@ -374,19 +384,15 @@ class StepPlan:
 
 
 def sam_batch_debug(batch: Batch, s1, l1, s2, l2, stream=None) -> None:
-    import torch
-    i32 = torch.int32
-    _check(_lib.sam_batch_debug(batch._h, _dev_ptr(s1, i32, "s1"), _dev_ptr(l1, i32, "l1"),
-                                _dev_ptr(s2, i32, "s2"), _dev_ptr(l2, i32, "l2"),
+    _check(_lib.sam_batch_debug(batch._h, _dev_ptr(s1, _i32, "s1"), _dev_ptr(l1, _i32, "l1"),
+                                _dev_ptr(s2, _i32, "s2"), _dev_ptr(l2, _i32, "l2"),
                                 _stream_ptr(stream)))
 
 
 def sam_batch_sizes(batch: Batch, text_len, n_states, n_trans, stream=None) -> None:
-    import torch
-    i32 = torch.int32
-    _check(_lib.sam_batch_sizes(batch._h, _dev_ptr(text_len, i32, "text_len"),
-                                _dev_ptr(n_states, i32, "n_states"),
-                                _dev_ptr(n_trans, i32, "n_trans"), _stream_ptr(stream)))
+    _check(_lib.sam_batch_sizes(batch._h, _dev_ptr(text_len, _i32, "text_len"),
+                                _dev_ptr(n_states, _i32, "n_states"),
+                                _dev_ptr(n_trans, _i32, "n_trans"), _stream_ptr(stream)))
 
 
 def sam_batch_status(batch: Batch, stream=None) -> int:
