@@ -347,9 +347,9 @@ int sam_batch_status(const sam_batch *batch, uint32_t *status, void *hip_stream)
  * corpus (about that much host and device memory), so that table offsets beyond
  * 32 bits are reached with a corpus that builds in a moment; bit 4 makes the
  * step kernel of every later sam_batch_init run with its two prefetching waves,
- * which otherwise join for batches of 128 sequences or more and for corpus
- * automata larger than 256 MB; bit 5 keeps them
- * out whatever the batch size (for measuring what they cost and bring); bit 6
+ * which otherwise join for rows of four tokens or more where the sequences' tables
+ * have 12 MiB or a sequence 14 000 tokens; bit 5 keeps them
+ * out whatever the sizes (for measuring what they cost and bring); bit 6
  * makes every later sam_build build on the device however small the corpus; bit 7
  * keeps the builds by the whole chip out: corpora are built on the host, prompts
  * too long for LDS by one workgroup each.  mode 0 restores the defaults.  Results are identical in every mode.

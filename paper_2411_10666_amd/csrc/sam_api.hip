@@ -29,17 +29,25 @@ int g_layout_override = 0;   // bit 0: always the wide layout, bit 1: tight slot
                              // bit 4: scout waves whatever the batch size, bit 5: never,
                              // bit 6: corpora on the device whatever their size,
                              // bit 7: no builds by the whole chip
-// Scout waves pay once the tables a step touches no longer stay in the caches from one
-// launch to the next: the per-sequence tables when many sequences share the caches, the
-// corpus automaton when it is larger than the last-level cache (256 MB).  Measured:
-// 8 sequences over 12 MB of corpus tables +4.5 % per step with scouts, 64 over 1.2 GB
-// -2 %, 256 over 12 GB -15 %.  They stop paying once the walking waves alone fill the
-// chip: with more than six sequences per compute unit the scouts take wave slots and
+// Scout waves pay where a step's rows are long enough to be looked at ahead of the walks, and the
+// sequences' tables are not in the L2 when it starts: because they fill it (12 of its 32 MB or more),
+// or because long prompts were built elsewhere and only their ends have been walked since.  Measured,
+// with scouts / without, us a round (rows of up to 8, of 16):
+//   tables  2.5 MB   16 x 3000 tokens     1.03  0.99      20 MB   64 x 6000      1.00  0.99   128 x 3000   1.00  0.98
+//           8.3 MB   16 x 10 000          1.05  1.02      33 MB   64 x 10 000    0.99  0.97
+//          10 MB     64 x 3000            1.04  1.02      67 MB   128 x 10 000   0.95  0.93
+//          13.7 MB   64 x 4096            1.02  1.00     328 MB   1024 x 6144          0.90
+//   after prompts that nearly fill them:  1 x 15 500 0.97 0.92   8 x 15 500 0.92 0.87   32 x 14 500 0.92 0.88
+//   wide layout, the same:                1 x 41 000 0.94 0.90   12 x 41 000 0.91 0.86   64 x 31 000 0.91 0.87
+//   rows of up to 3: 128 x 1024 1.07, 1024 x 3600 1.01; of 4: 32 x 16 000 0.97, 1 x 16 000 1.02; of 2: 1.01, 1.06
+// The corpus's size makes no difference (35 MB to 1.4 GB).  They stop paying once the walking waves
+// alone fill the chip: with more than six sequences per compute unit the scouts take wave slots and
 // issue cycles from other sequences' walks (1024 sequences on 256 units over 6 GB of
 // tables -9 % per step with scouts, 1536 -6 %, 2048 +9 %, 4096 +19 %, 8192 +27 %).
-constexpr int     kScoutMinBatch = 128;
+constexpr int     kScoutMinAccept = 4;
+constexpr int64_t kScoutMinTableBytes = 12 << 20;
+constexpr int     kScoutMinSeqLen = 14000;
 constexpr int     kScoutMaxSeqPerCu = 6;
-constexpr int64_t kScoutMinCorpusBytes = 256ll << 20;
 // buckets of 128 bytes that make a transition table of 4.5 GiB
 constexpr uint64_t kHugeTableBuckets = (1ull << 25) + (1ull << 22);
 // Tokens from which on the corpus automaton is built on the device: about fifty launches and a few
@@ -684,17 +692,17 @@ static BatchBytes batch_configure(BatchView &v, const sam_corpus *corpus, int32_
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         n_cu = 0;                          // unknown: no upper limit
-    const bool scouts_fit = n_cu <= 0 || (int64_t)batch <= (int64_t)n_cu * kScoutMaxSeqPerCu;
-    v.scout = ((g_layout_override & 32) == 0 &&
-               ((g_layout_override & 16) ||
-                (scouts_fit && (batch >= kScoutMinBatch ||
-                                (corpus && corpus->device_bytes > kScoutMinCorpusBytes))))) ? 1 : 0;
     v.has_static = has_static ? 1 : 0;
     BatchBytes b;
     b.text = (size_t)batch * max_seq_len * sizeof(int32_t);
     b.rec = (size_t)batch * v.max_states * rec_bytes;
     b.slots = (size_t)batch * v.dyn_buckets * 128;
     b.meta = (size_t)batch * sizeof(SeqMeta);
+    const bool scouts_fit = n_cu <= 0 || (int64_t)batch <= (int64_t)n_cu * kScoutMaxSeqPerCu;
+    const bool scouts_pay = max_accept >= kScoutMinAccept &&
+                            ((int64_t)(b.text + b.rec + b.slots) >= kScoutMinTableBytes || max_seq_len >= kScoutMinSeqLen);
+    v.scout = ((g_layout_override & 32) == 0 &&
+               ((g_layout_override & 16) || (scouts_fit && scouts_pay))) ? 1 : 0;
     return b;
 }
 

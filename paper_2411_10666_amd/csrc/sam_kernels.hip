@@ -1702,6 +1702,56 @@ __device__ __forceinline__ void scout_dynamic_compact(const DynSeq &D, uint32_t 
     asm volatile("" :: "v"(acc), "v"(st[0]), "v"(st[1]), "v"(st[2]), "v"(st[3]), "v"(st[4]));
 }
 
+// And in the wide layout (32-byte records, buckets of 8 slots of 16 bytes, fetched by 8 lanes: 8 start
+// positions at a time).
+__device__ __forceinline__ void scout_dynamic_wide(const DynSeq &D, uint32_t max_states, uint32_t tk,
+                                                   int n_starts, int lane)
+{
+    constexpr int kRounds = 3;                  // start positions 0 .. 23
+    const DynRec *rec_t = reinterpret_cast<const DynRec *>(D.rec);
+    const uint4 *slot_t = reinterpret_cast<const uint4 *>(D.slots);
+    const int g = lane >> 3, i = lane & 7;
+    uint32_t st[kRounds];                       // kNil: this start position is finished
+    uint32_t acc = 0;
+#pragma unroll
+    for (int r = 0; r < kRounds; r++) st[r] = 0;                // the root
+    for (int d = 0; d <= kScoutDepth; d++) {
+        uint2 rec[kRounds];
+        uint4 sl[kRounds];
+        uint32_t tt[kRounds];
+        bool on[kRounds];
+        bool any = false;
+#pragma unroll
+        for (int r = 0; r < kRounds; r++) {
+            const int j = g + 8 * r + d;
+            tt[r] = (uint32_t)__shfl((int)tk, j & 63);
+            on[r] = st[r] < max_states && j < n_starts && tt[r] != kNil;
+            rec[r] = make_uint2(kNil, 0);
+            sl[r] = make_uint4(kNil, kNil, 0, 0);
+            if (on[r]) {
+                rec[r] = *reinterpret_cast<const uint2 *>(&rec_t[st[r]].itok);
+                sl[r] = slot_t[(size_t)dyn_bucket(D, st[r], tt[r]) * 8 + i];
+            }
+            any |= on[r];
+        }
+        if (!__any(any)) break;
+#pragma unroll
+        for (int r = 0; r < kRounds; r++) {
+            const bool hit = on[r] && sl[r].x == st[r] && sl[r].y == tt[r];
+            const uint32_t gm = (uint32_t)(__ballot(hit) >> (g * 8)) & 0xFFu;
+            const uint32_t from = (uint32_t)__shfl((int)sl[r].z, g * 8 + (gm ? __builtin_ctz(gm) : 0));
+            uint32_t nxt = kNil;
+            if (on[r]) {
+                if (rec[r].x == tt[r]) nxt = rec[r].y;
+                else if (gm) nxt = from;
+            }
+            acc ^= rec[r].y;
+            st[r] = nxt;
+        }
+    }
+    asm volatile("" :: "v"(acc), "v"(st[0]), "v"(st[1]), "v"(st[2]));
+}
+
 }  // namespace
 
 // One workgroup per sequence: two walking waves, and with kScout two scouts.  kIngest: sequence b is fed
@@ -1780,6 +1830,7 @@ __global__ __launch_bounds__(kScout ? 256 : 128) void sam_feed_kernel(StaticView
                 if (B.has_static) scout_static(S, tk, n_starts, lane);
             } else {
                 if (L::kSlots == 16) scout_dynamic_compact(D, B.max_states, tk, n_starts, lane);
+                else scout_dynamic_wide(D, B.max_states, tk, n_starts, lane);
             }
         }
         return;
@@ -1811,6 +1862,17 @@ __global__ __launch_bounds__(kScout ? 256 : 128) void sam_feed_kernel(StaticView
                     warm = slots[(size_t)dyn_bucket(D, at, t0) * 16 + (lane & 15)].y;
                 else if (lane < 50 && up < B.max_states)
                     warm = reinterpret_cast<const uint4 *>(D.rec)[lane == 48 ? up : 0u].x;
+            }
+        }
+        if (kScout && L::kSlots == 8 && count > 0 && c.P != kNil) {
+            const uint32_t t0 = lane_get(first, 0);
+            if (t0 < vocab) {
+                const uint32_t up = c.RP.link == kNil ? 0u : c.RP.link;
+                const uint32_t at = lane < 8 ? c.P : (lane < 16 ? up : 0u);
+                if (lane < 24 && at < B.max_states)
+                    warm = reinterpret_cast<const uint4 *>(D.slots)[(size_t)dyn_bucket(D, at, t0) * 8 + (lane & 7)].z;
+                else if (lane < 26 && up < B.max_states)
+                    warm = reinterpret_cast<const DynRec *>(D.rec)[lane == 24 ? up : 0u].len;
             }
         }
         dyn_feed<L>(D, tok, count, vocab, lane, c, fault, kAsm, !kIngest, first);
