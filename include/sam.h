@@ -99,7 +99,8 @@ int sam_build(const int32_t *corpus_tokens, int64_t n_tokens, int32_t vocab,
 /*
  * Progress reports from sam_build / sam_build_host_only, for corpora that take
  * minutes: `fn` (NULL to switch off) is called on the building thread about every
- * 16 M tokens with phase "build", then during "finalize" and before "upload".
+ * 16 M tokens with phase "build" (once where the device builds), then during "finalize" and
+ * before "upload".
  * Process-wide; set it before the build call.
  */
 typedef void (*sam_progress_fn)(const char *phase, int64_t done, int64_t total, void *user);

@@ -399,6 +399,7 @@ static int corpus_build_device(sam_corpus *c, const int32_t *tokens, int64_t n, 
     HIP_TRY(bulk_corpus((const int32_t *)c->d_text, un, (uint32_t)vocab, (RootEnt *)c->d_root, w, &n_states, &n_trans,
                         &gave_up, nullptr));
     if (gave_up) return none();
+    if (g_progress) g_progress("finalize", 0, (int64_t)n_slots, g_progress_user);
     if (hipMalloc(&c->d_slots, n_slots * sizeof(Slot)) != hipSuccess) return none();
     // the second region (24 bytes a token) and the third (a quarter) are free again
     LinkPair *const d_pairs = (LinkPair *)w.second;
@@ -412,6 +413,7 @@ static int corpus_build_device(sam_corpus *c, const int32_t *tokens, int64_t n, 
         return fail(SAM_ENOMEM, "sam_build: out of host memory for the automaton");
     }
     static_assert(sizeof(HostState) == sizeof(BulkCorpus::State), "states are copied as they are");
+    if (g_progress) g_progress("upload", 0, 1, g_progress_user);       // the other way round, here
     HostSam &h = c->host;
     h.n_states = n_states;
     h.n_trans = n_trans;

@@ -364,8 +364,11 @@ hipError_t launch_ingest(const StaticView &S, const BatchView &B, const int32_t 
     // are more of them than units (sam_batch_reset, chip / workgroups, us: 1 prompt of 6500 tokens 0.45 /
     // 1.1 ms, 1 of 40 001 0.9 / 7.6, 12 of 40 001 1.2 / 8.1, 64 of 40 001 4.0 / 10.6, 256 of 6500 1.9 / 2.2, 600 of
     // 8000 4.2 / 5.8).  Of one token only, 3 of 16 000 tokens take 1.9 ms against 1.7; 3 of 40 001 4.5 against 5.0.
-    const bool bulk = max_tokens > lds_tokens && lds_tokens >= kBulkLdsTokens && !B.no_bulk;
-    if (bulk && (e = launch_bulk_prompts(B, seq_map, n_seqs, tokens, offsets, lds_tokens, max_tokens, true, stream)) != hipSuccess)
+    // (A captured call that is replayed with longer prompts than it was captured with leaves those to one
+    // workgroup each: its launches are made for the longest that the host knows of.)
+    const uint32_t bulk_tokens = n_beyond > 0 && lds_tokens >= kBulkLdsTokens && !B.no_bulk ? (uint32_t)sizes.longest : 0u;
+    if (bulk_tokens &&
+        (e = launch_bulk_prompts(B, seq_map, n_seqs, tokens, offsets, lds_tokens, bulk_tokens, true, stream)) != hipSuccess)
         return e;
     // workgroups for the corpus: a wave each sequence, a multiple of 8 workgroups
     auto walks = [&](int waves) { return B.has_static ? (((n_seqs + waves - 1) / waves + 7) & ~7) : 0; };
@@ -373,7 +376,7 @@ hipError_t launch_ingest(const StaticView &S, const BatchView &B, const int32_t 
 #define SAM_LAUNCH_PROMPT_T(COMPACT, ASM, T)                                                     \
     hipLaunchKernelGGL((sam_prompt_kernel<COMPACT, ASM, T>), dim3(n_static + n_seqs), dim3(T),    \
                        bytes, stream, S, B, seq_map, n_seqs, n_static, tokens, offsets,          \
-                       lds_tokens, max_tokens, bulk ? max_tokens : 0u)
+                       lds_tokens, max_tokens, bulk_tokens)
 #define SAM_LAUNCH_PROMPT(COMPACT, ASM)                                                          \
     do {                                                                                        \
         if (threads == 256) SAM_LAUNCH_PROMPT_T(COMPACT, ASM, 256);                              \
@@ -387,8 +390,8 @@ hipError_t launch_ingest(const StaticView &S, const BatchView &B, const int32_t 
     }
 #undef SAM_LAUNCH_PROMPT
 #undef SAM_LAUNCH_PROMPT_T
-    if ((e = hipGetLastError()) != hipSuccess || !bulk) return e;
-    return launch_bulk_prompts(B, seq_map, n_seqs, tokens, offsets, lds_tokens, max_tokens, false, stream);
+    if ((e = hipGetLastError()) != hipSuccess || !bulk_tokens) return e;
+    return launch_bulk_prompts(B, seq_map, n_seqs, tokens, offsets, lds_tokens, bulk_tokens, false, stream);
 }
 
 }  // namespace sam

@@ -153,3 +153,48 @@ def test_long_prompts_cut_at_a_bad_token(T, vocab):
         assert sam.sam_batch_status(batch) == (sam.SAM_STATUS_TOKEN if ps is whole else 0)
         seen.append(torch.cat([torch.stack(out[:3] + out[5:]).flatten(), draft.flatten()]).cpu())
     assert torch.equal(seen[0], seen[1]) and torch.equal(seen[0], seen[2])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("T", [(1 << 26) - 2, 1 << 26])
+def test_record_tables_around_4_gib(T):
+    """The wide layout's assembly has byte offsets of 32 bits: the largest table it takes, and one that is
+    left to the compiled loop."""
+    from parity_util import assert_same, run_gpu, run_oracle
+    rng = np.random.default_rng(3)
+    prompts = [_text("copies", 7000, 300, rng)]
+    acc = np.resize(prompts[0][3000:], (5, 1, 16)).astype(np.int32)
+    acc[:, :, 7] = rng.integers(0, 300, size=(5, 1))
+    cnt = np.full((5, 1), 16, dtype=np.int32)
+    g, status, _ = run_gpu(None, 300, prompts, acc, cnt, T, 16, 20)
+    r, _ = run_oracle(None, prompts, acc, cnt, 16, 20)
+    assert status == 0
+    assert_same(g, r, has_static=False)
+
+
+@pytest.mark.gpu
+def test_noalloc_batches_with_long_prompts():
+    """sam_batch_init_noalloc with prompts beyond LDS (its tables are 32 MB, its calls make no allocation),
+    then with short ones, against sam_batch_init."""
+    import torch
+    from paper_2411_10666_amd import binding as sam
+    rng = np.random.default_rng(8)
+    dev, T, vocab = torch.device("cuda"), 15_000, 900
+    for lengths in ((14_000, 200, 9000), (500, 20, 63)):
+        prompts = [_text("copies", n, vocab, rng) for n in lengths]
+        offs = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+        flat, d_offs = torch.from_numpy(np.concatenate(prompts)).to(dev), torch.from_numpy(offs).to(dev)
+        seen = []
+        for noalloc in (True, False):
+            batch = (sam.sam_batch_init_noalloc(None, flat, d_offs, offs, 3, vocab, T, 8, 8) if noalloc
+                     else sam.sam_batch_init(None, flat, d_offs, 3, vocab, T, 8, 8))
+            out = [torch.zeros(3, dtype=torch.int32, device=dev) for _ in range(10)]
+            draft = torch.zeros(3, 8, dtype=torch.int32, device=dev)
+            row = torch.from_numpy(np.stack([np.resize(p[5:], 8) for p in prompts])).to(dev)
+            sam.sam_batch_step(batch, row, torch.full_like(out[0], 8), out[0], draft, out[1], out[2])
+            sam.sam_batch_debug(batch, *out[3:7])
+            sam.sam_batch_sizes(batch, *out[7:])
+            assert sam.sam_batch_status(batch) == 0
+            seen.append(torch.cat([torch.stack(out[:3] + out[5:]).flatten(), draft.flatten()]).cpu())
+            del batch
+        assert torch.equal(*seen)
