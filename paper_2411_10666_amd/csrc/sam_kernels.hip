@@ -1929,9 +1929,15 @@ __global__ __launch_bounds__(kScout ? 256 : 128) void sam_feed_kernel(StaticView
 // sequence b through steps 0 .. n_steps-1 on its own, so no sequence waits for
 // the longest row of another and nothing is launched in between.  Step s reads
 // accepted[s, b, :] and counts[s, b] and writes row (s, b) of the outputs.  The
-// cursors stay in registers from step to step.
-template <class L, bool kAsm>
-__global__ __launch_bounds__(128) void sam_replay_kernel(StaticView S, BatchView B, int n_steps,
+// cursors stay in registers from step to step.  A step's count and row are asked for a step
+// ahead, and the static wave chooses and writes a step's draft while the dynamic wave is in the next
+// step already: one barrier a step, which hands over the dynamic cursor.  (512 sequences, rows of
+// up to 12: 5.99 us a step with counts and rows read when needed and two barriers, 5.54 now.)
+// Scouts look ahead over the next step's row, for long sequences: 12 of 30 000 tokens, rows of up to
+// 16, 7.47 us a step without, 6.75 with; but 64 of 4000 5.99 and 6.28, 1024 of 3600 8.18 and 8.27: no
+// sequence waits for the slowest here, and a step of short rows waits for the scouts.
+template <class L, bool kAsm, bool kScout>
+__global__ __launch_bounds__(kScout ? 256 : 128) void sam_replay_kernel(StaticView S, BatchView B, int n_steps,
                                                           const int32_t *__restrict__ accepted,
                                                           const int32_t *__restrict__ counts,
                                                           int32_t *__restrict__ match_len,
@@ -1939,7 +1945,7 @@ __global__ __launch_bounds__(128) void sam_replay_kernel(StaticView S, BatchView
                                                           int32_t *__restrict__ draft_len,
                                                           int32_t *__restrict__ source)
 {
-    __shared__ uint32_t sh[8];
+    __shared__ uint32_t hand[2][4];      // of even and odd steps: the dynamic cursor after them
     const int b = blockIdx.x;
     const int wave = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
@@ -1957,29 +1963,55 @@ __global__ __launch_bounds__(128) void sam_replay_kernel(StaticView S, BatchView
     c.rec_bytes = (uint32_t)B.max_states * (L::kSlots == 16 ? 16u : 32u);
     const uint32_t n_first = n_cur;
 
+    const int at = lane < B.max_accept ? lane : 0;
+    uint32_t next_count = (uint32_t)counts[b];
+    uint32_t next_row = (uint32_t)accepted[(size_t)b * B.max_accept + at];
+
     for (int step = 0; step < n_steps; step++) {
         const int32_t *tok = accepted + ((size_t)step * nb + b) * B.max_accept;
-        int64_t count = counts[(size_t)step * nb + b];
+        int64_t count = (int32_t)uni(next_count);
+        const uint32_t first = next_row;
+        const bool more = step + 1 < n_steps;
+        if (more) {
+            next_count = (uint32_t)counts[(size_t)(step + 1) * nb + b];
+            next_row = (uint32_t)tok[nb * B.max_accept + at];
+        }
+        if (kScout && wave >= 2) {
+            const int64_t ahead = more ? (int64_t)(int32_t)uni(next_count) : 0;
+            if (ahead > 0 && ahead <= B.max_accept) {
+                const uint32_t tk = scout_tokens(next_row, (int)ahead, vocab, lane);
+                const int n_starts = ahead < 64 ? (int)ahead : 64;
+                if (wave == 2) {
+                    if (B.has_static) scout_static(S, tk, n_starts, lane);
+                } else {
+                    if (L::kSlots == 16) scout_dynamic_compact(D, B.max_states, tk, n_starts, lane);
+                    else scout_dynamic_wide(D, B.max_states, tk, n_starts, lane);
+                }
+            }
+            __syncthreads();
+            continue;
+        }
         if (count < 0 || count > B.max_accept) { fault |= SAM_STATUS_COUNT_BIT; count = 0; }
         count = (int64_t)uni((uint32_t)count);
         if ((int64_t)n_cur + count > (int64_t)B.max_seq_len) { fault |= SAM_STATUS_CAPACITY_BIT; count = 0; }
+        uint32_t *const mine = hand[step & 1];
         if (wave == 0) {
-            if (B.has_static) static_feed(S, tok, count, vocab, lane, s, l, e, fault, kAsm);
+            if (B.has_static) static_feed(S, tok, count, vocab, lane, s, l, e, fault, kAsm, true, first);
         } else {
-            dyn_feed<L>(D, tok, count, vocab, lane, c, fault, kAsm);
+            dyn_feed<L>(D, tok, count, vocab, lane, c, fault, kAsm, true, first);
             if (lane == 0) {
-                sh[3] = c.P == kNil ? 0u : c.RP.len;
-                sh[4] = c.P == kNil ? 0u : c.RP.endpos;
-                sh[5] = c.n;
+                mine[0] = c.P == kNil ? 0u : c.RP.len;
+                mine[1] = c.P == kNil ? 0u : c.RP.endpos;
+                mine[2] = c.n;
             }
         }
         __syncthreads();                 // the step's text and wave 1's cursor are visible
-        n_cur = sh[5];
+        // (they are rewritten two steps on, behind the next barrier)
+        n_cur = mine[2];
         if (wave == 0)
-            emit_draft(S, B, b, lane, l, e, sh[3], sh[4], n_cur, match_len + (size_t)step * nb,
+            emit_draft(S, B, b, lane, l, e, mine[0], mine[1], n_cur, match_len + (size_t)step * nb,
                        draft + (size_t)step * nb * B.draft_len, draft_len + (size_t)step * nb,
                        source + (size_t)step * nb);
-        __syncthreads();                 // sh is rewritten by the next step
     }
 
     if (wave == 0) {
@@ -1987,7 +2019,7 @@ __global__ __launch_bounds__(128) void sam_replay_kernel(StaticView S, BatchView
             meta->s1 = s; meta->l1 = l; meta->e1 = e;
             if (fault & SAM_STATUS_INTERNAL_BIT) atomicOr(B.status, SAM_STATUS_INTERNAL_BIT);
         }
-    } else {
+    } else if (wave == 1) {
         if (c.n != n_first) flush_last<L>(D, c, lane);
         if (lane == 0) {
             store_cursor<L>(meta, c);
@@ -2288,14 +2320,22 @@ hipError_t launch_feed(const StaticView &S, const BatchView &B, const int32_t *s
     return hipGetLastError();
 }
 
+constexpr uint32_t kReplayScoutMinSeqLen = 14000;      // see the kernel
+
 hipError_t launch_replay(const StaticView &S, const BatchView &B, int n_steps,
                          const int32_t *accepted, const int32_t *counts, int32_t *match_len,
                          int32_t *draft, int32_t *draft_len, int32_t *source, hipStream_t stream)
 {
-    const dim3 grid(B.batch), block(128);
-#define SAM_LAUNCH_REPLAY(LAYOUT, ASM)                                                         \
-    hipLaunchKernelGGL((sam_replay_kernel<LAYOUT, ASM>), grid, block, 0, stream, S, B, n_steps, \
-                       accepted, counts, match_len, draft, draft_len, source)
+    const bool scout = B.scout && B.max_seq_len >= kReplayScoutMinSeqLen;
+    const dim3 grid(B.batch), block(scout ? 256 : 128);
+#define SAM_LAUNCH_REPLAY_S(LAYOUT, ASM, SCOUT)                                                 \
+    hipLaunchKernelGGL((sam_replay_kernel<LAYOUT, ASM, SCOUT>), grid, block, 0, stream, S, B,   \
+                       n_steps, accepted, counts, match_len, draft, draft_len, source)
+#define SAM_LAUNCH_REPLAY(LAYOUT, ASM)                                                          \
+    do {                                                                                        \
+        if (scout) SAM_LAUNCH_REPLAY_S(LAYOUT, ASM, true);                                       \
+        else SAM_LAUNCH_REPLAY_S(LAYOUT, ASM, false);                                            \
+    } while (0)
     const bool cxx = B.no_asm || (S.n_buckets >> 32);
     if (B.compact) {
         if (cxx) SAM_LAUNCH_REPLAY(CompactDyn, false); else SAM_LAUNCH_REPLAY(CompactDyn, true);
@@ -2304,6 +2344,7 @@ hipError_t launch_replay(const StaticView &S, const BatchView &B, int n_steps,
     } else {
         if (cxx) SAM_LAUNCH_REPLAY(WideDyn, false); else SAM_LAUNCH_REPLAY(WideDyn, true);
     }
+#undef SAM_LAUNCH_REPLAY_S
 #undef SAM_LAUNCH_REPLAY
     return hipGetLastError();
 }

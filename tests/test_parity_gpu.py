@@ -710,6 +710,50 @@ def test_replay_equals_stepwise(seed, vocab, with_corpus):
     assert sam.sam_batch_status(batch) == want
 
 
+@pytest.mark.parametrize("T,A,mode", [(13_999, 5, 0), (14_000, 1, 0), (14_000, 4, 0), (14_000, 70, 4), (14_000, 70, 0),
+                                      (30_000, 70, 0), (30_000, 16, 4)])
+def test_replay_of_long_sequences_equals_steps(T, A, mode):
+    """From 14000 tokens on, rows of 4 and more, the replay has scout waves; it reads counts and
+    rows a step ahead, also past faulty rows and of a single step.  Both table layouts and forms
+    of the token loops, against the step calls on a batch of the same prompts."""
+    import torch
+    from paper_2411_10666_amd import binding as sam
+    dev = torch.device("cuda:0")
+    B, L, steps, vocab = 3, 9, 40, 30
+    _say("replay of long sequences T=%d A=%d mode=%d" % (T, A, mode))
+    corpus, prompts, acc, counts = _random_case(95, vocab, 3000, B, T, A, L, steps)
+    counts[steps - 3, 1] = -1
+    counts[1, 2] = A + 1
+    acc[2, 0, 0], counts[2, 0] = vocab, 1
+    offs = np.zeros(B + 1, np.int64); offs[1:] = np.cumsum([len(p) for p in prompts])
+    i32 = dict(dtype=torch.int32, device=dev)
+    flat, offs = torch.from_numpy(np.concatenate(prompts)).to(dev), torch.from_numpy(offs).to(dev)
+    acc, counts = torch.from_numpy(acc).to(dev), torch.from_numpy(counts).to(dev)
+    gc = sam.sam_build(corpus, vocab)
+    sam.sam_set_layout_override(mode)
+    try:
+        batches = [sam.sam_batch_init(gc, flat, offs, B, vocab, T, A, L) for _ in range(2)]
+        outs = [[torch.zeros(steps, B, **i32), torch.zeros(steps, B, L, **i32),
+                 torch.zeros(steps, B, **i32), torch.zeros(steps, B, **i32)] for _ in range(2)]
+        for lo, hi in ((0, 1), (1, steps)):
+            sam.sam_batch_replay(batches[0], acc[lo:hi], counts[lo:hi], *[o[lo:hi] for o in outs[0]])
+        for s_ in range(steps):
+            sam.sam_batch_step(batches[1], acc[s_], counts[s_], *[o[s_] for o in outs[1]])
+    finally:
+        sam.sam_set_layout_override(0)
+    torch.cuda.synchronize()
+    after = []
+    for batch in batches:
+        cur, siz = [torch.empty(B, **i32) for _ in range(4)], [torch.empty(B, **i32) for _ in range(3)]
+        sam.sam_batch_debug(batch, *cur)
+        sam.sam_batch_sizes(batch, *siz)
+        after.append(torch.stack(cur + siz).cpu().numpy())
+    for a, b in zip(*outs):
+        assert np.array_equal(a.cpu().numpy(), b.cpu().numpy())
+    assert np.array_equal(*after)
+    assert [sam.sam_batch_status(b) for b in batches] == 2 * [sam.SAM_STATUS_COUNT | sam.SAM_STATUS_TOKEN]
+
+
 def test_reset_recycles_sequences():
     """Continuous batching: some sequences are replaced by new requests in the
     middle of a run; the others carry on untouched."""
