@@ -299,6 +299,11 @@ struct BulkTables {
     uint32_t n_buckets;
     const int32_t *tok;
     uint32_t n;
+    // The root gets a transition for every different token of the text, and exchanges of its list's head
+    // follow each other: a workgroup chains its own in LDS ([0] the last slot, kNil at first; [1] the
+    // first one) and hangs the chain into the root's list at its end.  (Walks of 12 prompts of 40 001
+    // tokens, vocabulary 32 000: 325 us with an exchange for each, 190 so; 512 of 8000 1.47 ms, 1.30.)
+    uint32_t *chain = nullptr;
 
     SAM_HD void store(uint32_t s, uint32_t len, uint32_t link, uint32_t endpos, uint32_t itok, uint32_t idst) const
     {
@@ -325,7 +330,15 @@ struct BulkTables {
     template <class C>
     SAM_HD void enter(C &ctx, uint32_t at, uint32_t v, uint32_t, uint32_t endpos, uint32_t dst) const
     {
-        L::fill(ctx, rec, slots, at, v, endpos, dst);
+        if (v) { L::fill(ctx, rec, slots, at, v, endpos, dst); return; }
+        const uint32_t before = ctx.exch(&chain[0], at);
+        if (before == kNil) chain[1] = at;
+        L::link_slot(slots, at, dst, before);
+    }
+    template <class C>
+    SAM_HD void hang(C &ctx) const
+    {
+        if (chain[0] != kNil) L::hang(ctx, rec, slots, chain[0], chain[1]);
     }
 };
 
@@ -341,6 +354,7 @@ struct BulkCorpus {
     RootEnt *root;
     const int32_t *tok;
     uint32_t n;
+    uint32_t *chain = nullptr;   // none is needed: the root's are in a table by token
 
     SAM_HD void store(uint32_t s, uint32_t len, uint32_t link, uint32_t endpos, uint32_t, uint32_t idst) const
     {
@@ -380,6 +394,8 @@ struct BulkCorpus {
         if (v == 0) root[t].dst = to;
         else dst[at] = to;
     }
+    template <class C>
+    SAM_HD void hang(C &) const {}
 };
 
 // ---- states and transitions -------------------------------------------------------

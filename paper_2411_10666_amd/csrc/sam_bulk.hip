@@ -610,9 +610,9 @@ enum class Phase { kOrder, kCommon, kInterval, kRepresent, kParent, kLeaf, kFirs
 
 // Three phases have hot spots: the nodes of frequent tokens, and the transitions between them, which
 // thousands of positions ask for at once.  Atomics on one address follow each other, so these phases
-// are launched in two parts, a twentieth of the text first (part: in 64ths): the other reads what the
-// first wrote and passes by.  (One launch: 700 000 tokens of corpus first ends 175 us, second ones 130,
-// walks 368.)
+// are launched in parts, a small one of the text first (part: in 64ths): the others read what it
+// wrote and pass by.  (700 000 tokens of corpus: first ends 175 us in one launch, 70 in two; second
+// ones 130, 40; walks 368, 300 in four.)
 struct Part { uint32_t lo, hi; };
 __host__ __device__ __forceinline__ uint32_t part_of(uint32_t count, uint32_t part)
 {
@@ -672,10 +672,11 @@ __global__ __launch_bounds__(256) void bulk_phase_kernel(Src src, uint32_t token
         for (size_t i = from; i < wipes; i += step) wipe[i] = make_uint4(kNil, kNil, kNil, kNil);
         for (uint32_t v = from; v < states; v += step) bulk_settle(ctx, q, out, states, v);
     } else if constexpr (P == Phase::kWalk) {
-        const auto out = src.store(blockIdx.y, q);
+        auto out = src.store(blockIdx.y, q);
         const uint32_t states = q.counts[kCntStates];
-        __shared__ uint32_t list[256], total;
-        if (threadIdx.x == 0) total = 0;
+        __shared__ uint32_t list[256], chain[2], total;
+        out.chain = chain;
+        if (threadIdx.x == 0) { total = 0; chain[0] = kNil; }
         __syncthreads();
         uint32_t made = 0;
         const uint32_t end = part_of(states, part.hi);
@@ -695,7 +696,10 @@ __global__ __launch_bounds__(256) void bulk_phase_kernel(Src src, uint32_t token
         made = wave_total(made);
         if (made && lane_id() == 0) atomicAdd(&total, made);
         __syncthreads();
-        if (threadIdx.x == 0 && total) ctx.add(&q.counts[kCntMade], total);
+        if (threadIdx.x == 0) {
+            out.hang(ctx);
+            if (total) ctx.add(&q.counts[kCntMade], total);
+        }
     } else {
         const IngestTree<I> t = q.tree();
         if constexpr (P == Phase::kParent)

@@ -1,4 +1,4 @@
-// A prompt's automaton built by a whole workgroup at once.
+// An automaton built from its whole text at once; here a prompt's, by one workgroup.
 //
 // Online extension (Algorithm 2) is a serial chain: one token after the other, each with
 // two or three dependent memory round trips.  A prompt is known in full, though, and what
@@ -155,6 +155,18 @@ struct IngestWide {
     {
         return ctx.fresh(&(reinterpret_cast<DynRec *>(rec) + s)->head);
     }
+    // transitions of the root that were chained apart: one more, and the whole chain into the root's list
+    static SAM_HD void link_slot(void *slots, uint32_t at, uint32_t dst, uint32_t next)
+    {
+        Slot *s = reinterpret_cast<Slot *>(slots) + at;
+        s->dst = dst;
+        s->w = next;
+    }
+    template <class C>
+    static SAM_HD void hang(C &ctx, void *rec, void *slots, uint32_t head, uint32_t tail)
+    {
+        (reinterpret_cast<Slot *>(slots) + tail)->w = ctx.exch(&reinterpret_cast<DynRec *>(rec)->head, head);
+    }
 };
 
 struct IngestCompact {
@@ -217,6 +229,14 @@ struct IngestCompact {
     static SAM_HD uint32_t head(C &ctx, void *rec, uint32_t s)
     {
         return widen(ctx.fresh(reinterpret_cast<uint32_t *>(rec) + 4 * (size_t)s + 1) >> 16);
+    }
+    static SAM_HD void link_slot(void *slots, uint32_t at, uint32_t dst, uint32_t next) { fill_next(slots, at, dst, next & 0xFFFFu); }
+    // the root's end position is 0
+    template <class C>
+    static SAM_HD void hang(C &ctx, void *rec, void *slots, uint32_t head, uint32_t tail)
+    {
+        const uint32_t old = ctx.exch(reinterpret_cast<uint32_t *>(rec) + 1, head << 16);
+        reinterpret_cast<uint16_t *>(slots)[4 * (size_t)tail + 3] = (uint16_t)(old >> 16);
     }
 };
 

@@ -18,7 +18,8 @@ namespace sam {
 // LDS and table accesses between about sixty barriers: the LDS pipeline is busy for 28 % of
 // the cycles, the vector ALUs for 37 %.  Measured, sam_batch_reset: one prompt of 6000 tokens 222 us,
 // 64 of 2048 137 us (1.2 ms token by token), 1024 of 2048 465 us, 1024 of 6000 1.19 ms (5.3 ms).  With
-// the arrays in the sequence's own tables the bound is the rate at which one compute unit gets
+// the arrays in the sequence's own tables (prompts beyond LDS, where the whole chip does not take them,
+// see launch_ingest) the bound is the rate at which one compute unit gets
 // scattered requests to the L2 through, 0.5 to 0.6 a nanosecond: 12 prompts of 40 001 tokens
 // 3.6 ms (46 ms).  Of the 165 us that one workgroup needs for 6000 tokens, the sort takes 75, the
 // intervals 19 and the transitions 61 (a compare-and-swap in the slot table each).  Two parts
@@ -362,7 +363,7 @@ hipError_t launch_ingest(const StaticView &S, const BatchView &B, const int32_t 
     // Prompts beyond LDS are built by the whole chip, phase by phase, wherever their tables have room for
     // that: one workgroup each is bound by the scattered accesses of its compute unit even where there
     // are more of them than units (sam_batch_reset, chip / workgroups, us: 1 prompt of 6500 tokens 0.45 /
-    // 1.1 ms, 1 of 40 001 0.9 / 7.6, 12 of 40 001 1.2 / 8.1, 64 of 40 001 4.0 / 10.6, 256 of 6500 1.9 / 2.2, 600 of
+    // 1.1 ms, 1 of 40 001 0.9 / 7.6, 12 of 40 001 1.1 / 8.1, 64 of 40 001 4.0 / 10.6, 256 of 6500 1.9 / 2.2, 600 of
     // 8000 4.2 / 5.8).  Of one token only, 3 of 16 000 tokens take 1.9 ms against 1.7; 3 of 40 001 4.5 against 5.0.
     // (A captured call that is replayed with longer prompts than it was captured with leaves those to one
     // workgroup each: its launches are made for the longest that the host knows of.)

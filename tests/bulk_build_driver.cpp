@@ -143,14 +143,20 @@ static uint32_t states_of(CpuCtx &ctx, BulkSeq<I> &q, uint32_t vocab, uint32_t k
 }
 
 template <class I, class S>
-static void transitions(CpuCtx &ctx, BulkSeq<I> &q, const S &out, uint32_t states)
+static void transitions(CpuCtx &ctx, BulkSeq<I> &q, S out, uint32_t states)
 {
-    uint32_t list[64];
+    uint32_t list[64], chain[2] = {kNil, kNil};
+    out.chain = chain;
     for (uint32_t v = 0; v < states; v++) {
         BulkWalk w;
         q.counts[kCntMade] += bulk_walk(ctx, q, out, states, v, w);
         if (w.more) bulk_long_walk(ctx, q, out, states, w, list);
+        if (v % 300 == 299) {                        // as if a workgroup ended here
+            out.hang(ctx);
+            chain[0] = kNil;
+        }
     }
+    out.hang(ctx);
 }
 
 template <class IL, class I>
