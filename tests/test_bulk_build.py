@@ -1,5 +1,5 @@
 """Automata built by the whole chip, phase by phase: corpora against the host builder, prompts too
-long for LDS against the CPU checker (their sizes: test_prompt_gpu.py), everything bit-exact."""
+long for LDS against the oracle (their sizes: test_prompt_gpu.py), everything bit-exact."""
 import os
 import shutil
 import subprocess
