@@ -333,6 +333,7 @@ static int corpus_build_device(sam_corpus *c, const int32_t *tokens, int64_t n, 
     *done = false;
     const uint64_t n_buckets = static_buckets_for(n), n_slots = n_buckets * kBucketSlots;
     if (n_slots >= 0xFFFFFFFFull) return SAM_OK;
+    bool room = false;             // the thread below writes it: it outlives scratch, which waits for the thread
     struct Scratch {
         std::vector<void *> all;
         std::thread host;
@@ -378,7 +379,6 @@ static int corpus_build_device(sam_corpus *c, const int32_t *tokens, int64_t n, 
     w.counts = (uint32_t *)(w.third + b3);
     w.rec = (BulkCorpus::State *)((char *)w.counts + bulk_up(4 * kBulkCounts));
     // the host's memory is made ready while the device works
-    bool room = false;
     try {
         scratch.host = std::thread([&] { room = c->host.reserve_for_copy(tokens, n, vocab, n_buckets); });
     } catch (...) {
