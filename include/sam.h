@@ -74,8 +74,9 @@ const char *sam_build_id(void);
 
 /*
  * Build-SAM (Algorithm 2) over `corpus_tokens`: on the device, by all of it at once, for corpora of
- * 10 000 tokens and more, on the host for smaller ones and where the device has no room for the
- * working arrays (about 200 bytes a token while it builds).  The automaton is the same.  Device
+ * 10 000 tokens and more, on the host for smaller ones, where the device has no room to build
+ * in (about 207 bytes a token while it does) and where more than 8 388 608 positions of the corpus
+ * end in the same few tokens.  The automaton is the same.  Device
  * memory then holds it as flat arrays: the corpus text, one record per
  * state with its suffix link, the link's length and up to two of its
  * transitions, a direct-indexed table of the root's transitions and a bucketed
@@ -353,7 +354,9 @@ int sam_batch_status(const sam_batch *batch, uint32_t *status, void *hip_stream)
  * out whatever the sizes (for measuring what they cost and bring); bit 6
  * makes every later sam_build build on the device however small the corpus; bit 7
  * keeps the builds by the whole chip out: corpora are built on the host, prompts
- * too long for LDS by one workgroup each.  mode 0 restores the defaults.  Results are identical in every mode.
+ * too long for LDS by one workgroup each; bits 8 to 10 hold the number of the device allocation (1 to 5, in
+ * the order in which they are made) that fails in every later sam_build on the device, so that the host
+ * builds.  mode 0 restores the defaults.  Results are identical in every mode.
  */
 int sam_set_layout_override(int mode);
 

@@ -30,7 +30,7 @@ int g_layout_override = 0;   // bit 0: always the wide layout, bit 1: tight slot
                              // bit 2: C++ token loops, bit 3: corpus table beyond 4 GiB,
                              // bit 4: scout waves whatever the batch size, bit 5: never,
                              // bit 6: corpora on the device whatever their size,
-                             // bit 7: no builds by the whole chip
+                             // bit 7: no builds by the whole chip, bits 8 to 10: see build_malloc
 // Scout waves pay where a step's rows are long enough to be looked at ahead of the walks, and the
 // sequences' tables are not in the L2 when it starts: because they fill it (12 of its 32 MB or more),
 // or because long prompts were built elsewhere and only their ends have been walked since.  Measured,
@@ -165,8 +165,20 @@ struct FinishScratch {
 };
 static size_t wide_bytes(uint32_t n_states) { return ((size_t)n_states + 31) / 32 * sizeof(uint32_t); }
 
-// What is on the device already: text, the root's transitions, the table of all others and the link
-// pairs.  State records are made from them, and the walks' table.
+// Device memory of sam_build.  Testing: the request that bits 8 to 10 of the layout override name finds none.
+enum BuildMemory { kNoRequest, kText, kRoot, kWork, kSlots, kRecords };
+static bool build_malloc(BuildMemory which, void **p, size_t bytes)
+{
+    *p = nullptr;
+    if (which == ((g_layout_override >> 8) & 7)) return false;
+    if (hipMalloc(p, bytes) == hipSuccess) return true;
+    (void)hipGetLastError();
+    *p = nullptr;
+    return false;
+}
+
+// What is on the device already: text, the root's transitions, the table of all others, the link
+// pairs and room for the state records, which are made from them, as is the walks' table.
 static int corpus_finish(sam_corpus *c, const FinishScratch &w)
 {
     const HostSam &h = c->host;
@@ -174,8 +186,7 @@ static int corpus_finish(sam_corpus *c, const FinishScratch &w)
     const size_t b_lr = (size_t)h.n_states * sizeof(LinkRec);
     const size_t b_root = (size_t)h.vocab * sizeof(RootEnt);
     // link pairs -> 32-byte state records with two transitions inline
-    hipError_t e = hipMalloc(&c->d_linkrec, b_lr);
-    if (e == hipSuccess) e = hipMemset(w.wide, 0, wide_bytes(h.n_states));
+    hipError_t e = hipMemset(w.wide, 0, wide_bytes(h.n_states));
     if (e == hipSuccess)
         e = launch_staterec(w.pairs, (Slot *)c->d_slots, (RootEnt *)c->d_root, (LinkRec *)c->d_linkrec,
                             w.wide, h.n_states, h.n_buckets * kBucketSlots, (uint32_t)h.vocab, nullptr);
@@ -253,6 +264,7 @@ static int corpus_upload(sam_corpus *c)
     HIP_TRY(hipMalloc(&c->d_text, b_text));
     HIP_TRY(hipMalloc(&c->d_root, b_root));
     HIP_TRY(hipMalloc(&c->d_slots, b_slots));
+    HIP_TRY(hipMalloc(&c->d_linkrec, (size_t)h.n_states * sizeof(LinkRec)));
     HIP_TRY(hipMemcpy(c->d_text, h.text.data(), b_text, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(c->d_root, h.root.data(), b_root, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(c->d_slots, h.slots, b_slots, hipMemcpyHostToDevice));
@@ -335,45 +347,33 @@ static int corpus_build_device(sam_corpus *c, const int32_t *tokens, int64_t n, 
     if (n_slots >= 0xFFFFFFFFull) return SAM_OK;
     bool room = false;             // the thread below writes it: it outlives scratch, which waits for the thread
     struct Scratch {
-        std::vector<void *> all;
+        void *work = nullptr;
         std::thread host;
         ~Scratch()
         {
             if (host.joinable()) host.join();
-            for (void *p : all) (void)hipFree(p);
+            if (work) (void)hipFree(work);
         }
     } scratch;
-    // every failure to allocate ends here: what was allocated is freed, the host builds
+    // every failure to allocate on the device ends here: what was allocated is freed, the host builds
     auto none = [&] {
-        (void)hipGetLastError();
         if (scratch.host.joinable()) scratch.host.join();
         corpus_release_device(c);
         c->host.~HostSam();
         new (&c->host) HostSam();
         return SAM_OK;
     };
-    auto take = [&](void **p, size_t bytes) {
-        if (hipMalloc(p, bytes) != hipSuccess) return false;
-        scratch.all.push_back(*p);
-        return true;
-    };
     HIP_TRY(hipGetDevice(&c->device));
     hipError_t e;
     const uint32_t un = (uint32_t)n;
     BulkWork w;
-    if (hipMalloc(&c->d_text, (size_t)n * sizeof(int32_t)) != hipSuccess ||
-        hipMalloc(&c->d_root, (size_t)vocab * sizeof(RootEnt)) != hipSuccess)
+    if (!build_malloc(kText, &c->d_text, (size_t)n * sizeof(int32_t)) ||
+        !build_malloc(kRoot, &c->d_root, (size_t)vocab * sizeof(RootEnt)))
         return none();
     const size_t b1 = bulk_first_bytes(un), b2 = bulk_up(bulk_second_bytes<uint32_t>(un)), b3 = bulk_up(bulk_third_bytes(un)),
                  br = (2 * (size_t)n + 1) * sizeof(BulkCorpus::State);
-    char *work = nullptr;
-    try {
-        scratch.all.reserve(4);
-    } catch (const std::bad_alloc &) {
-        return none();
-    }
-    if (!take((void **)&work, bulk_up(b1) + b2 + b3 + bulk_up(4 * kBulkCounts) + br)) return none();
-    w.first = work;
+    if (!build_malloc(kWork, &scratch.work, bulk_up(b1) + b2 + b3 + bulk_up(4 * kBulkCounts) + br)) return none();
+    w.first = (char *)scratch.work;
     w.second = w.first + bulk_up(b1);
     w.third = w.second + b2;
     w.counts = (uint32_t *)(w.third + b3);
@@ -400,7 +400,11 @@ static int corpus_build_device(sam_corpus *c, const int32_t *tokens, int64_t n, 
                         &gave_up, nullptr));
     if (gave_up) return none();
     if (g_progress) g_progress("finalize", 0, (int64_t)n_slots, g_progress_user);
-    if (hipMalloc(&c->d_slots, n_slots * sizeof(Slot)) != hipSuccess) return none();
+    // (the last two requests that the build cannot do without, and the most memory that it holds: about
+    // 207 bytes a token, where the host's build needs 130)
+    if (!build_malloc(kSlots, &c->d_slots, n_slots * sizeof(Slot)) ||
+        !build_malloc(kRecords, &c->d_linkrec, (size_t)n_states * sizeof(LinkRec)))
+        return none();
     // the second region (24 bytes a token) and the third (a quarter) are free again
     LinkPair *const d_pairs = (LinkPair *)w.second;
     const FinishScratch finish = {d_pairs, (uint32_t *)w.third, (unsigned long long *)w.counts};
@@ -1018,7 +1022,7 @@ int sam_set_progress_callback(sam_progress_fn fn, void *user)
 
 int sam_set_layout_override(int mode)
 {
-    if (mode < 0 || mode > 255) return fail(SAM_EINVAL, "sam_set_layout_override: mode is 0 .. 255");
+    if (mode < 0 || mode > 2047) return fail(SAM_EINVAL, "sam_set_layout_override: mode is 0 .. 2047");
     g_layout_override = mode;
     return SAM_OK;
 }

@@ -104,6 +104,39 @@ def test_steps_over_a_corpus_built_on_the_device(vocab, n):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("request_", [1, 2, 3, 4, 5])
+def test_no_room_on_the_device_to_build(tmp_path, request_):
+    """Whichever device allocation fails (text, root, working arrays, transitions, state records), the host
+    builds: the file is the one that its builder writes, the corpus serves a batch, and nothing stays behind."""
+    import torch
+    from parity_util import assert_same, run_gpu, run_oracle
+    from paper_2411_10666_amd import binding as sam
+    rng = np.random.default_rng(request_)
+    vocab, n = 400, 300_000
+    x = _text("copies", n, vocab, rng)
+    prompts = [x[k:k + 70].copy() for k in (0, n // 3, n - 70)]
+    acc = np.resize(x[100:], (4, 3, 8)).astype(np.int32)
+    cnt = np.full((4, 3), 8, dtype=np.int32)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    for _ in range(3):
+        try:
+            sam.sam_set_layout_override(request_ << 8)
+            corpus = sam.sam_build(x, vocab)
+        finally:
+            sam.sam_set_layout_override(0)
+        held = sam.sam_corpus_info(corpus)[2]
+    # 3 builds, one of them alive: the working arrays alone are 27 MB
+    assert free - torch.cuda.mem_get_info()[0] < held + (20 << 20)
+    host = sam.sam_build_host_only(x, vocab)
+    assert _saved(corpus, str(tmp_path / "a.sam"), n, vocab)[0] == _saved(host, str(tmp_path / "b.sam"), n, vocab)[0]
+    g, status, _ = run_gpu(x, vocab, prompts, acc, cnt, 200, 8, 10, gpu_corpus=corpus)
+    r, _ = run_oracle(x, prompts, acc, cnt, 8, 10)
+    assert status == 0
+    assert_same(g, r)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("bad", [-1, 50, 2**31 - 1])
 def test_corpus_token_outside_the_vocabulary(bad):
     from paper_2411_10666_amd import binding as sam
