@@ -354,9 +354,10 @@ int sam_batch_status(const sam_batch *batch, uint32_t *status, void *hip_stream)
  * out whatever the sizes (for measuring what they cost and bring); bit 6
  * makes every later sam_build build on the device however small the corpus; bit 7
  * keeps the builds by the whole chip out: corpora are built on the host, prompts
- * too long for LDS by one workgroup each; bits 8 to 10 hold the number of the device allocation (1 to 5, in
+ * too long for LDS by one workgroup each; bits 8 to 10 hold the number of the device allocation (1 to 6, in
  * the order in which they are made) that fails in every later sam_build on the device, so that the host
- * builds.  mode 0 restores the defaults.  Results are identical in every mode.
+ * builds, or 7: that of the smaller transition table at the first try, in every later sam_build and
+ * sam_corpus_load.  mode 0 restores the defaults.  Results are identical in every mode.
  */
 int sam_set_layout_override(int mode);
 

@@ -157,16 +157,17 @@ static void corpus_release_device(sam_corpus *c)
 }
 
 // Device memory that corpus_finish works in, the caller's: the link pairs, a bit for every state
-// and a count.
+// and a count.  done: an allocation that is not read once the records are made (the pairs lie in it).
 struct FinishScratch {
     const LinkPair     *pairs;
     uint32_t           *wide;
     unsigned long long *count;
+    void              **done;
 };
 static size_t wide_bytes(uint32_t n_states) { return ((size_t)n_states + 31) / 32 * sizeof(uint32_t); }
 
 // Device memory of sam_build.  Testing: the request that bits 8 to 10 of the layout override name finds none.
-enum BuildMemory { kNoRequest, kText, kRoot, kWork, kSlots, kRecords };
+enum BuildMemory { kNoRequest, kText, kRoot, kWork, kMarks, kSlots, kRecords, kTable };
 static bool build_malloc(BuildMemory which, void **p, size_t bytes)
 {
     *p = nullptr;
@@ -205,11 +206,18 @@ static int corpus_finish(sam_corpus *c, const FinishScratch &w)
         const uint64_t nb_new = (2 * (uint64_t)n_wide + 64 + kBucketSlots - 1) / kBucketSlots;
         if (e == hipSuccess && nb_new < h.n_buckets) {
             const size_t b_new = (size_t)nb_new * kBucketSlots * sizeof(Slot);
-            if (hipMalloc(&d_new, b_new) != hipSuccess) {
-                // no room for a second table beside the full one: the full one serves
-                (void)hipGetLastError();
-                d_new = nullptr;
-            } else {
+            if (!build_malloc(kTable, &d_new, b_new)) {
+                // no room for a second table beside all the rest: what is not read any more makes room (the
+                // count was waited for, so the records are made)
+                (void)hipFree(*w.done);
+                *w.done = nullptr;
+                if (hipMalloc(&d_new, b_new) != hipSuccess) {
+                    // still none: the full one serves
+                    (void)hipGetLastError();
+                    d_new = nullptr;
+                }
+            }
+            if (d_new) {
                 e = launch_fill_empty(d_new, b_new, nullptr);
                 if (e == hipSuccess)
                     e = launch_compact_slots((const Slot *)c->d_slots, w.wide,
@@ -269,14 +277,15 @@ static int corpus_upload(sam_corpus *c)
     HIP_TRY(hipMemcpy(c->d_root, h.root.data(), b_root, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(c->d_slots, h.slots, b_slots, hipMemcpyHostToDevice));
     const size_t b_wide = bulk_up(wide_bytes(h.n_states));
-    char *scratch = nullptr;
-    HIP_TRY(hipMalloc((void **)&scratch, bulk_up(b_pairs) + b_wide + sizeof(unsigned long long)));
-    const hipError_t e = hipMemcpy(scratch, lr.data(), b_pairs, hipMemcpyHostToDevice);
-    const int rc = e != hipSuccess
-                       ? fail_hip("sam_build: state records", e)
-                       : corpus_finish(c, {(const LinkPair *)scratch, (uint32_t *)(scratch + bulk_up(b_pairs)),
-                                           (unsigned long long *)(scratch + bulk_up(b_pairs) + b_wide)});
-    (void)hipFree(scratch);
+    void *pairs = nullptr, *marks = nullptr;
+    hipError_t e = hipMalloc(&pairs, b_pairs);
+    if (e == hipSuccess) e = hipMalloc(&marks, b_wide + sizeof(unsigned long long));
+    if (e == hipSuccess) e = hipMemcpy(pairs, lr.data(), b_pairs, hipMemcpyHostToDevice);
+    const int rc = e != hipSuccess ? fail_hip("sam_build: state records", e)
+                                   : corpus_finish(c, {(const LinkPair *)pairs, (uint32_t *)marks,
+                                                       (unsigned long long *)((char *)marks + b_wide), &pairs});
+    if (pairs) (void)hipFree(pairs);
+    if (marks) (void)hipFree(marks);
     return rc;
 }
 
@@ -347,12 +356,13 @@ static int corpus_build_device(sam_corpus *c, const int32_t *tokens, int64_t n, 
     if (n_slots >= 0xFFFFFFFFull) return SAM_OK;
     bool room = false;             // the thread below writes it: it outlives scratch, which waits for the thread
     struct Scratch {
-        void *work = nullptr;
+        void *work = nullptr, *marks = nullptr;
         std::thread host;
         ~Scratch()
         {
             if (host.joinable()) host.join();
             if (work) (void)hipFree(work);
+            if (marks) (void)hipFree(marks);
         }
     } scratch;
     // every failure to allocate on the device ends here: what was allocated is freed, the host builds
@@ -372,12 +382,14 @@ static int corpus_build_device(sam_corpus *c, const int32_t *tokens, int64_t n, 
         return none();
     const size_t b1 = bulk_first_bytes(un), b2 = bulk_up(bulk_second_bytes<uint32_t>(un)), b3 = bulk_up(bulk_third_bytes(un)),
                  br = (2 * (size_t)n + 1) * sizeof(BulkCorpus::State);
-    if (!build_malloc(kWork, &scratch.work, bulk_up(b1) + b2 + b3 + bulk_up(4 * kBulkCounts) + br)) return none();
+    if (!build_malloc(kWork, &scratch.work, bulk_up(b1) + b2 + br) ||
+        !build_malloc(kMarks, &scratch.marks, b3 + 4 * kBulkCounts))
+        return none();
     w.first = (char *)scratch.work;
     w.second = w.first + bulk_up(b1);
-    w.third = w.second + b2;
+    w.rec = (BulkCorpus::State *)(w.second + b2);
+    w.third = (char *)scratch.marks;
     w.counts = (uint32_t *)(w.third + b3);
-    w.rec = (BulkCorpus::State *)((char *)w.counts + bulk_up(4 * kBulkCounts));
     // the host's memory is made ready while the device works
     try {
         scratch.host = std::thread([&] { room = c->host.reserve_for_copy(tokens, n, vocab, n_buckets); });
@@ -407,7 +419,7 @@ static int corpus_build_device(sam_corpus *c, const int32_t *tokens, int64_t n, 
         return none();
     // the second region (24 bytes a token) and the third (a quarter) are free again
     LinkPair *const d_pairs = (LinkPair *)w.second;
-    const FinishScratch finish = {d_pairs, (uint32_t *)w.third, (unsigned long long *)w.counts};
+    const FinishScratch finish = {d_pairs, (uint32_t *)w.third, (unsigned long long *)w.counts, &scratch.work};
     e = launch_fill_empty(c->d_slots, n_slots * sizeof(Slot), nullptr);
     if (e == hipSuccess)
         e = bulk_corpus_tables((const int32_t *)c->d_text, un, (uint32_t)vocab, n_states, (RootEnt *)c->d_root, w,

@@ -104,9 +104,9 @@ def test_steps_over_a_corpus_built_on_the_device(vocab, n):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("request_", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("request_", [1, 2, 3, 4, 5, 6])
 def test_no_room_on_the_device_to_build(tmp_path, request_):
-    """Whichever device allocation fails (text, root, working arrays, transitions, state records), the host
+    """Whichever device allocation fails (text, root, two for working arrays, transitions, state records), the host
     builds: the file is the one that its builder writes, the corpus serves a batch, and nothing stays behind."""
     import torch
     from parity_util import assert_same, run_gpu, run_oracle
@@ -131,6 +131,34 @@ def test_no_room_on_the_device_to_build(tmp_path, request_):
     host = sam.sam_build_host_only(x, vocab)
     assert _saved(corpus, str(tmp_path / "a.sam"), n, vocab)[0] == _saved(host, str(tmp_path / "b.sam"), n, vocab)[0]
     g, status, _ = run_gpu(x, vocab, prompts, acc, cnt, 200, 8, 10, gpu_corpus=corpus)
+    r, _ = run_oracle(x, prompts, acc, cnt, 8, 10)
+    assert status == 0
+    assert_same(g, r)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("how", ["device", "host", "file"])
+def test_room_for_the_small_table_is_made(tmp_path, how):
+    """The table that the walks look up is asked for while working memory is still held.  Where there is no
+    room beside that, it is given back first: the full table does not stay."""
+    from parity_util import assert_same, run_gpu, run_oracle
+    from paper_2411_10666_amd import binding as sam
+    rng = np.random.default_rng(4)
+    vocab, n = 300, 40_000
+    x = _text("copies", n, vocab, rng)
+    sam.sam_corpus_save(sam.sam_build_host_only(x, vocab), str(tmp_path / "a.sam"))
+    built = []
+    for mode in (0, 7 << 8):
+        try:
+            sam.sam_set_layout_override(mode | (128 if how == "host" else 0))
+            built.append(sam.sam_corpus_load(str(tmp_path / "a.sam")) if how == "file" else sam.sam_build(x, vocab))
+        finally:
+            sam.sam_set_layout_override(0)
+    assert sam.sam_corpus_info(built[0]) == sam.sam_corpus_info(built[1])        # the device's bytes too
+    prompts = [x[k:k + 70].copy() for k in (0, n // 3, n - 70)]
+    acc = np.resize(x[100:], (4, 3, 8)).astype(np.int32)
+    cnt = np.full((4, 3), 8, dtype=np.int32)
+    g, status, _ = run_gpu(x, vocab, prompts, acc, cnt, 200, 8, 10, gpu_corpus=built[1])
     r, _ = run_oracle(x, prompts, acc, cnt, 8, 10)
     assert status == 0
     assert_same(g, r)
