@@ -160,6 +160,7 @@ struct CorpusSource {
 // ---- lanes working together ---------------------------------------------------------
 
 __device__ __forceinline__ uint32_t lane_id() { return threadIdx.x & 63; }
+__device__ __forceinline__ uint32_t uni(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
 
 __device__ __forceinline__ uint32_t wave_sums(uint32_t v)      // over the lower lanes and this one
 {
@@ -410,16 +411,11 @@ __global__ __launch_bounds__(kSort) void bulk_groups_kernel(Src src, uint32_t fi
     });
 }
 
-// A round of a group that is too large for counting: its places are sorted by their second names, in
-// 3 passes of 8 bits or 5 (an odd number, so that they end in the buffers of the next round), by
-// this workgroup alone.
-template <class I>
-__device__ void bulk_rank_large(SortLds &s, const BulkSeq<I> &q, uint32_t first, uint32_t round, uint32_t g)
+// Sorts `size` places by their second names, 8 bits a pass, from key and pos into to_key and to_pos and
+// back: in the former after an even number of passes.
+__device__ void sort_places(SortLds &s, uint32_t *key, uint32_t *pos, uint32_t *to_key, uint32_t *to_pos, uint32_t size,
+                            uint32_t passes)
 {
-    const uint32_t size = q.gs(round)[g] & ~kBulkStart;
-    uint32_t *key = q.sec + g, *to_key = q.sec2 + g;
-    uint32_t *pos = q.pos(first + round) + g, *to_pos = q.pos(first + round + 1) + g;
-    const uint32_t passes = q.n < (1u << 24) ? 3 : 5;
     for (uint32_t pass = 0; pass < passes; pass++) {
         const uint32_t shift = 8 * pass < 32 ? 8 * pass : 24;      // a fifth pass sorts by the fourth's digit again
         if (threadIdx.x < 256) s.base[threadIdx.x] = 0;
@@ -439,20 +435,216 @@ __device__ void bulk_rank_large(SortLds &s, const BulkSeq<I> &q, uint32_t first,
         key = to_key; pos = to_pos;
         to_key = k; to_pos = p;
     }
-    uint32_t *const to_gs = q.gs(round + 1) + g;
+}
+
+// Groups of the next round among the places from .. from + size of group g, sorted.
+template <class I>
+__device__ void part_sorted(SortLds &s, const BulkSeq<I> &q, uint32_t round, uint32_t g, uint32_t from, uint32_t size,
+                            const uint32_t *key, const uint32_t *pos)
+{
+    uint32_t *const to_gs = q.gs(round + 1) + g + from;
     each_group(s, 0, size, size, 0, [&](uint32_t k) { return key[k] != key[k - 1]; },
                [&](uint32_t k, uint32_t start, bool last) {
-                   if (k != start) to_gs[k] = g + start;
+                   if (k != start) to_gs[k] = g + from + start;
                    if (last) {
                        to_gs[start] = kBulkStart | (k + 1 - start);
-                       announce(q, round + 1, g + start, k + 1 - start);
+                       announce(q, round + 1, g + from + start, k + 1 - start);
                    }
-                   if (start) {
-                       q.name[pos[k]] = g + start;
-                       if (k == start) q.lev[g + k] = (uint8_t)(round + 1);
+                   if (from + start) {
+                       q.name[pos[k]] = g + from + start;
+                       if (k == start) q.lev[g + from + start] = (uint8_t)(round + 1);
                    }
                });
     __syncthreads();
+}
+
+// The same for up to kCounted places that are not sorted: by counting, in LDS.
+constexpr uint32_t kCounted = 256;
+template <class I>
+__device__ void part_counted(SortLds &s, const BulkSeq<I> &q, uint32_t round, uint32_t g, uint32_t from, uint32_t size,
+                             const uint32_t *key, uint32_t *pos)
+{
+    const uint32_t k = threadIdx.x, own = k < size ? key[k] : 0, v = k < size ? pos[k] : 0;
+    if (k < size) s.base[k] = own;
+    __syncthreads();
+    if (k < size) {
+        uint32_t less = 0, same = 0, before = 0;
+#pragma unroll 8
+        for (uint32_t j = 0; j < size; j++) {
+            const uint32_t x = s.base[j];
+            less += x < own;
+            same += x == own;
+            before += x == own && j < k;
+        }
+        const uint32_t start = g + from + less;
+        pos[less + before] = v;
+        q.gs(round + 1)[start + before] = before ? start : kBulkStart | same;
+        if (same > 1) q.ctl[kCtlActive + round + 1] = 1;
+        if (from + less) {
+            q.name[v] = start;
+            if (!before) q.lev[start] = (uint8_t)(round + 1);
+        }
+    }
+    __syncthreads();
+}
+
+// how many of the mask's bits belong to lower lanes
+__device__ __forceinline__ uint32_t lower_bits(unsigned long long mask)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+}
+
+// The places of group g that have the second name `pivot` to where they belong, those with smaller ones
+// in front of them and those with larger ones from `more` on, into to_key and to_pos.  Returns how
+// many are smaller.
+template <class I>
+__device__ uint32_t split_places(SortLds &s, const BulkSeq<I> &q, uint32_t first, uint32_t round, uint32_t g, uint32_t size,
+                                 uint32_t pivot, uint32_t &more)
+{
+    constexpr uint32_t kEach = 4;                    // places of a thread at a time
+    const uint32_t wave = uni(threadIdx.x >> 6), lane = lane_id();
+    const uint32_t *const key = q.sec + g, *const pos = q.pos(first + round) + g;
+    uint32_t *const to_key = q.sec2 + g, *const to_pos = q.pos(first + round + 1) + g;
+    uint32_t less = 0, same = 0;
+    for (uint32_t base = 0; base < size; base += kSort * kEach) {
+        uint32_t k[kEach];
+#pragma unroll
+        for (uint32_t r = 0; r < kEach; r++) {
+            const uint32_t at = base + r * kSort + threadIdx.x;
+            k[r] = key[at < size ? at : size - 1];   // (no branches: all loads are under way at once)
+            if (at >= size) k[r] = kNil;
+        }
+#pragma unroll
+        for (uint32_t r = 0; r < kEach; r++) {
+            less += k[r] < pivot;
+            same += k[r] == pivot;
+        }
+    }
+    less = wave_total(less);
+    same = wave_total(same);
+    if (lane == 0) { s.base[wave] = less; s.base[kWaves + wave] = same; }
+    __syncthreads();
+    less = same = 0;
+    for (uint32_t w = 0; w < kWaves; w++) { less += s.base[w]; same += s.base[kWaves + w]; }
+    less = uni(less);
+    same = uni(same);
+    more = less + same;
+    const uint32_t start = g + less;
+    uint32_t *const to_gs = q.gs(round + 1);
+    uint32_t at_less = 0, at_same = 0, at_more = more;       // where the next tile's go
+    // a wave takes 64 * kEach places side by side, and asks for the next ones before it stores these: a wait for
+    // loads is one for all stores before them
+    uint32_t next_k[kEach], next_v[kEach];
+    auto ask = [&](uint32_t lo) {
+#pragma unroll
+        for (uint32_t r = 0; r < kEach; r++) {
+            const uint32_t at = lo + 64 * r + lane, there = at < size ? at : size - 1;
+            next_k[r] = key[there];
+            next_v[r] = pos[there];
+        }
+    };
+    ask(wave * (64 * kEach));
+    for (uint32_t base = 0, turn = 0; base < size; base += kSort * kEach, turn ^= 1) {
+        uint32_t k[kEach], v[kEach];
+        uint32_t rank[kEach];                        // how many smaller ones of this wave are before it; equal ones above
+        const uint32_t lo = base + wave * (64 * kEach);
+#pragma unroll
+        for (uint32_t r = 0; r < kEach; r++) {
+            k[r] = lo + 64 * r + lane < size ? next_k[r] : kNil;
+            v[r] = next_v[r];
+        }
+        ask(lo + kSort * kEach);
+        uint32_t mine_less = 0, mine_same = 0;
+#pragma unroll
+        for (uint32_t r = 0; r < kEach; r++) {
+            const unsigned long long is_less = __ballot(k[r] < pivot), is_same = __ballot(k[r] == pivot);
+            rank[r] = (mine_less + lower_bits(is_less)) | (mine_same + lower_bits(is_same)) << 16;
+            mine_less += (uint32_t)__popcll(is_less);
+            mine_same += (uint32_t)__popcll(is_same);
+        }
+        // (the counts of the tile before are read until the barrier of the next one)
+        uint32_t *const part = s.count[turn];
+        if (lane == 0) { part[wave] = mine_less; part[kWaves + wave] = mine_same; }
+        __syncthreads();
+        uint32_t below = at_less, equal = at_same, above = at_more, all_less = 0, all_same = 0;
+        for (uint32_t w = 0; w < kWaves; w++) {
+            const uint32_t l = uni(part[w]), e = uni(part[kWaves + w]);
+            if (w < wave) {
+                below += l;
+                equal += e;
+                above += 64 * kEach - l - e;                 // (all of an earlier wave's are there)
+            }
+            all_less += l;
+            all_same += e;
+        }
+#pragma unroll
+        for (uint32_t r = 0; r < kEach; r++) {
+            const uint32_t l = rank[r] & 0xFFFFu, e = rank[r] >> 16;
+            if (lo + 64 * r + lane >= size) continue;
+            if (k[r] == pivot) {
+                const uint32_t place = equal + e;
+                to_pos[less + place] = v[r];
+                to_gs[start + place] = place ? start : kBulkStart | same;
+                if (less) q.name[v[r]] = start;
+            } else {
+                const uint32_t place = k[r] < pivot ? below + l : above + 64 * r + lane - l - e;
+                to_key[place] = k[r];
+                to_pos[place] = v[r];
+            }
+        }
+        at_less += all_less;
+        at_same += all_same;
+        at_more += kSort * kEach - all_less - all_same;      // (of the last tile: not used any more)
+    }
+    if (threadIdx.x == 0) {
+        announce(q, round + 1, start, same);
+        if (less) q.lev[start] = (uint8_t)(round + 1);
+    }
+    __syncthreads();
+    return less;
+}
+
+// A round of a group that is too large for counting, by this workgroup alone: its places are sorted by
+// their second names, in 3 passes or 5 (an odd number, so that they end in the buffers of the next round).
+// In runs of a token and in short periods most of the group's second names are the same, round after
+// round: there one pass takes those to their place, in front of them the smaller ones and behind the
+// larger ones, and only these are sorted.  What bounds it is one workgroup's round trips, 2.3 us for 2048
+// places.  (sam_build, ms, all places sorted / so / the host's builder: 700 000 equal tokens 101 / 25 / 39,
+// 8 M of them 1350 / 305 / 556, 100 000 11.5 / 3.8 / 2.6, 700 000 in a period of two 54 / 15 / 41.
+// sam_batch_reset of 600 prompts of 8000 equal tokens: 10.4 / 2.7, one workgroup each in all phases 3.1.)
+template <class I>
+__device__ void bulk_rank_large(SortLds &s, const BulkSeq<I> &q, uint32_t first, uint32_t round, uint32_t g)
+{
+    const uint32_t size = uni(q.gs(round)[g]) & ~kBulkStart, lane = lane_id();
+    uint32_t *const key = q.sec + g, *const to_key = q.sec2 + g;
+    uint32_t *const pos = q.pos(first + round) + g, *const to_pos = q.pos(first + round + 1) + g;
+    // the most frequent of 64 second names, and how many of them it is
+    const uint32_t sample = key[(uint64_t)size * lane / 64];
+    uint32_t alike = 0;
+    for (int d = 0; d < 64; d++) alike += (uint32_t)__shfl((int)sample, d) == sample;
+    uint32_t most = alike;
+    for (int d = 32; d; d /= 2) {
+        const uint32_t other = (uint32_t)__shfl_xor((int)most, d);
+        most = other > most ? other : most;
+    }
+    // split: what is smaller has come to the front, what is larger behind `more`
+    uint32_t more = 0, count = size, passes = q.n < (1u << 24) ? 3 : 5;
+    const bool split = uni(most) >= 32;
+    if (split) {
+        const uint32_t pivot = (uint32_t)__builtin_amdgcn_readlane((int)sample, __builtin_ctzll(__ballot(alike == most)));
+        count = split_places(s, q, first, round, g, size, pivot, more);
+        passes = q.n < (1u << 16) ? 2 : 4;
+    }
+    for (uint32_t from = 0;; from = more, count = size - more) {
+        if (count > kCounted) {
+            sort_places(s, (split ? to_key : key) + from, (split ? to_pos : pos) + from, (split ? key : to_key) + from,
+                        (split ? pos : to_pos) + from, count, passes);
+            part_sorted(s, q, round, g, from, count, to_key + from, to_pos + from);
+        } else if (count) {
+            part_counted(s, q, round, g, from, count, to_key + from, to_pos + from);
+        }
+        if (from == more) break;
+    }
 }
 
 template <class Src>
@@ -465,9 +657,11 @@ __global__ __launch_bounds__(256) void bulk_gather_kernel(Src src, uint32_t firs
 }
 
 // Workgroups 0 .. n_large-1 take the large groups, the others a run of places each.  The second names
-// of a group lie side by side, so what bounds this is counting: 12 operations for four of them.
+// of a group lie side by side, so what bounds this is counting: 12 operations for four of them.  (72
+// registers let seven waves into a SIMD; with the 107 that the large groups' part would take, four, the
+// counting of 600 prompts of 8000 tokens takes 3 to 10 % longer.)
 template <class Src>
-__global__ __launch_bounds__(kSort) void bulk_rank_kernel(Src src, uint32_t first, uint32_t round, uint32_t h,
+__global__ __launch_bounds__(kSort) __attribute__((amdgpu_num_vgpr(72))) void bulk_rank_kernel(Src src, uint32_t first, uint32_t round, uint32_t h,
                                                          uint32_t n_large)
 {
     __shared__ SortLds s;
@@ -476,7 +670,7 @@ __global__ __launch_bounds__(kSort) void bulk_rank_kernel(Src src, uint32_t firs
     if (blockIdx.x < n_large) {
         const uint32_t queued = q.ctl[kCtlQueued + round];
         for (uint32_t j = blockIdx.x; j < queued; j += n_large)
-            bulk_rank_large(s, q, first, round, q.queue(round)[j]);
+            bulk_rank_large(s, q, first, round, uni(q.queue(round)[j]));
         return;
     }
     bool more = false;
@@ -981,7 +1175,9 @@ void launch_round(const Src &src, uint32_t n, uint32_t n_seqs, const BulkSort &s
     const uint32_t first = (sort.passes - 1) & 1, large = n / kBulkLarge < 64 ? n / kBulkLarge + 1 : (n < (1u << 20) ? 64 : 1024);
     hipLaunchKernelGGL((bulk_gather_kernel<Src>), grid_for(n, 256, n_seqs), dim3(256), 0, stream, src, first, round, h);
     dim3 g = grid_for(n, kSort, n_seqs);
-    g.x += large;
+    // (workgroups go to the XCDs in turn: an odd number of them for a text, or all texts' first ones, which take
+    // the large groups, would meet on one of the eight)
+    g.x = (g.x + large) | 1;
     hipLaunchKernelGGL((bulk_rank_kernel<Src>), g, dim3(kSort), 0, stream, src, first, round, h, large);
 }
 

@@ -59,8 +59,6 @@ def _saved(corpus, path, n, vocab):
 def test_corpus_like_the_host_builders(tmp_path, n, kind, vocab):
     import torch
     from paper_2411_10666_amd import binding as sam
-    if n > 100_000 and kind == "one token":
-        n = 100_000
     x = _text(kind, n, vocab, np.random.default_rng(n))
     host = sam.sam_build_host_only(x, vocab)
     try:
@@ -79,6 +77,62 @@ def test_corpus_like_the_host_builders(tmp_path, n, kind, vocab):
     assert root == host_root and np.array_equal(slots, host_slots)
     loaded = sam.sam_corpus_load_host_only(str(tmp_path / "a.sam"))
     assert sam.sam_corpus_info(loaded)[:2] == sam.sam_corpus_info(host)[:2]
+
+
+def _runs(n, run, vocab, rng, token):
+    """Runs of one token (of `run` of them, of up to as many, or of one of two lengths) between other text."""
+    x = _text("zipf", n, vocab, rng)
+    at = int(rng.integers(0, 30))
+    while at < n:
+        k = run if run > 0 else int(rng.integers(1, -run))
+        x[at:at + k] = token
+        at += k + int(rng.integers(1, 60))
+    return x
+
+
+# groups beyond 1024 places whose second names are mostly the same: smaller and larger ones from none to more
+# than 256 (the most that are counted) and 2048 (a tile), names of up to 2 bytes and of more
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [2600, 9000, 66_000])
+@pytest.mark.parametrize("run", [1029, 2055, -300, -3000, 257, 50])
+@pytest.mark.parametrize("token", [0, 20, 59])
+def test_large_groups(n, run, token):
+    import torch
+    from paper_2411_10666_amd import binding as sam
+    vocab = 60
+    rng = np.random.default_rng([n, abs(run), token])
+    x = _runs(n, run, vocab, rng, token)
+    host = sam.sam_build_host_only(x, vocab)
+    try:
+        sam.sam_set_layout_override(64)
+        built = sam.sam_build(x, vocab)
+    finally:
+        sam.sam_set_layout_override(0)
+    assert sam.sam_corpus_info(built)[:2] == sam.sam_corpus_info(host)[:2]
+    for a, b in zip(sam.sam_corpus_export(built), sam.sam_corpus_export(host)):
+        assert np.array_equal(a, b)
+    if n < 6145:
+        return
+    # as prompts: by the whole chip and by one workgroup each
+    prompts = [x, x[:n - 1], x[n // 8:]]
+    dev, seen = torch.device("cuda"), []
+    offs = torch.from_numpy(np.concatenate([[0], np.cumsum([len(p) for p in prompts])])).to(dev)
+    flat = torch.from_numpy(np.concatenate(prompts)).to(dev)
+    for mode in (0, 128):
+        try:
+            sam.sam_set_layout_override(mode)
+            batch = sam.sam_batch_init(None, flat, offs, 3, vocab, n + 30, 16, 8, 0)
+        finally:
+            sam.sam_set_layout_override(0)
+        out = [torch.zeros(3, dtype=torch.int32, device=dev) for _ in range(8)]
+        draft = torch.zeros(3, 8, dtype=torch.int32, device=dev)
+        row = torch.from_numpy(np.stack([p[n // 2:n // 2 + 16] for p in prompts])).to(dev)
+        sam.sam_batch_step(batch, row, torch.full_like(out[0], 16), out[0], draft, out[1], out[2])
+        sam.sam_batch_debug(batch, None, None, *out[3:5])
+        sam.sam_batch_sizes(batch, *out[5:])
+        assert sam.sam_batch_status(batch) == 0
+        seen.append(torch.cat([torch.stack(out).flatten(), draft.flatten()]).cpu())
+    assert torch.equal(*seen)
 
 
 @pytest.mark.gpu
@@ -134,6 +188,20 @@ def test_no_room_on_the_device_to_build(tmp_path, request_):
     r, _ = run_oracle(x, prompts, acc, cnt, 8, 10)
     assert status == 0
     assert_same(g, r)
+
+
+@pytest.mark.gpu
+def test_group_too_large_for_the_device():
+    """More than 2^23 positions that end in the same tokens: the device gives up and the host builds."""
+    from paper_2411_10666_amd import binding as sam
+    n = (1 << 23) + 2000
+    corpus = sam.sam_build(np.full(n, 7, dtype=np.int32), 500)
+    assert sam.sam_corpus_info(corpus)[:2] == (n + 1, n)
+    length, link, endpos = sam.sam_corpus_export(corpus)
+    each = np.arange(n + 1)
+    assert np.array_equal(length, each) and np.array_equal(link, each - 1) and np.array_equal(endpos, each)
+    for state in (0, 1, n - 1):
+        assert sam.sam_corpus_find(corpus, state, 7) == state + 1
 
 
 @pytest.mark.gpu

@@ -1,5 +1,6 @@
 """A prompt taken whole is not slower than the same tokens fed one by one (to empty sequences,
-through sam_batch_step), for texts that are hard on the whole build.  Both are measured here, on
+through sam_batch_step), for texts that are hard on the whole build, and a corpus built on the device is
+not slower than on the host.  Both are measured here, on
 the same device, the shortest of several runs each; the build takes two thirds of the time at most."""
 import time
 
@@ -119,3 +120,58 @@ def test_tree_drafts_with_many_children(batch):
         del b
     print("128 entries, k = 1: %.0f us, k = 8: %.0f us" % (times[0] * 1e6, times[1] * 1e6), flush=True)
     assert times[1] < 1.5 * times[0]
+
+
+@pytest.mark.parametrize("kind", ["equal tokens", "period of two", "half equal", "padded documents"])
+def test_repeating_corpora(kind):
+    """Texts with few large groups, of which one workgroup sorts each (device 0.2 to 0.7 of the host's time as measured)."""
+    from paper_2411_10666_amd import binding as sam
+    rng = np.random.default_rng(3)
+    n = 700_000
+    x = np.full(n, 7, np.int32)
+    if kind == "period of two":
+        x[::2] = 3
+    elif kind == "half equal":
+        x[:n // 2] = rng.integers(0, 500, size=n // 2)
+    elif kind == "padded documents":
+        for at in range(0, n, 4000):
+            x[at:at + 500] = rng.integers(0, 500, size=500)
+    times = []
+    for mode in (0, 128):
+        try:
+            sam.sam_set_layout_override(mode)
+            times.append(_shortest(lambda: sam.sam_build(x, 500), 3))
+        finally:
+            sam.sam_set_layout_override(0)
+    print("device %.1f ms, host %.1f ms" % (times[0] * 1e3, times[1] * 1e3), flush=True)
+    assert times[0] < times[1]
+
+
+@pytest.mark.parametrize("kind", ["equal tokens", "period of two", "padding"])
+@pytest.mark.parametrize("batch,n", [(1, 6500), (600, 8000)])
+def test_many_repeating_prompts(kind, batch, n):
+    """Prompts beyond LDS by the whole chip take little longer than by one workgroup each at worst (1.0 of it as
+    measured; a quarter more allowed)."""
+    import torch
+    from paper_2411_10666_amd import binding as sam
+    rng = np.random.default_rng(n)
+    x = np.full(n, 7, np.int32)
+    if kind == "period of two":
+        x[::2] = 3
+    elif kind == "padding":
+        x[n * 3 // 4:] = rng.integers(0, 500, size=n - n * 3 // 4)
+    dev = torch.device("cuda")
+    flat = torch.from_numpy(np.tile(x, batch)).to(dev)
+    offsets = torch.arange(batch + 1, dtype=torch.int64, device=dev) * n
+    slots = torch.arange(batch, dtype=torch.int32, device=dev)
+    times = []
+    for mode in (0, 128):
+        try:
+            sam.sam_set_layout_override(mode)
+            b = sam.sam_batch_init(None, flat, torch.zeros_like(offsets), batch, 500, n + 8, 4, 4)
+        finally:
+            sam.sam_set_layout_override(0)
+        times.append(_shortest(lambda: sam.sam_batch_reset(b, slots, flat, offsets)))
+        del b
+    print("chip %.0f us, workgroups %.0f us" % (times[0] * 1e6, times[1] * 1e6), flush=True)
+    assert times[0] < 1.25 * times[1]
