@@ -64,6 +64,7 @@ template <class I>
 struct BulkSeq {
     const int32_t *tok;      // every token inside the vocabulary
     uint32_t n;
+    uint32_t of;             // the sequence
     uint32_t *counts;
     uint32_t *ctl;
     uint64_t *key0, *key1;   // [n] the last tokens, the very last on top

@@ -97,6 +97,7 @@ struct PromptSource {
     const int32_t *seq_map, *tokens;
     const int64_t *offsets;
     uint32_t lds_tokens, most;
+    SeqMeta *list;                   // where the prompts are listed, or none: all of them, one after the other
 
     __device__ __forceinline__ int sequence(uint32_t y) const { return seq_map ? seq_map[y] : (int)y; }
     __device__ __forceinline__ bool taken(uint32_t y) const
@@ -116,7 +117,9 @@ struct PromptSource {
     __device__ __forceinline__ uint32_t *counts(int b) const { return &B.meta[b].n_states; }
     __device__ __forceinline__ bool get(uint32_t y, BulkSeq<Ix> &q) const
     {
+        if (list) y = list[y].listed;
         const int b = sequence(y);
+        q.of = (uint32_t)b;
         const int64_t from = offsets[y], to = offsets[y + 1];
         q.n = B.meta[b].n;                   // (asked for with the offsets, not after them)
         if (!bulk_takes(B, to - from, lds_tokens, most) || q.n == 0) return false;
@@ -125,10 +128,9 @@ struct PromptSource {
         bulk_place(q, rec(b), slots(b), reinterpret_cast<char *>(B.dyn_text + (size_t)b * B.max_seq_len));
         return true;
     }
-    __device__ __forceinline__ Store store(uint32_t y, const BulkSeq<Ix> &q) const
+    __device__ __forceinline__ Store store(const BulkSeq<Ix> &q) const
     {
-        const int b = sequence(y);
-        return Store{rec(b), slots(b), B.dyn_buckets, q.tok, q.n};
+        return Store{rec((int)q.of), slots((int)q.of), B.dyn_buckets, q.tok, q.n};
     }
 };
 
@@ -154,7 +156,7 @@ struct CorpusSource {
         return Store{w.rec, reinterpret_cast<uint64_t *>(w.first),
                      reinterpret_cast<uint32_t *>(w.first + 16 * (size_t)n), 2 * n, root, tok, n};
     }
-    __device__ __forceinline__ Store store(uint32_t, const BulkSeq<uint32_t> &) const { return table(); }
+    __device__ __forceinline__ Store store(const BulkSeq<uint32_t> &) const { return table(); }
 };
 
 // ---- lanes working together ---------------------------------------------------------
@@ -847,7 +849,7 @@ __global__ __launch_bounds__(256) void bulk_phase_kernel(Src src, uint32_t token
         for (uint32_t c = from / 64; c < runs; c += step / 64)
             bulk_common(q, tokens, run, c, [&](uint32_t a, uint32_t b, uint32_t l) { return wave_agree(q.tok, a, b, l); });
     } else if constexpr (P == Phase::kSettle) {
-        const auto out = src.store(blockIdx.y, q);
+        const auto out = src.store(q);
         const uint32_t states = q.counts[kCntStates];
         // what held working arrays is empty again, the text is the sequence's
         typedef typename Src::Store Store;
@@ -860,13 +862,13 @@ __global__ __launch_bounds__(256) void bulk_phase_kernel(Src src, uint32_t token
         } else {
             wipe = reinterpret_cast<uint4 *>(out.slots);
             wipes = q.dirty / 16;
-            int32_t *const text = src.B.dyn_text + (size_t)src.sequence(blockIdx.y) * src.B.max_seq_len;
+            int32_t *const text = src.B.dyn_text + (size_t)q.of * src.B.max_seq_len;
             for (uint32_t i = from; i < q.n; i += step) text[i] = q.tok[i];
         }
         for (size_t i = from; i < wipes; i += step) wipe[i] = make_uint4(kNil, kNil, kNil, kNil);
         for (uint32_t v = from; v < states; v += step) bulk_settle(ctx, q, out, states, v);
     } else if constexpr (P == Phase::kWalk) {
-        auto out = src.store(blockIdx.y, q);
+        auto out = src.store(q);
         const uint32_t states = q.counts[kCntStates];
         __shared__ uint32_t list[256], chain[2], total;
         out.chain = chain;
@@ -908,7 +910,7 @@ __global__ __launch_bounds__(256) void bulk_phase_kernel(Src src, uint32_t token
                 if (!t.template first_end<true, true>(ctx, i)) ctx.bit_or(&q.counts[kCntCorrupt], 1u);
             if constexpr (P == Phase::kSecond) t.template second_end<true>(ctx, i);
             if constexpr (P == Phase::kMark) t.mark_clone(ctx, i);
-            if constexpr (P == Phase::kRecords) bulk_records(ctx, q, t, src.store(blockIdx.y, q), i);
+            if constexpr (P == Phase::kRecords) bulk_records(ctx, q, t, src.store(q), i);
         }
     }
 }
@@ -916,23 +918,27 @@ __global__ __launch_bounds__(256) void bulk_phase_kernel(Src src, uint32_t token
 // ---- prompts: begin and end -----------------------------------------------------
 
 // The text ends in front of its first token outside the vocabulary; until the end, meta->n says how
-// long it is.  One workgroup a sequence.
+// long it is.  One workgroup a sequence; those that are taken make the list.
 template <class Src>
 __global__ __launch_bounds__(1024) void bulk_begin_kernel(Src src)
 {
-    __shared__ uint32_t first_bad;
+    __shared__ uint32_t first_bad, before;
     if (!src.taken(blockIdx.x)) return;
     const int b = src.sequence(blockIdx.x);
     const uint32_t count = (uint32_t)(src.offsets[blockIdx.x + 1] - src.offsets[blockIdx.x]), vocab = (uint32_t)src.B.vocab;
     const int32_t *const tok = src.tokens + src.offsets[blockIdx.x];
     uint32_t *const ctl = reinterpret_cast<uint32_t *>(src.B.dyn_text + (size_t)b * src.B.max_seq_len);
-    if (threadIdx.x == 0) first_bad = count;
+    if (threadIdx.x == 0) { first_bad = count; before = 0; }
     if (threadIdx.x < kBulkCtl) ctl[threadIdx.x] = 0;          // (where bulk_place has it)
     __syncthreads();
     for (uint32_t j = threadIdx.x; j < count; j += 1024)
         if ((uint32_t)tok[j] >= vocab) atomicMin(&first_bad, j);
+    if (src.list)
+        for (uint32_t y = threadIdx.x; y < blockIdx.x; y += 1024)
+            if (src.taken(y)) atomicAdd(&before, 1u);
     __syncthreads();
     if (threadIdx.x == 0) {
+        if (src.list) src.list[before].listed = blockIdx.x;
         SeqMeta *const meta = &src.B.meta[b];
         if (first_bad < count) {
             meta->status |= SAM_STATUS_TOKEN_BIT;
@@ -952,8 +958,8 @@ __global__ __launch_bounds__(64) void bulk_end_kernel(Src src, uint32_t n_seqs)
     const uint32_t y = blockIdx.x * 64 + threadIdx.x;
     BulkSeq<typename Src::Index> q;
     if (y >= n_seqs || !src.get(y, q)) return;
-    const auto out = src.store(y, q);
-    SeqMeta *const meta = &src.B.meta[src.sequence(y)];
+    const auto out = src.store(q);
+    SeqMeta *const meta = &src.B.meta[q.of];
     if (q.counts[kCntCorrupt]) {
         meta->status |= SAM_STATUS_INTERNAL_BIT;
         atomicOr(src.B.status, SAM_STATUS_INTERNAL_BIT);
@@ -1182,26 +1188,28 @@ void launch_round(const Src &src, uint32_t n, uint32_t n_seqs, const BulkSort &s
 }
 
 template <class L, class I>
-hipError_t bulk_prompts(const BatchView &B, const int32_t *seq_map, int n_seqs, const int32_t *tokens,
+hipError_t bulk_prompts(const BatchView &B, const int32_t *seq_map, int n_seqs, int n_listed, const int32_t *tokens,
                         const int64_t *offsets, uint32_t lds_tokens, uint32_t most, bool begin, hipStream_t stream)
 {
     typedef PromptSource<L, I> Src;
     if (begin) {
         hipLaunchKernelGGL((bulk_begin_kernel<Src>), dim3(n_seqs), dim3(1024), 0, stream,
-                           Src{B, seq_map, tokens, offsets, lds_tokens, most});
+                           Src{B, seq_map, tokens, offsets, lds_tokens, most, n_listed ? B.meta : nullptr});
         return hipGetLastError();
     }
     // workgroups find their sequence in the grid's second index, which ends at 65535
-    for (int at = 0; at < n_seqs; at += 65535) {
-        const int count = n_seqs - at < 65535 ? n_seqs - at : 65535;
+    const int all = n_listed ? n_listed : n_seqs;
+    for (int at = 0; at < all; at += 65535) {
+        const int count = all - at < 65535 ? all - at : 65535;
         BatchView part = B;
-        if (!seq_map && at) {                      // sequences at .. : the batch as if it began there
+        if (!n_listed && !seq_map && at) {                      // sequences at .. : the batch as if it began there
             part.dyn_text += (size_t)at * B.max_seq_len;
             part.dyn_rec = (char *)B.dyn_rec + (size_t)at * B.max_states * (Src::kCompact ? sizeof(DynRecCompact) : sizeof(DynRec));
             part.dyn_slots = (char *)B.dyn_slots + (size_t)at * B.dyn_buckets * 128;
             part.meta += at;
         }
-        const Src src{part, seq_map ? seq_map + at : nullptr, tokens, offsets + at, lds_tokens, most};
+        const Src src = n_listed ? Src{B, seq_map, tokens, offsets, lds_tokens, most, B.meta + at}
+                                 : Src{part, seq_map ? seq_map + at : nullptr, tokens, offsets + at, lds_tokens, most, nullptr};
         const BulkSort sort = bulk_sort_for((uint32_t)B.vocab, 32);
         launch_sort(src, most, (uint32_t)count, sort, stream);
         uint32_t round = 0;
@@ -1215,12 +1223,12 @@ hipError_t bulk_prompts(const BatchView &B, const int32_t *seq_map, int n_seqs, 
 
 }  // namespace
 
-hipError_t launch_bulk_prompts(const BatchView &B, const int32_t *seq_map, int n_seqs, const int32_t *tokens,
+hipError_t launch_bulk_prompts(const BatchView &B, const int32_t *seq_map, int n_seqs, int n_listed, const int32_t *tokens,
                                const int64_t *offsets, uint32_t lds_tokens, uint32_t most, bool begin, hipStream_t stream)
 {
     return B.compact
-               ? bulk_prompts<IngestCompact, uint16_t>(B, seq_map, n_seqs, tokens, offsets, lds_tokens, most, begin, stream)
-               : bulk_prompts<IngestWide, uint32_t>(B, seq_map, n_seqs, tokens, offsets, lds_tokens, most, begin, stream);
+               ? bulk_prompts<IngestCompact, uint16_t>(B, seq_map, n_seqs, n_listed, tokens, offsets, lds_tokens, most, begin, stream)
+               : bulk_prompts<IngestWide, uint32_t>(B, seq_map, n_seqs, n_listed, tokens, offsets, lds_tokens, most, begin, stream);
 }
 
 hipError_t bulk_check(const int32_t *tok, uint32_t n, uint32_t vocab, uint32_t *at, hipStream_t stream)

@@ -6,9 +6,11 @@
 namespace sam {
 
 // Fresh sequences (launch_reset before) take those of their prompts that have more than lds_tokens
-// tokens and fit their tables (bulk_takes); `most`: what a prompt may have by then.  begin: only looks
-// for tokens outside the vocabulary; meta->n is how many there are in front of the first, from then on.
-hipError_t launch_bulk_prompts(const BatchView &B, const int32_t *seq_map, int n_seqs, const int32_t *tokens,
+// tokens and fit their tables (bulk_takes); `most`: what a prompt may have by then.  n_listed: how many
+// these are, where the host knows for sure, or 0: the launches cover all prompts.  begin: only looks
+// for tokens outside the vocabulary, and makes the list; meta->n is how many there are in front of the
+// first, from then on.
+hipError_t launch_bulk_prompts(const BatchView &B, const int32_t *seq_map, int n_seqs, int n_listed, const int32_t *tokens,
                                const int64_t *offsets, uint32_t lds_tokens, uint32_t most, bool begin, hipStream_t stream);
 
 __host__ __device__ __forceinline__ bool bulk_takes(const BatchView &B, int64_t count, uint32_t lds_tokens, uint32_t most)

@@ -114,7 +114,7 @@ struct SeqMeta {
     // next step starts without reading it back: s2 (kNil before the first
     // token), then len (= l2), link, min_endpos (= e2), head, itok, idst
     uint32_t s2, p_len, p_link, p_endpos, p_head, p_itok, p_idst;
-    uint32_t pad;
+    uint32_t listed;         // of entry k: the k-th prompt that the whole chip builds, while it does
 };
 
 // (state, token) -> 32-bit hash; the same function on host and device

@@ -362,14 +362,33 @@ hipError_t launch_ingest(const StaticView &S, const BatchView &B, const int32_t 
     }
     // Prompts beyond LDS are built by the whole chip, phase by phase, wherever their tables have room for
     // that: one workgroup each is bound by the scattered accesses of its compute unit even where there
-    // are more of them than units (sam_batch_reset, chip / workgroups, us: 1 prompt of 6500 tokens 0.45 /
-    // 1.1 ms, 1 of 40 001 0.9 / 7.6, 12 of 40 001 1.1 / 8.1, 64 of 40 001 4.0 / 10.6, 256 of 6500 1.9 / 2.2, 600 of
-    // 8000 4.2 / 5.8).  Of one token only, 3 of 16 000 tokens take 1.9 ms against 1.7; 3 of 40 001 4.5 against 5.0.
-    // (A captured call that is replayed with longer prompts than it was captured with leaves those to one
-    // workgroup each: its launches are made for the longest that the host knows of.)
-    const uint32_t bulk_tokens = n_beyond > 0 && lds_tokens >= kBulkLdsTokens && !B.no_bulk ? (uint32_t)sizes.longest : 0u;
-    if (bulk_tokens &&
-        (e = launch_bulk_prompts(B, seq_map, n_seqs, tokens, offsets, lds_tokens, bulk_tokens, true, stream)) != hipSuccess)
+    // are more of them than units.  sam_batch_reset, chip / workgroups, ms, Zipf text:
+    //   1 x 6500  0.30 / 0.46    1 x 16 000  0.35 / 1.2    1 x 100 000  0.60 / 8.2    12 x 40 000  0.65 / 3.3
+    //   64 x 30 000  1.5 / 3.0   256 x 9000  1.38 / 1.38   600 x 8000  2.5 / 2.9
+    // (period of 150: 1 x 6500 0.47 / 1.1, 12 x 40 000 1.4 / 9.4, 600 x 8000 3.6 / 7.1; of one token only:
+    // 1 x 6500 0.58 / 0.64, 12 x 40 000 1.6 / 5.2, 256 x 9000 1.67 / 1.55, 600 x 8000 2.6 / 3.1).
+    // The launches cover the prompts that are taken, which the begin kernel lists (one of 7000 among 1279 of 64
+    // tokens: 0.44 ms, of 100 000 1.5; with workgroups for all prompts 0.79 and 8.3; one workgroup each
+    // 0.51 and 8.9).  Few of them that one workgroup each builds while the others are built are left to
+    // that: the chip's phases follow the others' builds, and take 0.3 ms and more (chip / workgroups, ms, one of
+    // 6500 tokens among 1024 of 500 0.46 / 0.49, of 2000 0.66 / 0.58, of 4000 0.97 / 0.73; one of 9000 0.48 /
+    // 0.67, 0.66 / 0.76, 0.96 / 0.90; 64 of 6500 0.62 / 0.73, 0.82 / 0.91, 1.13 / 1.24).
+    // (A call that may be captured covers all prompts, by the host's longest: replayed with longer ones
+    // it leaves those to one workgroup each.)
+    uint32_t bulk_tokens = n_beyond > 0 && lds_tokens >= kBulkLdsTokens && !B.no_bulk ? (uint32_t)sizes.longest : 0u;
+    int n_listed = 0;
+    if (bulk_tokens && most == 0) {
+        int64_t others = sizes.total;
+        for (int i = 0; i < n_seqs; i++)
+            if (bulk_takes(B, prompt(i), lds_tokens, bulk_tokens)) {
+                n_listed++;
+                others -= prompt(i);
+            }
+        if (n_listed == 0 || (n_listed < 32 && sizes.longest < 4000 + others / 800)) bulk_tokens = n_listed = 0;
+        if (n_listed == n_seqs) n_listed = 0;
+    }
+    if (bulk_tokens && (e = launch_bulk_prompts(B, seq_map, n_seqs, n_listed, tokens, offsets, lds_tokens, bulk_tokens, true,
+                                                stream)) != hipSuccess)
         return e;
     // workgroups for the corpus: a wave each sequence, a multiple of 8 workgroups
     auto walks = [&](int waves) { return B.has_static ? (((n_seqs + waves - 1) / waves + 7) & ~7) : 0; };
@@ -392,7 +411,7 @@ hipError_t launch_ingest(const StaticView &S, const BatchView &B, const int32_t 
 #undef SAM_LAUNCH_PROMPT
 #undef SAM_LAUNCH_PROMPT_T
     if ((e = hipGetLastError()) != hipSuccess || !bulk_tokens) return e;
-    return launch_bulk_prompts(B, seq_map, n_seqs, tokens, offsets, lds_tokens, bulk_tokens, false, stream);
+    return launch_bulk_prompts(B, seq_map, n_seqs, n_listed, tokens, offsets, lds_tokens, bulk_tokens, false, stream);
 }
 
 }  // namespace sam

@@ -183,6 +183,54 @@ def test_matches_at_the_end(n, how):
     _compare(prompts, vocab, n + 40, 0, np.concatenate(parts))
 
 
+# a few prompts beyond LDS among many short ones, first and last among them (the whole chip builds those alone,
+# found through a list), too many to be few, and so much text in the others that one workgroup each builds
+# them; then again for some sequences of the batch, in another order
+@pytest.mark.parametrize("T,longest", [(9040, 7000), (9040, 9000), (20_040, 20_000)])
+@pytest.mark.parametrize("batch,many,short", [(200, 4, 60), (150, 40, 30), (1100, 3, 5500), (3, 2, 10)])
+def test_few_long_prompts(T, longest, batch, many, short):
+    import torch
+    from paper_2411_10666_amd import binding as sam
+    rng = np.random.default_rng(batch)
+    vocab = 300
+    lengths = rng.integers(0, short + 1, size=batch)
+    lengths[rng.permutation(batch)[:many]] = rng.integers(6145, longest, size=many)
+    lengths[0], lengths[-1] = longest, 6145
+    pool = _text("copies", 60_000, vocab, rng)
+    prompts = [pool[a:a + n] for a, n in zip(rng.integers(0, 60_000 - lengths), lengths)]
+    if batch * short < 1_000_000:
+        _compare(prompts, vocab, T, 0, _text("copies", 2000, vocab, rng))
+    dev = torch.device("cuda")
+    take = rng.permutation(batch)[:batch * 3 // 4 + 1]
+    order = rng.permutation(take)
+    again = [np.concatenate([prompts[i], [vocab]]).astype(np.int32) if k % 3 == 0 else prompts[i]
+             for k, i in enumerate(take)]              # every third one ends in a bad token
+    again = [p if len(p) <= T else p[:T] for p in again]
+
+    def flat(ps):
+        return (torch.from_numpy(np.concatenate(ps)).to(dev),
+                torch.from_numpy(np.cumsum([0] + [len(p) for p in ps])).to(dev))
+
+    seen = []
+    for mode in (0, 128):
+        try:
+            sam.sam_set_layout_override(mode)
+            b = sam.sam_batch_init(None, *flat(prompts), batch, vocab, T, 4, 4)
+        finally:
+            sam.sam_set_layout_override(0)
+        sam.sam_batch_reset(b, torch.from_numpy(order.astype(np.int32)).to(dev), *flat(again))
+        out = [torch.zeros(batch, dtype=torch.int32, device=dev) for _ in range(8)]
+        draft = torch.zeros(batch, 4, dtype=torch.int32, device=dev)
+        row = torch.from_numpy(np.stack([pool[i:i + 4] for i in range(batch)])).to(dev)
+        sam.sam_batch_step(b, row, torch.full_like(out[0], 4), out[0], draft, out[1], out[2])
+        sam.sam_batch_debug(b, None, None, *out[3:5])
+        sam.sam_batch_sizes(b, *out[5:])
+        assert sam.sam_batch_status(b) == sam.SAM_STATUS_TOKEN
+        seen.append(torch.cat([torch.stack(out).flatten(), draft.flatten()]).cpu())
+        del b
+    assert torch.equal(*seen)
+
+
 # a captured init, replayed with prompts of other lengths in the same buffers: longer ones than it was
 # captured with, within and beyond what LDS holds, in tables with room for the working arrays and without
 @pytest.mark.parametrize("captured,replayed,T", [(100, 300, 340), (100, 2500, 2600), (2000, 9000, 9040),

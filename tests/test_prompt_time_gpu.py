@@ -152,26 +152,44 @@ def test_repeating_corpora(kind):
 def test_many_repeating_prompts(kind, batch, n):
     """Prompts beyond LDS by the whole chip take little longer than by one workgroup each at worst (1.0 of it as
     measured; a quarter more allowed)."""
-    import torch
-    from paper_2411_10666_amd import binding as sam
     rng = np.random.default_rng(n)
     x = np.full(n, 7, np.int32)
     if kind == "period of two":
         x[::2] = 3
     elif kind == "padding":
         x[n * 3 // 4:] = rng.integers(0, 500, size=n - n * 3 // 4)
-    dev = torch.device("cuda")
-    flat = torch.from_numpy(np.tile(x, batch)).to(dev)
-    offsets = torch.arange(batch + 1, dtype=torch.int64, device=dev) * n
-    slots = torch.arange(batch, dtype=torch.int32, device=dev)
+    chip, workgroups = _chip_and_workgroups([x] * batch)
+    assert chip < 1.25 * workgroups
+
+
+def _chip_and_workgroups(prompts):
+    import torch
+    from paper_2411_10666_amd import binding as sam
+    dev, B = torch.device("cuda"), len(prompts)
+    lengths = [len(p) for p in prompts]
+    flat = torch.from_numpy(np.concatenate(prompts)).to(dev)
+    offsets = torch.from_numpy(np.cumsum([0] + lengths)).to(dev)
+    slots = torch.arange(B, dtype=torch.int32, device=dev)
     times = []
     for mode in (0, 128):
         try:
             sam.sam_set_layout_override(mode)
-            b = sam.sam_batch_init(None, flat, torch.zeros_like(offsets), batch, 500, n + 8, 4, 4)
+            b = sam.sam_batch_init(None, flat, torch.zeros_like(offsets), B, 32000, max(lengths) + 8, 4, 4)
         finally:
             sam.sam_set_layout_override(0)
         times.append(_shortest(lambda: sam.sam_batch_reset(b, slots, flat, offsets)))
         del b
     print("chip %.0f us, workgroups %.0f us" % (times[0] * 1e6, times[1] * 1e6), flush=True)
-    assert times[0] < 1.25 * times[1]
+    return times
+
+
+@pytest.mark.parametrize("batch,short", [(1280, 64), (1280, 2000), (640, 6000)])
+@pytest.mark.parametrize("longest", [6500, 100_000])
+def test_one_long_prompt_among_short_ones(batch, short, longest):
+    """(1.03 as long at most as measured; it was up to 1.7, where the chip's launches covered all prompts)"""
+    rng = np.random.default_rng(batch)
+    text = np.minimum((32000 * rng.random(longest + short) ** 5).astype(np.int64), 31999).astype(np.int32)
+    prompts = [text[:short]] * batch
+    prompts[batch // 3] = text[short:]
+    chip, workgroups = _chip_and_workgroups(prompts)
+    assert chip < 1.15 * workgroups
