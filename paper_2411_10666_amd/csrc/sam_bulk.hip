@@ -88,28 +88,29 @@ struct BulkCtx {
 
 // ---- where a text and its working arrays are -------------------------------------
 
-template <class L, class Ix>
+// kListed: the prompts that the begin kernel has listed, else all of them, one after the other
+template <class L, class Ix, bool kListed>
 struct PromptSource {
     typedef Ix Index;
     typedef BulkTables<L> Store;
-    static constexpr bool kCompact = L::kSlots == 16;
+    static constexpr bool kCompact = L::kSlots == 16, kList = kListed;
     BatchView B;
     const int32_t *seq_map, *tokens;
     const int64_t *offsets;
     uint32_t lds_tokens, most;
-    SeqMeta *list;                   // where the prompts are listed, or none: all of them, one after the other
+    SeqMeta *list;
 
     __device__ __forceinline__ int sequence(uint32_t y) const { return seq_map ? seq_map[y] : (int)y; }
     __device__ __forceinline__ bool taken(uint32_t y) const
     {
         return bulk_takes(B, offsets[y + 1] - offsets[y], lds_tokens, most);
     }
-    __device__ __forceinline__ char *rec(int b) const
+    __host__ __device__ __forceinline__ char *rec(int b) const
     {
         return reinterpret_cast<char *>(B.dyn_rec) +
                (size_t)b * B.max_states * (kCompact ? sizeof(DynRecCompact) : sizeof(DynRec));
     }
-    __device__ __forceinline__ char *slots(int b) const
+    __host__ __device__ __forceinline__ char *slots(int b) const
     {
         return reinterpret_cast<char *>(B.dyn_slots) + (size_t)b * B.dyn_buckets * 128;
     }
@@ -117,7 +118,7 @@ struct PromptSource {
     __device__ __forceinline__ uint32_t *counts(int b) const { return &B.meta[b].n_states; }
     __device__ __forceinline__ bool get(uint32_t y, BulkSeq<Ix> &q) const
     {
-        if (list) y = list[y].listed;
+        if (kListed) y = list[y].listed;
         const int b = sequence(y);
         q.of = (uint32_t)b;
         const int64_t from = offsets[y], to = offsets[y + 1];
@@ -933,12 +934,12 @@ __global__ __launch_bounds__(1024) void bulk_begin_kernel(Src src)
     __syncthreads();
     for (uint32_t j = threadIdx.x; j < count; j += 1024)
         if ((uint32_t)tok[j] >= vocab) atomicMin(&first_bad, j);
-    if (src.list)
+    if (Src::kList)
         for (uint32_t y = threadIdx.x; y < blockIdx.x; y += 1024)
             if (src.taken(y)) atomicAdd(&before, 1u);
     __syncthreads();
     if (threadIdx.x == 0) {
-        if (src.list) src.list[before].listed = blockIdx.x;
+        if (Src::kList) src.list[before].listed = blockIdx.x;
         SeqMeta *const meta = &src.B.meta[b];
         if (first_bad < count) {
             meta->status |= SAM_STATUS_TOKEN_BIT;
@@ -1187,29 +1188,31 @@ void launch_round(const Src &src, uint32_t n, uint32_t n_seqs, const BulkSort &s
     hipLaunchKernelGGL((bulk_rank_kernel<Src>), g, dim3(kSort), 0, stream, src, first, round, h, large);
 }
 
-template <class L, class I>
+template <class Src>
 hipError_t bulk_prompts(const BatchView &B, const int32_t *seq_map, int n_seqs, int n_listed, const int32_t *tokens,
                         const int64_t *offsets, uint32_t lds_tokens, uint32_t most, bool begin, hipStream_t stream)
 {
-    typedef PromptSource<L, I> Src;
     if (begin) {
         hipLaunchKernelGGL((bulk_begin_kernel<Src>), dim3(n_seqs), dim3(1024), 0, stream,
-                           Src{B, seq_map, tokens, offsets, lds_tokens, most, n_listed ? B.meta : nullptr});
+                           Src{B, seq_map, tokens, offsets, lds_tokens, most, B.meta});
         return hipGetLastError();
     }
     // workgroups find their sequence in the grid's second index, which ends at 65535
-    const int all = n_listed ? n_listed : n_seqs;
+    const int all = Src::kList ? n_listed : n_seqs;
     for (int at = 0; at < all; at += 65535) {
         const int count = all - at < 65535 ? all - at : 65535;
-        BatchView part = B;
-        if (!n_listed && !seq_map && at) {                      // sequences at .. : the batch as if it began there
-            part.dyn_text += (size_t)at * B.max_seq_len;
-            part.dyn_rec = (char *)B.dyn_rec + (size_t)at * B.max_states * (Src::kCompact ? sizeof(DynRecCompact) : sizeof(DynRec));
-            part.dyn_slots = (char *)B.dyn_slots + (size_t)at * B.dyn_buckets * 128;
-            part.meta += at;
+        Src src{B, seq_map, tokens, offsets, lds_tokens, most, B.meta + at};
+        if (!Src::kList) {
+            src.offsets += at;
+            if (seq_map) {
+                src.seq_map += at;
+            } else {                               // sequences at .. : the batch as if it began there
+                src.B.dyn_text += (size_t)at * B.max_seq_len;
+                src.B.dyn_rec = src.rec(at);
+                src.B.dyn_slots = src.slots(at);
+                src.B.meta += at;
+            }
         }
-        const Src src = n_listed ? Src{B, seq_map, tokens, offsets, lds_tokens, most, B.meta + at}
-                                 : Src{part, seq_map ? seq_map + at : nullptr, tokens, offsets + at, lds_tokens, most, nullptr};
         const BulkSort sort = bulk_sort_for((uint32_t)B.vocab, 32);
         launch_sort(src, most, (uint32_t)count, sort, stream);
         uint32_t round = 0;
@@ -1226,9 +1229,11 @@ hipError_t bulk_prompts(const BatchView &B, const int32_t *seq_map, int n_seqs, 
 hipError_t launch_bulk_prompts(const BatchView &B, const int32_t *seq_map, int n_seqs, int n_listed, const int32_t *tokens,
                                const int64_t *offsets, uint32_t lds_tokens, uint32_t most, bool begin, hipStream_t stream)
 {
-    return B.compact
-               ? bulk_prompts<IngestCompact, uint16_t>(B, seq_map, n_seqs, n_listed, tokens, offsets, lds_tokens, most, begin, stream)
-               : bulk_prompts<IngestWide, uint32_t>(B, seq_map, n_seqs, n_listed, tokens, offsets, lds_tokens, most, begin, stream);
+#define SAM_BULK(L, I, LISTED) \
+    bulk_prompts<PromptSource<L, I, LISTED>>(B, seq_map, n_seqs, n_listed, tokens, offsets, lds_tokens, most, begin, stream)
+    if (B.compact) return n_listed ? SAM_BULK(IngestCompact, uint16_t, true) : SAM_BULK(IngestCompact, uint16_t, false);
+    return n_listed ? SAM_BULK(IngestWide, uint32_t, true) : SAM_BULK(IngestWide, uint32_t, false);
+#undef SAM_BULK
 }
 
 hipError_t bulk_check(const int32_t *tok, uint32_t n, uint32_t vocab, uint32_t *at, hipStream_t stream)
@@ -1240,7 +1245,7 @@ hipError_t bulk_check(const int32_t *tok, uint32_t n, uint32_t vocab, uint32_t *
 hipError_t bulk_corpus(const int32_t *tok, uint32_t n, uint32_t vocab, RootEnt *root, const BulkWork &w,
                        uint32_t *n_states, uint64_t *n_trans, bool *gave_up, hipStream_t stream)
 {
-    // a group beyond this would keep one workgroup busy for a tenth of a second and more, each round
+    // to sort a group beyond this in full keeps one workgroup busy for a tenth of a second and more, each round
     constexpr uint32_t kMostLarge = 1u << 23;
     const CorpusSource src{tok, n, w, root};
     uint32_t ctl[kBulkCtl], counts[kBulkCounts];
