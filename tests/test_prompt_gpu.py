@@ -232,9 +232,12 @@ def test_few_long_prompts(T, longest, batch, many, short):
 
 
 # a captured init, replayed with prompts of other lengths in the same buffers: longer ones than it was
-# captured with, within and beyond what LDS holds, in tables with room for the working arrays and without
+# captured with, within and beyond what LDS holds, in tables with room for the working arrays and without;
+# captured beyond LDS (the whole chip's launches are in the graph): shorter ones, the same and longer ones
 @pytest.mark.parametrize("captured,replayed,T", [(100, 300, 340), (100, 2500, 2600), (2000, 9000, 9040),
-                                                 (70, 20_000, 20_040), (30, 500, 540)])
+                                                 (70, 20_000, 20_040), (30, 500, 540),
+                                                 (9000, 14_900, 15_000), (9000, 8000, 15_000),
+                                                 (20_000, 30_000, 30_040), (14_000, 100_000, 100_040)])
 def test_replayed_init_takes_longer_prompts(captured, replayed, T):
     import torch
     from paper_2411_10666_amd import binding as sam
