@@ -349,8 +349,8 @@ int sam_batch_status(const sam_batch *batch, uint32_t *status, void *hip_stream)
  * corpus (about that much host and device memory), so that table offsets beyond
  * 32 bits are reached with a corpus that builds in a moment; bit 4 makes the
  * step kernel of every later sam_batch_init run with its two prefetching waves,
- * which otherwise join for rows of four tokens or more where the sequences' tables
- * have 12 MiB or a sequence 14 000 tokens; bit 5 keeps them
+ * which otherwise join for rows of four tokens or more where rows and sequences
+ * are long enough together, or the corpus is large; bit 5 keeps them
  * out whatever the sizes (for measuring what they cost and bring); bit 6
  * makes every later sam_build build on the device however small the corpus; bit 7
  * keeps the builds by the whole chip out: corpora are built on the host, prompts

@@ -31,25 +31,35 @@ int g_layout_override = 0;   // bit 0: always the wide layout, bit 1: tight slot
                              // bit 4: scout waves whatever the batch size, bit 5: never,
                              // bit 6: corpora on the device whatever their size,
                              // bit 7: no builds by the whole chip, bits 8 to 10: see build_malloc
-// Scout waves pay where a step's rows are long enough to be looked at ahead of the walks, and the
-// sequences' tables are not in the L2 when it starts: because they fill it (12 of its 32 MB or more),
-// or because long prompts were built elsewhere and only their ends have been walked since.  Measured,
-// with scouts / without, us a round (rows of up to 8, of 16):
-//   tables  2.5 MB   16 x 3000 tokens     1.03  0.99      20 MB   64 x 6000      1.00  0.99   128 x 3000   1.00  0.98
-//           8.3 MB   16 x 10 000          1.05  1.02      33 MB   64 x 10 000    0.99  0.97
-//          10 MB     64 x 3000            1.04  1.02      67 MB   128 x 10 000   0.95  0.93
-//          13.7 MB   64 x 4096            1.02  1.00     328 MB   1024 x 6144          0.90
-//   after prompts that nearly fill them:  1 x 15 500 0.97 0.92   8 x 15 500 0.92 0.87   32 x 14 500 0.92 0.88
-//   wide layout, the same:                1 x 41 000 0.94 0.90   12 x 41 000 0.91 0.86   64 x 31 000 0.91 0.87
-//   rows of up to 3: 128 x 1024 1.07, 1024 x 3600 1.01; of 4: 32 x 16 000 0.97, 1 x 16 000 1.02; of 2: 1.01, 1.06
-// The corpus's size makes no difference (35 MB to 1.4 GB).  They stop paying once the walking waves
+// Scout waves look at a step's row ahead of the walks.  They pay where there is something to look at and
+// the walks would wait for it: the more, the longer the rows (the walks of a row are a chain, the
+// scouts' look-ups are not) and the longer the sequences (a short one's tables are in the caches from
+// the step before).  Measured, time with scouts over time without, rows of up to 4 / 8 / 16, small corpora:
+//   64 x 1000 tokens      1.04 1.01      1 x 3000        1.05 1.01     1 x 13 000        0.99 0.94
+//   64 x 3000        1.04 1.01 0.98      8 x 5000        1.00 0.96     8 x 13 000        0.96 0.91
+//   64 x 4000        1.03 0.99 0.97     32 x 9000   1.00 0.95 0.92   128 x 2500     1.03 1.00 0.98
+//   64 x 9000        0.99 0.95 0.92     32 x 13 500 0.98 0.94 0.91   128 x 5000     1.02 0.99 0.96
+//   1024 x 1000      1.04 1.01 0.98    256 x 10 000 0.97            1024 x 8000     0.97 (1024 x 7500, 6: 0.94)
+//   of up to 2: 1.0 to 1.13; of 3: 256 x 10 000 0.99, 12 x 41 000 1.00, 1 x 41 000 1.02; of 12: 1 x 5500 1.01, 8 x 4000
+//   0.98; of 24: 64 x 480 0.98, 8 x 1000 0.98; of 64: 1 x 500 1.00, 256 x 300 0.99
+// so the line is drawn at the tokens of a sequence times the square of a row's (8: 3900, 16: 980), three
+// times as high where all tables together stay in the caches, and dropped beyond the L2 (32 MB) for all but
+// short sequences.  A corpus makes no difference while the last-level cache (256 MB) holds it; walks over a larger one miss in it,
+// and with 128 sequences and more scouts pay for short ones too (over 7 GB, rows of up to 8 / 16: 128 x 1600 0.97
+// 0.95, 256 x 800 0.97 0.94, 1024 x 210 1.00 0.96; 128 x 800 1.02 1.01, 64 x 1000 1.05 1.03).
+// They stop paying once the walking waves
 // alone fill the chip: with more than six sequences per compute unit the scouts take wave slots and
 // issue cycles from other sequences' walks (1024 sequences on 256 units over 6 GB of
 // tables -9 % per step with scouts, 1536 -6 %, 2048 +9 %, 4096 +19 %, 8192 +27 %).
-constexpr int     kScoutMinAccept = 4;
-constexpr int64_t kScoutMinTableBytes = 12 << 20;
-constexpr int     kScoutMinSeqLen = 14000;
 constexpr int     kScoutMaxSeqPerCu = 6;
+bool scouts_pay(int64_t seq_len, int64_t accept, int64_t batch, int64_t table_bytes, int64_t corpus_bytes)
+{
+    if (accept < 4) return false;
+    const int64_t reach = seq_len * accept * accept, mb = 1 << 20;
+    return (reach >= 250000 && table_bytes >= 4 * mb) || reach >= 850000 ||
+           (table_bytes >= 40 * mb && seq_len >= 2500) ||
+           (corpus_bytes > 256 * mb && batch >= 128 && accept >= 8 && table_bytes >= 10 * mb);
+}
 // buckets of 128 bytes that make a transition table of 4.5 GiB
 constexpr uint64_t kHugeTableBuckets = (1ull << 25) + (1ull << 22);
 // Tokens from which on the corpus automaton is built on the device: about fifty launches and a few
@@ -740,10 +750,9 @@ static BatchBytes batch_configure(BatchView &v, const sam_corpus *corpus, int32_
     b.slots = (size_t)batch * v.dyn_buckets * 128;
     b.meta = (size_t)batch * sizeof(SeqMeta);
     const bool scouts_fit = n_cu <= 0 || (int64_t)batch <= (int64_t)n_cu * kScoutMaxSeqPerCu;
-    const bool scouts_pay = max_accept >= kScoutMinAccept &&
-                            ((int64_t)(b.text + b.rec + b.slots) >= kScoutMinTableBytes || max_seq_len >= kScoutMinSeqLen);
-    v.scout = ((g_layout_override & 32) == 0 &&
-               ((g_layout_override & 16) || (scouts_fit && scouts_pay))) ? 1 : 0;
+    const bool pay = scouts_pay(max_seq_len, max_accept, batch, (int64_t)(b.text + b.rec + b.slots),
+                                corpus ? corpus->device_bytes : 0);
+    v.scout = ((g_layout_override & 32) == 0 && ((g_layout_override & 16) || (scouts_fit && pay))) ? 1 : 0;
     return b;
 }
 

@@ -284,7 +284,7 @@ def test_multi_document_corpus_with_separators():
 @pytest.mark.parametrize("seed,vocab,A", [(90, 2, 5), (91, 4, 30), (92, 300, 70), (93, 32000, 16)])
 def test_scout_waves_change_nothing(seed, vocab, A, mode):
     """The step kernel with its two prefetching waves (testing mode bit 4; by default they
-    join at 128 sequences): rows shorter and longer than the scouts reach (64 lanes),
+    join where rows and sequences are long): rows shorter and longer than the scouts reach (64 lanes),
     empty and very short prompts (less history than the scouts look back), every table
     layout, both forms of the token loops.  The scouts only read, so every output must
     be what it is without them."""
@@ -710,10 +710,10 @@ def test_replay_equals_stepwise(seed, vocab, with_corpus):
     assert sam.sam_batch_status(batch) == want
 
 
-@pytest.mark.parametrize("T,A,mode", [(13_999, 5, 0), (14_000, 1, 0), (14_000, 4, 0), (14_000, 70, 4), (14_000, 70, 0),
-                                      (30_000, 70, 0), (30_000, 16, 4)])
+@pytest.mark.parametrize("T,A,mode", [(13_999, 5, 0), (14_000, 1, 0), (14_000, 4, 0), (14_000, 4, 16), (13_999, 8, 0),
+                                      (14_000, 8, 0), (14_000, 70, 4), (14_000, 70, 0), (30_000, 70, 0), (30_000, 16, 4)])
 def test_replay_of_long_sequences_equals_steps(T, A, mode):
-    """From 14000 tokens on, rows of 4 and more, the replay has scout waves; it reads counts and
+    """From 14000 tokens on the replay has scout waves where the steps have them; it reads counts and
     rows a step ahead, also past faulty rows and of a single step.  Both table layouts and forms
     of the token loops, against the step calls on a batch of the same prompts."""
     import torch
