@@ -7,6 +7,8 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <sanitizer/asan_interface.h>
+
 #include <algorithm>
 #include <random>
 #include <string>
@@ -58,14 +60,18 @@ static int bad(const char *what, uint32_t n, uint32_t at)
 struct Aligned {
     char *p;
     size_t bytes;
-    Aligned(size_t b, int fill) : p((char *)malloc(b + 128)), bytes(b)
+    Aligned(size_t b, int fill) : p((char *)aligned_alloc(128, room(b))), bytes(b)
     {
-        // the end of the block is the end of the region: behind it lies the sanitizer's zone
-        free(p);
-        p = (char *)aligned_alloc(128, (b + 127) / 128 * 128);
         memset(p, fill, b);
+        // what the block has behind the region is out of bounds too
+        ASAN_POISON_MEMORY_REGION(p + b, room(b) - b);
     }
-    ~Aligned() { free(p); }
+    ~Aligned()
+    {
+        ASAN_UNPOISON_MEMORY_REGION(p + bytes, room(bytes) - bytes);
+        free(p);
+    }
+    static size_t room(size_t b) { return (b + 127) / 128 * 128; }
 };
 
 // what the kernels with lanes working together do
