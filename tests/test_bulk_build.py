@@ -172,16 +172,17 @@ def test_no_room_on_the_device_to_build(tmp_path, request_):
     acc = np.resize(x[100:], (4, 3, 8)).astype(np.int32)
     cnt = np.full((4, 3), 8, dtype=np.int32)
     torch.cuda.synchronize()
-    free = torch.cuda.mem_get_info()[0]
-    for _ in range(3):
+    free = []
+    for _ in range(12):
         try:
             sam.sam_set_layout_override(request_ << 8)
             corpus = sam.sam_build(x, vocab)
         finally:
             sam.sam_set_layout_override(0)
-        held = sam.sam_corpus_info(corpus)[2]
-    # 3 builds, one of them alive: the working arrays alone are 27 MB
-    assert free - torch.cuda.mem_get_info()[0] < held + (20 << 20)
+        free.append(torch.cuda.mem_get_info()[0])
+    # The runtime's own buffers come with the first builds (39 MB seen), then what is free goes to and fro by the 2 MB that
+    # it gives out at a time.  The smallest of the arrays that could stay, the text, takes 1.2 MB a build: 9.6 MB in 8.
+    assert free[3] - free[11] < 8 << 20
     host = sam.sam_build_host_only(x, vocab)
     assert _saved(corpus, str(tmp_path / "a.sam"), n, vocab)[0] == _saved(host, str(tmp_path / "b.sam"), n, vocab)[0]
     g, status, _ = run_gpu(x, vocab, prompts, acc, cnt, 200, 8, 10, gpu_corpus=corpus)
