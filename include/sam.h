@@ -74,7 +74,8 @@ const char *sam_build_id(void);
 
 /*
  * Build-SAM (Algorithm 2) over `corpus_tokens`: on the device, by all of it at once, for corpora of
- * 10 000 tokens and more, on the host for smaller ones, where the device has no room to build
+ * 10 000 tokens and more, on the host for smaller ones, for those of up to 600 000 tokens of which so
+ * much repeats at short distances that the host is faster, where the device has no room to build
  * in (about 207 bytes a token while it does) and where more than 8 388 608 positions of the corpus
  * end in the same few tokens.  The automaton is the same.  Device
  * memory then holds it as flat arrays: the corpus text, one record per

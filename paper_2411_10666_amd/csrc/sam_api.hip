@@ -62,10 +62,52 @@ bool scouts_pay(int64_t seq_len, int64_t accept, int64_t batch, int64_t table_by
 }
 // buckets of 128 bytes that make a transition table of 4.5 GiB
 constexpr uint64_t kHugeTableBuckets = (1ull << 25) + (1ull << 22);
-// Tokens from which on the corpus automaton is built on the device: about fifty launches and a few
-// allocations take what the host needs for 10 000 tokens (sam_build, device / host, ms: 5000 tokens
-// 0.59 / 0.43, 10 000 0.66 / 0.72, 20 000 0.78 / 1.32, 100 000 1.8 / 6.4, 700 000 5.9 / 104, 6 M 42 / 1384).
-int64_t device_build_min() { return g_layout_override & 128 ? INT64_MAX : (g_layout_override & 64 ? 1 : 10000); }
+// Does the device build this corpus?  From 10 000 tokens on: about fifty launches and a few allocations
+// take what the host needs for those (sam_build, device / host, ms, Zipf text: 5000 tokens 0.62 / 0.38,
+// 10 000 0.68 / 0.65, 20 000 0.79 / 1.24, 100 000 1.6 / 6.2, 700 000 6.3 / 102, 6 M 23 / 1304; a large corpus'
+// copy to the host goes by the machine: 4.3 to 8.2 for 700 000).
+// Text that repeats is what the host is fast at (it stays in its caches) and the device slow: more rounds of the
+// sort, large groups that one workgroup takes each, and behind a run or a short period one wave that brings the next
+// token to as many states as the run is long.  So 16 places are looked at, whether what follows them is what was
+// there d tokens before:
+// - Where a share of them repeats, at a distance of up to 1024, the line is at 10 000 + 45 000 times that share
+//   (a period of 150: 20 000 tokens 1.01 / 0.74, 60 000 1.62 / 1.91; runs in a quarter of the text: 15 000 0.93 / 0.88,
+//   25 000 1.23 / 1.39; in half of it: 30 000 1.80 / 1.56, 40 000 1.98 / 2.13).
+// - Where one stretch over its period is more than a quarter of the text, at 250 000 (a run of half the text and then
+//   other text: 100 000 7.2 / 5.0, 200 000 15 / 10, 300 000 23 / 25; a period of 2: 100 000 5.3 / 3.6, 250 000 14.6 / 15.4; of
+//   5: 100 000 2.9 / 3.4).
+// - Where it is more than 0.6 of it and ends before the text does, at 600 000 (a run and another token: 300 000 31 / 20,
+//   500 000 54 / 43, 1 M 101 / 104; of three quarters: 300 000 28 / 19, 500 000 45 / 44; to the end of the text: 300 000
+//   11 / 15).
+bool device_builds(const int32_t *x, int64_t n)
+{
+    if (g_layout_override & 128) return false;
+    if (g_layout_override & 64) return true;
+    if (n < 10000) return false;
+    if (n >= 600000) return true;
+    constexpr int kLooks = 16, kSame = 16;
+    const int64_t most = n < 64000 ? 1024 : 4;       // (longer periods only move the first line)
+    int repeats = 0, run = 0;
+    int64_t before = 0, reach = 0;
+    bool inner = false;
+    for (int k = 1; k <= kLooks; k++) {
+        const int32_t *const at = x + (n - kSame) * k / kLooks;     // the last one is the text's end
+        int64_t d = 1;
+        while (d <= most && d <= at - x && !(at[-d] == at[0] && memcmp(at - d, at, kSame * sizeof(int32_t)) == 0)) d++;
+        if (d > most || d > at - x) d = 0;
+        run = d && d == before ? run + 1 : 1;
+        before = d;
+        if (!d) continue;
+        repeats++;
+        if (run * n / kLooks / d > reach) {
+            reach = run * n / kLooks / d;
+            inner = k < kLooks;
+        }
+    }
+    if (n < 10000 + 45000 * repeats / kLooks) return false;
+    if (reach > n / 4 && n < 250000) return false;
+    return !(10 * reach > 6 * n && inner);
+}
 HostSam::ProgressFn g_progress = nullptr;
 void *g_progress_user = nullptr;
 
@@ -461,8 +503,8 @@ static int build_common(const int32_t *tokens, int64_t n, int32_t vocab, bool up
     *out = nullptr;
     sam_corpus *c = new (std::nothrow) sam_corpus;
     if (!c) return fail(SAM_ENOMEM, "sam_build: out of host memory");
-    if (upload && tokens && n >= device_build_min() && n <= 0x7FFFFFFELL && vocab >= 1 &&
-        (g_layout_override & 8) == 0) {
+    if (upload && tokens && n >= 1 && n <= 0x7FFFFFFELL && vocab >= 1 && (g_layout_override & 8) == 0 &&
+        device_builds(tokens, n)) {
         bool done = false;
         if (g_progress) g_progress("build", 0, n, g_progress_user);
         const int rc = corpus_build_device(c, tokens, n, vocab, &done);

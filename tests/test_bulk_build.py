@@ -240,12 +240,16 @@ def test_corpus_token_outside_the_vocabulary(bad):
     x = np.zeros(30_000, dtype=np.int32)
     x[[12_345, 20_000]] = bad
     said = []
-    for build in (sam.sam_build, sam.sam_build_host_only):
+    for mode, build in ((64, sam.sam_build), (0, sam.sam_build), (0, sam.sam_build_host_only)):
         with pytest.raises(sam.SamError) as e:
-            build(x, 50)
+            try:
+                sam.sam_set_layout_override(mode)
+                build(x, 50)
+            finally:
+                sam.sam_set_layout_override(0)
         assert e.value.code == sam.SAM_ETOKEN
         said.append(str(e.value))
-    assert said[0] == said[1] and "12345" in said[0]
+    assert said[0] == said[1] == said[2] and "12345" in said[0]
 
 
 @pytest.mark.gpu

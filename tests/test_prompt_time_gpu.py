@@ -125,7 +125,6 @@ def test_tree_drafts_with_many_children(batch):
 @pytest.mark.parametrize("kind", ["equal tokens", "period of two", "half equal", "padded documents"])
 def test_repeating_corpora(kind):
     """Texts with few large groups, of which one workgroup sorts each (device 0.2 to 0.7 of the host's time as measured)."""
-    from paper_2411_10666_amd import binding as sam
     rng = np.random.default_rng(3)
     n = 700_000
     x = np.full(n, 7, np.int32)
@@ -136,15 +135,35 @@ def test_repeating_corpora(kind):
     elif kind == "padded documents":
         for at in range(0, n, 4000):
             x[at:at + 500] = rng.integers(0, 500, size=500)
+    device, host = _device_and_host(x, 500, 3)
+    assert device < host
+
+
+def _device_and_host(x, vocab, runs):
+    from paper_2411_10666_amd import binding as sam
     times = []
     for mode in (0, 128):
         try:
             sam.sam_set_layout_override(mode)
-            times.append(_shortest(lambda: sam.sam_build(x, 500), 3))
+            times.append(_shortest(lambda: sam.sam_build(x, vocab), runs))
         finally:
             sam.sam_set_layout_override(0)
-    print("device %.1f ms, host %.1f ms" % (times[0] * 1e3, times[1] * 1e3), flush=True)
-    assert times[0] < times[1]
+    print("sam_build %.2f ms, on the host %.2f ms" % (times[0] * 1e3, times[1] * 1e3), flush=True)
+    return times
+
+
+# of `part` of the text a period repeats throughout, then comes other text (another token, if it is all)
+@pytest.mark.parametrize("n", [12_000, 30_000, 100_000, 200_000, 500_000])
+@pytest.mark.parametrize("period,part", [(1, 1), (1, 0.75), (1, 0.5), (2, 1), (3, 1), (20, 1), (150, 1), (700, 1), (20, 0.5)])
+def test_repeating_corpora_of_any_size(n, period, part):
+    """Where the device is slower at text that repeats, the host builds (1.05 of its time at most as measured, but for one
+    text near a line 1.26; without the look at the text up to 2.7)."""
+    rng = np.random.default_rng(n)
+    x = (500 * rng.random(n) ** 4).astype(np.int32)
+    x[:int(n * part)] = np.resize(rng.integers(0, 500, size=period), int(n * part))
+    x[-1] = 9
+    built, host = _device_and_host(x, 500, 5)
+    assert built < 1.5 * host
 
 
 @pytest.mark.parametrize("kind", ["equal tokens", "period of two", "padding"])
