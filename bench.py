@@ -63,16 +63,16 @@ ALGO_BYTES_PER_MATCH_STEP = {
 # while those sources are unchanged.
 MEASURED_TRAFFIC = {
     # config 5, all 519 step launches of one schedule pass (8081.5 match-steps per launch):
-    # FETCH_SIZE mean 4146.77, WRITE_SIZE mean 995.13; the same counters read 131088.75
+    # FETCH_SIZE mean 4146.36, WRITE_SIZE mean 995.13; the same counters read 131088.75
     # and 262144.00 for a copy kernel that reads and writes 262144 KiB, i.e. 2.000 and
-    # 1.000 KiB per count: (4146.77 x 2.000 + 995.13) KiB = 9.512 MB per launch
-    "cfg5": {"bytes_per_match_step": 1177.0, "sources": "dc7bab32ddf8d57a"},
-    # config 3, 673 launches (1558.1 match-steps each): FETCH_SIZE 942.82 x 2.000 +
+    # 1.000 KiB per count: (4146.36 x 2.000 + 995.13) KiB = 9.511 MB per launch
+    "cfg5": {"bytes_per_match_step": 1176.9, "sources": "25b7c552887a5edc"},
+    # config 3, 673 launches (1558.1 match-steps each): FETCH_SIZE 942.91 x 2.000 +
     # WRITE_SIZE 204.75 x 1.000 KiB = 2.141 MB per launch
-    "cfg3": {"bytes_per_match_step": 1373.8, "sources": "dc7bab32ddf8d57a"},
-    # config 4 (no corpus), 273 launches (7681.9 match-steps each): 2541.92 x 2.000 +
-    # 1011.33 x 1.000 KiB = 6.242 MB per launch
-    "cfg4": {"bytes_per_match_step": 812.5, "sources": "dc7bab32ddf8d57a"},
+    "cfg3": {"bytes_per_match_step": 1373.9, "sources": "25b7c552887a5edc"},
+    # config 4 (no corpus), 273 launches (7681.9 match-steps each): 2541.83 x 2.000 +
+    # 1011.33 x 1.000 KiB = 6.241 MB per launch
+    "cfg4": {"bytes_per_match_step": 812.5, "sources": "25b7c552887a5edc"},
 }
 
 KERNEL_SOURCES = ["sam_kernels.hip", "sam_walk.h", "sam_layout.h", "sam_device.h"]
