@@ -21,7 +21,7 @@ namespace sam {
 // the arrays in the sequence's own tables (prompts beyond LDS, where the whole chip does not take them,
 // see launch_ingest) the bound is the rate at which one compute unit gets
 // scattered requests to the L2 through, 0.5 to 0.6 a nanosecond: 12 prompts of 40 001 tokens
-// 3.6 ms (46 ms).  Of the 165 us that one workgroup needs for 6000 tokens, the sort takes 75, the
+// 3.4 to 9.8 ms by their text (46 ms).  Of the 165 us that one workgroup needs for 6000 tokens, the sort takes 75, the
 // intervals 19 and the transitions 61 (a compare-and-swap in the slot table each).  Two parts
 // took longer: the nearest smaller values scanned in runs of 32 (130 us; now a tree of
 // minima of 8, one 16-byte read a level, 19) and the transitions walking the records in
@@ -362,11 +362,14 @@ hipError_t launch_ingest(const StaticView &S, const BatchView &B, const int32_t 
     }
     // Prompts beyond LDS are built by the whole chip, phase by phase, wherever their tables have room for
     // that: one workgroup each is bound by the scattered accesses of its compute unit even where there
-    // are more of them than units.  sam_batch_reset, chip / workgroups, ms, Zipf text:
+    // are more of them than units.  sam_batch_reset, chip / workgroups, ms, tokens
+    // = 32 000 u^5 of a uniform u:
     //   1 x 6500  0.30 / 0.46    1 x 16 000  0.35 / 1.2    1 x 100 000  0.60 / 8.2    12 x 40 000  0.65 / 3.3
     //   64 x 30 000  1.5 / 3.0   256 x 9000  1.38 / 1.38   600 x 8000  2.5 / 2.9
     // (period of 150: 1 x 6500 0.47 / 1.1, 12 x 40 000 1.4 / 9.4, 600 x 8000 3.6 / 7.1; of one token only:
-    // 1 x 6500 0.58 / 0.64, 12 x 40 000 1.6 / 5.2, 256 x 9000 1.67 / 1.55, 600 x 8000 2.6 / 3.1).
+    // 1 x 6500 0.58 / 0.64, 12 x 40 000 1.6 / 5.2, 256 x 9000 1.67 / 1.55, 600 x 8000 2.6 / 3.1; that and another token:
+    // 1 x 6500 1.07 / 2.18, 12 x 40 001 4.4 / 14.9, 600 x 8000 3.4 / 9.0; u^3 with copies of up to 200 tokens: 12 x 40 001
+    // 0.96 / 6.9).
     // The launches cover the prompts that are taken, which the begin kernel lists (one of 7000 among 1279 of 64
     // tokens: 0.44 ms, of 100 000 1.5; with workgroups for all prompts 0.79 and 8.3; one workgroup each
     // 0.51 and 8.9).  Few of them that one workgroup each builds while the others are built are left to

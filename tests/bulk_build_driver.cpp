@@ -1,8 +1,11 @@
-// An automaton built by phases over the whole chip (sam_bulk.h, the phases run one after the
-// other on the CPU, the sort's passes replaced by std::sort) against the token-by-token host
-// builder: ids, lengths, links, end positions and every transition, into a sequence's own tables in
-// both layouts and into the corpus's.  The regions have exactly the sizes that the library gives
-// them: an access outside one is seen by AddressSanitizer.
+// An automaton built by phases over the whole chip (sam_bulk.h, the phases run one after the other on
+// the CPU) against the token-by-token host builder: ids, lengths, links, end positions and every
+// transition, into a sequence's own tables in both layouts and into the corpus's.  What lanes or
+// workgroups do together has a plain form here: std::sort for the radix passes, counting for
+// groups of any size, loops for the minima and the running sums, one link after the other for the
+// states that a wave guesses (the kernels' own forms are compared with the host builder on the GPU).
+// The regions have exactly the sizes that the library gives them: an access outside one is seen by
+// AddressSanitizer.
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
